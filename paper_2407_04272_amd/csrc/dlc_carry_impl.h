@@ -30,8 +30,6 @@
 
 namespace dlc {
 
-typedef __attribute__((address_space(3))) uint32_t lds_u32;
-
 constexpr uint32_t kCarryBlk = 2;   // units (16-byte loads per lane) worked on together
 constexpr uint32_t kCarryLoad = 2;  // units loaded together, one such block ahead of the work (4: registers spill, slower)
 

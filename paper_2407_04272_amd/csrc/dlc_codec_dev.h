@@ -3,8 +3,6 @@
 #pragma once
 #include "dlc_internal.h"
 
-// phase time stamps for kernel micro-benchmarks; expands to nothing in the library
-
 namespace dlc {
 
 // ------------------------------------------------------------------------------------------------
@@ -30,6 +28,154 @@ __host__ __device__ inline uint32_t win_lo_of(uint32_t R) { return R > kWinBins 
 __host__ __device__ inline size_t plane_stride(const Geom& g) { return (size_t)g.G * kW * g.S; }
 // LDS of the histogram kernel in words: window [kWinBins + 1][kWinCopies] | exact counts [K]
 __host__ __device__ inline size_t hist_lds_bytes(uint32_t K) { return (((size_t)(kWinBins + 1) * kWinCopies + K) * 4 + 15) & ~size_t(15); }
+
+// ------------------------------------------------------------------------------------------------
+// quantise and count: one block of units of a table (used by the histogram kernel and by the kernel for small tables)
+// ------------------------------------------------------------------------------------------------
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+__device__ __forceinline__ void lds_count(uint32_t addr) {
+    __hip_atomic_fetch_add(reinterpret_cast<lds_u32*>(addr), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+struct HistC {
+    int ubias;          // window index of bin 0
+    uint32_t win_lo;    // symbol of window index 0
+    uint32_t lanebase;  // LDS address of this lane's copy of window row 0
+    uint32_t exact;     // LDS address of the exact counts
+    float Rf;
+    float first, last;  // kMagic + the lowest and the highest window index a bin inside the radius can have
+    float eb_sure;      // a bound a little below the table's
+};
+
+// A float of kMagicF + i, 0 <= i < 2^22, has i in its low bits, and adding kMagicF + i to a product in one fused operation
+// rounds the product to a whole number (half to even).
+constexpr float kMagicF = 12582912.0f;  // 1.5 * 2^23
+constexpr uint32_t kMagicBits = 0x4B400000u;
+
+template <bool LZ>
+__device__ __forceinline__ HistC hist_consts(const Geom& g, const QParam& q, uint32_t lds0, uint32_t lane) {
+    HistC H;
+    H.win_lo = win_lo_of(g.R);
+    H.ubias = (int)(g.R - H.win_lo);
+    H.lanebase = lds0 + (lane & (kWinCopies - 1u)) * 4u;
+    H.exact = lds0 + (kWinBins + 1u) * kWinCopies * 4u;
+    H.Rf = (float)g.R;
+    const int r1 = (int)g.R - 1;
+    H.first = kMagicF + (float)max(0, H.ubias - r1);
+    H.last = kMagicF + (float)min((int)(LZ ? kWinSkip : kWinEsc) - 1, H.ubias + r1);
+    // Inside the window (|bin| <= 127) an element that is within eb_sure of a bin's centre by one fused operation is in
+    // that bin and inside the bound by the quantiser's own roundings too: product and reciprocal are off by 2^-16 of a bin
+    // together, the reconstruction by 2^-16 of the bound, and the margin is 2^-13.  Where a denormal or an overflowing
+    // bound makes those relative errors larger, nothing is sure.
+    H.eb_sure = (q.eb > 1e-30f && q.eb < 1e30f) ? q.eb * (1.0f - 0x1p-13f) : -1.0f;
+    return H;
+}
+
+constexpr uint32_t kPastEnd = 0x80000001u;  // no element within the radius has this window index: a position past the end of the table
+constexpr uint32_t kHistBlk = 4;  // units whose loads are issued back to back
+
+// One block of kHistBlk units of one table; a unit is 256 consecutive elements (one 16-byte load per lane).
+// `rem` = elements of the table from the block's first element on, `n_units` = units of the block that are this
+// wavefront's.  FULL: all kHistBlk units are, and all their elements are inside the table (no masking at all).
+// Index 254 in the plane stands for an escape.  LZ (row matching): the window is one symbol narrower, because index
+// 253 stands for an element of a row that is stored as a reference (the row-matching kernels put it there
+// afterwards); the symbol that would have had that index goes the way of everything outside the window.
+//
+// What bounds it is what a wavefront issues per element.  The rule is an element well inside a bin of the window: one
+// fused operation rounds it to the window index (which then lies in the float's low bits: no conversion), one clamp, one
+// fused operation gives its distance from the bin's centre, and the address of its count is a shift and an addition.
+// A unit with any other element, one in thirty, goes through the quantiser's own arithmetic.  (With that arithmetic
+// for every element, 15 vector instructions each instead of 7, a work-group that counts a table of 262144 elements on its
+// own took 15 us longer.)
+template <bool F16, bool VEC, bool FULL>
+struct HistLoads {
+    float x[kHistBlk][4];
+    uint32_t valid[kHistBlk];
+    __device__ __forceinline__ void load(const uint8_t* base, uint32_t rem, uint32_t n_units, uint32_t lane) {
+        uint32_t raw[4];
+#pragma unroll
+        for (uint32_t u = 0; u < kHistBlk; ++u)
+            valid[u] = load4<F16, VEC>(base, lane * kV + u * (kW * kV), FULL ? 0xFFFFFFFFu : (u < n_units ? rem : 0u), x[u], raw);
+    }
+};
+
+template <bool F16, bool VEC, bool FULL, bool LZ, bool PLANE = true>
+__device__ __forceinline__ void hist_count(const HistLoads<F16, VEC, FULL>& D, uint32_t n_units, uint32_t lane, const QParam& q,
+                                           const HistC& H, uint32_t* plane) {
+    constexpr uint32_t kBins = LZ ? kWinSkip : kWinEsc;  // window indices that stand for a symbol
+    const float mg = kMagicF + (float)H.ubias;
+    const uint32_t rows = H.lanebase - kMagicBits * (kWinCopies * 4u);  // (modulo 2^32)
+#pragma unroll
+    for (uint32_t u = 0; u < kHistBlk; ++u) {
+        uint32_t sl[4];
+        float t[4];
+        bool sure = FULL || D.valid[u] == 0xFu;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float xv = D.x[u][v];
+            if constexpr (F16) {  // (the reconstruction is rounded to half: the quantiser's own test, as it is)
+                const float r = __builtin_rintf(xv * q.inv);
+                t[v] = __builtin_amdgcn_fmed3f(r + mg, H.first, H.last);
+                const float rc = t[v] - mg;
+                const float xh = __half2float(half_rne(rc * q.ebx2));
+                sure = sure & (rc == r) & (__builtin_fabsf(xv - xh) <= q.eb);
+            } else {
+                t[v] = __builtin_amdgcn_fmed3f(__builtin_fmaf(xv, q.inv, mg), H.first, H.last);
+                sure = sure & (__builtin_fabsf(__builtin_fmaf(mg - t[v], q.ebx2, xv)) <= H.eb_sure);
+            }
+        }
+        if (__builtin_expect(__ballot(!sure) == 0ull, 1)) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                sl[v] = __float_as_uint(t[v]);
+                lds_count((sl[v] << 6) + rows);
+            }
+            static_assert(kWinCopies * 4u == 64u, "a row of the window");
+            if constexpr (PLANE)
+                plane[u * kW + lane] = __builtin_amdgcn_perm(sl[1], sl[0], 0x0C0C0400u) | __builtin_amdgcn_perm(sl[3], sl[2], 0x04000C0Cu);
+            continue;
+        }
+        uint32_t w[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            // the quantiser (same arithmetic as quant_symbol), result as a window index
+            const float xv = D.x[u][v];
+            const float r = __builtin_rintf(xv * q.inv);
+            float xh = r * q.ebx2;
+            if constexpr (F16) xh = __half2float(half_rne(xh));
+            const float d = xv - xh;
+            const bool ok = (__builtin_fabsf(r) < H.Rf) & (__builtin_fabsf(d) <= q.eb);  // no short circuit: no branches
+            w[v] = (uint32_t)((int)r + H.ubias);  // (bins below the window wrap to just under 2^32)
+            sl[v] = w[v] < kBins ? w[v] : kWinBins;
+            sl[v] = ok ? sl[v] : kWinEsc;
+            if constexpr (FULL) {
+                lds_count(sl[v] * (kWinCopies * 4u) + H.lanebase);
+            } else {
+                if ((D.valid[u] >> v) & 1u) lds_count(sl[v] * (kWinCopies * 4u) + H.lanebase);
+                else { sl[v] = kWinBins; w[v] = kPastEnd; }
+            }
+        }
+        // index 255 is rare: count those elements exactly, by symbol (escapes are counted in window row 254, which
+        // the merge adds to symbol 0)
+        if (__ballot(max(max(sl[0], sl[1]), max(sl[2], sl[3])) == kWinBins) != 0ull) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (sl[v] == kWinBins && w[v] != kPastEnd) lds_count(H.exact + (w[v] + H.win_lo) * 4u);
+        }
+        // the window indices of these four elements, for the encode kernel (a unit of this wavefront only)
+        if constexpr (PLANE) {
+            if (FULL || u < n_units) plane[u * kW + lane] = sl[0] | (sl[1] << 8) | (sl[2] << 16) | (sl[3] << 24);
+        }
+    }
+}
+
+template <bool F16, bool VEC, bool FULL, bool LZ, bool PLANE = true>
+__device__ __forceinline__ void hist_block(const uint8_t* base, uint32_t rem, uint32_t n_units, uint32_t lane, const QParam& q,
+                                           const HistC& H, uint32_t* plane) {
+    HistLoads<F16, VEC, FULL> D;
+    D.load(base, rem, n_units, lane);
+    hist_count<F16, VEC, FULL, LZ, PLANE>(D, n_units, lane, q, H, plane);
+}
 
 // ------------------------------------------------------------------------------------------------
 // Huffman codebook of one table, built by one work-group of 256 threads from the table's histogram.
@@ -58,11 +204,20 @@ __device__ __forceinline__ uint32_t lane_read(uint32_t v, uint32_t l) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)l);
 }
 
+// the next lane's value; the last lane gets `last`
+__device__ __forceinline__ uint32_t lane_next(uint32_t v, uint32_t last) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)last, (int)v, 0x130 /* wave_shl:1 */, 0xF, 0xF, false);
+}
+
 // The whole tree of a table with at most 64 used symbols, built by one wavefront without touching memory:
-// lane i holds used symbol i (symbol order) on entry.  Leaves and merged nodes live one per lane; the merge
-// loop runs on wavefront-uniform values only (the queue heads sit in scalar registers, lane reads and writes
-// move them); depths come from pointer jumping.  Lengths above LM are limited as described above.  Returns the
-// code length of the symbol the lane came in with.  2 <= n <= 64.
+// lane i holds used symbol i (symbol order) on entry.  The merge keeps leaves and merged nodes in ONE list in lane
+// order, rising by weight: a step takes the two at the front off, moves the list up by two lanes and puts their sum
+// behind everything that is not heavier.  That is the two-queue merge's order, ties included: the leaves are in the
+// list from the start, so a leaf comes before every node of its weight, and of two nodes of one weight the older one
+// comes first.  What bounds a step is its chain of dependent instructions, and no lane number in it depends on an
+// earlier step (two queues with their heads read by computed lane numbers, the first form of this loop, took 345
+// cycles a step; k_codebook for 26 tables of 17 to 51 symbols: 23 us).  Depths come from pointer jumping.  Lengths
+// above LM are limited as described above.  Returns the code length of the symbol the lane came in with.  2 <= n <= 64.
 __device__ __forceinline__ uint32_t wave_huffman_lengths(uint32_t n, uint32_t LM, uint32_t cnt, uint32_t lane) {
     const uint32_t kInf = 0xFFFFFFFFu;
     // position in (count, symbol) order
@@ -74,26 +229,20 @@ __device__ __forceinline__ uint32_t wave_huffman_lengths(uint32_t n, uint32_t LM
     if (lane >= n) rank = lane;  // idle lanes keep their place
     // the sorted sequence: every lane sends its count to the lane of its rank
     const uint32_t sent = (uint32_t)__builtin_amdgcn_ds_permute((int)(rank << 2), (int)cnt);
-    const uint32_t s_cnt = lane < n ? sent : kInf;
-    // two-queue merge; a tie between the heads takes the leaf.  l0, l1: the two leaves at the head of the leaf
-    // queue; n0, n1: the same for the merged nodes (node k exists from step k + 1 on)
-    const uint32_t vw = s_cnt;
-    uint32_t vn = kInf, vpl = 0, vpn = 0;
-    uint32_t a = 0, bq = 0;
-    uint32_t l0 = lane_read(vw, 0), l1 = lane_read(vw, 1), n0 = kInf, n1 = kInf;
+    uint32_t w = lane < n ? sent : kInf;  // weights (a sum of all counts is less than 2^31: kInf is heavier than any)
+    uint32_t id = lane;                   // leaf at sorted position id, or 64 + k: merged node k
+    uint32_t vpl = 0, vpn = 0;            // the node above the leaf at sorted position `lane`; above node `lane`
     for (uint32_t k = 0; k + 1 < n; ++k) {
-        const bool f_leaf = l0 <= n0;
-        const uint32_t s1 = f_leaf ? l0 : n0;
-        const uint32_t c_l = f_leaf ? l1 : l0, c_n = f_leaf ? n0 : n1;
-        const bool s_leaf = c_l <= c_n;
-        const uint32_t s2 = s_leaf ? c_l : c_n;
-        if (f_leaf) { vpl = lane_put(vpl, a, k, lane); ++a; } else { vpn = lane_put(vpn, bq, k, lane); ++bq; }
-        if (s_leaf) { vpl = lane_put(vpl, a, k, lane); ++a; } else { vpn = lane_put(vpn, bq, k, lane); ++bq; }
-        vn = lane_put(vn, k, s1 + s2, lane);
-        l0 = a < n ? lane_read(vw, a) : kInf;
-        l1 = a + 1u < n ? lane_read(vw, a + 1u) : kInf;
-        n0 = bq <= k ? lane_read(vn, bq) : kInf;
-        n1 = bq + 1u <= k ? lane_read(vn, bq + 1u) : kInf;
+        const uint32_t sum = lane_read(w, 0) + lane_read(w, 1);
+        const uint32_t a = lane_read(id, 0), b = lane_read(id, 1);
+        const uint32_t w1 = lane_next(w, kInf), i1 = lane_next(id, 0u);
+        const uint32_t w2 = lane_next(w1, kInf), i2 = lane_next(i1, 0u);
+        const bool before = w2 <= sum;      // stays in front of the sum: it moves up by two lanes
+        const bool here = w1 <= sum;        // (the one in front of it does, or there is none) the sum's place
+        w = before ? w2 : (here ? sum : w1);
+        id = before ? i2 : (here ? 64u + k : i1);
+        vpl = (lane == a || lane == b) ? k : vpl;
+        vpn = (lane + 64u == a || lane + 64u == b) ? k : vpn;
     }
     // depth of every merged node (lane k = node k, the root is node n-2)
     const uint32_t root = n - 2u;
@@ -142,6 +291,19 @@ __device__ __forceinline__ uint32_t wave_huffman_lengths(uint32_t n, uint32_t LM
     return lane < n ? __shfl(len, rank, 64) : 0u;
 }
 
+// canonical codeword of every lane's symbol (the lanes are in symbol order; length 0: not used): the first code of each
+// length, then the rank among the symbols of that length.  below: the lanes before this one.
+__device__ __forceinline__ uint32_t wave_canonical_code(uint32_t len, uint32_t LM, uint64_t below) {
+    uint32_t code = 0, mine = 0;
+    for (uint32_t L = 1; L <= LM; ++L) {
+        code <<= 1;
+        const uint64_t same = __ballot(len == L);
+        mine = (len == L) ? code + (uint32_t)__popcll(same & below) : mine;
+        code += (uint32_t)__popcll(same);
+    }
+    return mine;
+}
+
 // The codebook of a table with at most 64 used symbols (the rule), by ONE wavefront: same inputs and outputs as
 // codebook_build below, which takes every other table.  The wavefront reads the histogram 64 symbols at a time,
 // gathers the used symbols into its lanes through `wsm` (LDS of this wavefront: 64 keys, then K entries of 16
@@ -188,15 +350,7 @@ __device__ __forceinline__ bool codebook_build_wave(const Geom& g, uint32_t* his
     const uint32_t sym = (uint32_t)(kv & 0xFFFFu);
     if (n_used >= 2u) {
         const uint32_t len = wave_huffman_lengths(n_used, g.LMAX, (uint32_t)(kv >> 16), lane);
-        // canonical codewords: first code of each length, then the rank among the symbols of that length (the lanes
-        // are in symbol order)
-        uint32_t code = 0, mine_code = 0;
-        for (uint32_t L = 1; L <= g.LMAX; ++L) {
-            code <<= 1;
-            const uint64_t same = __ballot(len == L);
-            mine_code = (len == L) ? code + (uint32_t)__popcll(same & below) : mine_code;
-            code += (uint32_t)__popcll(same);
-        }
+        const uint32_t mine_code = wave_canonical_code(len, g.LMAX, below);
         if (lane < n_used) ent[sym] = (uint16_t)((len << 12) | mine_code);
     }
     __builtin_amdgcn_wave_barrier();
@@ -222,6 +376,7 @@ __device__ __forceinline__ bool codebook_build_wave(const Geom& g, uint32_t* his
 // hist_t is read, copied to hist_view_t (inspection) and cleared, so that the next call starts from zero counts.
 // enc_t is written with device-scope stores: other work-groups of a running kernel may read it once they have
 // seen the caller's completion flag.
+template <uint32_t NT = 256>
 __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, uint32_t* hist_view_t, uint16_t* enc_t,
                                                uint8_t* lens_t, TMeta* tmeta_t, unsigned char* smem, CodebookShared& sh,
                                                uint32_t tid, uint32_t carry = 0) {
@@ -237,17 +392,18 @@ __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, 
     const uint32_t lane = tid & 63u, wave = tid >> 6;
 
     // each thread owns `per` consecutive symbols
-    const uint32_t per = (K + 255) / 256;
+    const uint32_t per = (K + NT - 1u) / NT;
     const uint32_t k0 = tid * per, k1 = min(K, k0 + per);
     uint32_t mine = 0;
     // the counts were added by device-scope atomics of other work-groups, possibly on other dies; a thread's loads
-    // go out together (at most 16: an alphabet of 4096 symbols)
-    uint32_t hv[16];
+    // go out together (an alphabet has at most 4096 symbols)
+    constexpr uint32_t kPer = (4096u + NT - 1u) / NT;
+    uint32_t hv[kPer];
 #pragma unroll
-    for (uint32_t i = 0; i < 16; ++i)
+    for (uint32_t i = 0; i < kPer; ++i)
         hv[i] = k0 + i < k1 ? __hip_atomic_load(&hist_t[k0 + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
 #pragma unroll
-    for (uint32_t i = 0; i < 16; ++i) {
+    for (uint32_t i = 0; i < kPer; ++i) {
         const uint32_t k = k0 + i;
         if (k >= k1) break;
         const uint32_t h = hv[i];
@@ -264,7 +420,7 @@ __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, 
     if (tid < kLmaxLimit + 2) sh.cl[tid] = 0;
     // compaction offsets of the used symbols (symbol order); the barriers inside also publish cnt[]
     uint32_t n_used;
-    const uint32_t my_off = block_excl_scan<4>(mine, scratch, tid, &n_used);
+    const uint32_t my_off = block_excl_scan<(int)(NT / 64u)>(mine, scratch, tid, &n_used);
     {
         uint32_t o = my_off;
         for (uint32_t k = k0; k < k1; ++k)
@@ -280,16 +436,7 @@ __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, 
             const uint64_t kv = lane < n_used ? key[lane] : ~0ull;  // lane i: the i-th used symbol
             const uint32_t sym = (uint32_t)(kv & 0xFFFFu);
             const uint32_t len = wave_huffman_lengths(n_used, g.LMAX, (uint32_t)(kv >> 16), lane);
-            // canonical codewords: first code of each length, then the rank among the symbols of that length (the
-            // lanes are in symbol order)
-            const uint64_t below = (1ull << lane) - 1ull;
-            uint32_t code = 0, mine_code = 0;
-            for (uint32_t L = 1; L <= g.LMAX; ++L) {
-                code <<= 1;
-                const uint64_t same = __ballot(len == L);
-                mine_code = (len == L) ? code + (uint32_t)__popcll(same & below) : mine_code;
-                code += (uint32_t)__popcll(same);
-            }
+            const uint32_t mine_code = wave_canonical_code(len, g.LMAX, (1ull << lane) - 1ull);
             if (lane < n_used) { len_s[sym] = (uint16_t)len; nodew[sym] = mine_code; }
             if (lane == 0) sh.codes_done = 1;
         }
@@ -297,7 +444,7 @@ __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, 
     } else if (n_used > 64) {
         const uint32_t n_escape = cnt[0];  // (cnt[] is scratch from here on:
         __syncthreads();                   //  once every thread has read this)
-        if (n_used <= 256) {
+        if (n_used <= NT) {
             // rank sort, a thread per key: the keys are distinct (the symbol is part of them), so a key's place is
             // the number of smaller keys; every thread reads the same key at a time (an LDS broadcast)
             uint64_t* tmp = reinterpret_cast<uint64_t*>(cnt);  // cnt[] and nodew[] together: K words of 64 bits
@@ -314,12 +461,12 @@ __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, 
         } else {
             uint32_t P = 2;
             while (P < n_used) P <<= 1;
-            for (uint32_t i = n_used + tid; i < P; i += 256) key[i] = ~0ull;  // pad to a power of two
+            for (uint32_t i = n_used + tid; i < P; i += NT) key[i] = ~0ull;  // pad to a power of two
             __syncthreads();
             // bitonic sort, ascending
             for (uint32_t size = 2; size <= P; size <<= 1) {
                 for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
-                    for (uint32_t i = tid; i < (P >> 1); i += 256) {
+                    for (uint32_t i = tid; i < (P >> 1); i += NT) {
                         uint32_t lo = 2 * i - (i & (stride - 1));
                         uint32_t hi = lo + stride;
                         bool up = (lo & size) == 0;
@@ -354,23 +501,23 @@ __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, 
             const uint32_t root = n_used - 2u;
             uint32_t* cur = cnt;
             uint32_t* nxt = nodew;
-            for (uint32_t k = tid; k + 1 < n_used; k += 256) cur[k] = k == root ? root : ((1u << 16) | parent_node[k]);
+            for (uint32_t k = tid; k + 1 < n_used; k += NT) cur[k] = k == root ? root : ((1u << 16) | parent_node[k]);
             __syncthreads();
             for (uint32_t span = 1; span < n_used; span <<= 1) {  // uniform trip count
-                for (uint32_t k = tid; k + 1 < n_used; k += 256) {
+                for (uint32_t k = tid; k + 1 < n_used; k += NT) {
                     const uint32_t me = cur[k], up = cur[me & 0xFFFFu];
                     nxt[k] = ((me >> 16) + (up >> 16)) << 16 | (up & 0xFFFFu);
                 }
                 __syncthreads();
                 uint32_t* sw = cur; cur = nxt; nxt = sw;
             }
-            for (uint32_t k = tid; k + 1 < n_used; k += 256) depth_node[k] = (uint16_t)(cur[k] >> 16);
+            for (uint32_t k = tid; k + 1 < n_used; k += NT) depth_node[k] = (uint16_t)(cur[k] >> 16);
             __syncthreads();
             if (tid == 0) cnt[0] = n_escape;  // read again at the end (nothing below writes cnt[])
         }
         // leaf depths; parent_leaf[] is reused to hold the depth of leaf i (sorted order)
         uint32_t local_max = 0;
-        for (uint32_t i = tid; i < n_used; i += 256) {
+        for (uint32_t i = tid; i < n_used; i += NT) {
             const uint32_t d = depth_node[parent_leaf[i]] + 1u;
             parent_leaf[i] = (uint16_t)d;
             local_max = max(local_max, d);
@@ -380,7 +527,7 @@ __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, 
     }
     if (n_used >= 2) {
         if (sh.maxlen > g.LMAX) {
-            for (uint32_t i = tid; i < n_used; i += 256) atomicAdd(&sh.cl[min((uint32_t)parent_leaf[i], g.LMAX)], 1u);
+            for (uint32_t i = tid; i < n_used; i += NT) atomicAdd(&sh.cl[min((uint32_t)parent_leaf[i], g.LMAX)], 1u);
             __syncthreads();
             if (tid == 0) {
                 const uint32_t LM = g.LMAX;
@@ -398,7 +545,7 @@ __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, 
                 sh.next[LM + 1] = acc;
             }
             __syncthreads();
-            for (uint32_t i = tid; i < n_used; i += 256) {
+            for (uint32_t i = tid; i < n_used; i += NT) {
                 const uint32_t rank = n_used - 1u - i;  // 0 = most frequent (leaves are sorted by rising count)
                 uint32_t L = 1;
                 while (L < g.LMAX && rank >= sh.next[L + 1]) ++L;
@@ -409,7 +556,7 @@ __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, 
             __syncthreads();
         }
         if (!sh.codes_done) {  // uniform
-            for (uint32_t i = tid; i < n_used; i += 256) len_s[(uint32_t)(key[i] & 0xFFFFu)] = parent_leaf[i];
+            for (uint32_t i = tid; i < n_used; i += NT) len_s[(uint32_t)(key[i] & 0xFFFFu)] = parent_leaf[i];
             __syncthreads();
             // codewords
             for (uint32_t k = k0; k < k1; ++k)
@@ -425,7 +572,7 @@ __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, 
             }
             __syncthreads();
             // a symbol's codeword: the first code of its length plus the number of smaller symbols of that length
-            for (uint32_t k = sym_lo + tid; k <= sym_hi; k += 256) {
+            for (uint32_t k = sym_lo + tid; k <= sym_hi; k += NT) {
                 const uint32_t L = len_s[k];
                 if (L) {
                     uint32_t r = 0;
@@ -471,6 +618,50 @@ __device__ __forceinline__ void codebook_build_four(const Geom& g, uint32_t t0, 
         codebook_build(g, hist + (size_t)ts * g.K, hist_view + (size_t)ts * g.K, enc + (size_t)ts * g.K, lens + (size_t)ts * g.K,
                        tmeta + ts, smem, sh, tid, carry);
     }
+}
+
+// The codebook of a table whose counts lie in LDS by window index (cnt[254]: the escapes), when it has at most 64 used
+// symbols, all of them inside the window; by ONE wavefront.  key: LDS for 64 keys; ent[256] (LDS, zeroed before): gets
+// len << 12 | codeword by window index.  Returns false, with ent untouched, when there are more than 64 used symbols.
+__device__ __forceinline__ bool codebook_window_wave(const Geom& g, const uint32_t* cnt, uint64_t* key, uint16_t* ent,
+                                                     TMeta* tmeta_t, uint32_t lane) {
+    const uint32_t win_lo = win_lo_of(g.R);
+    const uint64_t below = (1ull << lane) - 1ull;
+    const uint32_t n_escape = (uint32_t)__builtin_amdgcn_readfirstlane((int)cnt[kWinEsc]);
+    uint32_t n_used = n_escape ? 1u : 0u;  // the escape is symbol 0: the first in symbol order
+    if (n_escape && lane == 0) key[0] = ((uint64_t)n_escape << 16) | kWinEsc;
+    uint32_t cv[4];
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) cv[i] = i * 64u + lane < kWinEsc ? cnt[i * 64u + lane] : 0u;
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) {
+        const uint64_t m = __ballot(cv[i] != 0u);
+        const uint32_t at = n_used + (uint32_t)__popcll(m & below);
+        if (cv[i] != 0u && at < 64u) key[at] = ((uint64_t)cv[i] << 16) | (i * 64u + lane);
+        n_used += (uint32_t)__popcll(m);
+    }
+    if (n_used > 64u) return false;  // uniform
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const uint64_t kv = lane < n_used ? key[lane] : ~0ull;  // lane i: the i-th used symbol
+    const uint32_t idx = (uint32_t)(kv & 0xFFFFu);
+    if (n_used >= 2u) {
+        const uint32_t len = wave_huffman_lengths(n_used, g.LMAX, (uint32_t)(kv >> 16), lane);
+        const uint32_t code = wave_canonical_code(len, g.LMAX, below);
+        if (lane < n_used) ent[idx] = (uint16_t)((len << 12) | code);
+    }
+    const uint32_t sym = idx == kWinEsc ? 0u : win_lo + idx;
+    const uint32_t lo = lane_read(sym, 0), hi = (uint32_t)__builtin_amdgcn_readlane((int)sym, (int)(n_used ? n_used - 1u : 0u));
+    if (lane == 0) {
+        TMeta m;
+        m.n_used = n_used;
+        m.sym_lo = n_used ? lo : 0u;
+        m.sym_hi = n_used ? hi : 0u;
+        m.n_outliers = n_escape;
+        *tmeta_t = m;
+    }
+    return true;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -532,86 +723,6 @@ __device__ __forceinline__ uint32_t wg_scan(uint64_t* state, uint64_t epoch, uin
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     return excl;
-}
-
-// The same look-back in steps that can be spread through other work: issue() starts the loads of one step,
-// consume() uses them.  Between the two the caller does something else, so the latency of the records (they
-// live in device-coherent memory, a few hundred nanoseconds away) costs nothing.  The caller has published its
-// own aggregate record before the first step (publish_aggregate) and publishes the prefix when done.
-struct LookBack {
-    int64_t dom0;     // first work-group of the scan domain (records before it count as an empty prefix)
-    int64_t pos;      // nearest record not yet added
-    uint32_t excl;    // sum so far
-    uint32_t spins;
-    bool done, failed, pending;
-    uint64_t sv[4];
-};
-
-__device__ __forceinline__ void lb_publish_aggregate(uint64_t* state, uint64_t epoch, uint32_t wg, uint32_t total, uint32_t lane,
-                                                     uint32_t dom0 = 0) {
-    if (lane == 0)
-        __hip_atomic_store(&state[wg], (epoch << 34) | ((uint64_t)(wg == dom0 ? kFlagPrefix : kFlagAgg) << 32) | total,
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void lb_init(LookBack& L, uint32_t wg, uint32_t dom0 = 0) {
-    L.dom0 = (int64_t)dom0;
-    L.pos = (int64_t)wg - 1;
-    L.excl = 0;
-    L.spins = 0;
-    L.done = wg == dom0;
-    L.failed = false;
-    L.pending = false;
-}
-__device__ __forceinline__ void lb_issue(LookBack& L, const uint64_t* state, uint64_t epoch, uint32_t lane) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int64_t my = L.pos - (int64_t)(lane * 4u + (uint32_t)k);
-        L.sv[k] = my >= L.dom0 ? __hip_atomic_load(&state[my], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                               : ((epoch << 34) | ((uint64_t)kFlagPrefix << 32));  // before the domain's first work-group: an empty prefix
-    }
-    L.pending = true;
-}
-// true if the step made progress (false: a record nearer than the nearest prefix is not published yet)
-__device__ __forceinline__ bool lb_consume(LookBack& L, uint64_t epoch, uint32_t lane) {
-    uint32_t sum = 0;    // values up to and including the lane's first prefix record (or all four)
-    bool has_p = false;  // there is a prefix record among them
-    bool hole = false;   // an unpublished record comes before it
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const uint64_t sv = L.sv[k];
-        const uint32_t flag = (sv >> 34) == epoch ? (uint32_t)(sv >> 32) & 3u : 0u;
-        if (!has_p) {
-            hole = hole || flag == 0u;
-            sum += flag != 0u ? (uint32_t)sv : 0u;
-            has_p = flag == kFlagPrefix;
-        }
-    }
-    L.pending = false;
-    const uint64_t pm = __ballot(has_p);
-    const uint32_t first = pm ? (uint32_t)__ffsll((unsigned long long)pm) - 1u : 64u;  // lane of the nearest prefix
-    if (__ballot(hole && lane <= first) != 0ull) return false;
-    L.excl += wave_sum(lane <= first ? sum : 0u);
-    if (pm) L.done = true;
-    else L.pos -= 256;
-    return true;
-}
-// runs the remaining steps to the end (bounded) and publishes the prefix record
-__device__ __forceinline__ void lb_finish(LookBack& L, uint64_t* state, uint64_t epoch, uint32_t wg, uint32_t total, uint32_t lane,
-                                          Ctrl* ctrl) {
-    while (!L.done && !L.failed) {
-        if (!L.pending) lb_issue(L, state, epoch, lane);
-        if (!lb_consume(L, epoch, lane)) {
-            if (++L.spins > kSpinLimit) {  // never expected; the bound only guarantees termination
-                if (lane == 0) { set_status(ctrl, DLC_ESTATE); atomicOr(&ctrl->abort, kAbortInternal); }
-                L.failed = true;
-            } else {
-                __builtin_amdgcn_s_sleep(1);
-            }
-        }
-    }
-    if ((int64_t)wg > L.dom0 && !L.failed && lane == 0)
-        __hip_atomic_store(&state[wg], (epoch << 34) | ((uint64_t)kFlagPrefix << 32) | (uint32_t)(L.excl + total),
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // escape records of one group, in increasing element index, behind its chunk words, for a group with more escapes

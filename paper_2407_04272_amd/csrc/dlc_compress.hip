@@ -11,11 +11,20 @@
 namespace dlc {
 
 void launch_encode_64(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
-                      uint64_t capacity, uint32_t bpt, hipStream_t s);
+                      uint64_t capacity, hipStream_t s);
+void launch_table_64(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
+                     uint64_t capacity, hipStream_t s);
+hipError_t encode_set_attributes_64();
 void launch_encode_128(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
-                       uint64_t capacity, uint32_t bpt, hipStream_t s);
+                      uint64_t capacity, hipStream_t s);
+void launch_table_128(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
+                     uint64_t capacity, hipStream_t s);
+hipError_t encode_set_attributes_128();
 void launch_encode_256(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
-                       uint64_t capacity, uint32_t bpt, hipStream_t s);
+                      uint64_t capacity, hipStream_t s);
+void launch_table_256(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
+                     uint64_t capacity, hipStream_t s);
+hipError_t encode_set_attributes_256();
 void launch_encode_carry_64(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
                             uint64_t capacity, uint32_t bpt, hipStream_t s);
 void launch_encode_carry_128(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
@@ -52,77 +61,6 @@ hipError_t launch_quantize(const Geom& g, const void* payload, const QParam* qp,
 //   grid: T * bpt work-groups of 4 wavefronts; a work-group stays inside one table, counts into its LDS
 //   histogram and merges that into the table's global one at the end.
 // ------------------------------------------------------------------------------------------------
-typedef __attribute__((address_space(3))) uint32_t lds_u32;
-__device__ __forceinline__ void lds_count(uint32_t addr) {
-    __hip_atomic_fetch_add(reinterpret_cast<lds_u32*>(addr), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-struct HistC {
-    int ubias;          // window index of bin 0
-    uint32_t win_lo;    // symbol of window index 0
-    uint32_t lanebase;  // LDS address of this lane's copy of window row 0
-    uint32_t exact;     // LDS address of the exact counts
-};
-
-// hook for micro-benchmarks (counting switched off); the library counts
-
-constexpr uint32_t kPastEnd = 0x80000001u;  // no element within the radius has this window index: a position past the end of the table
-constexpr uint32_t kHistBlk = 4;  // units whose loads are issued back to back
-
-// One block of kHistBlk units of one table; a unit is 256 consecutive elements (one 16-byte load per lane).
-// `rem` = elements of the table from the block's first element on, `n_units` = units of the block that are this
-// wavefront's.  FULL: all kHistBlk units are, and all their elements are inside the table (no masking at all).
-// Index 254 in the plane stands for an escape.  LZ (row matching): the window is one symbol narrower, because index
-// 253 stands for an element of a row that is stored as a reference (the row-matching kernels put it there
-// afterwards); the symbol that would have had that index goes the way of everything outside the window.
-template <bool F16, bool VEC, bool FULL, bool LZ, bool PLANE = true>
-__device__ __forceinline__ void hist_block(const uint8_t* base, uint32_t rem, uint32_t n_units, uint32_t lane, const QParam& q,
-                                           float Rf, const HistC& H, uint32_t* plane) {
-    constexpr uint32_t kBins = LZ ? kWinSkip : kWinEsc;  // window indices that stand for a symbol
-    float x[kHistBlk][4];
-    uint32_t raw[kHistBlk][4];
-    uint32_t valid[kHistBlk];
-#pragma unroll
-    for (uint32_t u = 0; u < kHistBlk; ++u) {
-        const uint32_t lim = FULL ? 0xFFFFFFFFu : (u < n_units ? rem : 0u);
-        valid[u] = load4<F16, VEC>(base, lane * kV + u * (kW * kV), lim, x[u], raw[u]);
-    }
-#pragma unroll
-    for (uint32_t u = 0; u < kHistBlk; ++u) {
-        uint32_t w[4], sl[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            // the quantiser (same arithmetic as quant_symbol), result as a window index
-            const float xv = x[u][v];
-            const float r = __builtin_rintf(xv * q.inv);
-            float xh = r * q.ebx2;
-            if constexpr (F16) xh = __half2float(half_rne(xh));
-            const float d = xv - xh;
-            const bool ok = (__builtin_fabsf(r) < Rf) & (__builtin_fabsf(d) <= q.eb);  // no short circuit: no branches
-            w[v] = (uint32_t)((int)r + H.ubias);  // (bins below the window wrap to just under 2^32)
-            sl[v] = w[v] < kBins ? w[v] : kWinBins;
-            sl[v] = ok ? sl[v] : kWinEsc;
-            if constexpr (FULL) {
-                lds_count(sl[v] * (kWinCopies * 4u) + H.lanebase);
-            } else {
-                if ((valid[u] >> v) & 1u) lds_count(sl[v] * (kWinCopies * 4u) + H.lanebase);
-                else { sl[v] = kWinBins; w[v] = kPastEnd; }
-            }
-        }
-        // index 255 is rare: count those elements exactly, by symbol (escapes are counted in window row 254, which
-        // the merge adds to symbol 0)
-        if (__ballot(max(max(sl[0], sl[1]), max(sl[2], sl[3])) == kWinBins) != 0ull) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                if (sl[v] == kWinBins && w[v] != kPastEnd) lds_count(H.exact + (w[v] + H.win_lo) * 4u);
-        }
-        // the window indices of these four elements, for the encode kernel (a unit of this wavefront only)
-        if constexpr (PLANE) {
-            if (FULL || u < n_units) plane[u * kW + lane] = sl[0] | (sl[1] << 8) | (sl[2] << 16) | (sl[3] << 24);
-        }
-    }
-}
-
 // The payload is cut into units of 256 elements, U per table, and every wavefront of the grid gets the same
 // number of consecutive units (table after table), so that all of them finish together whatever the shape is.
 // A work-group whose units touch several tables handles them one table at a time.
@@ -143,13 +81,8 @@ __global__ __launch_bounds__(256) void k_hist(const void* payload, Geom g, const
     const uint32_t upg = sa.upg, gstride = sa.gstride;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t lds0 = (uint32_t)(uintptr_t)lh;
-    HistC H;
-    H.win_lo = win_lo_of(g.R);
-    H.ubias = (int)(g.R - H.win_lo);
-    H.lanebase = lds0 + (lane & (kWinCopies - 1u)) * 4u;
-    H.exact = lds0 + (kWinBins + 1u) * kWinCopies * 4u;
+    const uint32_t win_lo = win_lo_of(g.R);
     const uint32_t n_words = (kWinBins + 1u) * kWinCopies + g.K;
-    const float Rf = (float)g.R;
     const uint64_t total_units = (uint64_t)g.T * U;
     // this wavefront's units [w0, w1) and the work-group's [g0, g1), as global unit numbers
     const uint64_t g0 = (uint64_t)blockIdx.x * 4u * units_per_wave;
@@ -164,6 +97,7 @@ __global__ __launch_bounds__(256) void k_hist(const void* payload, Geom g, const
         }
         __syncthreads();
         const QParam q = qp[t];
+        const HistC H = hist_consts<LZ>(g, q, lds0, lane);
         const uint8_t* tab = static_cast<const uint8_t*>(payload) + (size_t)t * g.n * g.es;
         // my units inside table t
         const uint64_t t0 = (uint64_t)t * U, t1 = t0 + U;
@@ -182,8 +116,8 @@ __global__ __launch_bounds__(256) void k_hist(const void* payload, Geom g, const
                 const uint32_t rem = g.n - first;
                 const uint32_t n_units = min(kHistBlk, ue - u);
                 uint32_t* plane = SAMPLE ? nullptr : reinterpret_cast<uint32_t*>(sym_plane + (size_t)t * plane_stride(g) + first);
-                if (n_units == kHistBlk && rem >= kHistBlk * kW * kV) hist_block<F16, VEC, true, LZ, !SAMPLE>(base, rem, n_units, lane, q, Rf, H, plane);
-                else hist_block<F16, VEC, false, LZ, !SAMPLE>(base, rem, n_units, lane, q, Rf, H, plane);
+                if (n_units == kHistBlk && rem >= kHistBlk * kW * kV) hist_block<F16, VEC, true, LZ, !SAMPLE>(base, rem, n_units, lane, q, H, plane);
+                else hist_block<F16, VEC, false, LZ, !SAMPLE>(base, rem, n_units, lane, q, H, plane);
             }
         }
         __syncthreads();
@@ -192,7 +126,7 @@ __global__ __launch_bounds__(256) void k_hist(const void* payload, Geom g, const
         const uint32_t* exact = lh + (kWinBins + 1u) * kWinCopies;
         for (uint32_t k = tid; k < g.K; k += 256) {
             uint32_t s = exact[k];
-            const uint32_t w = k - H.win_lo;
+            const uint32_t w = k - win_lo;
             if (w < (LZ ? kWinSkip : kWinEsc)) {
                 const uint32_t* row = lh + w * kWinCopies;
                 for (uint32_t c = 0; c < kWinCopies; ++c) s += row[(c + tid) & (kWinCopies - 1u)];
@@ -629,43 +563,61 @@ hipError_t launch_compress(const Geom& g, const void* payload, uint8_t* out, uin
         }
         return hipGetLastError();
     }
-    // histogram
-    {
-        // equal shares of 16 units (16 KiB of fp32) per wavefront: measured best on MI355X, a little ahead of one
-        // share per resident wavefront
-        const uint32_t U = (g.n + kW * kV - 1) / (kW * kV);
-        const uint64_t total_units = (uint64_t)g.T * U;
-        const uint32_t units_per_wave = 4 * kHistBlk;
-        const uint32_t grid_n = (uint32_t)((total_units + 4ull * units_per_wave - 1) / (4ull * units_per_wave));
-        const size_t sm = hist_lds_bytes(g.K);
-        dim3 grid(grid_n), block(256);
-        if (prof_on(pl, P_HIST)) prof_begin(prof, P_HIST, s);
-#define DLC_HIST(FF, V, L) hipLaunchKernelGGL((k_hist<FF, V, L>), grid, block, sm, s, payload, g, w.qp, w.hist, w.sym_plane, U, units_per_wave, SampleArgs{})
-        if (g.lz) {  // row matching wants D % 4 == 0, which makes every table start 16-byte aligned with n % 4 == 0
-            if (f16) DLC_HIST(true, true, true); else DLC_HIST(false, true, true);
-        } else if (f16) { if (g.vec) DLC_HIST(true, true, false); else DLC_HIST(true, false, false); }
-        else { if (g.vec) DLC_HIST(false, true, false); else DLC_HIST(false, false, false); }
-#undef DLC_HIST
-        if (prof_on(pl, P_HIST)) prof_end(prof, P_HIST, s);
-    }
-    if (g.lz) {  // row matching: which rows repeat an earlier one; their elements leave the plane and the counts again
-        hipError_t e = launch_row_match(g, payload, w, s);
-        if (e != hipSuccess) return e;
-    }
-    if (prof_on(pl, P_CODEBOOK)) prof_begin(prof, P_CODEBOOK, s);
+    // Small tables go from payload to coded groups in one launch, a work-group per table.  Up to eight groups that is the
+    // shorter way whatever the number of tables (one launch for three; 26 tables of eight groups: 43 us a call against
+    // 45).  Up to sixteen, what a work-group has wavefronts for, it is where there are tables enough to keep the compute
+    // units busy (128 tables of sixteen groups: 67 us against 74; 26 tables: 69 against 48).  Row matching needs every row's
+    // symbols before it knows the counts: it keeps the launches apart, and so do many tables
+    // of a large alphabet, whose scratch memory would leave a compute unit one work-group at a time.
+    const bool fused = !g.lz && (g.G <= 8u || (g.G <= 16u && g.T >= 128u)) && (g.T <= 256u || g.K <= 1024u);
     const uint32_t tpw = codebook_tables_per_wg(g);
-    hipLaunchKernelGGL(k_codebook, dim3((g.T + tpw - 1u) / tpw), dim3(256), codebook_smem(g.K), s, g, w.hist, w.hist_view, w.enc, w.lens,
-                       w.tmeta, 0u, tpw);
-    if (prof_on(pl, P_CODEBOOK)) prof_end(prof, P_CODEBOOK, s);
-    {
-        const uint32_t bpt = (g.G + 3) / 4;
+    if (fused) {
         if (prof_on(pl, P_ENCODE)) prof_begin(prof, P_ENCODE, s);
         switch (g.S) {
-            case 64: launch_encode_64(g, F, payload, w, epoch, out, capacity, bpt, s); break;
-            case 128: launch_encode_128(g, F, payload, w, epoch, out, capacity, bpt, s); break;
-            default: launch_encode_256(g, F, payload, w, epoch, out, capacity, bpt, s); break;
+            case 64: launch_table_64(g, F, payload, w, epoch, out, capacity, s); break;
+            case 128: launch_table_128(g, F, payload, w, epoch, out, capacity, s); break;
+            default: launch_table_256(g, F, payload, w, epoch, out, capacity, s); break;
         }
         if (prof_on(pl, P_ENCODE)) prof_end(prof, P_ENCODE, s);
+    } else {
+        // histogram
+        {
+            // equal shares of 16 units (16 KiB of fp32) per wavefront: measured best on MI355X, a little ahead of one
+            // share per resident wavefront
+            const uint32_t U = (g.n + kW * kV - 1) / (kW * kV);
+            const uint64_t total_units = (uint64_t)g.T * U;
+            // (a small payload is cut finer, so that there is a work-group for every compute unit)
+            uint32_t units_per_wave = 4 * kHistBlk;
+            while (units_per_wave > kHistBlk && total_units < 4ull * 256u * units_per_wave) units_per_wave -= kHistBlk;
+            const uint32_t grid_n = (uint32_t)((total_units + 4ull * units_per_wave - 1) / (4ull * units_per_wave));
+            const size_t sm = hist_lds_bytes(g.K);
+            dim3 grid(grid_n), block(256);
+            if (prof_on(pl, P_HIST)) prof_begin(prof, P_HIST, s);
+#define DLC_HIST(FF, V, L) hipLaunchKernelGGL((k_hist<FF, V, L>), grid, block, sm, s, payload, g, w.qp, w.hist, w.sym_plane, U, units_per_wave, SampleArgs{})
+            if (g.lz) {  // row matching wants D % 4 == 0, which makes every table start 16-byte aligned with n % 4 == 0
+                if (f16) DLC_HIST(true, true, true); else DLC_HIST(false, true, true);
+            } else if (f16) { if (g.vec) DLC_HIST(true, true, false); else DLC_HIST(true, false, false); }
+            else { if (g.vec) DLC_HIST(false, true, false); else DLC_HIST(false, false, false); }
+#undef DLC_HIST
+            if (prof_on(pl, P_HIST)) prof_end(prof, P_HIST, s);
+        }
+        if (g.lz) {  // row matching: which rows repeat an earlier one; their elements leave the plane and the counts again
+            hipError_t e = launch_row_match(g, payload, w, s);
+            if (e != hipSuccess) return e;
+        }
+        if (prof_on(pl, P_CODEBOOK)) prof_begin(prof, P_CODEBOOK, s);
+        hipLaunchKernelGGL(k_codebook, dim3((g.T + tpw - 1u) / tpw), dim3(256), codebook_smem(g.K), s, g, w.hist, w.hist_view, w.enc, w.lens,
+                           w.tmeta, 0u, tpw);
+        if (prof_on(pl, P_CODEBOOK)) prof_end(prof, P_CODEBOOK, s);
+        {
+            if (prof_on(pl, P_ENCODE)) prof_begin(prof, P_ENCODE, s);
+            switch (g.S) {
+                case 64: launch_encode_64(g, F, payload, w, epoch, out, capacity, s); break;
+                case 128: launch_encode_128(g, F, payload, w, epoch, out, capacity, s); break;
+                default: launch_encode_256(g, F, payload, w, epoch, out, capacity, s); break;
+            }
+            if (prof_on(pl, P_ENCODE)) prof_end(prof, P_ENCODE, s);
+        }
     }
     if (prof_on(pl, P_FINALIZE)) prof_begin(prof, P_FINALIZE, s);
     hipLaunchKernelGGL(k_finalize, finalize_grid(g), dim3(1024), 0, s, g, F, w.tmeta, w.lens, w.qp, w.ctrl, w.word_start,
@@ -683,6 +635,9 @@ hipError_t compress_set_attributes() {
     if (e == hipSuccess)
         e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_post), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)codebook_smem(4096));
+    if (e == hipSuccess) e = encode_set_attributes_64();
+    if (e == hipSuccess) e = encode_set_attributes_128();
+    if (e == hipSuccess) e = encode_set_attributes_256();
     return e;
 }
 

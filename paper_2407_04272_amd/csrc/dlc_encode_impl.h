@@ -1,314 +1,680 @@
-// The encode kernel for one chunk size S (DLC_S, defined by the including source file: one file per S keeps
-// the compile times apart).
+// The encode kernels for one chunk size S (DLC_S, defined by the including source file: one file per S keeps the
+// compile times apart): k_encode, which codes the symbol plane of tables of any size with codebooks that are there
+// already, and k_table, which does everything from the payload to the coded groups of a small table in one launch.
+#include <algorithm>
+
 #include "dlc_codec_dev.h"
 
 #define DLC_CAT2(a, b) a##b
 #define DLC_CAT(a, b) DLC_CAT2(a, b)
 
-// wavefronts per SIMD the register allocation aims at
-#define DLC_ENC_WAVES(S) ((S) == 128 ? 3 : 4)
-
 namespace dlc {
 
 // ------------------------------------------------------------------------------------------------
-// bit-packed encode.
-//   walk 1: read the group's window indices from the symbol plane the histogram kernel has written (one byte per
-//           element: 0..253 = symbol win_lo + index, 254 = escape, 255 = everything else), keep them in registers
-//           four to a word, look up the code length of each in LDS and sum the chunk's bits.  Index 255 is rare (a
-//           symbol outside the window, a position past the end of the table): its element is quantised again,
-//           with the code from the full table.  Escapes are counted and where they are is remembered.
-//   scan  : chunk word counts inside the wavefront; the wavefronts' totals (chunk words + two words per
-//           escape) are joined per work-group, and the work-groups' totals across the grid by a single-pass
-//           look-back (ordered work-group ids: a work-group only ever waits for work-groups that started
-//           earlier)
-//   walk 2: look up length and codeword of the kept indices (index 255: the element itself once more), join the
-//           two codes of a pair, shift into a 64-bit accumulator, store whole words at the chunk's offset
-//   escapes: their records (element index, raw bits; in increasing element index, behind the group's chunk words)
-//           are written from the offsets kept in LDS during walk 1, up to 128 per group; a group with more walks
-//           its elements once more in a rolled loop
-// Keeping bytes instead of (length, codeword) entries halves the registers a wavefront holds between the walks,
-// which doubles the wavefronts per SIMD: the kernel is bound by latency (global scan, table look-ups, stores),
-// not by arithmetic.
+// bit-packed encode of groups, one wavefront per group, one walk.
+//   walk  : lane l codes chunk l of its group.  A word of the symbol plane (four window indices) is two look-ups in a
+//           table of PAIRS of symbols in LDS: one dot product of the word's bytes with (4P, 4) is the LDS address of a
+//           pair's entry (joined codeword << 8 | joined length; P = how many symbols the table's used range spans).
+//           The four codewords are appended to a 64-bit accumulator, and the word they complete is stored without a
+//           branch to the lane's LDS column (the row of the last complete word, again and again).  Nothing has to be
+//           known before: there is no first walk that adds the lengths up.
+//   scan  : chunk word counts inside the wavefront, the wavefronts' totals joined per work-group, the work-groups'
+//           totals across the grid by a single-pass look-back (ordered work-group ids: a work-group only ever waits for
+//           work-groups that started earlier)
+//   copy  : the columns to their places, a team of lanes per chunk.  A column holds `cap` words; a group with a longer
+//           chunk is walked again for every further `cap` words (the words of other passes fall on rows nobody reads).
+//   escapes: their records (element index, raw bits; in increasing element index, behind the group's chunk words) are
+//           written from offsets kept in LDS during the walk, up to kEncRecs per group; a group with more walks its
+//           elements once more
+// A table whose used symbols span more than pair_max takes the codewords one by one.  An index with no place in
+// the tables (an escape, a symbol outside the window, a position past the end of the table) sends its word of the plane
+// the long way, for the whole wavefront; a group of which it is known that there are none is not even tested.
+// The kernel this replaced walked every group twice, three 16-bit look-ups an element, fully unrolled: 10 vector
+// instructions an element against 5, and a single group took 40 us, most of it instruction fetches (here the loops are
+// a few hundred instructions).
 // ------------------------------------------------------------------------------------------------
-typedef __attribute__((address_space(3))) uint16_t lds_u16;
-__device__ __forceinline__ uint32_t lds_read16(uint32_t addr, uint32_t byte_off) {
-    return *reinterpret_cast<lds_u16*>(reinterpret_cast<__attribute__((address_space(3))) unsigned char*>(addr) + byte_off);
+constexpr uint32_t kEncRecs = 128;   // escapes a wavefront remembers in LDS (their offsets in the group)
+constexpr uint32_t kColPitch = 65;   // words from a row of the columns to the next: rows of one column lie in different banks
+constexpr uint32_t kPairMax = 63;    // 4P must fit a byte
+
+// LDS of an encoding work-group, in bytes from `at` on: window entries, escape offsets, pair table, columns
+struct EncLds {
+    uint32_t ent, recs, pair, stage, end;
+};
+__host__ __device__ inline EncLds enc_lds(uint32_t nw, uint32_t waves, uint32_t cap, uint32_t pair_max) {
+    EncLds L;
+    L.ent = 0;
+    L.recs = 512u;
+    L.pair = L.recs + nw * kEncRecs * 2u;
+    L.stage = L.pair + ((pair_max * pair_max * 4u + 15u) & ~15u);
+    L.end = L.stage + waves * (cap + 2u) * kColPitch * 4u;
+    return L;
 }
 
-
-// (length << 12 | codeword) of the element at `off` of the group, quantised again; *is_escape says whether it is one
+// (length << 12 | codeword) of the element at `off` of the group, quantised again (a symbol outside the window).  The
+// codewords may come from this very launch: they are read past the caches.
 template <bool F16>
 __device__ __forceinline__ uint32_t entry_of_element(const uint8_t* gbase, uint32_t off, const QParam& q, float Rf, int R,
-                                                     const uint16_t* enc_t, uint32_t* is_escape) {
+                                                     const uint16_t* enc_t) {
     float x;
     if constexpr (F16) x = __half2float(__ushort_as_half(reinterpret_cast<const unsigned short*>(gbase)[off]));
     else x = reinterpret_cast<const float*>(gbase)[off];
-    const uint32_t sym = quant_symbol<F16>(x, q, Rf, R);
-    *is_escape = sym == 0u ? 1u : 0u;
-    return enc_t[sym];
+    return __hip_atomic_load(&enc_t[quant_symbol<F16>(x, q, Rf, R)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ bool has_ff_byte(uint32_t m) {
-    return ((m & 0xFFu) == 0xFFu) | ((m & 0xFF00u) == 0xFF00u) | ((m & 0xFF0000u) == 0xFF0000u) | (m >= 0xFF000000u);
+struct EmitEnv {
+    const uint8_t* gbase;  // first element of the group
+    uint32_t rem;          // elements of the table from there on
+    uint32_t lane;
+    QParam q;
+    float Rf;
+    int R;
+    const uint16_t* enc_t;  // the table's codebook in memory
+    const uint16_t* ent;    // the same by window index, in LDS
+    uint32_t w01, w23, c0;  // a plane word's bytes . w01 + c0 = LDS address of its first pair's entry (w23: of its second's)
+    uint32_t lo4, over4;    // (byte - lo) + over has its high bit set where the byte has no place in the pair table
+    uint32_t col;           // LDS address of this lane's column
+    uint32_t row_max;       // the last row (takes what is not wanted)
+    uint16_t* recs;
+};
+
+struct EmitState {
+    uint64_t acc;   // the chunk's bits so far, the latest at the low end
+    uint32_t nbt;   // how many (in a later pass: less the bits of the passes before, modulo 2^32)
+    uint32_t nesc;  // escapes of the wavefront so far (uniform)
+};
+
+__device__ __forceinline__ void emit_piece(const EmitEnv& E, EmitState& S, uint32_t code, uint32_t len) {  // len <= 32
+    S.acc = (S.acc << len) | code;
+    S.nbt += len;
+    const uint32_t row = min(S.nbt >> 5, E.row_max);
+    *reinterpret_cast<lds_u32*>(E.col + __umul24(row, kColPitch * 4u)) =
+        __builtin_amdgcn_alignbit((uint32_t)(S.acc >> 32), (uint32_t)S.acc, S.nbt);  // (shift: nbt mod 32)
 }
 
-template <int S, bool F16, bool VEC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DLC_ENC_WAVES(S))))
-void k_encode(const void* payload, const uint8_t* sym_plane, Geom g, FixedLayout F, const QParam* qp, const uint16_t* enc,
-              const TMeta* tmeta, Ctrl* ctrl, uint64_t* state, uint64_t epoch, uint8_t* out, uint64_t capacity, uint32_t bpt,
-              uint32_t* word_start, uint32_t* word_end) {
-    __shared__ __align__(16) uint16_t s_len[256], s_code[256];  // by window index; entry 255 is empty
-    __shared__ uint32_t s_wg, s_tot[4], s_ct[4], s_excl, s_dead;
-    // LDS staging per wavefront: room for a group of up to 4.7 bits per symbol, which is what four work-groups per
-    // compute unit leave (with 4 bits a payload compressed 7 times no longer fitted and the kernel took twice as long)
-    constexpr uint32_t kStageWords = 75u * (uint32_t)S / 8u;
-    __shared__ __align__(16) uint32_t s_stage[4 * kStageWords];
-    // escapes a wavefront remembers in LDS (their offsets in the group; the raw bits are read again when the records
-    // are written); a group with more walks its elements again
-    constexpr uint32_t kEncRecs = 128;
-    __shared__ uint16_t s_recs[4 * kEncRecs];
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (tid == 0) s_wg = atomicAdd(&ctrl->ticket, 1u);
-    __syncthreads();
-    const uint32_t wg = __builtin_amdgcn_readfirstlane(s_wg);
-    const uint32_t t = wg / bpt, b = wg % bpt;
-    // the destination this table belongs to: its container starts `capacity` bytes after the previous one, its
-    // groups are numbered and its words are placed from 0, so the scan over work-groups starts anew at its first
-    const uint32_t dst = t / g.TD, tl = t - dst * g.TD;
-    const uint32_t dom0 = dst * g.TD * bpt;
-    out += (uint64_t)dst * capacity;
-    const uint32_t win_lo = win_lo_of(g.R);
-    const uint16_t* enc_t = enc + (size_t)t * g.K;
-    {
-        // (index 254 is the escape, symbol 0; with row matching index 253 marks an element of a row that is stored as
-        // a reference: no bits)
-        const uint32_t c = win_lo + tid;
-        const uint32_t e = tid == kWinEsc ? enc_t[0] : ((tid < win_bins(g.lz) && c < g.K) ? enc_t[c] : 0u);
-        s_len[tid] = (uint16_t)(e >> 12);
-        s_code[tid] = (uint16_t)(e & 0xFFFu);
+// two pairs, each (joined codeword << 8 | joined length), one after the other: at most 24 bits each
+__device__ __forceinline__ void emit_two(const EmitEnv& E, EmitState& S, uint32_t e01, uint32_t e23) {
+    emit_piece(E, S, e01 >> 8, e01 & 31u);
+    emit_piece(E, S, e23 >> 8, e23 & 31u);
+}
+
+__device__ __forceinline__ uint32_t pair_entry(uint32_t a, uint32_t b) {  // of two (length << 12 | codeword)
+    const uint32_t lb = b >> 12;
+    return (((a & 0xFFFu) << lb | (b & 0xFFFu)) << 8) | ((a >> 12) + lb);
+}
+
+// a word of the plane the long way; `off`: its first element's offset in the group; rec: remember its escapes
+template <bool F16>
+__device__ __forceinline__ void emit_slow(const EmitEnv& E, EmitState& S, uint32_t m, uint32_t off, bool rec) {
+    uint32_t e[4], em = 0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const uint32_t b = (m >> (8 * v)) & 0xFFu;
+        const bool in = off + (uint32_t)v < E.rem;  // (whatever the plane holds past the end of the table does not count)
+        e[v] = in ? E.ent[b] : 0u;
+        if (in && b == kWinBins) e[v] = entry_of_element<F16>(E.gbase, off + (uint32_t)v, E.q, E.Rf, E.R, E.enc_t);
+        em |= (in && b == kWinEsc) ? 1u << v : 0u;
     }
-    __syncthreads();
-    const uint32_t grp = b * 4 + wave;
-    const bool active = grp < g.G;  // uniform over the wavefront; an idle wavefront only takes part in the barriers
-    const uint32_t gid = tl * g.G + (active ? grp : 0u);  // group number inside the container
-    const QParam q = qp[t];
-    const float Rf = (float)g.R;
-    const uint8_t* tab = static_cast<const uint8_t*>(payload) + (size_t)t * g.n * g.es;
+    // the records of these escapes, in element order (the walk meets the elements of a group in increasing index:
+    // turn, lane, position)
+    if (rec && __ballot(em != 0u) != 0ull) {
+        const uint32_t cnt = __popc(em);
+        const uint32_t incl = wave_incl_scan(cnt, E.lane);
+        uint32_t r = S.nesc + incl - cnt;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if ((em >> v) & 1u) {
+                if (r < kEncRecs) E.recs[r] = (uint16_t)(off + (uint32_t)v);
+                ++r;
+            }
+        S.nesc += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    }
+    emit_two(E, S, pair_entry(e[0], e[1]), pair_entry(e[2], e[3]));
+}
+
+constexpr uint32_t kEmitBlk = 4;  // words of the plane a trip of the walk takes; those of the next two are on their way meanwhile
+
+// the N words of one trip (at p and every kW words on).  PAIR: the pair table serves (else the codewords one by one);
+// CHECK: a byte may have no place in the tables; LZ: a word may belong to a row that is stored as a reference (all
+// four bytes 253: no bits)
+template <bool F16, bool PAIR, bool CHECK, bool LZ, uint32_t N>
+__device__ __forceinline__ void emit_block(const EmitEnv& E, EmitState& S, const uint32_t (&m)[N], const uint32_t* p, uint32_t off, bool rec) {
+    uint32_t e01[N], e23[N];
+    uint32_t w[N];
+    bool bad = false;
+#pragma unroll
+    for (uint32_t u = 0; u < N; ++u) {
+        w[u] = m[u];
+        const bool ref = LZ && PAIR && w[u] == 0x01010101u * kWinSkip;
+        if constexpr (CHECK) {
+            if constexpr (PAIR) {
+                const uint32_t d = w[u] - E.lo4;
+                const bool b = (((d | (d + E.over4)) & 0x80808080u) != 0u) & !ref;
+                w[u] = b ? E.lo4 : w[u];  // (an address inside the table)
+                bad |= b;
+            } else {  // (index 254 or 255)
+                const uint32_t x = ~(w[u] | 0x01010101u);
+                bad |= ((x - 0x01010101u) & ~x & 0x80808080u) != 0u;
+            }
+        }
+        if (ref) w[u] = E.lo4;
+    }
+    if (CHECK && __builtin_expect(__ballot(bad) != 0ull, 0)) {  // uniform over the wavefront
+#pragma clang loop unroll(disable)
+        for (uint32_t u = 0; u < N; ++u) emit_slow<F16>(E, S, p[u * kW], off + u * (kW * kV), rec);
+        return;
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < N; ++u) {
+        if constexpr (PAIR) {
+            e01[u] = *reinterpret_cast<lds_u32*>(__builtin_amdgcn_udot4(w[u], E.w01, E.c0, false));
+            e23[u] = *reinterpret_cast<lds_u32*>(__builtin_amdgcn_udot4(w[u], E.w23, E.c0, false));
+        } else {
+            e01[u] = pair_entry(E.ent[w[u] & 0xFFu], E.ent[(w[u] >> 8) & 0xFFu]);
+            e23[u] = pair_entry(E.ent[(w[u] >> 16) & 0xFFu], E.ent[w[u] >> 24]);
+        }
+    }
+    uint32_t L[N], most = 0;
+#pragma unroll
+    for (uint32_t u = 0; u < N; ++u) {
+        if (LZ && PAIR && m[u] == 0x01010101u * kWinSkip) { e01[u] = 0u; e23[u] = 0u; }
+        L[u] = (e01[u] + e23[u]) & 63u;  // (48 bits at most)
+        most = max(most, L[u]);
+    }
+    if (__builtin_expect(__ballot(most > 32u) == 0ull, 1)) {  // the rule: four codewords as one piece of at most 32 bits
+#pragma unroll
+        for (uint32_t u = 0; u < N; ++u) emit_piece(E, S, ((e01[u] >> 8) << (e23[u] & 31u)) | (e23[u] >> 8), L[u]);
+    } else {
+#pragma unroll
+        for (uint32_t u = 0; u < N; ++u) emit_two(E, S, e01[u], e23[u]);
+    }
+}
+
+// a walk over the first `els` elements of the group: trips of whole turns, the rest a turn at a time
+template <bool F16, bool PAIR, bool CHECK, bool LZ>
+__device__ __forceinline__ void emit_turns(const EmitEnv& E, EmitState& S, const uint32_t* plane, uint32_t els, bool rec) {
+    const uint32_t* p = plane + E.lane;
+    const uint32_t whole = els / (kW * kV) & ~(kEmitBlk - 1u), turns = (els + kW * kV - 1u) / (kW * kV);
+    if (whole) {
+        uint32_t na[kEmitBlk], nb[kEmitBlk];  // the words of the next trip and of the one after it
+        const uint32_t last = whole - kEmitBlk;
+#pragma unroll
+        for (uint32_t u = 0; u < kEmitBlk; ++u) na[u] = p[u * kW];
+#pragma unroll
+        for (uint32_t u = 0; u < kEmitBlk; ++u) nb[u] = p[(min(kEmitBlk, last) + u) * kW];
+#pragma clang loop unroll(disable)
+        for (uint32_t j = 0; j < whole; j += kEmitBlk) {
+            uint32_t m[kEmitBlk];
+#pragma unroll
+            for (uint32_t u = 0; u < kEmitBlk; ++u) { m[u] = na[u]; na[u] = nb[u]; }
+            const uint32_t jn = min(j + 2u * kEmitBlk, last);
+#pragma unroll
+            for (uint32_t u = 0; u < kEmitBlk; ++u) nb[u] = p[(jn + u) * kW];
+            emit_block<F16, PAIR, CHECK, LZ>(E, S, m, p + j * kW, E.lane * kV + j * (kW * kV), rec);
+        }
+    }
+#pragma clang loop unroll(disable)
+    for (uint32_t j = whole; j < turns; ++j) emit_slow<F16>(E, S, p[j * kW], E.lane * kV + j * (kW * kV), rec);
+}
+
+// What a work-group knows when its tables are in LDS
+struct GroupJob {
+    uint32_t t, tl, dst;    // the table, its place in its container, the container
+    uint32_t wg, dom0;      // this work-group's place in the scan, the first of its scan domain
+    uint32_t grp;           // this wavefront's group (>= g.G: none; the wavefront then only takes part in the barriers)
+    uint32_t lo, P;         // the used symbols span the window indices [lo, lo + P)
+    bool pairs;             // the pair table is there
+    bool special;           // an index without a place in the tables can occur
+    uint32_t cap;           // words of a column
+    uint32_t lds0;          // LDS address of the areas
+    EncLds L;
+};
+
+// walk, scan, copy (see above) for the groups of a work-group of NW wavefronts
+template <int S, bool F16, bool VEC, bool LZ, uint32_t NW>
+__device__ __forceinline__ void encode_groups(const GroupJob& J, const void* payload, const uint8_t* sym_plane, const Geom& g,
+                                              const FixedLayout& F, const QParam* qp, const uint16_t* enc, Ctrl* ctrl, uint64_t* state,
+                                              uint64_t epoch, uint8_t* out, uint64_t capacity, uint32_t* word_start, uint32_t* word_end,
+                                              unsigned char* smem, uint32_t tid) {
+    __shared__ uint32_t s_tot[NW], s_excl, s_dead;
+    const uint32_t lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t grp = J.grp, t = J.t, cap = J.cap;
+    const bool active = grp < g.G;  // uniform over the wavefront
+    const uint32_t gid = J.tl * g.G + (active ? grp : 0u);  // group number inside the container
     const uint32_t gstart = grp * (kW * (uint32_t)S);
-    const uint8_t* gbase = tab + (size_t)gstart * g.es;
-    const uint32_t rem = active ? g.n - gstart : 0u;
-    // can index 255 occur in this group at all?  (an escape, a symbol outside the window, a ragged last group)
-    const TMeta tm = tmeta[t];
-    const bool plain = tm.n_outliers == 0u && tm.sym_lo >= win_lo && tm.sym_hi < win_lo + win_bins(g.lz) && rem >= kW * (uint32_t)S;
-    const uint32_t a_len = (uint32_t)(uintptr_t)s_len, d_code = (uint32_t)(uintptr_t)s_code - a_len;
-
-    uint32_t ix[S / 4];  // window indices, four to a word, in element order
-    uint32_t bits = 0, my_esc = 0, nrec = 0;
-    uint16_t* const recs = s_recs + wave * kEncRecs;
-    if (active) {
-        const uint32_t* plane = reinterpret_cast<const uint32_t*>(sym_plane + (size_t)t * plane_stride(g) + gstart);
-        const bool ragged = rem < kW * (uint32_t)S;  // uniform: the table ends inside this group
-#pragma clang loop unroll(full)
-        for (int j = 0; j < S / 4; ++j) ix[j] = plane[(uint32_t)j * kW + lane];
-        constexpr int kB1 = 4;  // words whose table reads are in flight together
-#pragma clang loop unroll(full)
-        for (int jb = 0; jb < S / 4; jb += kB1) {
-            if (ragged) {  // whatever the plane holds past the end of the table does not count
-#pragma clang loop unroll(full)
-                for (int u = 0; u < kB1; ++u) {
-                    const uint32_t off = lane * kV + (uint32_t)(jb + u) * (kW * kV);
-                    uint32_t m = ix[jb + u];
-#pragma clang loop unroll(full)
-                    for (int v = 0; v < 4; ++v) m |= (off + (uint32_t)v < rem) ? 0u : (0xFFu << (8 * v));
-                    ix[jb + u] = m;
+    const uint8_t* const gbase = static_cast<const uint8_t*>(payload) + ((size_t)t * g.n + gstart) * g.es;
+    const uint32_t* const plane = reinterpret_cast<const uint32_t*>(sym_plane + (size_t)t * plane_stride(g) + gstart);
+    EmitEnv E;
+    E.gbase = gbase;
+    E.rem = active ? g.n - gstart : 0u;
+    E.lane = lane;
+    E.q = qp[t];
+    E.Rf = (float)g.R;
+    E.R = (int)g.R;
+    E.enc_t = enc + (size_t)t * g.K;
+    E.ent = reinterpret_cast<const uint16_t*>(smem + J.L.ent);
+    E.w01 = (4u * J.P) | (4u << 8);
+    E.w23 = E.w01 << 16;
+    E.c0 = J.lds0 + J.L.pair - 4u * J.lo * (J.P + 1u);
+    E.lo4 = J.lo * 0x01010101u;
+    E.over4 = (128u - J.P) * 0x01010101u;
+    E.row_max = cap + 1u;
+    uint32_t* const rows = reinterpret_cast<uint32_t*>(smem + J.L.stage) + (active ? wave : 0u) * ((cap + 2u) * kColPitch);
+    E.col = J.lds0 + (uint32_t)((unsigned char*)rows - smem) + lane * 4u;
+    E.recs = reinterpret_cast<uint16_t*>(smem + J.L.recs) + wave * kEncRecs;
+    const uint32_t in_group = min(E.rem, kW * (uint32_t)S);
+    EmitState St;
+    uint32_t nw = 0, lane_off = 0, chunk_total = 0, n_esc = 0, pass_base = 0;
+    uint32_t* gw = nullptr;
+    for (uint32_t pass = 0;;) {
+        St.acc = 0;
+        St.nbt = 0u - pass_base * 32u;
+        St.nesc = 0;
+        if (active) {
+            const bool rec = pass == 0;
+            if (J.pairs) {
+                if (J.special) emit_turns<F16, true, true, LZ>(E, St, plane, in_group, rec);
+                else emit_turns<F16, true, false, LZ>(E, St, plane, in_group, rec);
+            } else {
+                emit_turns<F16, false, true, LZ>(E, St, plane, in_group, rec);
+            }
+            if (St.nbt & 31u)  // the chunk's last, partly filled word
+                *reinterpret_cast<lds_u32*>(E.col + min((St.nbt >> 5) + 1u, E.row_max) * (kColPitch * 4u)) =
+                    (uint32_t)St.acc << (32u - (St.nbt & 31u));
+        }
+        if (pass == 0) {
+            nw = active ? (St.nbt + 31u) >> 5 : 0u;
+            n_esc = St.nesc;
+            const uint32_t incl = wave_incl_scan(nw, lane);
+            lane_off = incl - nw;
+            chunk_total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            const uint32_t total = chunk_total + 2u * n_esc;  // 0 for an idle wavefront
+            if (lane == 0) s_tot[wave] = total;
+            __syncthreads();
+            if (wave == 0) {
+                uint32_t wg_total = 0;
+                for (uint32_t k = 0; k < NW; ++k) wg_total += s_tot[k];
+                bool failed = false;
+                const uint32_t excl = wg_scan(state, epoch, J.wg, wg_total, lane, ctrl, &failed, J.dom0);
+                if (lane == 0) { s_excl = excl; s_dead = failed ? 1u : 0u; }
+            }
+            __syncthreads();
+            if (!active) return;
+            uint32_t excl = s_excl;
+            for (uint32_t k = 0; k < wave; ++k) excl += s_tot[k];
+            bool dead = s_dead != 0u;  // nothing may be written to the container
+            if (F.off_payload + 4ull * ((uint64_t)excl + total) > capacity) {
+                if (!dead && lane == 0) { set_status(ctrl, DLC_ECAPACITY); atomicOr(&ctrl->abort, kAbortCapacity); }
+                dead = true;
+            }
+            if (lane == 0) {
+                if (grp == 0) word_start[t] = excl;
+                if (grp == g.G - 1) word_end[t] = excl + total;
+            }
+            if (dead) return;
+            out[F.off_chunk + (uint64_t)gid * kW + lane] = (uint8_t)nw;
+            if (lane == 0) reinterpret_cast<uint32_t*>(out + F.off_group)[gid] = excl;
+            gw = reinterpret_cast<uint32_t*>(out + F.off_payload) + excl;
+        }
+        // the columns come from other lanes of this wavefront: its LDS accesses complete in order, the compiler must keep
+        // them in order too
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        {
+            // a team of lanes copies a chunk, a word a lane (as many lanes as a chunk has words at 4 bits a symbol; the
+            // teams' chunks lie so far apart that no two lanes meet in a bank)
+            constexpr uint32_t TL = (uint32_t)S / 8u;
+            const uint32_t team = lane / TL, k0 = lane % TL;
+            const uint32_t n_here = nw > pass_base ? min(nw - pass_base, cap) : 0u;
+            const uint32_t mine = ((lane_off + pass_base) << 8) | n_here;
+            for (uint32_t k = 0; __ballot(n_here > k) != 0ull; k += TL) {  // uniform
+                const uint32_t* const rl = rows + min(k + k0 + 1u, cap + 1u) * kColPitch;
+#pragma clang loop unroll(disable)
+                for (uint32_t i0 = 0; i0 < TL; i0 += 8u) {  // eight chunks in flight: nothing in between waits
+                    uint32_t oc[8], v[8];
+#pragma unroll
+                    for (uint32_t u = 0; u < 8u; ++u) {
+                        const uint32_t c = i0 + u + team * TL;
+                        oc[u] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(c * 4u), (int)mine);
+                        v[u] = rl[c];
+                    }
+#pragma unroll
+                    for (uint32_t u = 0; u < 8u; ++u)
+                        if (k + k0 < (oc[u] & 255u)) gw[(oc[u] >> 8) + k + k0] = v[u];
                 }
             }
-            uint32_t l[kB1][4];
-#pragma clang loop unroll(full)
-            for (int u = 0; u < kB1; ++u)
-#pragma clang loop unroll(full)
-                for (int v = 0; v < 4; ++v) l[u][v] = lds_read16(a_len + (((ix[jb + u] >> (8 * v)) & 0xFFu) << 1), 0);
-#pragma clang loop unroll(full)
-            for (int u = 0; u < kB1; ++u) bits += l[u][0] + l[u][1] + l[u][2] + l[u][3];
-            if (!plain) {  // uniform over the wavefront
-#pragma clang loop unroll(full)
-                for (int u = 0; u < kB1; ++u) {
-                    const uint32_t m = ix[jb + u];
-                    if (__ballot(has_ff_byte(m | 0x01010101u)) == 0ull) continue;  // nothing but window indices
-                    uint32_t em = 0;  // which of the four are escapes (their bits are counted above: the table has their code)
-#pragma clang loop unroll(full)
-                    for (int v = 0; v < 4; ++v) em |= (((m >> (8 * v)) & 0xFFu) == kWinEsc ? 1u : 0u) << v;
-                    my_esc += __popc(em);
-                    if (__ballot(has_ff_byte(m)) != 0ull) {  // symbols outside the window
-#pragma clang loop unroll(full)
-                        for (int v = 0; v < 4; ++v) {
-                            const uint32_t off = lane * kV + (uint32_t)(jb + u) * (kW * kV) + (uint32_t)v;
-                            if (((m >> (8 * v)) & 0xFFu) == 0xFFu && off < rem) {
-                                uint32_t esc;
-                                bits += entry_of_element<F16>(gbase, off, q, Rf, (int)g.R, enc_t, &esc) >> 12;
-                            }
-                        }
-                    }
-                    // the records of these escapes, in element order (the walk meets the elements of a group in
-                    // increasing index: turn, lane, position); kept in LDS while they fit
-                    if (__ballot(em != 0u) != 0ull) {
-                        const uint32_t cnt = __popc(em);
-                        const uint32_t incl = wave_incl_scan(cnt, lane);
-                        uint32_t r = nrec + incl - cnt;
-#pragma clang loop unroll(full)
-                        for (int v = 0; v < 4; ++v)
-                            if ((em >> v) & 1u) {
-                                if (r < kEncRecs) recs[r] = (uint16_t)(lane * kV + (uint32_t)(jb + u) * (kW * kV) + (uint32_t)v);
-                                ++r;
-                            }
-                        nrec += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-                    }
-                }
-            }
         }
+        if (__ballot(nw > pass_base + cap) == 0ull) break;  // uniform
+        ++pass;
+        pass_base += cap;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    const uint32_t n_esc = (plain || !active) ? 0u : wave_sum(my_esc);
-    const uint32_t nw = (bits + 31u) >> 5;
-    const uint32_t incl = wave_incl_scan(nw, lane);
-    const uint32_t lane_off = incl - nw;
-    const uint32_t chunk_total = __shfl(incl, 63, 64);
-    const uint32_t total = chunk_total + 2u * n_esc;  // 0 for an idle wavefront
-
-    // offsets: one scan record per work-group; the wavefronts' totals are joined through LDS.  The look-back over
-    // the records of earlier work-groups is done by the first wavefront, a step at a time, in between its emit
-    // work: walk 2 writes into an LDS staging buffer, which needs no global offset yet, and the words are copied to
-    // their place (coalesced) once the offset is known.  A work-group with a group too large for the staging
-    // buffer waits for its offset first and emits straight to memory.
-    if (lane == 0) { s_tot[wave] = total; s_ct[wave] = chunk_total; }
-    __syncthreads();
-    const uint32_t wg_total = s_tot[0] + s_tot[1] + s_tot[2] + s_tot[3];
-    const bool staged = max(max(s_ct[0], s_ct[1]), max(s_ct[2], s_ct[3])) <= kStageWords;  // uniform over the work-group
-    LookBack L;
-    lb_init(L, wg, dom0);
-    if (wave == 0) lb_publish_aggregate(state, epoch, wg, wg_total, lane, dom0);
-    if (!staged) {
-        if (wave == 0) {
-            lb_finish(L, state, epoch, wg, wg_total, lane, ctrl);
-            if (lane == 0) { s_excl = L.excl; s_dead = L.failed ? 1u : 0u; }
-        }
-        __syncthreads();
-    }
-    uint32_t excl = 0;
-    bool dead = false;  // nothing may be written to the container
-    if (!staged) {
-        dead = s_dead != 0u;
-        excl = s_excl;
-        for (uint32_t k = 0; k < wave; ++k) excl += s_tot[k];
-        if (F.off_payload + 4ull * ((uint64_t)excl + total) > capacity) {
-            if (active && !dead && lane == 0) { set_status(ctrl, DLC_ECAPACITY); atomicOr(&ctrl->abort, kAbortCapacity); }
-            dead = true;
-        }
-    }
-    uint32_t* const stage = s_stage + wave * kStageWords;
-    if (active && !(dead && !staged)) {
-        uint32_t* p = staged ? stage + lane_off : reinterpret_cast<uint32_t*>(out + F.off_payload) + excl + lane_off;
-        uint64_t acc = 0;
-        uint32_t nb = 0;
-        constexpr int kB2 = 2;  // words of indices whose table reads are in flight together
-#pragma clang loop unroll(full)
-        for (int jb = 0; jb < S / 4; jb += kB2) {
-            if (staged && wave == 0 && !L.done && (jb % 8) == 0) {  // uniform: one look-back step per eight words
-                if (L.pending) (void)lb_consume(L, epoch, lane);
-                if (!L.done) lb_issue(L, state, epoch, lane);
-            }
-            uint32_t l[kB2][4], c[kB2][4];
-#pragma clang loop unroll(full)
-            for (int u = 0; u < kB2; ++u) {
-                uint32_t m = ix[jb + u];
-                asm volatile("" : "+v"(m));  // unpack here, not where the word was made
-#pragma clang loop unroll(full)
-                for (int v = 0; v < 4; ++v) {
-                    const uint32_t a = a_len + (((m >> (8 * v)) & 0xFFu) << 1);
-                    l[u][v] = lds_read16(a, 0);
-                    c[u][v] = lds_read16(a, d_code);
-                }
-                if (!plain && __ballot(has_ff_byte(m)) != 0ull) {  // uniform over the wavefront
-#pragma clang loop unroll(full)
-                    for (int v = 0; v < 4; ++v) {
-                        const uint32_t off = lane * kV + (uint32_t)(jb + u) * (kW * kV) + (uint32_t)v;
-                        if (((m >> (8 * v)) & 0xFFu) == 0xFFu && off < rem) {
-                            uint32_t esc;
-                            const uint32_t e = entry_of_element<F16>(gbase, off, q, Rf, (int)g.R, enc_t, &esc);
-                            l[u][v] = e >> 12;
-                            c[u][v] = e & 0xFFFu;
-                        }
-                    }
-                }
-            }
-#pragma clang loop unroll(full)
-            for (int u = 0; u < kB2; ++u)
-#pragma clang loop unroll(full)
-                for (int h = 0; h < 2; ++h) {
-                    const uint32_t len = l[u][2 * h] + l[u][2 * h + 1];  // a pair: at most 24 bits
-                    acc = (acc << len) | ((c[u][2 * h] << l[u][2 * h + 1]) | c[u][2 * h + 1]);
-                    nb += len;
-                    if (nb >= 32u) {
-                        nb -= 32u;
-                        *p++ = (uint32_t)(acc >> nb);
-                    }
-                }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        if (nb) *p = (uint32_t)(acc << (32u - nb));
-    }
-    if (staged) {
-        if (wave == 0) {
-            lb_finish(L, state, epoch, wg, wg_total, lane, ctrl);
-            if (lane == 0) { s_excl = L.excl; s_dead = L.failed ? 1u : 0u; }
-        }
-        __syncthreads();  // also: the staging buffers are complete
-        dead = s_dead != 0u;
-        excl = s_excl;
-        for (uint32_t k = 0; k < wave; ++k) excl += s_tot[k];
-        if (F.off_payload + 4ull * ((uint64_t)excl + total) > capacity) {
-            if (active && !dead && lane == 0) { set_status(ctrl, DLC_ECAPACITY); atomicOr(&ctrl->abort, kAbortCapacity); }
-            dead = true;
-        }
-    }
-    if (!active) return;
-    if (lane == 0) {
-        if (grp == 0) word_start[t] = excl;
-        if (grp == g.G - 1) word_end[t] = excl + total;
-    }
-    if (dead) return;
-    out[F.off_chunk + (uint64_t)gid * kW + lane] = (uint8_t)nw;
-    if (lane == 0) reinterpret_cast<uint32_t*>(out + F.off_group)[gid] = excl;
-    uint32_t* gw = reinterpret_cast<uint32_t*>(out + F.off_payload) + excl;
-    if (staged)
-        for (uint32_t k = lane; k < chunk_total; k += 64) gw[k] = stage[k];
     if (n_esc != 0u) {  // uniform over the wavefront
         uint32_t* rec = gw + chunk_total;
         if (n_esc <= kEncRecs) {  // the records were kept on the way
             for (uint32_t k = lane; k < n_esc; k += 64) {
-                const uint32_t off = recs[k];
+                const uint32_t off = E.recs[k];
                 rec[2u * k] = gstart + off;
                 if constexpr (F16) rec[2u * k + 1] = reinterpret_cast<const uint16_t*>(gbase)[off];
                 else rec[2u * k + 1] = reinterpret_cast<const uint32_t*>(gbase)[off];
             }
         } else {
-            emit_escapes<S, F16, VEC>(rec, lane, gbase, reinterpret_cast<const uint32_t*>(sym_plane + (size_t)t * plane_stride(g) + gstart),
-                                      gstart, rem);
+            emit_escapes<S, F16, VEC>(rec, lane, gbase, plane, gstart, E.rem);
         }
     }
 }
 
-void DLC_CAT(launch_encode_, DLC_S)(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch,
-                                    uint8_t* out, uint64_t capacity, uint32_t bpt, hipStream_t s) {
+// the pair table of the window indices [lo, lo + P), by NT threads
+__device__ __forceinline__ void build_pairs(uint32_t* pair, const uint16_t* ent, uint32_t lo, uint32_t P, uint32_t tid, uint32_t nt) {
+    const uint32_t magic = (1u << 20) / P + 1u;  // i / P for i < P * P <= 63 * 63: exact
+    for (uint32_t i = tid; i < P * P; i += nt) {
+        const uint32_t a = (i * magic) >> 20, b = i - a * P;
+        pair[i] = pair_entry(ent[lo + a], ent[lo + b]);
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// groups of tables of any size, from the symbol plane, with the codebooks in memory
+// ------------------------------------------------------------------------------------------------
+template <int S, bool F16, bool VEC, bool LZ, uint32_t NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4)))
+void k_encode(const void* payload, const uint8_t* sym_plane, Geom g, FixedLayout F, const QParam* qp, const uint16_t* enc,
+              const TMeta* tmeta, Ctrl* ctrl, uint64_t* state, uint64_t epoch, uint8_t* out, uint64_t capacity, uint32_t bpt,
+              uint32_t* word_start, uint32_t* word_end, uint32_t cap, uint32_t pair_max) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ uint32_t s_wg, s_lo, s_hi;
+    const uint32_t tid = threadIdx.x;
+    if (tid == 0) { s_wg = atomicAdd(&ctrl->ticket, 1u); s_lo = 255u; s_hi = 0u; }
+    __syncthreads();
+    GroupJob J;
+    J.wg = __builtin_amdgcn_readfirstlane(s_wg);
+    J.t = J.wg / bpt;
+    J.grp = (J.wg % bpt) * NW + __builtin_amdgcn_readfirstlane(tid >> 6);
+    // the destination this table belongs to: its container starts `capacity` bytes after the previous one, its
+    // groups are numbered and its words are placed from 0, so the scan over work-groups starts anew at its first
+    J.dst = J.t / g.TD;
+    J.tl = J.t - J.dst * g.TD;
+    J.dom0 = J.dst * g.TD * bpt;
+    J.cap = cap;
+    J.lds0 = (uint32_t)(uintptr_t)smem;
+    J.L = enc_lds(NW, NW, cap, pair_max);
+    const uint32_t win_lo = win_lo_of(g.R);
+    const uint16_t* enc_t = enc + (size_t)J.t * g.K;
+    uint16_t* ent = reinterpret_cast<uint16_t*>(smem + J.L.ent);
+    const TMeta tm = tmeta[J.t];
+    for (uint32_t i = tid; i < 256u; i += 64u * NW) {
+        // (index 254 is the escape, symbol 0; with row matching index 253 marks an element of a row that is stored as
+        // a reference: no bits)
+        const uint32_t c = win_lo + i;
+        const bool sym = i < win_bins(LZ ? 1u : 0u) && c < g.K;
+        const uint32_t e = i == kWinEsc ? enc_t[0] : (sym ? enc_t[c] : 0u);
+        ent[i] = (uint16_t)e;
+        // the span of the used symbols inside the window (a table with one used symbol has a code of length 0 for it)
+        if (sym && c != 0u && (e != 0u || (tm.n_used == 1u && c == tm.sym_lo))) { atomicMin(&s_lo, i); atomicMax(&s_hi, i); }
+    }
+    __syncthreads();
+    J.lo = min(s_lo, s_hi);
+    J.P = s_hi - J.lo + 1u;
+    J.pairs = J.P <= pair_max;
+    J.special = tm.n_outliers != 0u || (tm.n_used == 1u && tm.sym_lo == 0u) || (tm.sym_lo != 0u && tm.sym_lo < win_lo) ||
+                tm.sym_hi >= win_lo + win_bins(LZ ? 1u : 0u);
+    if (J.pairs) {
+        build_pairs(reinterpret_cast<uint32_t*>(smem + J.L.pair), ent, J.lo, J.P, tid, 64u * NW);
+        __syncthreads();
+    }
+    encode_groups<S, F16, VEC, LZ, NW>(J, payload, sym_plane, g, F, qp, enc, ctrl, state, epoch, out + (uint64_t)J.dst * capacity,
+                                       capacity, word_start, word_end, smem, tid);
+}
+
+// ------------------------------------------------------------------------------------------------
+// small tables: quantise, count, codebook, encode, a work-group per table
+//   The counts of a table are complete when its work-group's barrier says so, so the codebook needs no launch of its
+//   own and nothing waits for another work-group before the scan.  The payload is read once; the symbol plane goes
+//   through the caches.  What bounds it: with few tables the chain of latencies (loads, one wavefront's tree, the
+//   walk), with many the walk's instructions and the payload's way from memory.
+// ------------------------------------------------------------------------------------------------
+template <int S, bool F16, bool VEC, uint32_t NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4)))
+void k_table(const void* payload, uint8_t* sym_plane, Geom g, FixedLayout F, const QParam* qp, uint32_t* hist_view, uint16_t* enc,
+             uint8_t* lens, TMeta* tmeta, Ctrl* ctrl, uint64_t* state, uint64_t epoch, uint8_t* out, uint64_t capacity,
+             uint32_t* word_start, uint32_t* word_end, uint32_t cap, uint32_t pair_max) {
+    constexpr uint32_t NT = 64u * NW;
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ CodebookShared s_cb;
+    __shared__ uint32_t s_cnt[256];
+    __shared__ uint64_t s_key[64];
+    __shared__ uint32_t s_wg, s_lo, s_hi, s_fast;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid == 0) { s_wg = atomicAdd(&ctrl->ticket, 1u); s_lo = 255u; s_hi = 0u; s_fast = 0u; }
+    // counts: window rows and exact counts, as in the histogram kernel
+    uint32_t* const lh = reinterpret_cast<uint32_t*>(smem);
+    const uint32_t* const exact = lh + (kWinBins + 1u) * kWinCopies;
+    {
+        uint4* z = reinterpret_cast<uint4*>(lh);
+        const uint32_t n4 = ((kWinBins + 1u) * kWinCopies + g.K + 3u) / 4u;
+        for (uint32_t k = tid; k < n4; k += NT) z[k] = make_uint4(0, 0, 0, 0);
+    }
+    __syncthreads();
+    GroupJob J;
+    J.wg = __builtin_amdgcn_readfirstlane(s_wg);
+    const uint32_t t = J.wg;  // a work-group per table, in ticket order
+    J.t = t;
+    J.grp = wave;
+    J.dst = t / g.TD;
+    J.tl = t - J.dst * g.TD;
+    J.dom0 = J.dst * g.TD;
+    J.cap = cap;
+    J.lds0 = (uint32_t)(uintptr_t)smem;
+    J.L = enc_lds(NW, min(NW, g.G), cap, pair_max);
+    {
+        const QParam q = qp[t];
+        const HistC H = hist_consts<false>(g, q, J.lds0, lane);
+        const uint8_t* tab = static_cast<const uint8_t*>(payload) + (size_t)t * g.n * g.es;
+        uint8_t* plane_t = sym_plane + (size_t)t * plane_stride(g);
+        const uint32_t U = (g.n + kW * kV - 1u) / (kW * kV);  // units of 256 elements, a block of four at a time
+        const uint32_t whole = g.n / (kW * kV);               // units that lie inside the table
+        auto first_of = [&](uint32_t u) { return tab + (size_t)u * (kW * kV) * g.es; };
+        auto plane_of = [&](uint32_t u) { return reinterpret_cast<uint32_t*>(plane_t + u * (kW * kV)); };
+        // whole blocks, the next one's loads on their way while one is counted; then the block that the table ends in
+        uint32_t u = wave * kHistBlk;
+        HistLoads<F16, VEC, true> A, B;
+        bool more = u + kHistBlk <= whole;
+        if (more) A.load(first_of(u), 0u, kHistBlk, lane);
+        while (more) {
+            const uint32_t v = u + NW * kHistBlk;
+            const bool next = v + kHistBlk <= whole;
+            if (next) B.load(first_of(v), 0u, kHistBlk, lane);
+            hist_count<F16, VEC, true, false>(A, kHistBlk, lane, q, H, plane_of(u));
+            u = v;
+            if (!next) break;
+            const uint32_t w = v + NW * kHistBlk;
+            more = w + kHistBlk <= whole;
+            if (more) A.load(first_of(w), 0u, kHistBlk, lane);
+            hist_count<F16, VEC, true, false>(B, kHistBlk, lane, q, H, plane_of(v));
+            u = w;
+        }
+        if (u < U)
+            hist_block<F16, VEC, false, false>(first_of(u), g.n - u * (kW * kV), min(kHistBlk, U - u), lane, q, H, plane_of(u));
+    }
+    __syncthreads();
+    for (uint32_t r = tid; r < 256u; r += NT) {  // the copies of a row (skewed start: different banks)
+        uint32_t s = 0;
+        for (uint32_t c = 0; c < kWinCopies; ++c) s += lh[r * kWinCopies + ((c + r) & (kWinCopies - 1u))];
+        s_cnt[r] = s;
+        const uint64_t used = __ballot(r < kWinEsc && s != 0u);  // (whole wavefronts: 256 is a multiple of NT or NT of 256)
+        if (used != 0ull && lane == 0) {
+            atomicMin(&s_lo, r + (uint32_t)__builtin_ctzll(used));
+            atomicMax(&s_hi, r + 63u - (uint32_t)__builtin_clzll(used));
+        }
+    }
+    __syncthreads();
+    const uint32_t n_other = s_cnt[kWinBins];  // elements outside the window (counted exactly, by symbol)
+    uint32_t* const view_t = hist_view + (size_t)t * g.K;
+    uint16_t* const enc_t = enc + (size_t)t * g.K;
+    uint8_t* const lens_t = lens + (size_t)t * g.K;
+    const uint32_t win_lo = win_lo_of(g.R);
+    auto in_window = [&](uint32_t k, uint32_t& idx) {  // symbol -> window index
+        idx = k == 0u ? kWinEsc : k - win_lo;
+        return k == 0u || (k >= win_lo && idx < kWinEsc);
+    };
+    for (uint32_t k = tid; k < g.K; k += NT) {  // the table's counts (inspection, and the codebook of the next call where it is carried)
+        uint32_t idx;
+        const uint32_t s = (in_window(k, idx) ? s_cnt[idx] : 0u) + exact[k];
+        __hip_atomic_store(&view_t[k], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();  // (the counts are dead in LDS from here on, but for s_cnt)
+    uint16_t* const ent = reinterpret_cast<uint16_t*>(smem + J.L.ent);
+    for (uint32_t i = tid; i < 256u; i += NT) ent[i] = 0;
+    __syncthreads();
+    if (n_other == 0u && wave == 0) {
+        const bool done = codebook_window_wave(g, s_cnt, s_key, ent, tmeta + t, lane);
+        if (lane == 0) s_fast = done ? 1u : 0u;
+    }
+    __syncthreads();
+    if (s_fast) {  // uniform
+        for (uint32_t k = tid; k < g.K; k += NT) {
+            uint32_t idx;
+            const uint32_t e = in_window(k, idx) ? ent[idx] : 0u;
+            enc_t[k] = (uint16_t)e;
+            lens_t[k] = (uint8_t)(e >> 12);
+        }
+    } else {  // many symbols, or symbols outside the window: from the counts in memory
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        codebook_build<NT>(g, view_t, view_t, enc_t, lens_t, tmeta + t, smem, s_cb, tid, 0u);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        for (uint32_t i = tid; i < 256u; i += NT) {
+            const uint32_t k = i == kWinEsc ? 0u : win_lo + i;
+            ent[i] = i <= kWinEsc && k < g.K ? __hip_atomic_load(&enc_t[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : (uint16_t)0;
+        }
+        __syncthreads();
+    }
+    J.lo = min(s_lo, s_hi);
+    J.P = s_hi - J.lo + 1u;
+    J.pairs = J.P <= pair_max;
+    J.special = n_other != 0u || s_cnt[kWinEsc] != 0u;
+    if (J.pairs) {
+        build_pairs(reinterpret_cast<uint32_t*>(smem + J.L.pair), ent, J.lo, J.P, tid, NT);
+        __syncthreads();
+    }
+    encode_groups<S, F16, VEC, false, NW>(J, payload, sym_plane, g, F, qp, enc, ctrl, state, epoch, out + (uint64_t)J.dst * capacity,
+                                          capacity, word_start, word_end, smem, tid);
+}
+
+// ---- launches ------------------------------------------------------------------------------------------------------
+constexpr uint32_t kLdsMax = 160u * 1024u;        // of a compute unit
+constexpr uint32_t kTableStatic = 3072u;          // LDS that k_table declares itself (rounded up)
+constexpr uint32_t kEncStatic = 256u;
+constexpr uint32_t kEncLdsMax = kLdsMax - kEncStatic;
+
+// the pair table gets what is left of `budget`
+static inline uint32_t pair_max_for(uint32_t budget, uint32_t nw, uint32_t waves, uint32_t cap) {
+    uint32_t p = kPairMax;
+    while (p > 8u && enc_lds(nw, waves, cap, p).end > budget) --p;
+    return p;
+}
+
+template <uint32_t NW>
+static void DLC_CAT(encode_launch_, DLC_S)(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch,
+                                           uint8_t* out, uint64_t capacity, hipStream_t s) {
     constexpr int S = DLC_S;
-    dim3 grid(g.T * bpt), block(256);
-    const size_t sm = 0;
+    const uint32_t bpt = (g.G + NW - 1u) / NW;
+    dim3 grid(g.T * bpt), block(64 * NW);
+    // sixteen wavefronts a compute unit share its LDS: columns of 4 bits a symbol.  Where the grid leaves room, longer
+    // columns (up to the longest code), so that no group is walked twice.
+    const uint32_t per_cu = std::min(16u / NW, std::max(1u, (g.T * bpt + 255u) / 256u));
+    const uint32_t budget = std::min(kLdsMax / per_cu, kEncLdsMax) - kEncStatic;
+    uint32_t cap = (uint32_t)S * 12u / 32u;
+    while (cap > (uint32_t)S / 8u && enc_lds(NW, NW, cap, 56u).end > budget) --cap;
+    const uint32_t pair_max = pair_max_for(budget, NW, NW, cap);
+    const size_t sm = enc_lds(NW, NW, cap, pair_max).end;
     const bool f16 = g.dtype == DLC_F16;
-#define DLC_ENC(FF, V)                                                                                          \
-    hipLaunchKernelGGL((k_encode<S, FF, V>), grid, block, sm, s, payload, w.sym_plane, g, F, w.qp, w.enc, w.tmeta, w.ctrl, w.state, epoch, \
-                       out, capacity, bpt, w.word_start, w.word_end)
-    if (f16) { if (g.vec) DLC_ENC(true, true); else DLC_ENC(true, false); }
-    else { if (g.vec) DLC_ENC(false, true); else DLC_ENC(false, false); }
+#define DLC_ENC(FF, V, LZ)                                                                                            \
+    hipLaunchKernelGGL((k_encode<S, FF, V, LZ, NW>), grid, block, sm, s, payload, w.sym_plane, g, F, w.qp, w.enc, w.tmeta, w.ctrl, w.state, \
+                       epoch, out, capacity, bpt, w.word_start, w.word_end, cap, pair_max)
+    if (g.lz) { if (f16) DLC_ENC(true, true, true); else DLC_ENC(false, true, true); }  // (dim % 4 == 0 there)
+    else if (f16) { if (g.vec) DLC_ENC(true, true, false); else DLC_ENC(true, false, false); }
+    else { if (g.vec) DLC_ENC(false, true, false); else DLC_ENC(false, false, false); }
 #undef DLC_ENC
+}
+
+void DLC_CAT(launch_encode_, DLC_S)(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch,
+                                    uint8_t* out, uint64_t capacity, hipStream_t s) {
+    // four groups a work-group where that spreads a small payload over more compute units
+    if (g.G <= 4u || g.T * ((g.G + 3u) / 4u) <= 512u) DLC_CAT(encode_launch_, DLC_S)<4u>(g, F, payload, w, epoch, out, capacity, s);
+    else DLC_CAT(encode_launch_, DLC_S)<8u>(g, F, payload, w, epoch, out, capacity, s);
+}
+
+template <uint32_t NW>
+static void DLC_CAT(table_launch_, DLC_S)(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch,
+                                          uint8_t* out, uint64_t capacity, uint32_t cap, uint32_t budget, hipStream_t s) {
+    constexpr int S = DLC_S;
+    dim3 grid(g.T), block(64 * NW);
+    const uint32_t waves = std::min(NW, g.G);
+    const uint32_t pair_max = pair_max_for(budget, NW, waves, cap);
+    size_t sm = enc_lds(NW, waves, cap, pair_max).end;
+    sm = std::max(sm, std::max(hist_lds_bytes(g.K), codebook_smem(g.K)));
+    const bool f16 = g.dtype == DLC_F16;
+#define DLC_TAB(FF, V)                                                                                                \
+    hipLaunchKernelGGL((k_table<S, FF, V, NW>), grid, block, sm, s, payload, w.sym_plane, g, F, w.qp, w.hist_view, w.enc, w.lens, w.tmeta, \
+                       w.ctrl, w.state, epoch, out, capacity, w.word_start, w.word_end, cap, pair_max)
+    if (f16) { if (g.vec) DLC_TAB(true, true); else DLC_TAB(true, false); }
+    else { if (g.vec) DLC_TAB(false, true); else DLC_TAB(false, false); }
+#undef DLC_TAB
+}
+
+void DLC_CAT(launch_table_, DLC_S)(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch,
+                                   uint8_t* out, uint64_t capacity, hipStream_t s) {
+    constexpr uint32_t S = DLC_S;
+    if (g.T <= 256u) {
+        // no more tables than compute units: a work-group has one to itself.  Sixteen wavefronts read a table of more than
+        // one unit each; the columns are as long as the LDS allows (12 bits a symbol is the longest code)
+        uint32_t cap = S * 12u / 32u;
+        while (cap > S / 8u && enc_lds(16u, std::min(16u, g.G), cap, 56u).end > kLdsMax - kTableStatic) --cap;
+        if (g.n <= 16u * kW * kV) DLC_CAT(table_launch_, DLC_S)<4u>(g, F, payload, w, epoch, out, capacity, cap, kLdsMax - kTableStatic, s);
+        else DLC_CAT(table_launch_, DLC_S)<16u>(g, F, payload, w, epoch, out, capacity, cap, kLdsMax - kTableStatic, s);
+    } else {
+        // as many wavefronts as the table has groups, twelve to sixteen a compute unit
+        const uint32_t cap = S / 8u;
+        if (g.G <= 2u) DLC_CAT(table_launch_, DLC_S)<2u>(g, F, payload, w, epoch, out, capacity, cap, kLdsMax / 6u - kTableStatic, s);
+        else if (g.G <= 4u) DLC_CAT(table_launch_, DLC_S)<4u>(g, F, payload, w, epoch, out, capacity, cap, kLdsMax / 3u - kTableStatic, s);
+        else if (g.G <= 8u) DLC_CAT(table_launch_, DLC_S)<8u>(g, F, payload, w, epoch, out, capacity, cap, kLdsMax / 2u - kTableStatic, s);
+        else DLC_CAT(table_launch_, DLC_S)<16u>(g, F, payload, w, epoch, out, capacity, cap, kLdsMax - kTableStatic, s);
+    }
+}
+
+template <uint32_t NW>
+static hipError_t DLC_CAT(encode_attributes_, DLC_S)() {
+    constexpr int S = DLC_S;
+    const int bytes = (int)(kLdsMax - kTableStatic);
+    const void* ks[] = {reinterpret_cast<const void*>(k_table<S, false, false, NW>), reinterpret_cast<const void*>(k_table<S, false, true, NW>),
+                        reinterpret_cast<const void*>(k_table<S, true, false, NW>), reinterpret_cast<const void*>(k_table<S, true, true, NW>)};
+    for (const void* k : ks) {
+        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+hipError_t DLC_CAT(encode_set_attributes_, DLC_S)() {
+    constexpr int S = DLC_S;
+    hipError_t e = DLC_CAT(encode_attributes_, DLC_S)<2u>();
+    if (e == hipSuccess) e = DLC_CAT(encode_attributes_, DLC_S)<4u>();
+    if (e == hipSuccess) e = DLC_CAT(encode_attributes_, DLC_S)<8u>();
+    if (e == hipSuccess) e = DLC_CAT(encode_attributes_, DLC_S)<16u>();
+    const void* ks[] = {reinterpret_cast<const void*>(k_encode<S, false, false, false, 8u>), reinterpret_cast<const void*>(k_encode<S, false, true, false, 8u>),
+                        reinterpret_cast<const void*>(k_encode<S, true, false, false, 8u>), reinterpret_cast<const void*>(k_encode<S, true, true, false, 8u>),
+                        reinterpret_cast<const void*>(k_encode<S, false, true, true, 8u>), reinterpret_cast<const void*>(k_encode<S, true, true, true, 8u>),
+                        reinterpret_cast<const void*>(k_encode<S, false, false, false, 4u>), reinterpret_cast<const void*>(k_encode<S, false, true, false, 4u>),
+                        reinterpret_cast<const void*>(k_encode<S, true, false, false, 4u>), reinterpret_cast<const void*>(k_encode<S, true, true, false, 4u>),
+                        reinterpret_cast<const void*>(k_encode<S, false, true, true, 4u>), reinterpret_cast<const void*>(k_encode<S, true, true, true, 4u>)};
+    for (const void* k : ks)
+        if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kEncLdsMax);
+    return e;
 }
 
 }  // namespace dlc

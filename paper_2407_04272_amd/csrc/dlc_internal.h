@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "dlc.h"
 
 namespace dlc {
@@ -176,18 +178,25 @@ __device__ __forceinline__ uint32_t load4(const void* gbase, uint32_t off, uint3
     }
 }
 
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+// inclusive prefix sum over the 64 lanes (all of them active), in registers: four shifts inside the rows of sixteen
+// lanes, then the rows' sums handed on (six dependent instructions; as six LDS permutes it took 700 cycles)
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, uint32_t) {
+    auto dpp = [](uint32_t x, auto ctrl, auto rows) {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, decltype(rows)::value, 0xF, false);
+    };
+    using std::integral_constant;
+    v += dpp(v, integral_constant<int, 0x111>{}, integral_constant<int, 0xF>{});  // row_shr:1
+    v += dpp(v, integral_constant<int, 0x112>{}, integral_constant<int, 0xF>{});  // row_shr:2
+    v += dpp(v, integral_constant<int, 0x114>{}, integral_constant<int, 0xF>{});  // row_shr:4
+    v += dpp(v, integral_constant<int, 0x118>{}, integral_constant<int, 0xF>{});  // row_shr:8
+    v += dpp(v, integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});  // row_bcast:15 into rows 1 and 3
+    v += dpp(v, integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});  // row_bcast:31 into rows 2 and 3
     return v;
 }
 
-// inclusive prefix sum over the 64 lanes
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, uint32_t lane) {
-    for (int o = 1; o < 64; o <<= 1) {
-        uint32_t u = __shfl_up(v, o, 64);
-        if (lane >= (uint32_t)o) v += u;
-    }
-    return v;
+// sum over the 64 lanes (all of them active)
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v, 0u), 63);
 }
 
 // Exclusive prefix sum over a work-group of NW wavefronts (blockDim.x == 64*NW); every thread gets the
