@@ -211,6 +211,22 @@ static int stats_workspace(const Geom& g, Ws& w) {
     return DLC_OK;
 }
 
+// The kernels' limits of dynamic LDS, set once per device (a hundred calls of the runtime: 0.5 ms of every dlc_create
+// otherwise).
+static hipError_t set_kernel_attributes(int device) {
+    constexpr int kDevices = 64;
+    static std::mutex mu;
+    static bool done[kDevices] = {};
+    std::lock_guard<std::mutex> lock(mu);
+    const bool known = device >= 0 && device < kDevices;
+    if (known && done[device]) return hipSuccess;
+    hipError_t e = compress_set_attributes();
+    if (e == hipSuccess) e = decompress_set_attributes();
+    if (e == hipSuccess) e = row_match_set_attributes();
+    if (e == hipSuccess && known) done[device] = true;
+    return e;
+}
+
 extern "C" int dlc_create(dlc_ctx** out, const dlc_config* cfg) {
     if (!out) return DLC_EINVAL;
     *out = nullptr;
@@ -236,7 +252,7 @@ extern "C" int dlc_create(dlc_ctx** out, const dlc_config* cfg) {
         row_match_multipliers(mult.data(), g.D / 4u);
         if (hipMemcpy(c->ws.rm_mult, mult.data(), 4 * mult.size(), hipMemcpyHostToDevice) != hipSuccess) { (void)hipFree(base); delete c; return DLC_EHIP; }
     }
-    if (compress_set_attributes() != hipSuccess || decompress_set_attributes() != hipSuccess || row_match_set_attributes() != hipSuccess) {
+    if (set_kernel_attributes(c->device) != hipSuccess) {
         (void)hipGetLastError();
         (void)hipFree(base);
         delete c;

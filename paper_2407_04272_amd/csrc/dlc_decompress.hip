@@ -131,45 +131,50 @@ __global__ __launch_bounds__(256) void k_dec_refs(Geom g, FixedLayout F, const u
 // three bits hold it), adv = len1 + len2 then.  Otherwise single = 1 and adv = len1: a second look-up follows,
 // rare for the short codes of frequent symbols.
 //
-// The bit stream words reach the lanes through LDS: every lane copies the next kWin words of its chunk
-// into column `lane` of a [kWin][64] staging array of its wavefront (bank = lane, so the lanes never
-// collide whatever word each of them is at) and refills its window from there.  The decode loop then
-// holds no global load, so nothing in it ever waits for memory: the stores just stream out.
+// The bit stream words reach the lanes through LDS: the words of a group lie one after the other, so a wavefront copies
+// them as they lie (256 bytes an instruction) and every lane reads its own from where its chunk starts.  A group of more
+// words than the staging area (4 bits a symbol with two work-groups on a compute unit) goes a window at a time instead:
+// every lane copies the next kWin words of its chunk into column `lane` of a [kWin][64] array.  That was once the rule; its
+// loads touch 64 lines an instruction, 30 of them a group, and eight wavefronts of a compute unit waited 10 us for them.
+// The decode loop holds no global load, so nothing in it ever waits for memory: the stores just stream out.
 //
 // Per table the work-groups add up the escapes they have applied; the last one to finish compares the sum with the
 // directory entry (counters in the workspace, zero between calls).
 // ------------------------------------------------------------------------------------------------
-constexpr uint32_t kWin = 30;                         // staged words per lane (two work-groups share a CU's LDS)
+constexpr uint32_t kWin = 30;                         // staged words per lane, in columns
+constexpr uint32_t kStage = kWin * kW;                // words of a wavefront's staging area at least (two work-groups share a CU's LDS)
 constexpr uint32_t kDecWaves = 8;                     // wavefronts per work-group; 4 or 2 for tables of fewer groups (a
                                                       // destination's piece of a table can be two groups: no idle wavefronts)
 constexpr uint32_t kSkipWords = 256 * kW / kV / 32;   // row matching: a bit per row of a group, rows of at least four elements
 
-struct DecScratch {  // lives in the staging area until the decode table is complete
+struct DecScratch {  // lives in the staging area until the decode table is complete; one[] is followed by sorted[K] and len[K]
     uint32_t ok;
     uint32_t cl[kLmaxLimit + 2], first[kLmaxLimit + 2], index[kLmaxLimit + 2];
-    uint16_t sorted[4096];
     uint16_t one[1 << kLmaxLimit];  // len << 12 | symbol of the codeword that prefixes the LMAX-bit string i
-    uint8_t len[4096];
+    __device__ uint16_t* sorted() { return reinterpret_cast<uint16_t*>(this + 1); }
+    __device__ uint8_t* len(uint32_t K) { return reinterpret_cast<uint8_t*>(sorted() + K); }
 };
-// bytes behind the decode table: the staging arrays of the NW wavefronts, or the scratch where that is larger
-__host__ __device__ constexpr uint32_t dec_area_bytes(uint32_t nw) {
-    return nw * kWin * kW * 4u > (uint32_t)((sizeof(DecScratch) + 15u) & ~15u) ? nw * kWin * kW * 4u : (uint32_t)((sizeof(DecScratch) + 15u) & ~15u);
+// bytes behind the decode table: the staging areas (`stage` words) of nw wavefronts, or the scratch where that is larger
+__host__ __device__ constexpr uint32_t dec_area_bytes(uint32_t nw, uint32_t stage, uint32_t K) {
+    return nw * stage * 4u > (uint32_t)((sizeof(DecScratch) + 3u * K + 15u) & ~15u) ? nw * stage * 4u : (uint32_t)((sizeof(DecScratch) + 3u * K + 15u) & ~15u);
 }
 
 // (len << 12 | symbol) of the codeword that prefixes the LMAX-bit string i: its length is one more than the number of
 // limits at or below i (limit[l] = first string that no codeword of length <= l prefixes)
-__device__ __forceinline__ uint32_t dec_first_code(const DecScratch& sc, const uint32_t (&limit)[kLmaxLimit + 1], uint32_t i,
+__device__ __forceinline__ uint32_t dec_first_code(DecScratch& sc, const uint32_t (&limit)[kLmaxLimit + 1], uint32_t i,
                                                    uint32_t LMAX) {
     uint32_t l = 1;
 #pragma unroll
     for (uint32_t k = 1; k < (uint32_t)kLmaxLimit; ++k) l += (i >= limit[k]) ? 1u : 0u;
     const uint32_t c = i >> (LMAX - l);
-    return (l << 12) | sc.sorted[sc.index[l] + (c - sc.first[l])];
+    return (l << 12) | sc.sorted()[sc.index[l] + (c - sc.first[l])];
 }
+
+typedef __attribute__((address_space(3))) uint32_t lds_word_t;
 
 template <bool F16, bool VEC, uint32_t NW>
 __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const uint8_t* comp, uint64_t comp_bytes,
-                                                        Ctrl* ctrl, void* outp, uint32_t wpt, uint32_t iters,
+                                                        Ctrl* ctrl, void* outp, uint32_t wpt, uint32_t iters, uint32_t stage_words,
                                                         uint32_t* esc_seen, uint32_t* arrived) {
     constexpr uint32_t kDecThreads = 64u * NW;
     extern __shared__ __align__(16) uint32_t s_lut[];  // [1 << LMAX] decode table, then NW staging arrays
@@ -203,46 +208,63 @@ __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const
     if (tid < kLmaxLimit + 2) sc.cl[tid] = 0;
     __syncthreads();
     const uint32_t nl = H.ok ? H.sym_hi - H.sym_lo + 1u : 0u;
+    uint8_t* const sc_len = sc.len(g.K);
     for (uint32_t i = tid; i < nl; i += kDecThreads) {
         const uint32_t l = comp[H.cb + i];
-        sc.len[i] = (uint8_t)l;
+        sc_len[i] = (uint8_t)l;
         if (l > g.LMAX) sc.ok = 0;
         else if (l) atomicAdd(&sc.cl[l], 1u);
     }
-    // One group of a wavefront: its words (the chunks', then two per escape) checked against the container, then the
-    // lanes' next kWin chunk words fetched into registers.  Branch-free, all loads in flight together: an index past
-    // the chunk's end reads its last word instead (an empty chunk reads the word at its position, which still lies
-    // inside the container: code-length blocks follow the payload) and is masked to zero when it goes to LDS.
-    struct GroupPlace { bool ok; uint32_t n_esc, total; const uint32_t* chunk; };
+    // One group of a wavefront: its words (the chunks', then two per escape) checked against the container.
+    struct GroupPlace { bool ok; uint32_t n_esc, total, off; const uint32_t* words; };  // off: the lane's chunk starts there
     auto group_place = [&](const GroupHead& h) {
         GroupPlace P;
         const uint32_t incl = wave_incl_scan(h.cw, lane);
-        P.total = __shfl(incl, 63, 64);
+        P.total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
         const uint64_t gend = h.gnext == 0xFFFFFFFFu ? H.words_total : (uint64_t)h.gnext;
         P.ok = !(gend > H.words_total || (uint64_t)h.goff + P.total > gend || ((gend - h.goff - P.total) & 1ull));
         P.n_esc = P.ok ? (uint32_t)((gend - h.goff - P.total) >> 1) : 0u;
-        P.chunk = reinterpret_cast<const uint32_t*>(comp + F.off_payload) + h.goff + (incl - h.cw);
+        P.words = reinterpret_cast<const uint32_t*>(comp + F.off_payload) + h.goff;
+        P.off = incl - h.cw;
         return P;
     };
-    auto fetch_words = [&](const uint32_t* chunk, uint32_t cw, uint32_t from, uint32_t (&w)[kWin]) {
+    uint32_t* const stage = s_lut + lut_n + wave * stage_words;
+    // The first kStage words of the group as they lie, into registers.  Branch-free, all loads in flight together: an
+    // index past the group's end reads its last word instead (an empty group the word at its position, which still lies
+    // inside the container: code-length blocks follow the payload).
+    auto fetch_group = [&](const GroupPlace& P, uint32_t (&w)[kWin]) {
+        const uint32_t last = P.total ? P.total - 1u : 0u;
+#pragma unroll
+        for (uint32_t k = 0; k < kWin; ++k) w[k] = P.words[min(k * kW + lane, last)];
+    };
+    auto put_group = [&](const GroupPlace& P, const uint32_t (&w)[kWin]) {
+#pragma unroll
+        for (uint32_t k = 0; k < kWin; ++k) stage[k * kW + lane] = w[k];
+        for (uint32_t k = kStage + lane; k < P.total; k += kW) stage[k] = P.words[k];
+    };
+    // the next kWin words of the lane's chunk (`cw` words from `off` on), for its column; zeros past the chunk's end
+    auto fetch_columns = [&](const GroupPlace& P, uint32_t cw, uint32_t from, uint32_t (&w)[kWin]) {
+        const uint32_t* const chunk = P.words + P.off;
         const uint32_t last = cw ? cw - 1u : 0u;
 #pragma unroll
         for (uint32_t k = 0; k < kWin; ++k) w[k] = chunk[min(from + k, last)];
     };
-    uint32_t* const stage = reinterpret_cast<uint32_t*>(s_lut + lut_n) + wave * (kWin * kW) + lane;  // my column
-    auto put_words = [&](uint32_t cw, uint32_t from, const uint32_t (&w)[kWin]) {
+    auto put_columns = [&](uint32_t cw, uint32_t from, const uint32_t (&w)[kWin]) {
 #pragma unroll
-        for (uint32_t k = 0; k < kWin; ++k) stage[k * kW] = from + k < cw ? w[k] : 0u;
+        for (uint32_t k = 0; k < kWin; ++k) stage[k * kW + lane] = from + k < cw ? w[k] : 0u;
     };
     // the first group's words are on their way while the decode table is made
     GroupPlace gp;
-    gp.ok = false; gp.n_esc = 0; gp.total = 0; gp.chunk = nullptr;
+    gp.ok = false; gp.n_esc = 0; gp.total = 0; gp.off = 0; gp.words = nullptr;
     uint32_t w_first[kWin];
 #pragma unroll
     for (uint32_t k = 0; k < kWin; ++k) w_first[k] = 0;
     if (H.ok && grp_first < g.G) {
         gp = group_place(gh);
-        if (gp.ok) fetch_words(gp.chunk, gh.cw, 0, w_first);
+        if (gp.ok) {
+            if (gp.total <= stage_words) fetch_group(gp, w_first);
+            else fetch_columns(gp, gh.cw, 0, w_first);
+        }
     }
     // the container as a whole: its escapes are those of its tables (first work-group of the container)
     if (H.ok && tl == 0 && b == 0) {
@@ -270,7 +292,7 @@ __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const
     const bool ok2 = sc.ok != 0;  // every thread reads the same value, then nobody writes before the barrier
     __syncthreads();
     if (ok2 && H.n_used == 1) {
-        if (tid == 0 && (H.sym_lo != H.sym_hi || sc.len[0] != 0)) sc.ok = 0;
+        if (tid == 0 && (H.sym_lo != H.sym_hi || sc_len[0] != 0)) sc.ok = 0;
         // length 0: every look-up gives one symbol and moves on by nothing
         for (uint32_t i = tid; i < lut_n; i += kDecThreads) s_lut[i] = 0x80000000u | ((H.sym_lo - g.R) & 0xFFFu);
     } else if (ok2) {
@@ -297,12 +319,12 @@ __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const
                 const uint64_t below = (1ull << lane) - 1ull;
                 for (uint32_t base = 0; base < nl; base += 64) {
                     const uint32_t i = base + lane;
-                    const uint32_t L = i < nl ? sc.len[i] : 0u;
+                    const uint32_t L = i < nl ? sc_len[i] : 0u;
                     if (__ballot(L != 0u) == 0ull) continue;  // (a stretch of unused symbols: the escape symbol's code can lie far below the others)
 #pragma unroll
                     for (uint32_t l = 1; l <= (uint32_t)kLmaxLimit; ++l) {
                         const uint64_t m = __ballot(L == l);
-                        if (L == l) sc.sorted[fill[l] + (uint32_t)__popcll(m & below)] = (uint16_t)(H.sym_lo + i);
+                        if (L == l) sc.sorted()[fill[l] + (uint32_t)__popcll(m & below)] = (uint16_t)(H.sym_lo + i);
                         fill[l] += (uint32_t)__popcll(m);
                     }
                 }
@@ -334,12 +356,21 @@ __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const
                 *reinterpret_cast<uint4*>(&sc.one[i0]) = v;
             }
             __syncthreads();  // (uniform: sc.ok was read after a barrier and nothing has written it since)
-            for (uint32_t i = tid; i < lut_n; i += kDecThreads) {
-                const uint32_t e1 = sc.one[i], l1 = e1 >> 12;
-                const uint32_t e2 = sc.one[(i << l1) & (lut_n - 1u)], l2 = e2 >> 12;  // what follows the first codeword
-                const bool both = l1 + l2 <= g.LMAX && l1 <= 8u;  // the second codeword lies inside the LMAX bits too
-                const uint32_t q1 = ((e1 & 0xFFFu) - g.R) & 0xFFFu, q2 = ((e2 & 0xFFFu) - g.R) & 0xFFFu;
-                s_lut[i] = both ? ((l1 + l2) << 27) | ((l1 - 1u) << 24) | (q2 << 12) | q1 : 0x80000000u | (l1 << 27) | q1;
+            for (uint32_t i0 = tid; i0 < lut_n; i0 += kDecThreads * 4u) {  // four strings in flight per thread
+                uint32_t e1[4], e2[4];
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k) e1[k] = sc.one[(i0 + k * kDecThreads) & (lut_n - 1u)];
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k)  // what follows the first codeword
+                    e2[k] = sc.one[((i0 + k * kDecThreads) << (e1[k] >> 12)) & (lut_n - 1u)];
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k) {
+                    const uint32_t i = i0 + k * kDecThreads, l1 = e1[k] >> 12, l2 = e2[k] >> 12;
+                    const bool both = l1 + l2 <= g.LMAX && l1 <= 8u;  // the second codeword lies inside the LMAX bits too
+                    const uint32_t q1 = ((e1[k] & 0xFFFu) - g.R) & 0xFFFu, q2 = ((e2[k] & 0xFFFu) - g.R) & 0xFFFu;
+                    if (i < lut_n)
+                        s_lut[i] = both ? ((l1 + l2) << 27) | ((l1 - 1u) << 24) | (q2 << 12) | q1 : 0x80000000u | (l1 << 27) | q1;
+                }
             }
         }
     }
@@ -352,48 +383,56 @@ __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const
         const float ebx2 = H.ebx2;
         const uint32_t lshift = 32u - g.LMAX;
         uint8_t* tab = static_cast<uint8_t*>(outp) + (size_t)t * g.n * g.es;
-        const uint32_t turns = g.S / kV;
         const uint32_t* const ref = H.ref_off ? reinterpret_cast<const uint32_t*>(comp + H.ref_off) : nullptr;
-        uint32_t* const skipbits = reinterpret_cast<uint32_t*>(s_lut + lut_n) + dec_area_bytes(NW) / 4u + wave * kSkipWords;
+        uint32_t* const skipbits = reinterpret_cast<uint32_t*>(s_lut + lut_n) + dec_area_bytes(NW, stage_words, g.K) / 4u + wave * kSkipWords;
         for (uint32_t it = 0; it < iters; ++it) {
             const uint32_t grp = grp_first + it * NW;
             if (grp >= g.G) break;  // whole wavefront
             // A lane's place in its bit stream: the two words w0, w1 it is decoding from, `c` bits of w0 already used
-            // (0..31), the word after them in `nxt`, fetched ahead from the staging rows; kr = staging row of `nxt`,
-            // wbase = chunk word index of staging row 0.
-            uint32_t wbase = 0, kr = 0;
-            if (it == 0) {
-                if (gp.ok) put_words(gh.cw, 0, w_first);
-            } else {
+            // (0..31), the word after them in `nxt`, fetched ahead from the staging area; na = LDS address of `nxt`, its
+            // words 1 << sh bytes apart from n0 on, which is word `wbase` of the chunk.
+            if (it != 0) {
                 gh = group_head(grp);
                 gp = group_place(gh);
-                if (gp.ok) {
-                    uint32_t w[kWin];
-                    fetch_words(gp.chunk, gh.cw, 0, w);
-                    put_words(gh.cw, 0, w);
-                }
             }
             if (!gp.ok) {
                 bad = true;
                 continue;
             }
             const uint32_t cw = gh.cw, n_esc = gp.n_esc, total = gp.total;
-            const uint32_t* const chunk = gp.chunk;
-            // the words from `nxt` on, anew, so that `nxt` is row 0
-            // more = words of the chunk past row 0 of the staging rows, less one: a lane needs new rows when `nxt` is
-            // among the last two rows (a turn moves at most two words on) and kr < more
-            int more = (int)cw - 1;
-            auto restage = [&]() {
-                wbase += kr;
-                more -= (int)kr;
-                kr = 0;
+            const bool linear = total <= stage_words;  // uniform
+            const uint32_t st0 = (uint32_t)(uintptr_t)stage;
+            if (linear) {
+                if (it != 0) fetch_group(gp, w_first);
+                put_group(gp, w_first);
+            } else {
+                if (it != 0) fetch_columns(gp, cw, 0, w_first);
+                put_columns(cw, 0, w_first);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // (other lanes' words)
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const uint32_t sh = linear ? 2u : 8u;
+            const uint32_t n0 = st0 + (linear ? gp.off : lane) * 4u;
+            const uint32_t na_max = linear ? st0 + (stage_words - 1u) * 4u : n0 + ((kWin - 1u) << 8);
+            uint32_t wbase = 0, na = n0, c = 0;
+            // columns: a lane needs new rows when `nxt` is among the last two (a turn moves at most two words on), unless its
+            // chunk ends in the rows it has
+            uint32_t renew_at = (!linear && cw > kWin) ? n0 + ((kWin - 2u) << 8) : 0xFFFFFFFFu;
+            auto lds_word = [&](uint32_t a) { return *reinterpret_cast<lds_word_t*>(min(a, na_max)); };
+            auto restage = [&]() {  // the words from `nxt` on, anew, so that `nxt` is row 0
+                wbase += (na - n0) >> 8;
+                na = n0;
                 uint32_t w[kWin];
-                fetch_words(chunk, cw, wbase, w);
-                put_words(cw, wbase, w);
+                fetch_columns(gp, cw, wbase, w);
+                put_columns(cw, wbase, w);
+                renew_at = cw > wbase + kWin ? n0 + ((kWin - 2u) << 8) : 0xFFFFFFFFu;
             };
-            uint32_t w0 = stage[0], w1 = stage[kW], nxt = stage[2u * kW], c = 0;
-            kr = 2;
+            uint32_t w0 = lds_word(na), w1 = lds_word(na + (1u << sh)), nxt = lds_word(na + (2u << sh));
+            na += 2u << sh;
+            const uint32_t one_word = 1u << sh;
             const uint32_t base = grp * (kW * g.S) + lane * kV;
+            const uint32_t turns = (min(g.n - grp * (kW * g.S), kW * g.S) + kW * kV - 1u) / (kW * kV);  // (the table can end in this group)
             // row matching: which rows of this group refer to another row, as a bit per row in LDS (at most 64*S/4 rows)
             const uint32_t row_lo = (grp * (kW * g.S)) / g.D;
             if (ref != nullptr) {
@@ -409,9 +448,7 @@ __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const
             }
             for (uint32_t j = 0; j < turns; ++j) {
                 const uint32_t idx = base + j * (kW * kV);
-                // a turn moves at most two more words; restage (whole wavefront) when a lane that still has words to
-                // fetch could run off its rows
-                if (__ballot(kr >= kWin - 2u && (int)kr < more) != 0ull) restage();
+                if (__ballot(na >= renew_at) != 0ull) restage();  // (whole wavefront)
                 bool coded = idx < g.n;
                 if (ref != nullptr && coded) {  // a row that refers to another has no bits in the stream; it is copied afterwards
                     const uint32_t r = idx / g.D - row_lo;
@@ -439,13 +476,13 @@ __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const
                             }
                         }
                         c += adv;
-                        // past the end of w0: move on by a word (the row after `nxt` is read whether or not: same value then)
+                        // past the end of w0: move on by a word (`nxt` is read whether or not: same value then)
                         const bool step = c > 31u;
                         w0 = step ? w1 : w0;
                         w1 = step ? nxt : w1;
                         c &= 31u;
-                        kr += step ? 1u : 0u;
-                        nxt = stage[min(kr, kWin - 1u) * kW];  // (rows past the chunk's end are zero)
+                        na += step ? one_word : 0u;
+                        nxt = lds_word(na);  // (what lies past the chunk's end is never part of a codeword of its own)
                         v4[h2 * 2] = (float)((int)(e << 20) >> 20) * ebx2;
                         v4[h2 * 2 + 1] = (float)q2 * ebx2;
                     }
@@ -474,8 +511,8 @@ __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const
                     }
                 }
             }
-            // a chunk's codewords end inside its words: w0 is chunk word wbase + kr - 2, and c of its bits are used
-            if (__ballot(32u * (wbase + kr - 2u) + c > 32u * cw) != 0ull) bad = true;
+            // a chunk's codewords end inside its words: w0 is two words before `nxt`, and c of its bits are used
+            if (__ballot(32u * (wbase + ((na - n0) >> sh) - 2u) + c > 32u * cw) != 0ull) bad = true;
             if (n_esc != 0u) {  // uniform over the wavefront: verbatim values over the decoded placeholders
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_s_waitcnt(0);  // the wavefront's own stores above are out before the overwrites below
@@ -560,15 +597,18 @@ hipError_t launch_decompress(const Geom& g, const uint8_t* comp, uint64_t comp_b
         // a work-group decodes `iters` blocks of nw groups of one table, a wavefront each: enough blocks to spread the
         // cost of its decode table, enough work-groups (a few thousand) to fill the chip whatever the shape, and no
         // more wavefronts than a table has groups
-        const uint32_t nw = g.G >= 6u ? kDecWaves : (g.G >= 3u ? 4u : 2u);
+        // (a small grid takes the wavefronts all the same: they make the decode table sooner)
+        const uint32_t nw = (g.G >= 6u || (uint64_t)g.T * g.G <= 512u) ? kDecWaves : (g.G >= 3u ? 4u : 2u);
         const uint32_t bpt = (g.G + nw - 1) / nw;
         const uint64_t blocks = (uint64_t)g.T * bpt;
         const uint32_t iters = (uint32_t)std::min<uint64_t>(4, std::max<uint64_t>(1, blocks / 2048));
         const uint32_t wpt = (bpt + iters - 1) / iters;  // work-groups per table
         dim3 grid(g.T * wpt), block(64 * nw);
-        const size_t sm = ((size_t)4 << g.LMAX) + dec_area_bytes(nw) + (g.lz ? (size_t)nw * kSkipWords * 4 : 0);
+        // a grid that leaves compute units free can have larger staging areas: 6 bits a symbol
+        const uint32_t stage = (uint64_t)g.T * wpt <= 256u ? 3072u : kStage;
+        const size_t sm = ((size_t)4 << g.LMAX) + dec_area_bytes(nw, stage, g.K) + (g.lz ? (size_t)nw * kSkipWords * 4 : 0);
         if (prof_on(pl, P_DECODE)) prof_begin(prof, P_DECODE, s);
-#define DLC_DEC2(FF, V, N) hipLaunchKernelGGL((k_decode<FF, V, N>), grid, block, sm, s, g, F, comp, (uint64_t)comp_bytes, w.ctrl, out, wpt, iters, w.dec_esc, w.dec_arrive)
+#define DLC_DEC2(FF, V, N) hipLaunchKernelGGL((k_decode<FF, V, N>), grid, block, sm, s, g, F, comp, (uint64_t)comp_bytes, w.ctrl, out, wpt, iters, stage, w.dec_esc, w.dec_arrive)
 #define DLC_DEC(FF, V) do { if (nw == 8u) DLC_DEC2(FF, V, 8u); else if (nw == 4u) DLC_DEC2(FF, V, 4u); else DLC_DEC2(FF, V, 2u); } while (0)
         if (f16) { if (g.vec) DLC_DEC(true, true); else DLC_DEC(true, false); }
         else { if (g.vec) DLC_DEC(false, true); else DLC_DEC(false, false); }
@@ -586,7 +626,7 @@ hipError_t launch_decompress(const Geom& g, const uint8_t* comp, uint64_t comp_b
 
 template <uint32_t NW>
 static hipError_t decode_set_attributes() {
-    const int bytes = (4 << kLmaxLimit) + (int)dec_area_bytes(NW) + (int)(NW * kSkipWords * 4);
+    const int bytes = (4 << kLmaxLimit) + (int)dec_area_bytes(NW, 3072u, 4096u) + (int)(NW * kSkipWords * 4);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_decode<false, false, NW>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (e == hipSuccess)
