@@ -209,29 +209,32 @@ __device__ __forceinline__ uint32_t lane_next(uint32_t v, uint32_t last) {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)last, (int)v, 0x130 /* wave_shl:1 */, 0xF, 0xF, false);
 }
 
-// The whole tree of a table with at most 64 used symbols, built by one wavefront without touching memory:
-// lane i holds used symbol i (symbol order) on entry.  The merge keeps leaves and merged nodes in ONE list in lane
+// The whole tree of a table with at most 64 used symbols, built by one wavefront in registers (`par`: 128 bytes of LDS for
+// turning children into parents at the end): lane i holds used symbol i (symbol order) on entry.  The merge keeps leaves and merged nodes in ONE list in lane
 // order, rising by weight: a step takes the two at the front off, moves the list up by two lanes and puts their sum
 // behind everything that is not heavier.  That is the two-queue merge's order, ties included: the leaves are in the
 // list from the start, so a leaf comes before every node of its weight, and of two nodes of one weight the older one
 // comes first.  What bounds a step is its chain of dependent instructions, and no lane number in it depends on an
 // earlier step (two queues with their heads read by computed lane numbers, the first form of this loop, took 345
-// cycles a step; k_codebook for 26 tables of 17 to 51 symbols: 23 us).  Depths come from pointer jumping.  Lengths
+// cycles a step; k_codebook for 26 tables of 17 to 51 symbols: 23 us, now 13).  Depths come from pointer jumping.  Lengths
 // above LM are limited as described above.  Returns the code length of the symbol the lane came in with.  2 <= n <= 64.
-__device__ __forceinline__ uint32_t wave_huffman_lengths(uint32_t n, uint32_t LM, uint32_t cnt, uint32_t lane) {
+__device__ __forceinline__ uint32_t wave_huffman_lengths(uint32_t n, uint32_t LM, uint32_t cnt, uint32_t lane, uint8_t* par) {
     const uint32_t kInf = 0xFFFFFFFFu;
     // position in (count, symbol) order
     uint32_t rank = 0;
-    for (uint32_t j = 0; j < n; ++j) {
-        const uint32_t cj = lane_read(cnt, j);
-        rank += (cj < cnt || (cj == cnt && j < lane)) ? 1u : 0u;
+    for (uint32_t j0 = 0; j0 < n; j0 += 4u) {
+#pragma unroll
+        for (uint32_t u = 0; u < 4u; ++u) {  // (lanes past n - 1, four at a time at most, do not count)
+            const uint32_t j = j0 + u, cj = lane_read(cnt, j & 63u);
+            rank += (j < n && (cj < cnt || (cj == cnt && j < lane))) ? 1u : 0u;
+        }
     }
     if (lane >= n) rank = lane;  // idle lanes keep their place
     // the sorted sequence: every lane sends its count to the lane of its rank
     const uint32_t sent = (uint32_t)__builtin_amdgcn_ds_permute((int)(rank << 2), (int)cnt);
     uint32_t w = lane < n ? sent : kInf;  // weights (a sum of all counts is less than 2^31: kInf is heavier than any)
     uint32_t id = lane;                   // leaf at sorted position id, or 64 + k: merged node k
-    uint32_t vpl = 0, vpn = 0;            // the node above the leaf at sorted position `lane`; above node `lane`
+    uint32_t kids = 0;                    // lane k: the two that node k was made of
     for (uint32_t k = 0; k + 1 < n; ++k) {
         const uint32_t sum = lane_read(w, 0) + lane_read(w, 1);
         const uint32_t a = lane_read(id, 0), b = lane_read(id, 1);
@@ -241,23 +244,28 @@ __device__ __forceinline__ uint32_t wave_huffman_lengths(uint32_t n, uint32_t LM
         const bool here = w1 <= sum;        // (the one in front of it does, or there is none) the sum's place
         w = before ? w2 : (here ? sum : w1);
         id = before ? i2 : (here ? 64u + k : i1);
-        vpl = (lane == a || lane == b) ? k : vpl;
-        vpn = (lane + 64u == a || lane + 64u == b) ? k : vpn;
+        kids = lane == k ? (a | (b << 8)) : kids;
     }
+    if (lane + 1u < n) {
+        par[kids & 127u] = (uint8_t)lane;
+        par[kids >> 8] = (uint8_t)lane;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    // the node above the leaf at sorted position `lane`; above node `lane` (idle lanes: anything)
+    const uint32_t vpl = par[lane] & 63u, vpn = par[64u + lane] & 63u;
     // depth of every merged node (lane k = node k, the root is node n-2)
     const uint32_t root = n - 2u;
     uint32_t p = (lane < root) ? vpn : lane;
     uint32_t d = (lane < root) ? 1u : 0u;
-#pragma unroll
-    for (int r = 0; r < 6; ++r) {
+    for (int r = 0; r < 6 && __ballot(lane < root && p != root) != 0ull; ++r) {  // (until every node has reached the root)
         const uint32_t dd = __shfl(d, p, 64), pp = __shfl(p, p, 64);
         d += dd;
         p = pp;
     }
     uint32_t len = lane < n ? __shfl(d, vpl, 64) + 1u : 0u;  // of the leaf at sorted position `lane`
-    uint32_t m = len;
-    for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor(m, o, 64));
-    if (m > LM) {
+    if (__ballot(len > LM) != 0ull) {
         // cut to LM, then repair the Kraft sum: a code of length LM pairs up with a code taken from the deepest
         // shorter level, one unit at a time.  Lane L of clv holds the number of codes of length L.
         const uint32_t lc = min(len, LM);
@@ -348,8 +356,10 @@ __device__ __forceinline__ bool codebook_build_wave(const Geom& g, uint32_t* his
     __builtin_amdgcn_wave_barrier();
     const uint64_t kv = lane < n_used ? key[lane] : ~0ull;  // lane i: the i-th used symbol
     const uint32_t sym = (uint32_t)(kv & 0xFFFFu);
+    const uint32_t lo = lane_read(sym, 0), hi = lane_read(sym, n_used ? n_used - 1u : 0u);
+    __builtin_amdgcn_wave_barrier();  // (the keys' memory is used again)
     if (n_used >= 2u) {
-        const uint32_t len = wave_huffman_lengths(n_used, g.LMAX, (uint32_t)(kv >> 16), lane);
+        const uint32_t len = wave_huffman_lengths(n_used, g.LMAX, (uint32_t)(kv >> 16), lane, reinterpret_cast<uint8_t*>(key));
         const uint32_t mine_code = wave_canonical_code(len, g.LMAX, below);
         if (lane < n_used) ent[sym] = (uint16_t)((len << 12) | mine_code);
     }
@@ -362,8 +372,8 @@ __device__ __forceinline__ bool codebook_build_wave(const Geom& g, uint32_t* his
     if (lane == 0) {
         TMeta m;
         m.n_used = n_used;
-        m.sym_lo = n_used ? (uint32_t)(key[0] & 0xFFFFu) : 0u;
-        m.sym_hi = n_used ? (uint32_t)(key[n_used - 1u] & 0xFFFFu) : 0u;
+        m.sym_lo = n_used ? lo : 0u;
+        m.sym_hi = n_used ? hi : 0u;
         m.n_outliers = n_escape;  // symbol 0 = escape
         *tmeta_t = m;
     }
@@ -435,7 +445,7 @@ __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, 
         if (wave == 0) {
             const uint64_t kv = lane < n_used ? key[lane] : ~0ull;  // lane i: the i-th used symbol
             const uint32_t sym = (uint32_t)(kv & 0xFFFFu);
-            const uint32_t len = wave_huffman_lengths(n_used, g.LMAX, (uint32_t)(kv >> 16), lane);
+            const uint32_t len = wave_huffman_lengths(n_used, g.LMAX, (uint32_t)(kv >> 16), lane, reinterpret_cast<uint8_t*>(scratch));
             const uint32_t mine_code = wave_canonical_code(len, g.LMAX, (1ull << lane) - 1ull);
             if (lane < n_used) { len_s[sym] = (uint16_t)len; nodew[sym] = mine_code; }
             if (lane == 0) sh.codes_done = 1;
@@ -647,7 +657,7 @@ __device__ __forceinline__ bool codebook_window_wave(const Geom& g, const uint32
     const uint64_t kv = lane < n_used ? key[lane] : ~0ull;  // lane i: the i-th used symbol
     const uint32_t idx = (uint32_t)(kv & 0xFFFFu);
     if (n_used >= 2u) {
-        const uint32_t len = wave_huffman_lengths(n_used, g.LMAX, (uint32_t)(kv >> 16), lane);
+        const uint32_t len = wave_huffman_lengths(n_used, g.LMAX, (uint32_t)(kv >> 16), lane, reinterpret_cast<uint8_t*>(key));
         const uint32_t code = wave_canonical_code(len, g.LMAX, below);
         if (lane < n_used) ent[idx] = (uint16_t)((len << 12) | code);
     }

@@ -208,9 +208,14 @@ __device__ __forceinline__ void finalize_dest(const Geom& g, const FixedLayout& 
     for (uint32_t base = 0; base < T; base += NT) {
         const uint32_t t = base + tid;
         TMeta m;
-        uint32_t cb = 0, no = 0, nl = 0;
+        uint32_t cb = 0, no = 0, nl = 0, w0 = 0, w1 = 0, eb_bits = 0;
         if (t < T) {
             m = tmeta[t];
+            if (first) {  // (what the directory needs, together with the rest: one latency)
+                w0 = __hip_atomic_load(&word_start[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                w1 = __hip_atomic_load(&word_end[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                eb_bits = qp[t].eb_bits;
+            }
             if (first && esc_count) {  // single-pass path: the codebook is older than the payload, the escapes were counted by the encode kernel
                 m.n_outliers = esc_count[t];
                 esc_count[t] = 0;
@@ -252,15 +257,13 @@ __device__ __forceinline__ void finalize_dest(const Geom& g, const FixedLayout& 
             }
         }
         if (first && t < T) {
-            const uint64_t w0 = __hip_atomic_load(&word_start[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint64_t w1 = __hip_atomic_load(&word_end[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             uint8_t* d = out + kHeaderBytes + (uint64_t)kDirBytes * t;
             uint32_t* d32 = reinterpret_cast<uint32_t*>(d);
-            d32[0] = qp[t].eb_bits; d32[1] = m.n_used; d32[2] = m.sym_lo; d32[3] = m.sym_hi; d32[4] = m.n_outliers;
+            d32[0] = eb_bits; d32[1] = m.n_used; d32[2] = m.sym_lo; d32[3] = m.sym_hi; d32[4] = m.n_outliers;
             d32[5] = g.G;
             uint64_t* d64 = reinterpret_cast<uint64_t*>(d + 24);
-            d64[0] = off_cb + cb_carry + cb_ex; d64[1] = 0; d64[2] = w0; d64[3] = w1 - w0;
-            table_bytes[t] = 4ull * (w1 - w0) + cb + (uint64_t)(kW + 4u) * g.G + kDirBytes;
+            d64[0] = off_cb + cb_carry + cb_ex; d64[1] = 0; d64[2] = w0; d64[3] = (uint64_t)(w1 - w0);
+            table_bytes[t] = 4ull * (uint64_t)(w1 - w0) + cb + (uint64_t)(kW + 4u) * g.G + kDirBytes;
         }
         cb_carry += cb_tot;
         nout_carry += no_tot;
@@ -370,13 +373,14 @@ __device__ __forceinline__ void finalize_dest(const Geom& g, const FixedLayout& 
     }
 }
 
-__global__ __launch_bounds__(1024) void k_finalize(Geom g, FixedLayout F, const TMeta* tmeta, const uint8_t* __restrict__ lens,
+template <uint32_t NT>
+__global__ __launch_bounds__(NT) void k_finalize(Geom g, FixedLayout F, const TMeta* tmeta, const uint8_t* __restrict__ lens,
                                                    const QParam* qp, Ctrl* ctrl, const uint32_t* word_start,
                                                    const uint32_t* word_end, uint8_t* __restrict__ out, uint64_t capacity,
                                                    uint64_t* out_bytes, uint32_t* esc_count, const uint8_t* rm_on,
                                                    const uint32_t* rm_ref, uint32_t* bsum) {
     // blockIdx.y: the destination whose container this work-group helps to finish
-    finalize_dest<1024>(g, F, tmeta, lens, qp, ctrl, word_start, word_end, out, capacity, out_bytes, esc_count, rm_on, rm_ref, bsum,
+    finalize_dest<NT>(g, F, tmeta, lens, qp, ctrl, word_start, word_end, out, capacity, out_bytes, esc_count, rm_on, rm_ref, bsum,
                         blockIdx.y, blockIdx.x, gridDim.x);
 }
 
@@ -502,10 +506,12 @@ __global__ __launch_bounds__(256) void k_post(Geom g, FixedLayout F, const uint3
     }
 }
 
-// work-groups of the finalize kernel: a wavefront per table, sixteen wavefronts per work-group
+// work-groups of the finalize kernel (sixteen wavefronts each, four where a container has at most 256 tables: they start
+// sooner and a scan is shorter)
+static inline uint32_t finalize_threads(const Geom& g) { return g.TD <= 256u ? 256u : 1024u; }
 static inline dim3 finalize_grid(const Geom& g) {
     // a wavefront per table for the code-length blocks; with row matching a work-group per table copies its references
-    const uint32_t per_wg = g.lz ? 1u : 16u;
+    const uint32_t per_wg = g.lz ? 1u : finalize_threads(g) / 64u;
     return dim3(std::min<uint32_t>((std::min<uint32_t>(g.TD, 1024u) + per_wg - 1u) / per_wg, 64u), g.ND);
 }
 
@@ -620,8 +626,11 @@ hipError_t launch_compress(const Geom& g, const void* payload, uint8_t* out, uin
         }
     }
     if (prof_on(pl, P_FINALIZE)) prof_begin(prof, P_FINALIZE, s);
-    hipLaunchKernelGGL(k_finalize, finalize_grid(g), dim3(1024), 0, s, g, F, w.tmeta, w.lens, w.qp, w.ctrl, w.word_start,
-                       w.word_end, out, capacity, out_bytes, (uint32_t*)nullptr, g.lz ? (const uint8_t*)w.rm_on : nullptr, (const uint32_t*)w.rm_ref, (uint32_t*)nullptr);
+#define DLC_FIN(N) hipLaunchKernelGGL(k_finalize<N>, finalize_grid(g), dim3(N), 0, s, g, F, w.tmeta, w.lens, w.qp, w.ctrl, w.word_start, \
+                                      w.word_end, out, capacity, out_bytes, (uint32_t*)nullptr, g.lz ? (const uint8_t*)w.rm_on : nullptr, \
+                                      (const uint32_t*)w.rm_ref, (uint32_t*)nullptr)
+    if (finalize_threads(g) == 256u) DLC_FIN(256); else DLC_FIN(1024);
+#undef DLC_FIN
     if (prof_on(pl, P_FINALIZE)) prof_end(prof, P_FINALIZE, s);
     if (w.carry != 0)  // the codebook the next call will use: this call's counts (kept as the copy), escape symbol included
         hipLaunchKernelGGL(k_codebook, dim3((g.T + tpw - 1u) / tpw), dim3(256), codebook_smem(g.K), s, g, w.hist_view, w.hist_view, w.enc_next,

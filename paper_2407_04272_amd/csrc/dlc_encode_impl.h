@@ -478,24 +478,22 @@ void k_table(const void* payload, uint8_t* sym_plane, Geom g, FixedLayout F, con
         const uint32_t whole = g.n / (kW * kV);               // units that lie inside the table
         auto first_of = [&](uint32_t u) { return tab + (size_t)u * (kW * kV) * g.es; };
         auto plane_of = [&](uint32_t u) { return reinterpret_cast<uint32_t*>(plane_t + u * (kW * kV)); };
-        // whole blocks, the next one's loads on their way while one is counted; then the block that the table ends in
+        // whole blocks, the loads of the next two on their way while one is counted (memory takes 3 us to answer when all
+        // compute units ask, and there are few wavefronts); then the block that the table ends in
         uint32_t u = wave * kHistBlk;
-        HistLoads<F16, VEC, true> A, B;
-        bool more = u + kHistBlk <= whole;
-        if (more) A.load(first_of(u), 0u, kHistBlk, lane);
-        while (more) {
-            const uint32_t v = u + NW * kHistBlk;
-            const bool next = v + kHistBlk <= whole;
-            if (next) B.load(first_of(v), 0u, kHistBlk, lane);
-            hist_count<F16, VEC, true, false>(A, kHistBlk, lane, q, H, plane_of(u));
-            u = v;
-            if (!next) break;
-            const uint32_t w = v + NW * kHistBlk;
-            more = w + kHistBlk <= whole;
-            if (more) A.load(first_of(w), 0u, kHistBlk, lane);
-            hist_count<F16, VEC, true, false>(B, kHistBlk, lane, q, H, plane_of(v));
-            u = w;
-        }
+        constexpr uint32_t kStep = NW * kHistBlk;
+        HistLoads<F16, VEC, true> A, B, C;
+        auto have = [&](uint32_t v) { return v + kHistBlk <= whole; };  // uniform over the wavefront
+        if (have(u)) A.load(first_of(u), 0u, kHistBlk, lane);
+        if (have(u + kStep)) B.load(first_of(u + kStep), 0u, kHistBlk, lane);
+        auto turn = [&](HistLoads<F16, VEC, true>& now, HistLoads<F16, VEC, true>& later) {
+            if (!have(u)) return false;
+            if (have(u + 2u * kStep)) later.load(first_of(u + 2u * kStep), 0u, kHistBlk, lane);
+            hist_count<F16, VEC, true, false>(now, kHistBlk, lane, q, H, plane_of(u));
+            u += kStep;
+            return true;
+        };
+        while (turn(A, C) && turn(B, A) && turn(C, B)) {}
         if (u < U)
             hist_block<F16, VEC, false, false>(first_of(u), g.n - u * (kW * kV), min(kHistBlk, U - u), lane, q, H, plane_of(u));
     }
