@@ -249,7 +249,7 @@ __device__ __forceinline__ void carry_load(const CarryEnv& E, uint32_t jb, float
     uint32_t raw[4];
 #pragma unroll
     for (uint32_t u = 0; u < kCarryLoad; ++u)
-        valid[u] = load4<F16, VEC>(E.gbase, E.lane * kV + (jb + u) * (kW * kV), FULL ? 0xFFFFFFFFu : E.rem, x[u], raw);
+        valid[u] = load4<F16, VEC, FULL>(E.gbase, E.lane * kV + (jb + u) * (kW * kV), FULL ? 0xFFFFFFFFu : E.rem, x[u], raw);
 }
 
 // One walk over a group: lane l codes chunk l (at turn j the four elements group_base + j*256 + 4*l .. +3).  The

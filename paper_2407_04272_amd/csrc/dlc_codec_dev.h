@@ -95,7 +95,7 @@ struct HistLoads {
         uint32_t raw[4];
 #pragma unroll
         for (uint32_t u = 0; u < kHistBlk; ++u)
-            valid[u] = load4<F16, VEC>(base, lane * kV + u * (kW * kV), FULL ? 0xFFFFFFFFu : (u < n_units ? rem : 0u), x[u], raw);
+            valid[u] = load4<F16, VEC, FULL>(base, lane * kV + u * (kW * kV), FULL ? 0xFFFFFFFFu : (u < n_units ? rem : 0u), x[u], raw);
     }
 };
 

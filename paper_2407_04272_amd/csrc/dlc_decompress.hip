@@ -446,6 +446,7 @@ __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const
                 }
                 __builtin_amdgcn_wave_barrier();
             }
+            const bool edge = g.n - grp * (kW * g.S) < kW * g.S;  // uniform
             for (uint32_t j = 0; j < turns; ++j) {
                 const uint32_t idx = base + j * (kW * kV);
                 if (__ballot(na >= renew_at) != 0ull) restage();  // (whole wavefront)
@@ -469,7 +470,7 @@ __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const
                                 adv += (int)e2 < 0 ? (e2 >> 27) & 15u : ((e2 >> 24) & 7u) + 1u;
                             }
                         }
-                        if constexpr (!VEC) {  // a turn can reach past the table's end: such a position has no bits
+                        if (!VEC && edge) {  // a turn can reach past the table's end: such a position has no bits
                             if (idx + (uint32_t)(h2 * 2) + 1u >= g.n) {
                                 const uint32_t l1 = (int)e < 0 ? (e >> 27) & 15u : ((e >> 24) & 7u) + 1u;
                                 adv = idx + (uint32_t)(h2 * 2) < g.n ? l1 : 0u;
@@ -486,10 +487,11 @@ __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const
                         v4[h2 * 2] = (float)((int)(e << 20) >> 20) * ebx2;
                         v4[h2 * 2 + 1] = (float)q2 * ebx2;
                     }
-                    // streaming stores: the output is written once and is larger than the caches
-                    if constexpr (VEC) {
+                    // streaming stores: the output is written once and is larger than the caches (four elements at once want
+                    // no more than an element's alignment)
+                    if (VEC || idx + 3u < g.n) {
                         if constexpr (F16) {
-                            typedef uint32_t u2v __attribute__((ext_vector_type(2)));
+                            typedef std::conditional_t<VEC, u32x2, u32x2_any> u2v;
                             u2v o;
                             o.x = (uint32_t)__half_as_ushort(half_rne(v4[0])) |
                                   ((uint32_t)__half_as_ushort(half_rne(v4[1])) << 16);
@@ -497,9 +499,9 @@ __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const
                                   ((uint32_t)__half_as_ushort(half_rne(v4[3])) << 16);
                             __builtin_nontemporal_store(o, reinterpret_cast<u2v*>(reinterpret_cast<uint16_t*>(tab) + idx));
                         } else {
-                            typedef float f4v __attribute__((ext_vector_type(4)));
-                            f4v o4 = {v4[0], v4[1], v4[2], v4[3]};
-                            __builtin_nontemporal_store(o4, reinterpret_cast<f4v*>(reinterpret_cast<float*>(tab) + idx));
+                            typedef std::conditional_t<VEC, u32x4, u32x4_any> u4v;
+                            u4v o4 = {__float_as_uint(v4[0]), __float_as_uint(v4[1]), __float_as_uint(v4[2]), __float_as_uint(v4[3])};
+                            __builtin_nontemporal_store(o4, reinterpret_cast<u4v*>(reinterpret_cast<float*>(tab) + idx));
                         }
                     } else {
 #pragma unroll

@@ -131,28 +131,36 @@ __device__ __forceinline__ uint32_t quant_symbol(float x, const QParam& q, float
     return ok ? (uint32_t)((int)r + R) : 0u;
 }
 
+// four elements of fp32 or half precision on their own boundary, and on an element's
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
 // Four consecutive elements of a group: `gbase` points at the group's first element (uniform over the
 // wavefront), `off` is the element offset inside the group (off % 4 == 0, off < 64*S), `rem` the number of
 // table elements from the group's start on.  Returns the mask of valid positions (off + v < rem); raw[]
 // holds the bit patterns.  Branch-free: a position past the end reads the group's first element instead
 // (always a legal address) and is masked out, so that the loads of several turns can be in flight together;
 // offsets stay 32-bit so that one scalar base and one small vector offset address every load.
-template <bool F16, bool VEC>
+// WHOLE: all four positions of every lane are inside the table.  A load of four elements then wants no more than their own
+// alignment (VEC: every table starts on a 16-byte, or 8-byte, boundary); without it the elements are loaded one by one.
+template <bool F16, bool VEC, bool WHOLE = false>
 __device__ __forceinline__ uint32_t load4(const void* gbase, uint32_t off, uint32_t rem, float x[4], uint32_t raw[4]) {
     const char* gb = static_cast<const char*>(gbase);
-    if constexpr (VEC) {
-        const bool in = off < rem;
+    if constexpr (VEC || WHOLE) {
+        const bool in = WHOLE || off < rem;
         const uint32_t o2 = in ? off : 0u;
         // streaming loads: the payload is read once per kernel and is larger than the caches, so it is kept from
         // displacing what the caches hold (measured: the histogram kernel 150 -> 88 us inside the compress/decompress loop)
         if constexpr (F16) {
-            typedef uint32_t u2v __attribute__((ext_vector_type(2)));
+            typedef std::conditional_t<VEC, u32x2, u32x2_any> u2v;
             const u2v w = __builtin_nontemporal_load(reinterpret_cast<const u2v*>(gb + o2 * 2u));
             raw[0] = w.x & 0xFFFFu; raw[1] = w.x >> 16; raw[2] = w.y & 0xFFFFu; raw[3] = w.y >> 16;
 #pragma unroll
             for (int v = 0; v < 4; ++v) x[v] = __half2float(__ushort_as_half((unsigned short)raw[v]));
         } else {
-            typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+            typedef std::conditional_t<VEC, u32x4, u32x4_any> u4v;
             const u4v w = __builtin_nontemporal_load(reinterpret_cast<const u4v*>(gb + o2 * 4u));
             raw[0] = w.x; raw[1] = w.y; raw[2] = w.z; raw[3] = w.w;
 #pragma unroll
