@@ -201,13 +201,12 @@ static int stats_workspace(const Geom& g, Ws& w) {
     const size_t o_own = take(2ull * g.T * g.B * 4);
     const size_t o_mult = take(16ull * g.D);
     const size_t o_hash = take(2ull * g.T * g.B * 8);
-    const size_t o_mm = take(8ull * g.T);
-    const size_t o_un = take(8ull * g.T);
+    const size_t o_mm = take(16ull * g.T + 8ull);  // what the host reads: ranges, counts, collisions, status
     uint8_t* base = nullptr;
     if (hipMalloc((void**)&base, off) != hipSuccess) { (void)hipGetLastError(); return DLC_ENOMEM; }
     w.stats_base = base; w.stats_bytes = off;
     w.probe = (QParam*)(base + o_probe); w.st_own = (uint32_t*)(base + o_own); w.st_mult = (uint32_t*)(base + o_mult);
-    w.rowhash = (uint64_t*)(base + o_hash); w.st_minmax = (uint32_t*)(base + o_mm); w.st_unique = (uint32_t*)(base + o_un);
+    w.rowhash = (uint64_t*)(base + o_hash); w.st_minmax = (uint32_t*)(base + o_mm); w.st_unique = w.st_minmax + 2 * (size_t)g.T;
     return DLC_OK;
 }
 
@@ -258,12 +257,15 @@ extern "C" int dlc_create(dlc_ctx** out, const dlc_config* cfg) {
         delete c;
         return DLC_EHIP;
     }
-    if (hipHostMalloc((void**)&c->pin, sizeof(QParam) * g.T * dlc_ctx::kRing, hipHostMallocDefault) != hipSuccess) {
+    // (behind the ring: two slots for the statistics' probe bounds and results, 16 bytes a table and two words)
+    if (hipHostMalloc((void**)&c->pin, sizeof(QParam) * g.T * (dlc_ctx::kRing + 2), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         (void)hipFree(base);
         delete c;
         return DLC_ENOMEM;
     }
+    static_assert(2 * sizeof(QParam) >= 16 + 8, "the statistics' results fit two slots");
+    c->ws.st_pin = c->pin + (size_t)g.T * dlc_ctx::kRing;
     for (int i = 0; i < dlc_ctx::kRing; ++i)
         if (hipEventCreateWithFlags(&c->pin_ev[i], hipEventDisableTiming) != hipSuccess) {
             dlc_destroy(c);
@@ -612,20 +614,20 @@ extern "C" int dlc_stats(dlc_ctx* c, const void* d_payload, const float* probe_e
     hipStream_t s = (hipStream_t)stream;
     Ws& w = c->ws;
     if (const int rc = stats_workspace(g, w); rc != DLC_OK) return rc;
-    std::vector<QParam> pq(g.T);
+    // (one pinned buffer serves the way up and the way down: the call waits for each before the next)
+    QParam* const pq = static_cast<QParam*>(w.st_pin);
     for (uint32_t t = 0; t < g.T; ++t) pq[t] = make_qparam(probe_eb[t]);
-    std::vector<uint32_t> mm(2 * g.T), un(2 * g.T);
-    if (hipMemcpyAsync(w.probe, pq.data(), sizeof(QParam) * g.T, hipMemcpyHostToDevice, s) != hipSuccess) return DLC_EHIP;
+    if (hipMemcpyAsync(w.probe, pq, sizeof(QParam) * g.T, hipMemcpyHostToDevice, s) != hipSuccess) return DLC_EHIP;
     for (uint32_t attempt = 0; attempt < 4; ++attempt) {
         // (the first kernel of the reduction clears the range words, the counts and the collision counter)
-        if (launch_stats(g, d_payload, w.probe, w, 0x51ED270Bu * (attempt + 1), s) != hipSuccess) return DLC_EHIP;
-        uint32_t collide = 0;
-        int32_t st = 0;
-        if (hipMemcpyAsync(mm.data(), w.st_minmax, 8ull * g.T, hipMemcpyDeviceToHost, s) != hipSuccess) return DLC_EHIP;
-        if (hipMemcpyAsync(un.data(), w.st_unique, 8ull * g.T, hipMemcpyDeviceToHost, s) != hipSuccess) return DLC_EHIP;
-        if (hipMemcpyAsync(&collide, &w.ctrl->collide, 4, hipMemcpyDeviceToHost, s) != hipSuccess) return DLC_EHIP;
-        if (hipMemcpyAsync(&st, &w.ctrl->status, 4, hipMemcpyDeviceToHost, s) != hipSuccess) return DLC_EHIP;
-        if (hipStreamSynchronize(s) != hipSuccess) return DLC_EHIP;
+        hipError_t e = launch_stats(g, d_payload, w.probe, w, 0x51ED270Bu * (attempt + 1), s);
+        // ranges, counts, collisions and status lie together: one copy brings them (four, from pageable memory, took 100 us)
+        const uint32_t* const mm = static_cast<const uint32_t*>(w.st_pin);
+        const uint32_t* const un = mm + 2 * (size_t)g.T;
+        if (e == hipSuccess) e = hipMemcpyAsync(w.st_pin, w.st_minmax, 16ull * g.T + 8ull, hipMemcpyDeviceToHost, s);
+        if (hipStreamSynchronize(s) != hipSuccess || e != hipSuccess) return DLC_EHIP;
+        const uint32_t collide = un[2 * (size_t)g.T];
+        const int32_t st = (int32_t)un[2 * (size_t)g.T + 1];
         if (st != DLC_OK) {
             if (hipMemset(&w.ctrl->status, 0, 4) != hipSuccess) return DLC_EHIP;
             return st;

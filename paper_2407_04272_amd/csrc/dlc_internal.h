@@ -291,7 +291,8 @@ struct Ws {
     uint32_t* st_own = nullptr;    // [2][T][B] the smallest row index with the row's hash
     uint32_t* st_mult = nullptr;   // [D][4] multipliers of the row hashes
     uint32_t* st_minmax = nullptr; // [T][2] order-preserving encodings
-    uint32_t* st_unique = nullptr; // [T][2]
+    uint32_t* st_unique = nullptr; // [T][2], then the collisions and the status word of the call
+    void* st_pin = nullptr;        // pinned host memory for the probe bounds and for the results
 };
 
 // profiling hooks used by the launchers (implemented in dlc_api.hip)

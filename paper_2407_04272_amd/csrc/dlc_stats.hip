@@ -305,6 +305,12 @@ __global__ __launch_bounds__(256) void k_stats_verify(const void* payload, Geom 
     if (__ballot(differ) != 0ull && lane == 0) atomicAdd(&ctrl->collide, 1u);
 }
 
+// the words of the control block that the host wants, behind the results
+__global__ void k_stats_result(const Ctrl* ctrl, uint32_t* out) {
+    out[0] = ctrl->collide;
+    out[1] = (uint32_t)ctrl->status;
+}
+
 hipError_t launch_stats(const Geom& g, const void* payload, const QParam* probe, const Ws& w, uint32_t salt, hipStream_t s) {
     // few, long-running work-groups per table: every wavefront ends with atomics on its table's two range words
     const uint32_t blocks_x = std::min<uint32_t>((g.B + 255u) / 256u, DLC_STATS_BLOCKS);  // a wavefront takes 64 rows at a time
@@ -332,6 +338,7 @@ hipError_t launch_stats(const Geom& g, const void* payload, const QParam* probe,
     if (g.dtype == DLC_F16) { if (vec) DLC_ST_VERIFY(true, 4); else DLC_ST_VERIFY(true, 1); }
     else { if (vec) DLC_ST_VERIFY(false, 4); else DLC_ST_VERIFY(false, 1); }
 #undef DLC_ST_VERIFY
+    hipLaunchKernelGGL(k_stats_result, dim3(1), dim3(1), 0, s, w.ctrl, w.st_unique + 2 * (size_t)g.T);
     return hipGetLastError();
 }
 
