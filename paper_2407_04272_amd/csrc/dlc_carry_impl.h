@@ -257,19 +257,20 @@ __device__ __forceinline__ void carry_load(const CarryEnv& E, uint32_t jb, float
 // (xa, va) are already on their way when the walk starts.
 template <int S, bool F16, bool VEC, bool FULL, bool REWALK = false>
 __device__ __forceinline__ void carry_walk(const CarryEnv& E, CarryState& St, float (&xa)[kCarryLoad][4], uint32_t (&va)[kCarryLoad]) {
-    constexpr uint32_t N = (uint32_t)S / kV;  // turns
+    constexpr uint32_t N = (uint32_t)S / kV;  // turns of a whole group; the table can end in this one
+    const uint32_t n_turns = FULL ? N : min(N, ((E.rem + kW * kV - 1u) / (kW * kV) + 2u * kCarryLoad - 1u) & ~(2u * kCarryLoad - 1u));
     static_assert(N % (2 * kCarryLoad) == 0 && kCarryLoad % kCarryBlk == 0, "two load blocks per trip, whole work blocks per load block");
     typedef const float (&XBlk)[kCarryBlk][4];
     typedef const uint32_t (&VBlk)[kCarryBlk];
     float xb[kCarryLoad][4];
     uint32_t vb[kCarryLoad];
-    for (uint32_t jb = 0; jb < N; jb += 2 * kCarryLoad) {
+    for (uint32_t jb = 0; jb < n_turns; jb += 2 * kCarryLoad) {
         set_wave_priority(jb / (2 * kCarryLoad) + E.rank);
         carry_load<F16, VEC, FULL>(E, jb + kCarryLoad, xb, vb);
 #pragma unroll
         for (uint32_t k = 0; k < kCarryLoad; k += kCarryBlk)
             carry_block<F16, FULL, REWALK>(E, reinterpret_cast<XBlk>(xa[k]), reinterpret_cast<VBlk>(va[k]), jb + k, St);
-        if (jb + 2 * kCarryLoad < N) carry_load<F16, VEC, FULL>(E, jb + 2 * kCarryLoad, xa, va);
+        if (jb + 2 * kCarryLoad < n_turns) carry_load<F16, VEC, FULL>(E, jb + 2 * kCarryLoad, xa, va);
 #pragma unroll
         for (uint32_t k = 0; k < kCarryLoad; k += kCarryBlk)
             carry_block<F16, FULL, REWALK>(E, reinterpret_cast<XBlk>(xb[k]), reinterpret_cast<VBlk>(vb[k]), jb + kCarryLoad + k, St);
@@ -281,7 +282,7 @@ template <int S, bool F16, bool VEC>
 __device__ __forceinline__ void carry_emit_escapes(uint32_t* rec, uint32_t lane, const uint8_t* gbase, uint32_t gstart,
                                                    uint32_t rem, const QParam& q, float Rf, int R, const uint16_t* enc_t) {
     uint32_t opos = 0;
-    for (uint32_t j = 0; j < (uint32_t)S / kV; ++j) {
+    for (uint32_t j = 0; j < (uint32_t)S / kV && j * (kW * kV) < rem; ++j) {
         const uint32_t off = lane * kV + j * (kW * kV);
         float x[4];
         uint32_t raw[4];
