@@ -435,6 +435,9 @@ __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const
             const uint32_t turns = (min(g.n - grp * (kW * g.S), kW * g.S) + kW * kV - 1u) / (kW * kV);  // (the table can end in this group)
             // row matching: which rows of this group refer to another row, as a bit per row in LDS (at most 64*S/4 rows)
             const uint32_t row_lo = (grp * (kW * g.S)) / g.D;
+            // local / D as a multiplication (a division of its own is a third of a turn's instructions): with the reciprocal
+            // rounded up it is exact while local * D < 2^32, and local < 64 * S + D
+            const uint32_t row_magic = (ref != nullptr && g.D > 1u && g.D <= 32768u) ? 0xFFFFFFFFu / g.D + 1u : 0u;
             if (ref != nullptr) {
                 const uint32_t last_el = min(g.n, (grp + 1u) * (kW * g.S)) - 1u;
                 const uint32_t n_rows = last_el / g.D - row_lo + 1u;  // <= 64*S/4 because dim % 4 == 0 here
@@ -452,7 +455,7 @@ __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const
                 if (__ballot(na >= renew_at) != 0ull) restage();  // (whole wavefront)
                 bool coded = idx < g.n;
                 if (ref != nullptr && coded) {  // a row that refers to another has no bits in the stream; it is copied afterwards
-                    const uint32_t r = idx / g.D - row_lo;
+                    const uint32_t local = idx - row_lo * g.D, r = row_magic ? __umulhi(local, row_magic) : local / g.D;
                     coded = ((skipbits[r >> 5] >> (r & 31u)) & 1u) == 0u;
                 }
                 if (coded) {
