@@ -161,6 +161,7 @@ __global__ __launch_bounds__(256) void k_codebook(Geom g, uint32_t* hist, uint32
 // many, four tables per work-group, a wavefront each (a quarter of the work-groups, and no idle wavefronts while
 // one of them builds the tree).
 static inline uint32_t codebook_tables_per_wg(const Geom& g) { return g.T >= 512u ? 4u : 1u; }
+static inline size_t codebook_lds(const Geom& g, uint32_t tpw) { return tpw == 4u ? codebook_four_smem(g.K) : codebook_smem(g.K); }
 
 // ------------------------------------------------------------------------------------------------
 // finalize: code-length blocks behind the payload, header, directory, padding, size metadata; clears the
@@ -542,7 +543,7 @@ hipError_t launch_compress(const Geom& g, const void* payload, uint8_t* out, uin
         if (prof_on(pl, P_HIST)) prof_end(prof, P_HIST, s);
         if (prof_on(pl, P_CODEBOOK)) prof_begin(prof, P_CODEBOOK, s);
         const uint32_t tpw = codebook_tables_per_wg(g);
-        hipLaunchKernelGGL(k_codebook, dim3((g.T + tpw - 1u) / tpw), dim3(256), codebook_smem(g.K), s, g, w.hist, w.hist_view, w.enc, w.lens,
+        hipLaunchKernelGGL(k_codebook, dim3((g.T + tpw - 1u) / tpw), dim3(256), codebook_lds(g, tpw), s, g, w.hist, w.hist_view, w.enc, w.lens,
                            w.tmeta, 1u, tpw);
         if (prof_on(pl, P_CODEBOOK)) prof_end(prof, P_CODEBOOK, s);
     }
@@ -562,7 +563,7 @@ hipError_t launch_compress(const Geom& g, const void* payload, uint8_t* out, uin
             const uint32_t nf = std::min<uint32_t>((std::min<uint32_t>(g.TD, 256u) + 3u) / 4u, 64u);  // a wavefront per table's code-length block
             if (prof_on(pl, P_POST)) prof_begin(prof, P_POST, s);
             const uint32_t tpw = w.sample != 0 ? 0u : codebook_tables_per_wg(g);
-            hipLaunchKernelGGL(k_post, dim3((tpw ? (g.T + tpw - 1u) / tpw : 0u) + g.ND * nf + n_place), dim3(256), codebook_smem(g.K), s, g, F, w.gtot, w.bsum,
+            hipLaunchKernelGGL(k_post, dim3((tpw ? (g.T + tpw - 1u) / tpw : 0u) + g.ND * nf + n_place), dim3(256), codebook_lds(g, tpw), s, g, F, w.gtot, w.bsum,
                                w.bsum_next, w.slots, (uint64_t)carry_slot_words(g), w.ctrl, out, capacity, wpd, nf, w.word_start,
                                w.word_end, w.tmeta, w.lens, w.qp, out_bytes, w.esc_count, w.hist, w.hist_view, w.enc_next,
                                w.lens_next, w.tmeta_next, tpw);
@@ -613,7 +614,7 @@ hipError_t launch_compress(const Geom& g, const void* payload, uint8_t* out, uin
             if (e != hipSuccess) return e;
         }
         if (prof_on(pl, P_CODEBOOK)) prof_begin(prof, P_CODEBOOK, s);
-        hipLaunchKernelGGL(k_codebook, dim3((g.T + tpw - 1u) / tpw), dim3(256), codebook_smem(g.K), s, g, w.hist, w.hist_view, w.enc, w.lens,
+        hipLaunchKernelGGL(k_codebook, dim3((g.T + tpw - 1u) / tpw), dim3(256), codebook_lds(g, tpw), s, g, w.hist, w.hist_view, w.enc, w.lens,
                            w.tmeta, 0u, tpw);
         if (prof_on(pl, P_CODEBOOK)) prof_end(prof, P_CODEBOOK, s);
         {
@@ -634,17 +635,17 @@ hipError_t launch_compress(const Geom& g, const void* payload, uint8_t* out, uin
 #undef DLC_FIN
     if (prof_on(pl, P_FINALIZE)) prof_end(prof, P_FINALIZE, s);
     if (w.carry != 0)  // the codebook the next call will use: this call's counts (kept as the copy), escape symbol included
-        hipLaunchKernelGGL(k_codebook, dim3((g.T + tpw - 1u) / tpw), dim3(256), codebook_smem(g.K), s, g, w.hist_view, w.hist_view, w.enc_next,
+        hipLaunchKernelGGL(k_codebook, dim3((g.T + tpw - 1u) / tpw), dim3(256), codebook_lds(g, tpw), s, g, w.hist_view, w.hist_view, w.enc_next,
                            w.lens_next, w.tmeta_next, 1u, tpw);
     return hipGetLastError();
 }
 
 hipError_t compress_set_attributes() {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_codebook), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)codebook_smem(4096));
+                                       (int)codebook_four_smem(4096));
     if (e == hipSuccess)
         e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_post), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)codebook_smem(4096));
+                                (int)codebook_four_smem(4096));
     if (e == hipSuccess) e = encode_set_attributes_64();
     if (e == hipSuccess) e = encode_set_attributes_128();
     if (e == hipSuccess) e = encode_set_attributes_256();
