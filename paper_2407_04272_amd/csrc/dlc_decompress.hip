@@ -1,5 +1,7 @@
 // Decompression kernels for gfx950: container validation, decode tables and chunk-parallel decode in one kernel,
 // escape scatter, row copies.
+#include <stddef.h>
+
 #include <algorithm>
 
 #include "dlc_internal.h"
@@ -150,10 +152,11 @@ constexpr uint32_t kSkipWords = 256 * kW / kV / 32;   // row matching: a bit per
 struct DecScratch {  // lives in the staging area until the decode table is complete; one[] is followed by sorted[K] and len[K]
     uint32_t ok;
     uint32_t cl[kLmaxLimit + 2], first[kLmaxLimit + 2], index[kLmaxLimit + 2];
-    uint16_t one[1 << kLmaxLimit];  // len << 12 | symbol of the codeword that prefixes the LMAX-bit string i
+    alignas(16) uint16_t one[1 << kLmaxLimit];  // len << 12 | symbol of the codeword that prefixes the LMAX-bit string i; filled 16 bytes at a time
     __device__ uint16_t* sorted() { return reinterpret_cast<uint16_t*>(this + 1); }
     __device__ uint8_t* len(uint32_t K) { return reinterpret_cast<uint8_t*>(sorted() + K); }
 };
+static_assert(offsetof(DecScratch, one) % 16 == 0 && sizeof(DecScratch) % 16 == 0, "stores of 16 bytes (the decode table before it has at least 16 entries)");
 // bytes behind the decode table: the staging areas (`stage` words) of nw wavefronts, or the scratch where that is larger
 __host__ __device__ constexpr uint32_t dec_area_bytes(uint32_t nw, uint32_t stage, uint32_t K) {
     return nw * stage * 4u > (uint32_t)((sizeof(DecScratch) + 3u * K + 15u) & ~15u) ? nw * stage * 4u : (uint32_t)((sizeof(DecScratch) + 3u * K + 15u) & ~15u);
