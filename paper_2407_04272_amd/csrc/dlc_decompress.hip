@@ -135,16 +135,18 @@ __global__ __launch_bounds__(256) void k_dec_refs(Geom g, FixedLayout F, const u
 //
 // The bit stream words reach the lanes through LDS: the words of a group lie one after the other, so a wavefront copies
 // them as they lie (256 bytes an instruction) and every lane reads its own from where its chunk starts.  A group of more
-// words than the staging area (4 bits a symbol with two work-groups on a compute unit) goes a window at a time instead:
-// every lane copies the next kWin words of its chunk into column `lane` of a [kWin][64] array.  That was once the rule; its
-// loads touch 64 lines an instruction, 30 of them a group, and eight wavefronts of a compute unit waited 10 us for them.
-// The decode loop holds no global load, so nothing in it ever waits for memory: the stores just stream out.
+// words than the staging area (3.75 bits a symbol with two work-groups on a compute unit) goes a window at a time instead:
+// the next kWin words of every chunk, a row of the staging area each, copied by a team of lanes a chunk.  (A lane copying
+// its own chunk's words touched 64 lines an instruction: 512 MiB at 4.3 bits a symbol 139 us, now 125; at 6.4 bits 166, now
+// 137.)  Nothing in the decode loop but a new window waits for memory: the stores just stream out.
 //
 // Per table the work-groups add up the escapes they have applied; the last one to finish compares the sum with the
 // directory entry (counters in the workspace, zero between calls).
 // ------------------------------------------------------------------------------------------------
-constexpr uint32_t kWin = 30;                         // staged words per lane, in columns
-constexpr uint32_t kStage = kWin * kW;                // words of a wavefront's staging area at least (two work-groups share a CU's LDS)
+constexpr int kWaitLoads = 0x0F70;                    // s_waitcnt vmcnt(0) and nothing else
+constexpr uint32_t kRows = 30;                        // a wavefront's staging area has at least kRows words a lane (two work-groups share a CU's LDS)
+constexpr uint32_t kStage = kRows * kW;
+constexpr uint32_t kWin = 29;                         // words of a chunk in a window (odd: the lanes' rows start in different banks)
 constexpr uint32_t kDecWaves = 8;                     // wavefronts per work-group; 4 or 2 for tables of fewer groups (a
                                                       // destination's piece of a table can be two groups: no idle wavefronts)
 constexpr uint32_t kSkipWords = 256 * kW / kV / 32;   // row matching: a bit per row of a group, rows of at least four elements
@@ -176,7 +178,7 @@ __device__ __forceinline__ uint32_t dec_first_code(DecScratch& sc, const uint32_
 typedef __attribute__((address_space(3))) uint32_t lds_word_t;
 
 template <bool F16, bool VEC, uint32_t NW>
-__global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const uint8_t* comp, uint64_t comp_bytes,
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) void k_decode(Geom g, FixedLayout F, const uint8_t* comp, uint64_t comp_bytes,
                                                         Ctrl* ctrl, void* outp, uint32_t wpt, uint32_t iters, uint32_t stage_words,
                                                         uint32_t* esc_seen, uint32_t* arrived) {
     constexpr uint32_t kDecThreads = 64u * NW;
@@ -235,38 +237,62 @@ __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const
     // The first kStage words of the group as they lie, into registers.  Branch-free, all loads in flight together: an
     // index past the group's end reads its last word instead (an empty group the word at its position, which still lies
     // inside the container: code-length blocks follow the payload).
-    auto fetch_group = [&](const GroupPlace& P, uint32_t (&w)[kWin]) {
+    auto word_at = [&](const GroupPlace& P, uint32_t i) {  // (a 32-bit byte offset from a uniform base: one register an address)
+        return *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(P.words) + i * 4u);
+    };
+    auto fetch_group = [&](const GroupPlace& P, uint32_t (&w)[kRows]) {
         const uint32_t last = P.total ? P.total - 1u : 0u;
 #pragma unroll
-        for (uint32_t k = 0; k < kWin; ++k) w[k] = P.words[min(k * kW + lane, last)];
+        for (uint32_t k = 0; k < kRows; ++k) w[k] = word_at(P, min(k * kW + lane, last));
     };
-    auto put_group = [&](const GroupPlace& P, const uint32_t (&w)[kWin]) {
+    auto put_group = [&](const GroupPlace& P, const uint32_t (&w)[kRows]) {
 #pragma unroll
-        for (uint32_t k = 0; k < kWin; ++k) stage[k * kW + lane] = w[k];
+        for (uint32_t k = 0; k < kRows; ++k) stage[k * kW + lane] = w[k];
         for (uint32_t k = kStage + lane; k < P.total; k += kW) stage[k] = P.words[k];
     };
-    // the next kWin words of the lane's chunk (`cw` words from `off` on), for its column; zeros past the chunk's end
-    auto fetch_columns = [&](const GroupPlace& P, uint32_t cw, uint32_t from, uint32_t (&w)[kWin]) {
-        const uint32_t* const chunk = P.words + P.off;
-        const uint32_t last = cw ? cw - 1u : 0u;
+    // A window: the words of every chunk from its lane's `from` on (counted inside the chunk), min(TL, kWin) a chunk, by
+    // teams of TL lanes, a chunk a team; the loads [I0, I0 + w's size) of the TL that make the window.  What follows a chunk's
+    // end comes from the next chunk; nothing past the group's end is read.
+    auto fetch_window = [&](auto tl, auto i0, const GroupPlace& P, uint32_t from, auto& w) {
+        constexpr uint32_t TL = decltype(tl)::value, I0 = decltype(i0)::value;
+        const uint32_t at = P.off + from, team = lane / TL, k = lane % TL, last = P.total - 1u;
 #pragma unroll
-        for (uint32_t k = 0; k < kWin; ++k) w[k] = chunk[min(from + k, last)];
+        for (uint32_t i = 0; i < sizeof(w) / 4u; ++i)
+            w[i] = word_at(P, min((uint32_t)__builtin_amdgcn_ds_bpermute((int)(((I0 + i) * (kW / TL) + team) * 4u), (int)at) + k, last));
     };
-    auto put_columns = [&](uint32_t cw, uint32_t from, const uint32_t (&w)[kWin]) {
+    auto put_window = [&](auto tl, auto i0, const auto& w) {
+        constexpr uint32_t TL = decltype(tl)::value, I0 = decltype(i0)::value;
+        const uint32_t team = lane / TL, k = lane % TL;
+        if (k < kWin) {
 #pragma unroll
-        for (uint32_t k = 0; k < kWin; ++k) stage[k * kW + lane] = from + k < cw ? w[k] : 0u;
+            for (uint32_t i = 0; i < sizeof(w) / 4u; ++i) stage[((I0 + i) * (kW / TL) + team) * kWin + k] = w[i];
+        }
     };
+    // the words come from other lanes of the wavefront.  The wait: a window's lanes that store nothing leave their loads unread,
+    // and without it, which costs nothing here, the compiler waits for those inside the loop of the turns, and so for every
+    // turn's store (a single group: 27.6 us -> 30)
+    auto staged = [&]() {
+        __builtin_amdgcn_s_waitcnt(kWaitLoads);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    using std::integral_constant;
+    constexpr integral_constant<uint32_t, 0> k0{};
+    constexpr integral_constant<uint32_t, 16> k16{};
+    constexpr integral_constant<uint32_t, 32> k32{};
+    constexpr integral_constant<uint32_t, kRows> kr{};
     // the first group's words are on their way while the decode table is made
     GroupPlace gp;
     gp.ok = false; gp.n_esc = 0; gp.total = 0; gp.off = 0; gp.words = nullptr;
-    uint32_t w_first[kWin];
+    uint32_t w_first[kRows];
 #pragma unroll
-    for (uint32_t k = 0; k < kWin; ++k) w_first[k] = 0;
+    for (uint32_t k = 0; k < kRows; ++k) w_first[k] = 0;
     if (H.ok && grp_first < g.G) {
         gp = group_place(gh);
         if (gp.ok) {
             if (gp.total <= stage_words) fetch_group(gp, w_first);
-            else fetch_columns(gp, gh.cw, 0, w_first);
+            else fetch_window(k32, k0, gp, 0u, w_first);
         }
     }
     // the container as a whole: its escapes are those of its tables (first work-group of the container)
@@ -392,8 +418,8 @@ __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const
             const uint32_t grp = grp_first + it * NW;
             if (grp >= g.G) break;  // whole wavefront
             // A lane's place in its bit stream: the two words w0, w1 it is decoding from, `c` bits of w0 already used
-            // (0..31), the word after them in `nxt`, fetched ahead from the staging area; na = LDS address of `nxt`, its
-            // words 1 << sh bytes apart from n0 on, which is word `wbase` of the chunk.
+            // (0..31), the word after them in `nxt`, fetched ahead from the staging area; na = LDS address of `nxt`, n0 that of
+            // word `wbase` of the chunk.
             if (it != 0) {
                 gh = group_head(grp);
                 gp = group_place(gh);
@@ -409,31 +435,39 @@ __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const
                 if (it != 0) fetch_group(gp, w_first);
                 put_group(gp, w_first);
             } else {
-                if (it != 0) fetch_columns(gp, cw, 0, w_first);
-                put_columns(cw, 0, w_first);
+                if (it != 0) fetch_window(k32, k0, gp, 0u, w_first);
+                put_window(k32, k0, w_first);
+                uint32_t w[32u - kRows];
+                fetch_window(k32, kr, gp, 0u, w);
+                put_window(k32, kr, w);
             }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // (other lanes' words)
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const uint32_t sh = linear ? 2u : 8u;
-            const uint32_t n0 = st0 + (linear ? gp.off : lane) * 4u;
-            const uint32_t na_max = linear ? st0 + (stage_words - 1u) * 4u : n0 + ((kWin - 1u) << 8);
+            staged();
+            const uint32_t n0 = st0 + (linear ? gp.off : lane * kWin) * 4u;
+            const uint32_t na_max = st0 + (stage_words - 1u) * 4u;
             uint32_t wbase = 0, na = n0, c = 0;
-            // columns: a lane needs new rows when `nxt` is among the last two (a turn moves at most two words on), unless its
-            // chunk ends in the rows it has
-            uint32_t renew_at = (!linear && cw > kWin) ? n0 + ((kWin - 2u) << 8) : 0xFFFFFFFFu;
+            // windows: a lane needs a new one when `nxt` is among the last two words (a turn moves at most two words on), unless
+            // its chunk ends in the one it has
+            uint32_t renew_at = (!linear && cw > kWin) ? n0 + (kWin - 2u) * 4u : 0xFFFFFFFFu;
             auto lds_word = [&](uint32_t a) { return *reinterpret_cast<lds_word_t*>(min(a, na_max)); };
-            auto restage = [&]() {  // the words from `nxt` on, anew, so that `nxt` is row 0
-                wbase += (na - n0) >> 8;
+            auto renew = [&]() {  // the words from `nxt` on, anew, so that `nxt` is the first
+                wbase += (na - n0) >> 2;
                 na = n0;
-                uint32_t w[kWin];
-                fetch_columns(gp, cw, wbase, w);
-                put_columns(cw, wbase, w);
-                renew_at = cw > wbase + kWin ? n0 + ((kWin - 2u) << 8) : 0xFFFFFFFFu;
+                const uint32_t left = cw > wbase ? cw - wbase : 0u;
+                uint32_t w[16];
+                if (__ballot(left > 16u) != 0ull) {
+                    fetch_window(k32, k0, gp, wbase, w);
+                    put_window(k32, k0, w);
+                    fetch_window(k32, k16, gp, wbase, w);
+                    put_window(k32, k16, w);
+                } else {  // the last words of all chunks
+                    fetch_window(k16, k0, gp, wbase, w);
+                    put_window(k16, k0, w);
+                }
+                staged();
+                renew_at = left > kWin ? n0 + (kWin - 2u) * 4u : 0xFFFFFFFFu;
             };
-            uint32_t w0 = lds_word(na), w1 = lds_word(na + (1u << sh)), nxt = lds_word(na + (2u << sh));
-            na += 2u << sh;
-            const uint32_t one_word = 1u << sh;
+            uint32_t w0 = lds_word(na), w1 = lds_word(na + 4u), nxt = lds_word(na + 8u);
+            na += 8u;
             const uint32_t base = grp * (kW * g.S) + lane * kV;
             const uint32_t turns = (min(g.n - grp * (kW * g.S), kW * g.S) + kW * kV - 1u) / (kW * kV);  // (the table can end in this group)
             // row matching: which rows of this group refer to another row, as a bit per row in LDS (at most 64*S/4 rows)
@@ -455,7 +489,7 @@ __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const
             const bool edge = g.n - grp * (kW * g.S) < kW * g.S;  // uniform
             for (uint32_t j = 0; j < turns; ++j) {
                 const uint32_t idx = base + j * (kW * kV);
-                if (__ballot(na >= renew_at) != 0ull) restage();  // (whole wavefront)
+                if (__ballot(na >= renew_at) != 0ull) renew();  // (whole wavefront)
                 bool coded = idx < g.n;
                 if (ref != nullptr && coded) {  // a row that refers to another has no bits in the stream; it is copied afterwards
                     const uint32_t local = idx - row_lo * g.D, r = row_magic ? __umulhi(local, row_magic) : local / g.D;
@@ -488,7 +522,7 @@ __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const
                         w0 = step ? w1 : w0;
                         w1 = step ? nxt : w1;
                         c &= 31u;
-                        na += step ? one_word : 0u;
+                        na += step ? 4u : 0u;
                         nxt = lds_word(na);  // (what lies past the chunk's end is never part of a codeword of its own)
                         v4[h2 * 2] = (float)((int)(e << 20) >> 20) * ebx2;
                         v4[h2 * 2 + 1] = (float)q2 * ebx2;
@@ -520,7 +554,7 @@ __global__ __launch_bounds__(64 * NW) void k_decode(Geom g, FixedLayout F, const
                 }
             }
             // a chunk's codewords end inside its words: w0 is two words before `nxt`, and c of its bits are used
-            if (__ballot(32u * (wbase + ((na - n0) >> sh) - 2u) + c > 32u * cw) != 0ull) bad = true;
+            if (__ballot(32u * (wbase + ((na - n0) >> 2) - 2u) + c > 32u * cw) != 0ull) bad = true;
             if (n_esc != 0u) {  // uniform over the wavefront: verbatim values over the decoded placeholders
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_s_waitcnt(0);  // the wavefront's own stores above are out before the overwrites below

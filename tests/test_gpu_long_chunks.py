@@ -1,0 +1,75 @@
+"""Chunks of more words than the kernels keep in LDS at a time (4 bits a symbol in a grid that fills the chip): the group
+encoder's further passes over a group and the decoder's windows, against the oracle byte for byte."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import to_device
+
+pytestmark = pytest.mark.gpu
+
+EB = np.float32(2.0 ** -10)  # bins are exact multiples of 2^-9
+
+
+def _payload(rng, kind, shape):
+    name, arg = kind
+    n = int(np.prod(shape))
+    if name == "span":       # `arg` neighbouring symbols, all equally frequent: 33 words a chunk of 256 at 17, 43 at 40, 54 at 100
+        b = rng.integers(0, arg, n).astype(np.float32) - arg // 2
+    elif name == "wide":     # symbols outside the window on both sides: up to 96 words
+        b = np.rint(rng.standard_normal(n, np.float32) * arg)
+    else:                    # "escapes": long codes and `arg` escapes in a thousand elements
+        b = np.rint(rng.standard_normal(n, np.float32) * 12)
+        b[rng.random(n, np.float32) < arg / 1000.0] = 4000
+    return (np.where(np.abs(b) < 3000, np.clip(b, -511, 511), b) * np.float32(2 * EB)).reshape(shape)
+
+
+def _check(T, B, D, S, dtype, rows, x):
+    import torch
+    from paper_2407_04272_amd import binding as b
+    x = x.astype(dtype)
+    ebs = np.full(T, EB, np.float32)
+    cfg = b.make_config(b.F16 if dtype == np.float16 else b.F32, T, B, D, 512, S, 12, b.FLAG_ROW_MATCH if rows else 0)
+    ctx = b.Context(cfg)
+    ctx.set_error_bounds(eb=ebs)
+    cap = b.dlc_compress_bound(cfg)
+    out = torch.full((cap + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+    sizes = torch.zeros(1 + T, dtype=torch.int64, device="cuda")
+    d = to_device(x)
+    rec = torch.full_like(d, 7.0)
+    for _ in range(2):  # (the second call finds what the first has left in the workspace)
+        assert ctx.compress(d, out, sizes, capacity=cap) == 0 and ctx.sync_status() == 0
+    h, n = out.cpu().numpy(), int(sizes[0])
+    assert np.all(h[cap:] == 0xA5)
+    o = oracle.compress(x, ebs, 512, S, 12, row_match=True if rows else None)
+    assert o.rc == 0 and n == o.data.size and np.array_equal(h[:n], o.data)
+    assert ctx.decompress(out, n, rec) == 0 and ctx.sync_status() == 0
+    rc, orec = oracle.decompress(o.data, x.shape, dtype)
+    u = np.uint16 if dtype == np.float16 else np.uint32
+    assert rc == 0 and np.array_equal(rec.cpu().numpy().view(u), orec.view(u))
+
+
+KINDS = [("span", 17), ("span", 40), ("span", 100), ("wide", 90), ("escapes", 2), ("escapes", 30)]
+_ids = [f"{a}{b}" for a, b in KINDS]
+
+
+@pytest.mark.parametrize("kind", KINDS, ids=_ids)
+@pytest.mark.parametrize("T,B,D,S,dtype", [
+    (104, 17 * 128 - 3, 128, 256, np.float32),  # eight groups a work-group, sixteen wavefronts a compute unit
+    (260, 150, 109, 256, np.float32),           # a work-group a table, more tables than compute units; n % 4 != 0, a ragged group
+    (3, 20 * 128, 128, 256, np.float16),        # a small grid: longer columns, larger staging areas
+    (530, 128, 64, 128, np.float32),            # chunks of 128: 17 to 48 words
+])
+def test_default_path(kind, T, B, D, S, dtype):
+    if dtype == np.float16 and kind[0] == "escapes":
+        kind = (kind[0], kind[1] / 10)
+    rng = np.random.default_rng(T + kind[1] * 7919 if isinstance(kind[1], int) else T)
+    _check(T, B, D, S, dtype, False, _payload(rng, kind, (T, B, D)))
+
+
+@pytest.mark.parametrize("kind", KINDS, ids=_ids)
+@pytest.mark.parametrize("T,B,D,dtype", [(258, 640, 128, np.float32), (520, 130, 128, np.float16)])  # eight and four groups a work-group
+def test_row_matching(kind, T, B, D, dtype):
+    rng = np.random.default_rng(T + kind[1])
+    x = _payload(rng, kind, (T, (B + 1) // 2, D))
+    _check(T, B, D, 256, dtype, True, np.take_along_axis(x, rng.integers(0, x.shape[1], (T, B, 1)), axis=1))
