@@ -53,17 +53,6 @@ __host__ __device__ inline EncLds enc_lds(uint32_t nw, uint32_t waves, uint32_t 
     return L;
 }
 
-// (length << 12 | codeword) of the element at `off` of the group, quantised again (a symbol outside the window).  The
-// codewords may come from this very launch: they are read past the caches.
-template <bool F16>
-__device__ __forceinline__ uint32_t entry_of_element(const uint8_t* gbase, uint32_t off, const QParam& q, float Rf, int R,
-                                                     const uint16_t* enc_t) {
-    float x;
-    if constexpr (F16) x = __half2float(__ushort_as_half(reinterpret_cast<const unsigned short*>(gbase)[off]));
-    else x = reinterpret_cast<const float*>(gbase)[off];
-    return __hip_atomic_load(&enc_t[quant_symbol<F16>(x, q, Rf, R)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 struct EmitEnv {
     const uint8_t* gbase;  // first element of the group
     uint32_t rem;          // elements of the table from there on
@@ -105,18 +94,36 @@ __device__ __forceinline__ uint32_t pair_entry(uint32_t a, uint32_t b) {  // of 
     return (((a & 0xFFFu) << lb | (b & 0xFFFu)) << 8) | ((a >> 12) + lb);
 }
 
+// (length << 12 | codeword) of the elements of a plane word that lie outside the window (bits of `out`), quantised again:
+// their loads go out together, and so do the look-ups (one element after the other, each of them two round trips: 512 MiB
+// with 4 % of the elements outside 1845 us a call, now 1160).  The codewords may come from this very launch: they are read
+// past the caches.
+template <bool F16, bool VEC>
+__device__ __forceinline__ void entries_outside(const EmitEnv& E, uint32_t off, uint32_t out, uint32_t (&e)[4]) {
+    float x[4];
+    uint32_t raw[4], sym[4], got[4];
+    (void)load4<F16, VEC>(E.gbase, off, E.rem, x, raw);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sym[v] = (out >> v) & 1u ? quant_symbol<F16>(x[v], E.q, E.Rf, E.R) : 0u;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) got[v] = __hip_atomic_load(&E.enc_t[sym[v]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) e[v] = (out >> v) & 1u ? got[v] : e[v];
+}
+
 // a word of the plane the long way; `off`: its first element's offset in the group; rec: remember its escapes
-template <bool F16>
+template <bool F16, bool VEC>
 __device__ __forceinline__ void emit_slow(const EmitEnv& E, EmitState& S, uint32_t m, uint32_t off, bool rec) {
-    uint32_t e[4], em = 0;
+    uint32_t e[4], em = 0, out = 0;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const uint32_t b = (m >> (8 * v)) & 0xFFu;
         const bool in = off + (uint32_t)v < E.rem;  // (whatever the plane holds past the end of the table does not count)
         e[v] = in ? E.ent[b] : 0u;
-        if (in && b == kWinBins) e[v] = entry_of_element<F16>(E.gbase, off + (uint32_t)v, E.q, E.Rf, E.R, E.enc_t);
+        out |= (in && b == kWinBins) ? 1u << v : 0u;
         em |= (in && b == kWinEsc) ? 1u << v : 0u;
     }
+    if (__ballot(out != 0u) != 0ull) entries_outside<F16, VEC>(E, off, out, e);
     // the records of these escapes, in element order (the walk meets the elements of a group in increasing index:
     // turn, lane, position)
     if (rec && __ballot(em != 0u) != 0ull) {
@@ -139,7 +146,7 @@ constexpr uint32_t kEmitBlk = 4;  // words of the plane a trip of the walk takes
 // the N words of one trip (at p and every kW words on).  PAIR: the pair table serves (else the codewords one by one);
 // CHECK: a byte may have no place in the tables; LZ: a word may belong to a row that is stored as a reference (all
 // four bytes 253: no bits)
-template <bool F16, bool PAIR, bool CHECK, bool LZ, uint32_t N>
+template <bool F16, bool VEC, bool PAIR, bool CHECK, bool LZ, uint32_t N>
 __device__ __forceinline__ void emit_block(const EmitEnv& E, EmitState& S, const uint32_t (&m)[N], const uint32_t* p, uint32_t off, bool rec) {
     uint32_t e01[N], e23[N];
     uint32_t w[N];
@@ -163,7 +170,7 @@ __device__ __forceinline__ void emit_block(const EmitEnv& E, EmitState& S, const
     }
     if (CHECK && __builtin_expect(__ballot(bad) != 0ull, 0)) {  // uniform over the wavefront
 #pragma clang loop unroll(disable)
-        for (uint32_t u = 0; u < N; ++u) emit_slow<F16>(E, S, p[u * kW], off + u * (kW * kV), rec);
+        for (uint32_t u = 0; u < N; ++u) emit_slow<F16, VEC>(E, S, p[u * kW], off + u * (kW * kV), rec);
         return;
     }
 #pragma unroll
@@ -193,7 +200,7 @@ __device__ __forceinline__ void emit_block(const EmitEnv& E, EmitState& S, const
 }
 
 // a walk over the first `els` elements of the group: trips of whole turns, the rest a turn at a time
-template <bool F16, bool PAIR, bool CHECK, bool LZ>
+template <bool F16, bool VEC, bool PAIR, bool CHECK, bool LZ>
 __device__ __forceinline__ void emit_turns(const EmitEnv& E, EmitState& S, const uint32_t* plane, uint32_t els, bool rec) {
     const uint32_t* p = plane + E.lane;
     const uint32_t whole = els / (kW * kV) & ~(kEmitBlk - 1u), turns = (els + kW * kV - 1u) / (kW * kV);
@@ -212,11 +219,11 @@ __device__ __forceinline__ void emit_turns(const EmitEnv& E, EmitState& S, const
             const uint32_t jn = min(j + 2u * kEmitBlk, last);
 #pragma unroll
             for (uint32_t u = 0; u < kEmitBlk; ++u) nb[u] = p[(jn + u) * kW];
-            emit_block<F16, PAIR, CHECK, LZ>(E, S, m, p + j * kW, E.lane * kV + j * (kW * kV), rec);
+            emit_block<F16, VEC, PAIR, CHECK, LZ>(E, S, m, p + j * kW, E.lane * kV + j * (kW * kV), rec);
         }
     }
 #pragma clang loop unroll(disable)
-    for (uint32_t j = whole; j < turns; ++j) emit_slow<F16>(E, S, p[j * kW], E.lane * kV + j * (kW * kV), rec);
+    for (uint32_t j = whole; j < turns; ++j) emit_slow<F16, VEC>(E, S, p[j * kW], E.lane * kV + j * (kW * kV), rec);
 }
 
 // What a work-group knows when its tables are in LDS
@@ -275,10 +282,10 @@ __device__ __forceinline__ void encode_groups(const GroupJob& J, const void* pay
         if (active) {
             const bool rec = pass == 0;
             if (J.pairs) {
-                if (J.special) emit_turns<F16, true, true, LZ>(E, St, plane, in_group, rec);
-                else emit_turns<F16, true, false, LZ>(E, St, plane, in_group, rec);
+                if (J.special) emit_turns<F16, VEC, true, true, LZ>(E, St, plane, in_group, rec);
+                else emit_turns<F16, VEC, true, false, LZ>(E, St, plane, in_group, rec);
             } else {
-                emit_turns<F16, false, true, LZ>(E, St, plane, in_group, rec);
+                emit_turns<F16, VEC, false, true, LZ>(E, St, plane, in_group, rec);
             }
             if (St.nbt & 31u)  // the chunk's last, partly filled word
                 *reinterpret_cast<lds_u32*>(E.col + min((St.nbt >> 5) + 1u, E.row_max) * (kColPitch * 4u)) =
