@@ -22,7 +22,11 @@ namespace dlc {
 //           totals across the grid by a single-pass look-back (ordered work-group ids: a work-group only ever waits for
 //           work-groups that started earlier)
 //   copy  : the columns to their places, a team of lanes per chunk.  A column holds `cap` words; a group with a longer
-//           chunk is walked again for every further `cap` words (the words of other passes fall on rows nobody reads).
+//           chunk is walked again for every further `cap` words (the words of other passes fall on rows nobody reads), from
+//           the last trip on at which no column could have been full yet: the walk remembers its state there.  (From the start
+//           every time: 512 MiB at a ratio of 7.2, where nearly every group has a few words too many, 243 us a call, now 216; 5.9:
+//           278, now 254.  The further walks stay out of the first one's code: one loop over all of them cost the main path
+//           6 us, and tables with escapes 110.)
 //   escapes: their records (element index, raw bits; in increasing element index, behind the group's chunk words) are
 //           written from offsets kept in LDS during the walk, up to kEncRecs per group; a group with more walks its
 //           elements once more
@@ -69,10 +73,18 @@ struct EmitEnv {
     uint16_t* recs;
 };
 
+constexpr uint32_t kEmitBlk = 4;  // words of the plane a trip of the walk takes; those of the next two are on their way meanwhile
+constexpr uint32_t kTripBits = kEmitBlk * kV * (uint32_t)kLmaxLimit;  // a trip adds no more to a chunk
+
 struct EmitState {
     uint64_t acc;   // the chunk's bits so far, the latest at the low end
     uint32_t nbt;   // how many (in a later pass: less the bits of the passes before, modulo 2^32)
     uint32_t nesc;  // escapes of the wavefront so far (uniform)
+};
+
+struct EmitMark {   // a walk's state before turn j (a multiple of kEmitBlk)
+    uint64_t acc;
+    uint32_t nbt, j;
 };
 
 __device__ __forceinline__ void emit_piece(const EmitEnv& E, EmitState& S, uint32_t code, uint32_t len) {  // len <= 32
@@ -141,8 +153,6 @@ __device__ __forceinline__ void emit_slow(const EmitEnv& E, EmitState& S, uint32
     emit_two(E, S, pair_entry(e[0], e[1]), pair_entry(e[2], e[3]));
 }
 
-constexpr uint32_t kEmitBlk = 4;  // words of the plane a trip of the walk takes; those of the next two are on their way meanwhile
-
 // the N words of one trip (at p and every kW words on).  PAIR: the pair table serves (else the codewords one by one);
 // CHECK: a byte may have no place in the tables; LZ: a word may belong to a row that is stored as a reference (all
 // four bytes 253: no bits)
@@ -199,20 +209,30 @@ __device__ __forceinline__ void emit_block(const EmitEnv& E, EmitState& S, const
     }
 }
 
-// a walk over the first `els` elements of the group: trips of whole turns, the rest a turn at a time
+// a walk over the first `els` elements of the group, from turn `from` on (a multiple of kEmitBlk): trips of whole turns, the
+// rest (at most kEmitBlk turns) a turn at a time.  Returns its state at the first trip in which a chunk could pass `limit` +
+// kTripBits bits, or at the end of the trips.
 template <bool F16, bool VEC, bool PAIR, bool CHECK, bool LZ>
-__device__ __forceinline__ void emit_turns(const EmitEnv& E, EmitState& S, const uint32_t* plane, uint32_t els, bool rec) {
+__device__ __forceinline__ EmitMark emit_turns(const EmitEnv& E, EmitState& S, const uint32_t* plane, uint32_t els, uint32_t from, int limit, bool rec) {
     const uint32_t* p = plane + E.lane;
     const uint32_t whole = els / (kW * kV) & ~(kEmitBlk - 1u), turns = (els + kW * kV - 1u) / (kW * kV);
-    if (whole) {
+    EmitMark M;
+    M.j = 0xFFFFFFFFu;
+    if (from < whole) {
         uint32_t na[kEmitBlk], nb[kEmitBlk];  // the words of the next trip and of the one after it
         const uint32_t last = whole - kEmitBlk;
 #pragma unroll
-        for (uint32_t u = 0; u < kEmitBlk; ++u) na[u] = p[u * kW];
+        for (uint32_t u = 0; u < kEmitBlk; ++u) na[u] = p[(from + u) * kW];
 #pragma unroll
-        for (uint32_t u = 0; u < kEmitBlk; ++u) nb[u] = p[(min(kEmitBlk, last) + u) * kW];
+        for (uint32_t u = 0; u < kEmitBlk; ++u) nb[u] = p[(min(from + kEmitBlk, last) + u) * kW];
 #pragma clang loop unroll(disable)
-        for (uint32_t j = 0; j < whole; j += kEmitBlk) {
+        for (uint32_t j = from; j < whole; j += kEmitBlk) {
+            if (__ballot((int)S.nbt > limit) != 0ull) {  // uniform
+                M.acc = S.acc;
+                M.nbt = S.nbt;
+                M.j = j;
+                limit = 0x7FFFFFFF;
+            }
             uint32_t m[kEmitBlk];
 #pragma unroll
             for (uint32_t u = 0; u < kEmitBlk; ++u) { m[u] = na[u]; na[u] = nb[u]; }
@@ -222,8 +242,14 @@ __device__ __forceinline__ void emit_turns(const EmitEnv& E, EmitState& S, const
             emit_block<F16, VEC, PAIR, CHECK, LZ>(E, S, m, p + j * kW, E.lane * kV + j * (kW * kV), rec);
         }
     }
+    if (M.j == 0xFFFFFFFFu) {
+        M.acc = S.acc;
+        M.nbt = S.nbt;
+        M.j = whole;
+    }
 #pragma clang loop unroll(disable)
     for (uint32_t j = whole; j < turns; ++j) emit_slow<F16, VEC>(E, S, p[j * kW], E.lane * kV + j * (kW * kV), rec);
+    return M;
 }
 
 // What a work-group knows when its tables are in LDS
@@ -272,94 +298,101 @@ __device__ __forceinline__ void encode_groups(const GroupJob& J, const void* pay
     E.col = J.lds0 + (uint32_t)((unsigned char*)rows - smem) + lane * 4u;
     E.recs = reinterpret_cast<uint16_t*>(smem + J.L.recs) + wave * kEncRecs;
     const uint32_t in_group = min(E.rem, kW * (uint32_t)S);
+    // a state marked below this many bits (in the trip before it, kTripBits more) has no word of the next pass behind it
+    const int limit = (int)(cap * 32u - kTripBits);
+    auto last_word = [&](const EmitState& St) {  // the chunk's last, partly filled word
+        if (St.nbt & 31u)
+            *reinterpret_cast<lds_u32*>(E.col + min((St.nbt >> 5) + 1u, E.row_max) * (kColPitch * 4u)) = (uint32_t)St.acc << (32u - (St.nbt & 31u));
+    };
     EmitState St;
-    uint32_t nw = 0, lane_off = 0, chunk_total = 0, n_esc = 0, pass_base = 0;
-    uint32_t* gw = nullptr;
-    for (uint32_t pass = 0;;) {
-        St.acc = 0;
-        St.nbt = 0u - pass_base * 32u;
-        St.nesc = 0;
-        if (active) {
-            const bool rec = pass == 0;
-            if (J.pairs) {
-                if (J.special) emit_turns<F16, VEC, true, true, LZ>(E, St, plane, in_group, rec);
-                else emit_turns<F16, VEC, true, false, LZ>(E, St, plane, in_group, rec);
-            } else {
-                emit_turns<F16, VEC, false, true, LZ>(E, St, plane, in_group, rec);
-            }
-            if (St.nbt & 31u)  // the chunk's last, partly filled word
-                *reinterpret_cast<lds_u32*>(E.col + min((St.nbt >> 5) + 1u, E.row_max) * (kColPitch * 4u)) =
-                    (uint32_t)St.acc << (32u - (St.nbt & 31u));
+    St.acc = 0;
+    St.nbt = 0;
+    St.nesc = 0;
+    EmitMark M;
+    M.acc = 0;
+    M.nbt = 0;
+    M.j = 0;
+    if (active) {
+        if (J.pairs) {
+            if (J.special) M = emit_turns<F16, VEC, true, true, LZ>(E, St, plane, in_group, 0u, limit, true);
+            else M = emit_turns<F16, VEC, true, false, LZ>(E, St, plane, in_group, 0u, limit, true);
+        } else {
+            M = emit_turns<F16, VEC, false, true, LZ>(E, St, plane, in_group, 0u, limit, true);
         }
-        if (pass == 0) {
-            nw = active ? (St.nbt + 31u) >> 5 : 0u;
-            n_esc = St.nesc;
-            const uint32_t incl = wave_incl_scan(nw, lane);
-            lane_off = incl - nw;
-            chunk_total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-            const uint32_t total = chunk_total + 2u * n_esc;  // 0 for an idle wavefront
-            if (lane == 0) s_tot[wave] = total;
-            __syncthreads();
-            if (wave == 0) {
-                uint32_t wg_total = 0;
-                for (uint32_t k = 0; k < NW; ++k) wg_total += s_tot[k];
-                bool failed = false;
-                const uint32_t excl = wg_scan(state, epoch, J.wg, wg_total, lane, ctrl, &failed, J.dom0);
-                if (lane == 0) { s_excl = excl; s_dead = failed ? 1u : 0u; }
-            }
-            __syncthreads();
-            if (!active) return;
-            uint32_t excl = s_excl;
-            for (uint32_t k = 0; k < wave; ++k) excl += s_tot[k];
-            bool dead = s_dead != 0u;  // nothing may be written to the container
-            if (F.off_payload + 4ull * ((uint64_t)excl + total) > capacity) {
-                if (!dead && lane == 0) { set_status(ctrl, DLC_ECAPACITY); atomicOr(&ctrl->abort, kAbortCapacity); }
-                dead = true;
-            }
-            if (lane == 0) {
-                if (grp == 0) word_start[t] = excl;
-                if (grp == g.G - 1) word_end[t] = excl + total;
-            }
-            if (dead) return;
-            out[F.off_chunk + (uint64_t)gid * kW + lane] = (uint8_t)nw;
-            if (lane == 0) reinterpret_cast<uint32_t*>(out + F.off_group)[gid] = excl;
-            gw = reinterpret_cast<uint32_t*>(out + F.off_payload) + excl;
-        }
-        // the columns come from other lanes of this wavefront: its LDS accesses complete in order, the compiler must keep
-        // them in order too
+        last_word(St);
+    }
+    const uint32_t nw = active ? (St.nbt + 31u) >> 5 : 0u, n_esc = St.nesc;
+    const uint32_t incl = wave_incl_scan(nw, lane);
+    const uint32_t lane_off = incl - nw;
+    const uint32_t chunk_total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    const uint32_t total = chunk_total + 2u * n_esc;  // 0 for an idle wavefront
+    if (lane == 0) s_tot[wave] = total;
+    __syncthreads();
+    if (wave == 0) {
+        uint32_t wg_total = 0;
+        for (uint32_t k = 0; k < NW; ++k) wg_total += s_tot[k];
+        bool failed = false;
+        const uint32_t excl = wg_scan(state, epoch, J.wg, wg_total, lane, ctrl, &failed, J.dom0);
+        if (lane == 0) { s_excl = excl; s_dead = failed ? 1u : 0u; }
+    }
+    __syncthreads();
+    if (!active) return;
+    uint32_t excl = s_excl;
+    for (uint32_t k = 0; k < wave; ++k) excl += s_tot[k];
+    bool dead = s_dead != 0u;  // nothing may be written to the container
+    if (F.off_payload + 4ull * ((uint64_t)excl + total) > capacity) {
+        if (!dead && lane == 0) { set_status(ctrl, DLC_ECAPACITY); atomicOr(&ctrl->abort, kAbortCapacity); }
+        dead = true;
+    }
+    if (lane == 0) {
+        if (grp == 0) word_start[t] = excl;
+        if (grp == g.G - 1) word_end[t] = excl + total;
+    }
+    if (dead) return;
+    out[F.off_chunk + (uint64_t)gid * kW + lane] = (uint8_t)nw;
+    if (lane == 0) reinterpret_cast<uint32_t*>(out + F.off_group)[gid] = excl;
+    uint32_t* const gw = reinterpret_cast<uint32_t*>(out + F.off_payload) + excl;
+    // the columns come from other lanes of this wavefront: its LDS accesses complete in order, the compiler must keep
+    // them in order too
+    auto in_order = [] {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        {
-            // a team of lanes copies a chunk, a word a lane (as many lanes as a chunk has words at 4 bits a symbol; the
-            // teams' chunks lie so far apart that no two lanes meet in a bank)
-            constexpr uint32_t TL = (uint32_t)S / 8u;
-            const uint32_t team = lane / TL, k0 = lane % TL;
-            const uint32_t n_here = nw > pass_base ? min(nw - pass_base, cap) : 0u;
-            const uint32_t mine = ((lane_off + pass_base) << 8) | n_here;
-            for (uint32_t k = 0; __ballot(n_here > k) != 0ull; k += TL) {  // uniform
-                const uint32_t* const rl = rows + min(k + k0 + 1u, cap + 1u) * kColPitch;
+    };
+    // the columns' words to their places; they are the words from `first` on of their chunks.
+    // A team of lanes copies a chunk, a word a lane (as many lanes as a chunk has words at 4 bits a symbol; the
+    // teams' chunks lie so far apart that no two lanes meet in a bank)
+    auto copy = [&](uint32_t first) {
+        in_order();
+        constexpr uint32_t TL = (uint32_t)S / 8u;
+        const uint32_t team = lane / TL, k0 = lane % TL;
+        const uint32_t n_here = nw > first ? min(nw - first, cap) : 0u;
+        const uint32_t mine = ((lane_off + first) << 8) | n_here;
+        for (uint32_t k = 0; __ballot(n_here > k) != 0ull; k += TL) {  // uniform
+            const uint32_t* const rl = rows + min(k + k0 + 1u, cap + 1u) * kColPitch;
 #pragma clang loop unroll(disable)
-                for (uint32_t i0 = 0; i0 < TL; i0 += 8u) {  // eight chunks in flight: nothing in between waits
-                    uint32_t oc[8], v[8];
+            for (uint32_t i0 = 0; i0 < TL; i0 += 8u) {  // eight chunks in flight: nothing in between waits
+                uint32_t oc[8], v[8];
 #pragma unroll
-                    for (uint32_t u = 0; u < 8u; ++u) {
-                        const uint32_t c = i0 + u + team * TL;
-                        oc[u] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(c * 4u), (int)mine);
-                        v[u] = rl[c];
-                    }
-#pragma unroll
-                    for (uint32_t u = 0; u < 8u; ++u)
-                        if (k + k0 < (oc[u] & 255u)) gw[(oc[u] >> 8) + k + k0] = v[u];
+                for (uint32_t u = 0; u < 8u; ++u) {
+                    const uint32_t c = i0 + u + team * TL;
+                    oc[u] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(c * 4u), (int)mine);
+                    v[u] = rl[c];
                 }
+#pragma unroll
+                for (uint32_t u = 0; u < 8u; ++u)
+                    if (k + k0 < (oc[u] & 255u)) gw[(oc[u] >> 8) + k + k0] = v[u];
             }
         }
-        if (__ballot(nw > pass_base + cap) == 0ull) break;  // uniform
-        ++pass;
-        pass_base += cap;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    copy(0u);
+    for (uint32_t first = cap; __ballot(nw > first) != 0ull; first += cap) {  // uniform; the codewords one by one from here on
+        in_order();
+        St.acc = M.acc;
+        St.nbt = M.nbt - cap * 32u;  // (what is counted from the pass's first word on may be below zero)
+        M = emit_turns<F16, VEC, false, true, LZ>(E, St, plane, in_group, M.j, limit, false);
+        last_word(St);
+        copy(first);
     }
     if (n_esc != 0u) {  // uniform over the wavefront
         uint32_t* rec = gw + chunk_total;
