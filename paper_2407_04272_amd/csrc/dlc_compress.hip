@@ -572,12 +572,17 @@ hipError_t launch_compress(const Geom& g, const void* payload, uint8_t* out, uin
         return hipGetLastError();
     }
     // Small tables go from payload to coded groups in one launch, a work-group per table.  Up to eight groups that is the
-    // shorter way whatever the number of tables (one launch for three; 26 tables of eight groups: 43 us a call against
-    // 45).  Up to sixteen, what a work-group has wavefronts for, it is where there are tables enough to keep the compute
-    // units busy (128 tables of sixteen groups: 67 us against 74; 26 tables: 69 against 48).  Row matching needs every row's
+    // shorter way whatever the number of tables (one launch for three; 26 tables of eight groups: 35.6 us a call against
+    // 36.3, one of one group 17.6 against 24.8).  From nine to sixteen groups, what a work-group has wavefronts for, a
+    // work-group has a compute unit to itself, and it is the shorter way where there are tables enough to keep the compute units
+    // busy (128 tables of sixteen groups: 65 us against 75; 64: 57 against 51; 26: 53 against 40), but not where a second
+    // round of work-groups is nearly empty, and less so the longer the codes are (at ratios of 10 and 5.9: 257 tables of
+    // twelve groups 110 and 197 us against 98 and 153; 300: 113 and 202 against 109 and 168; 350: 118 and 205 against 121 and
+    // 184; 400: 124 and 211 against 132 and 197; 512: 142 and 229 against 159 and 344).  Row matching needs every row's
     // symbols before it knows the counts: it keeps the launches apart, and so do many tables
     // of a large alphabet, whose scratch memory would leave a compute unit one work-group at a time.
-    const bool fused = !g.lz && (g.G <= 8u || (g.G <= 16u && g.T >= 128u)) && (g.T <= 256u || g.K <= 1024u);
+    const bool whole_rounds = (g.T >= 128u && g.T <= 256u) || g.T > 352u;
+    const bool fused = !g.lz && (g.G <= 8u || (g.G <= 16u && whole_rounds)) && (g.T <= 256u || g.K <= 1024u);
     const uint32_t tpw = codebook_tables_per_wg(g);
     if (fused) {
         if (prof_on(pl, P_ENCODE)) prof_begin(prof, P_ENCODE, s);
