@@ -678,6 +678,13 @@ void DLC_CAT(launch_table_, DLC_S)(const Geom& g, const FixedLayout& F, const vo
         while (cap > S / 8u && enc_lds(16u, std::min(16u, g.G), cap, 56u).end > kLdsMax - kTableStatic) --cap;
         if (g.n <= 16u * kW * kV) DLC_CAT(table_launch_, DLC_S)<4u>(g, F, payload, w, epoch, out, capacity, cap, kLdsMax - kTableStatic, s);
         else DLC_CAT(table_launch_, DLC_S)<16u>(g, F, payload, w, epoch, out, capacity, cap, kLdsMax - kTableStatic, s);
+    } else if (g.T <= 512u && g.G <= 8u) {
+        // two work-groups of eight wavefronts a compute unit, one round of them, with columns as long as that leaves.  (Two
+        // wavefronts for tables of one or two groups: 300 tables of one group at ratios of 10 and 4.9 37 and 103 us a call, so 33
+        // and 86; of four groups, four wavefronts: 50 and 117, so 51 and 112.)
+        uint32_t cap = S * 12u / 32u;
+        while (cap > S / 8u && enc_lds(8u, g.G, cap, 40u).end > kLdsMax / 2u - kTableStatic) --cap;
+        DLC_CAT(table_launch_, DLC_S)<8u>(g, F, payload, w, epoch, out, capacity, cap, kLdsMax / 2u - kTableStatic, s);
     } else {
         // as many wavefronts as the table has groups, twelve to sixteen a compute unit
         const uint32_t cap = S / 8u;
