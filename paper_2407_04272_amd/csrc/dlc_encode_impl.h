@@ -140,15 +140,19 @@ __device__ __forceinline__ void emit_slow(const EmitEnv& E, EmitState& S, uint32
     // turn, lane, position)
     if (rec && __ballot(em != 0u) != 0ull) {
         const uint32_t cnt = __popc(em);
-        const uint32_t incl = wave_incl_scan(cnt, E.lane);
-        uint32_t r = S.nesc + incl - cnt;
+        if (S.nesc < kEncRecs) {  // uniform
+            const uint32_t incl = wave_incl_scan(cnt, E.lane);
+            uint32_t r = S.nesc + incl - cnt;
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-            if ((em >> v) & 1u) {
-                if (r < kEncRecs) E.recs[r] = (uint16_t)(off + (uint32_t)v);
-                ++r;
-            }
-        S.nesc += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            for (int v = 0; v < 4; ++v)
+                if ((em >> v) & 1u) {
+                    if (r < kEncRecs) E.recs[r] = (uint16_t)(off + (uint32_t)v);
+                    ++r;
+                }
+            S.nesc += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        } else {  // (their group is walked once more for them: they are only counted from here on)
+            S.nesc += (uint32_t)__popcll(__ballot(cnt & 1u)) + 2u * (uint32_t)__popcll(__ballot(cnt & 2u)) + 4u * (uint32_t)__popcll(__ballot(cnt & 4u));
+        }
     }
     emit_two(E, S, pair_entry(e[0], e[1]), pair_entry(e[2], e[3]));
 }
