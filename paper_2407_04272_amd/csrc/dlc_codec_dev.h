@@ -318,9 +318,10 @@ __device__ __forceinline__ uint32_t wave_canonical_code(uint32_t len, uint32_t L
 // gathers the used symbols into its lanes through `wsm` (LDS of this wavefront: 64 keys, then K entries of 16
 // bits), builds the tree in registers, and writes the K entries of the table and the code lengths.  Returns false,
 // with the histogram untouched, when the table has more than 64 used symbols.
-// An alphabet of 16 or 32 symbols (radius 8, 16) is narrower than the wavefront: the lanes past it touch nothing, the
-// memory behind a table's counts and codes is the next table's.  (K is a power of two: from 64 on every lane has a symbol.)
+//   K: a multiple of 64.  (Radius 8 and 16 give 16 and 32 symbols; the memory behind such a table's counts and codes is
+//   the next table's: those go to codebook_build.)
 //   wsm: 512 + 2 * K bytes, 8-byte aligned.
+constexpr uint32_t kWaveAlphabet = 64;  // least alphabet of codebook_build_wave (every larger one is a power of two)
 __host__ __device__ constexpr size_t codebook_wave_smem(uint32_t K) { return 512 + 2 * (size_t)K; }
 __host__ __device__ constexpr size_t codebook_four_smem(uint32_t K) {
     return codebook_smem(K) > 4 * codebook_wave_smem(K) ? codebook_smem(K) : 4 * codebook_wave_smem(K);
@@ -329,7 +330,6 @@ __device__ __forceinline__ bool codebook_build_wave(const Geom& g, uint32_t* his
                                                     uint8_t* lens_t, TMeta* tmeta_t, unsigned char* wsm, uint32_t lane,
                                                     uint32_t carry) {
     const uint32_t K = g.K;
-    const bool has = lane < K;  // this lane has symbols
     uint64_t* key = reinterpret_cast<uint64_t*>(wsm);            // [64] count << 16 | symbol of the used symbols, symbol order
     uint16_t* ent = reinterpret_cast<uint16_t*>(wsm + 512);      // [K] len << 12 | codeword
     const uint64_t below = (1ull << lane) - 1ull;
@@ -339,7 +339,7 @@ __device__ __forceinline__ bool codebook_build_wave(const Geom& g, uint32_t* his
         uint32_t hv[16];
 #pragma unroll
         for (uint32_t i = 0; i < 16; ++i)
-            hv[i] = has && kb + i * 64u < K ? __hip_atomic_load(&hist_t[kb + i * 64u + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+            hv[i] = kb + i * 64u < K ? __hip_atomic_load(&hist_t[kb + i * 64u + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
 #pragma unroll
         for (uint32_t i = 0; i < 16; ++i) {
             const uint32_t k = kb + i * 64u + lane;
@@ -347,9 +347,9 @@ __device__ __forceinline__ bool codebook_build_wave(const Geom& g, uint32_t* his
             const uint32_t h = hv[i];
             // a codebook that is carried to the next call always has a code for the escape symbol
             const uint32_t c = h + ((carry != 0u && k == 0u) ? 1u : 0u);
-            if (has && hist_t != hist_view_t) hist_view_t[k] = h;  // (the copy itself can be the source: it is left as it is)
+            if (hist_t != hist_view_t) hist_view_t[k] = h;  // (the copy itself can be the source: it is left as it is)
             if (kb + i == 0u) n_escape = (uint32_t)__builtin_amdgcn_readfirstlane((int)c);
-            if (has) ent[k] = 0;
+            ent[k] = 0;
             const uint64_t m = __ballot(c != 0u);
             const uint32_t at = n_used + (uint32_t)__popcll(m & below);
             if (c != 0u && at < 64u) key[at] = ((uint64_t)c << 16) | k;
@@ -357,7 +357,7 @@ __device__ __forceinline__ bool codebook_build_wave(const Geom& g, uint32_t* his
         }
     }
     if (n_used > 64u) return false;  // uniform
-    if (has && hist_t != hist_view_t)
+    if (hist_t != hist_view_t)
         for (uint32_t k0 = 0; k0 < K; k0 += 64)
             __hip_atomic_store(&hist_t[k0 + lane], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __builtin_amdgcn_wave_barrier();
@@ -371,7 +371,7 @@ __device__ __forceinline__ bool codebook_build_wave(const Geom& g, uint32_t* his
         if (lane < n_used) ent[sym] = (uint16_t)((len << 12) | mine_code);
     }
     __builtin_amdgcn_wave_barrier();
-    for (uint32_t k0 = 0; has && k0 < K; k0 += 64) {
+    for (uint32_t k0 = 0; k0 < K; k0 += 64) {
         const uint32_t e = ent[k0 + lane];
         __hip_atomic_store(&enc_t[k0 + lane], (uint16_t)e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         lens_t[k0 + lane] = (uint8_t)(e >> 12);

@@ -160,7 +160,7 @@ __global__ __launch_bounds__(256) void k_codebook(Geom g, uint32_t* hist, uint32
 // With few tables a work-group per table (all its threads read the histogram: the shortest way to one codebook); with
 // many, four tables per work-group, a wavefront each (a quarter of the work-groups, and no idle wavefronts while
 // one of them builds the tree).
-static inline uint32_t codebook_tables_per_wg(const Geom& g) { return g.T >= 512u ? 4u : 1u; }
+static inline uint32_t codebook_tables_per_wg(const Geom& g) { return g.T >= 512u && g.K >= kWaveAlphabet ? 4u : 1u; }
 static inline size_t codebook_lds(const Geom& g, uint32_t tpw) { return tpw == 4u ? codebook_four_smem(g.K) : codebook_smem(g.K); }
 
 // ------------------------------------------------------------------------------------------------
