@@ -585,13 +585,13 @@ hipError_t launch_compress(const Geom& g, const void* payload, uint8_t* out, uin
     const bool fused = !g.lz && (g.G <= 8u || (g.G <= 16u && whole_rounds)) && (g.T <= 256u || g.K <= 1024u);
     const uint32_t tpw = codebook_tables_per_wg(g);
     if (fused) {
-        if (prof_on(pl, P_ENCODE)) prof_begin(prof, P_ENCODE, s);
+        if (prof_on(pl, P_TABLE)) prof_begin(prof, P_TABLE, s);
         switch (g.S) {
             case 64: launch_table_64(g, F, payload, w, epoch, out, capacity, s); break;
             case 128: launch_table_128(g, F, payload, w, epoch, out, capacity, s); break;
             default: launch_table_256(g, F, payload, w, epoch, out, capacity, s); break;
         }
-        if (prof_on(pl, P_ENCODE)) prof_end(prof, P_ENCODE, s);
+        if (prof_on(pl, P_TABLE)) prof_end(prof, P_TABLE, s);
     } else {
         // histogram
         {

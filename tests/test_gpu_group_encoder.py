@@ -30,6 +30,24 @@ def _bins(rng, kind, shape):
     return b.reshape(shape)
 
 
+def test_profile_names_the_kernels_that_ran():
+    import torch
+    from paper_2407_04272_amd import binding as b
+    for batch, ran in ((256, {"k_table", "k_finalize"}), (20 * 64, {"k_hist", "k_codebook", "k_encode", "k_finalize"})):
+        cfg = b.make_config(b.F32, 2, batch, 64, 512, 64, 12, 0)
+        ctx = b.Context(cfg)
+        ctx.set_error_bounds(eb=np.full(2, EB, np.float32))
+        x = torch.randn((2, batch, 64), device="cuda") * 0.01
+        out = torch.empty(b.dlc_compress_bound(cfg), dtype=torch.uint8, device="cuda")
+        sizes = torch.zeros(3, dtype=torch.int64, device="cuda")
+        for level, want in ((1, ran & {"k_table", "k_encode"}), (2, ran)):
+            ctx.profile_enable(level)
+            assert ctx.compress(x, out, sizes) == 0 and ctx.sync_status() == 0
+            prof = ctx.profile_read()
+            assert {k for k, (ms, n) in prof.items() if n} == want
+            assert all(n == 1 and ms > 0 for k, (ms, n) in prof.items() if k in want)
+
+
 def _check(T, B, D, S, R, dtype, nd, kind, seed):
     import torch
     from paper_2407_04272_amd import binding as b
