@@ -214,7 +214,7 @@ __device__ __forceinline__ void carry_block(const CarryEnv& E, const float (&x)[
             // increasing index: turn, lane, position); their offsets are kept while they fit.
             if (__ballot(em != 0u) != 0ull) {
                 const uint32_t cnt = __popc(em);
-                const uint32_t incl = wave_incl_scan(cnt, E.lane);
+                const uint32_t incl = wave_incl_scan(cnt);
                 uint32_t r = S.nrec + incl - cnt;
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
@@ -296,7 +296,7 @@ __device__ __forceinline__ void carry_emit_escapes(uint32_t* rec, uint32_t lane,
         }
         if (__ballot(esc != 0u) == 0ull) continue;
         const uint32_t cnt = __popc(esc);
-        const uint32_t incl = wave_incl_scan(cnt, lane);
+        const uint32_t incl = wave_incl_scan(cnt);
         uint32_t r = opos + incl - cnt;
 #pragma unroll
         for (int v = 0; v < 4; ++v)
@@ -485,7 +485,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         const uint32_t nw = (St.nbt + 31u) >> 5;
         const bool spilled = __ballot(nw > CAP) != 0ull;  // uniform: a chunk of this group did not fit its LDS words
         const uint32_t n_esc = active ? wave_sum(St.esc) : 0u;
-        const uint32_t incl = wave_incl_scan(nw, lane);
+        const uint32_t incl = wave_incl_scan(nw);
         const uint32_t lane_off = incl - nw;
         const uint32_t chunk_total = __shfl(incl, 63, 64);
         const uint32_t total = chunk_total + 2u * n_esc;  // 0 for an idle wavefront

@@ -179,9 +179,9 @@ __device__ __forceinline__ void hist_block(const uint8_t* base, uint32_t rem, ui
 }
 
 // ------------------------------------------------------------------------------------------------
-// Huffman codebook of one table, built by one work-group of 256 threads from the table's histogram.
-//   leaves ordered by (count, symbol); two queues (leaves, merged nodes in creation order); a tie
-//   between the queue heads takes the leaf; longest code above LMAX: lengths are cut to LMAX, the
+// Huffman codebook of one table, built by one work-group (NT threads) from the table's histogram.
+//   leaves ordered by (count, symbol); two queues (leaves, merged nodes in creation order; one list in their order
+//   where a wavefront holds all used symbols); a tie between the queue heads takes the leaf; longest code above LMAX: lengths are cut to LMAX, the
 //   Kraft sum is repaired one unit at a time (a code of length LMAX pairs up with a code taken from
 //   the deepest shorter level) and the resulting lengths are handed out most frequent symbol first;
 //   canonical codewords in (length, symbol) order.  One used symbol: length 0.
@@ -762,7 +762,7 @@ __device__ __forceinline__ void emit_escapes(uint32_t* rec, uint32_t lane, const
             esc |= (((valid >> v) & 1u) && ((m >> (8 * v)) & 0xFFu) == kWinEsc) ? (1u << v) : 0u;
         if (__ballot(esc != 0u) == 0ull) continue;
         const uint32_t cnt = __popc(esc);
-        const uint32_t incl = wave_incl_scan(cnt, lane);
+        const uint32_t incl = wave_incl_scan(cnt);
         uint32_t r = opos + incl - cnt;
 #pragma unroll
         for (int v = 0; v < 4; ++v)

@@ -165,7 +165,7 @@ static inline size_t codebook_lds(const Geom& g, uint32_t tpw) { return tpw == 4
 
 // ------------------------------------------------------------------------------------------------
 // finalize: code-length blocks behind the payload, header, directory, padding, size metadata; clears the
-// per-call control words for the next call.  Work-groups of 1024 threads: every work-group works out where the
+// per-call control words for the next call.  Every work-group (256 threads, or 1024: finalize_threads) works out where the
 // code-length blocks go (a scan over the tables) and writes the blocks of its share of the tables, a wavefront
 // per table; the first work-group also writes everything else.
 // ------------------------------------------------------------------------------------------------

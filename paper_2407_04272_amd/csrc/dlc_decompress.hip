@@ -224,7 +224,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
     struct GroupPlace { bool ok; uint32_t n_esc, total, off; const uint32_t* words; };  // off: the lane's chunk starts there
     auto group_place = [&](const GroupHead& h) {
         GroupPlace P;
-        const uint32_t incl = wave_incl_scan(h.cw, lane);
+        const uint32_t incl = wave_incl_scan(h.cw);
         P.total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
         const uint64_t gend = h.gnext == 0xFFFFFFFFu ? H.words_total : (uint64_t)h.gnext;
         P.ok = !(gend > H.words_total || (uint64_t)h.goff + P.total > gend || ((gend - h.goff - P.total) & 1ull));

@@ -141,7 +141,7 @@ __device__ __forceinline__ void emit_slow(const EmitEnv& E, EmitState& S, uint32
     if (rec && __ballot(em != 0u) != 0ull) {
         const uint32_t cnt = __popc(em);
         if (S.nesc < kEncRecs) {  // uniform
-            const uint32_t incl = wave_incl_scan(cnt, E.lane);
+            const uint32_t incl = wave_incl_scan(cnt);
             uint32_t r = S.nesc + incl - cnt;
 #pragma unroll
             for (int v = 0; v < 4; ++v)
@@ -326,7 +326,7 @@ __device__ __forceinline__ void encode_groups(const GroupJob& J, const void* pay
         last_word(St);
     }
     const uint32_t nw = active ? (St.nbt + 31u) >> 5 : 0u, n_esc = St.nesc;
-    const uint32_t incl = wave_incl_scan(nw, lane);
+    const uint32_t incl = wave_incl_scan(nw);
     const uint32_t lane_off = incl - nw;
     const uint32_t chunk_total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
     const uint32_t total = chunk_total + 2u * n_esc;  // 0 for an idle wavefront

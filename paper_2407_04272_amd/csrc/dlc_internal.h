@@ -188,7 +188,7 @@ __device__ __forceinline__ uint32_t load4(const void* gbase, uint32_t off, uint3
 
 // inclusive prefix sum over the 64 lanes (all of them active), in registers: four shifts inside the rows of sixteen
 // lanes, then the rows' sums handed on (six dependent instructions; as six LDS permutes it took 700 cycles)
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, uint32_t) {
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
     auto dpp = [](uint32_t x, auto ctrl, auto rows) {
         return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, decltype(rows)::value, 0xF, false);
     };
@@ -204,7 +204,7 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, uint32_t) {
 
 // sum over the 64 lanes (all of them active)
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v, 0u), 63);
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v), 63);
 }
 
 // Exclusive prefix sum over a work-group of NW wavefronts (blockDim.x == 64*NW); every thread gets the
@@ -212,12 +212,12 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
 template <int NW>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* red, uint32_t tid, uint32_t* total) {
     const uint32_t lane = tid & 63u, wave = tid >> 6;
-    const uint32_t incl = wave_incl_scan(v, lane);
+    const uint32_t incl = wave_incl_scan(v);
     if (lane == 63) red[wave] = incl;
     __syncthreads();
     if (wave == 0) {
         const uint32_t w = lane < (uint32_t)NW ? red[lane] : 0u;
-        const uint32_t wi = wave_incl_scan(w, lane);
+        const uint32_t wi = wave_incl_scan(w);
         if (lane < (uint32_t)NW) red[lane] = wi - w;
         if (lane == NW - 1) red[NW] = wi;
     }

@@ -1,5 +1,6 @@
 """The encoders of whole groups (small tables in one launch, larger ones from the symbol plane) at the sizes and symbol
-distributions where their branches change, against the oracle byte for byte."""
+distributions where their branches change, against the oracle byte for byte.  (Groups that are walked more than once:
+test_gpu_long_chunks.py.)"""
 import numpy as np
 import pytest
 
