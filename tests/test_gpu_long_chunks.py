@@ -73,3 +73,28 @@ def test_row_matching(kind, T, B, D, dtype):
     rng = np.random.default_rng(T + kind[1])
     x = _payload(rng, kind, (T, (B + 1) // 2, D))
     _check(T, B, D, 256, dtype, True, np.take_along_axis(x, rng.integers(0, x.shape[1], (T, B, 1)), axis=1))
+
+
+@pytest.mark.parametrize("kind", [("span", 5), ("span", 17), ("span", 100)], ids=["linear", "two_windows", "three_windows"])
+def test_a_chunk_that_ends_early_is_refused(kind):
+    """A word of one chunk booked to the next: the group's words are all there, the chunk's last codeword reaches past its end."""
+    import torch
+    from paper_2407_04272_amd import binding as b
+    T, B, D, S = 260, 150, 128, 256
+    x = _payload(np.random.default_rng(5), kind, (T, B, D))
+    ebs = np.full(T, EB, np.float32)
+    ctx = b.Context(b.make_config(b.F32, T, B, D, 512, S, 12, 0))
+    ctx.set_error_bounds(eb=ebs)
+    good = oracle.compress(x, ebs, 512, S, 12).data
+    off_chunk = int(good[48:].view(np.uint64)[3])  # after escapes, words and the group table's offset
+    rec = torch.zeros((T, B, D), dtype=torch.float32, device="cuda")
+    assert ctx.decompress(to_device(good), good.size, rec) == 0 and ctx.sync_status() == 0
+    for chunk in (0, 30, 62, 64 * 517 + 17):
+        bad = good.copy()
+        bad[off_chunk + chunk] -= 1
+        bad[off_chunk + chunk + 1] += 1
+        assert oracle.decompress(bad, x.shape, x.dtype)[0] != 0
+        assert ctx.decompress(to_device(bad), bad.size, rec) == 0
+        assert ctx.sync_status() == b.ECORRUPT, chunk
+    assert ctx.decompress(to_device(good), good.size, rec) == 0 and ctx.sync_status() == 0
+    assert np.array_equal(rec.cpu().numpy().view(np.uint32), oracle.decompress(good, x.shape, x.dtype)[1].view(np.uint32))
