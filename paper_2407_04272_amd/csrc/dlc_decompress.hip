@@ -126,12 +126,20 @@ __global__ __launch_bounds__(256) void k_dec_refs(Geom g, FixedLayout F, const u
 // validation.
 //
 // A lane's symbols hang on one another (the next look-up needs the length of the code before it), so the time a
-// group takes is the length of that chain.  The decode table therefore answers for two codewords at a time:
-//   entry[i] = single << 31 | adv << 27 | (len1 - 1) << 24 | bin2 << 12 | bin1     for the LMAX-bit string i,
-// bin = symbol - R as a signed 12-bit number (what the reconstruction multiplies by 2 * bound); bin1: the codeword
-// that prefixes i, len1 its length; bin2: the codeword after it when both fit into the LMAX bits (and len1 <= 8:
-// three bits hold it), adv = len1 + len2 then.  Otherwise single = 1 and adv = len1: a second look-up follows,
-// rare for the short codes of frequent symbols.
+// group takes is the length of that chain.  The decode table therefore answers for two codewords at a time
+// (dec_entry): the bins of both, and `adv`, the bits they take.  Where the second does not fit into the LMAX bits,
+// single = 1 and adv = len1: a second look-up follows, rare for the short codes of frequent symbols.
+//
+// With few groups the decoder is bound by the latencies of a turn (four symbols a lane), each look-up a round trip to LDS,
+// so the turn is built to have little between them.  The staged words are stored with their bits reversed and the
+// table is indexed by reversed strings: the stream then runs from the low end of a word to the high end, and a position
+// in it is one number `p`, whose low five bits are a shift by themselves.  A turn reads the 96 bits around its place
+// from LDS and shifts 64 out of them, which is all that four codewords can need: no words are carried from turn to
+// turn and none is moved on under a condition.  `p` counts from 30, from the word before the chunk's first: the
+// window starts two bits before the next codeword, and masked it is a table entry's byte offset as it is.  Measured against
+// two words and a prefetched third in registers, moved on after every look-up, with 12-bit bins converted one by one (75
+// instructions a turn, now 35): 26 tables of 2048 x 64 36.7 us, now 31.0 (a turn of a wavefront 730 cycles, now 600); seven of
+// 2999 x 37 38, now 28; 512 MiB, where the stores bound it, 115.5, now 111.4.
 //
 // The bit stream words reach the lanes through LDS: the words of a group lie one after the other, so a wavefront copies
 // them as they lie (256 bytes an instruction) and every lane reads its own from where its chunk starts.  A group of more
@@ -154,11 +162,10 @@ constexpr uint32_t kSkipWords = 256 * kW / kV / 32;   // row matching: a bit per
 struct DecScratch {  // lives in the staging area until the decode table is complete; one[] is followed by sorted[K] and len[K]
     uint32_t ok;
     uint32_t cl[kLmaxLimit + 2], first[kLmaxLimit + 2], index[kLmaxLimit + 2];
-    alignas(16) uint16_t one[1 << kLmaxLimit];  // len << 12 | symbol of the codeword that prefixes the LMAX-bit string i; filled 16 bytes at a time
+    alignas(16) uint16_t one[1 << kLmaxLimit];  // len << 12 | symbol of the codeword that the LMAX-bit string starts with whose first bit is bit 0 of the index
     __device__ uint16_t* sorted() { return reinterpret_cast<uint16_t*>(this + 1); }
     __device__ uint8_t* len(uint32_t K) { return reinterpret_cast<uint8_t*>(sorted() + K); }
 };
-static_assert(offsetof(DecScratch, one) % 16 == 0 && sizeof(DecScratch) % 16 == 0, "stores of 16 bytes (the decode table before it has at least 16 entries)");
 // bytes behind the decode table: the staging areas (`stage` words) of nw wavefronts, or the scratch where that is larger
 __host__ __device__ constexpr uint32_t dec_area_bytes(uint32_t nw, uint32_t stage, uint32_t K) {
     return nw * stage * 4u > (uint32_t)((sizeof(DecScratch) + 3u * K + 15u) & ~15u) ? nw * stage * 4u : (uint32_t)((sizeof(DecScratch) + 3u * K + 15u) & ~15u);
@@ -176,21 +183,76 @@ __device__ __forceinline__ uint32_t dec_first_code(DecScratch& sc, const uint32_
 }
 
 typedef __attribute__((address_space(3))) uint32_t lds_word_t;
+typedef __attribute__((address_space(3))) uint8_t lds_byte_t;
+__device__ __forceinline__ uint32_t lds_word(const lds_byte_t* base, uint32_t off) { return *reinterpret_cast<const lds_word_t*>(base + off); }
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 
-template <bool F16, bool VEC, uint32_t NW>
+// An entry of the decode table, for the codewords of symbols s1 and s2 (s2 where both fit: `both`), l1 and l2 bits long.
+// WIDE == false (radius up to 512): the bins b = symbol - R as binary16 numbers 1024 + b, of which only the low eleven bits
+// vary: one AND-OR makes a pair of them, a packed addition takes the 1024 off (exact: integers up to 2048) and one
+// fused multiply-add each makes the product with 2 * bound, converted on the way.
+//   single << 31 | adv << 27 | low bits of 1024 + b2 << 16 | len1 << 11 | low bits of 1024 + b1
+// WIDE (radius 1024 and 2048): the bins as signed 12-bit numbers; len1 has three bits, so a first code of more than 8 stays alone.
+//   single << 31 | adv << 27 | (len1 - 1) << 24 | b2 << 12 | b1
+constexpr uint32_t kHalfLow = 0x07FF07FFu, kHalfHigh = 0x60006000u;
+template <bool WIDE>
+__device__ __forceinline__ uint32_t dec_entry(uint32_t s1, uint32_t l1, uint32_t s2, uint32_t l2, uint32_t R, uint32_t LMAX) {
+    if constexpr (WIDE) {
+        const uint32_t q1 = (s1 - R) & 0xFFFu, q2 = (s2 - R) & 0xFFFu;
+        return l1 + l2 <= LMAX && l1 <= 8u ? ((l1 + l2) << 27) | ((l1 - 1u) << 24) | (q2 << 12) | q1 : 0x80000000u | (l1 << 27) | q1;
+    } else {
+        // binary16 of t in [512, 1536): 0x6000 + 2 (t - 512) below 1024, 0x6400 + (t - 1024) from there on
+        auto low = [&](uint32_t s) { const uint32_t t = s + 1024u - R; return t < 1024u ? 2u * t - 1024u : t; };
+        const uint32_t e1 = (l1 << 11) | low(s1);
+        return l1 + l2 <= LMAX ? ((l1 + l2) << 27) | (low(s2) << 16) | e1 : 0x80000000u | (l1 << 27) | e1;
+    }
+}
+template <bool WIDE>
+__device__ __forceinline__ uint32_t dec_len1(uint32_t e) {
+    if constexpr (WIDE) return (int)e < 0 ? (e >> 27) & 15u : ((e >> 24) & 7u) + 1u;
+    else return (e >> 11) & 15u;
+}
+template <bool WIDE>  // e with the first symbol of f as its second
+__device__ __forceinline__ uint32_t dec_join(uint32_t e, uint32_t f) {
+    if constexpr (WIDE) return (e & 0xFFFu) | (f << 12 & 0xFFF000u);
+    else return (e & 0xFFFFu) | (f << 16 & 0x07FF0000u);
+}
+template <bool WIDE>  // the two reconstructions: the product of a whole number and 2 * bound, rounded once
+__device__ __forceinline__ void dec_values(uint32_t e, uint32_t half_high, float ebx2, float* v) {
+    if constexpr (WIDE) {
+        v[0] = (float)((int)(e << 20) >> 20) * ebx2;
+        v[1] = (float)((int)(e << 8) >> 20) * ebx2;
+    } else {
+        union { uint32_t u; half2_t h; } b;
+        b.u = (e & kHalfLow) | half_high;
+        b.h -= half2_t{(_Float16)1024.0f, (_Float16)1024.0f};
+        v[0] = __builtin_fmaf((float)b.h.x, ebx2, 0.0f);
+        v[1] = __builtin_fmaf((float)b.h.y, ebx2, 0.0f);
+    }
+}
+constexpr uint32_t kDecBit0 = 30;  // `p` at a chunk's first bit
+struct DecTail {
+    unsigned long long sum[kDecWaves];
+    uint32_t bad, pad;
+};
+constexpr uint32_t kDecPad = 512;  // bytes behind the staging areas: a damaged chunk runs at most 256 codes of 12 bits past its words' start
+
+template <bool F16, bool VEC, bool WIDE, uint32_t NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) void k_decode(Geom g, FixedLayout F, const uint8_t* comp, uint64_t comp_bytes,
                                                         Ctrl* ctrl, void* outp, uint32_t wpt, uint32_t iters, uint32_t stage_words,
                                                         uint32_t* esc_seen, uint32_t* arrived) {
     constexpr uint32_t kDecThreads = 64u * NW;
-    extern __shared__ __align__(16) uint32_t s_lut[];  // [1 << LMAX] decode table, then NW staging arrays
-    __shared__ uint32_t s_bad;
-    __shared__ unsigned long long s_sum[NW];
+    // [1 << LMAX] decode table, NW staging arrays (the scratch before), row matching's bits, padding, DecTail.  All of the kernel's
+    // LDS is in this one piece, which therefore starts at LDS address 0: a masked window is a table entry's address as it is
+    extern __shared__ __align__(16) uint32_t s_lut[];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t t = blockIdx.x / wpt, b = blockIdx.x % wpt;
     const uint32_t dst = t / g.TD, tl = t - dst * g.TD;  // the container this table is in, and its place there
     comp += (uint64_t)dst * comp_bytes;
     const uint32_t lut_n = 1u << g.LMAX;
     DecScratch& sc = *reinterpret_cast<DecScratch*>(s_lut + lut_n);
+    DecTail& tail = *reinterpret_cast<DecTail*>(reinterpret_cast<unsigned char*>(s_lut + lut_n) + dec_area_bytes(NW, stage_words, g.K) +
+                                                (g.lz ? NW * kSkipWords * 4u : 0u) + kDecPad);
     const uint32_t* const goffs = reinterpret_cast<const uint32_t*>(comp + F.off_group);
     const uint32_t n_groups = g.TD * g.G;
     // What a group's decoding starts from sits in the sections whose place the geometry fixes (the host has made
@@ -209,7 +271,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
     gh.cw = 0; gh.goff = 0; gh.gnext = 0;
     if (grp_first < g.G) gh = group_head(grp_first);
     const DecHead H = dec_validate(g, F, comp, comp_bytes, tl);
-    if (tid == 0) { sc.ok = H.ok ? 1u : 0u; s_bad = 0u; }
+    if (tid == 0) { sc.ok = H.ok ? 1u : 0u; tail.bad = 0u; }
     if (tid < kLmaxLimit + 2) sc.cl[tid] = 0;
     __syncthreads();
     const uint32_t nl = H.ok ? H.sym_hi - H.sym_lo + 1u : 0u;
@@ -247,15 +309,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
     };
     auto put_group = [&](const GroupPlace& P, const uint32_t (&w)[kRows]) {
 #pragma unroll
-        for (uint32_t k = 0; k < kRows; ++k) stage[k * kW + lane] = w[k];
-        for (uint32_t k = kStage + lane; k < P.total; k += kW) stage[k] = P.words[k];
+        for (uint32_t k = 0; k < kRows; ++k) stage[k * kW + lane] = __builtin_bitreverse32(w[k]);
+        for (uint32_t k = kStage + lane; k < P.total; k += kW) stage[k] = __builtin_bitreverse32(P.words[k]);
     };
     // A window: the words of every chunk from its lane's `from` on (counted inside the chunk), min(TL, kWin) a chunk, by
     // teams of TL lanes, a chunk a team; the loads [I0, I0 + w's size) of the TL that make the window.  What follows a chunk's
     // end comes from the next chunk; nothing past the group's end is read.
     auto fetch_window = [&](auto tl, auto i0, const GroupPlace& P, uint32_t from, auto& w) {
         constexpr uint32_t TL = decltype(tl)::value, I0 = decltype(i0)::value;
-        const uint32_t at = P.off + from, team = lane / TL, k = lane % TL, last = P.total - 1u;
+        uint32_t ln = lane;
+        asm volatile("" : "+v"(ln));  // (worked out where it is needed: hoisted out of the loops, the lane numbers below took 46 registers)
+        const uint32_t at = P.off + from, team = ln / TL, k = ln % TL, last = P.total - 1u;
 #pragma unroll
         for (uint32_t i = 0; i < sizeof(w) / 4u; ++i)
             w[i] = word_at(P, min((uint32_t)__builtin_amdgcn_ds_bpermute((int)(((I0 + i) * (kW / TL) + team) * 4u), (int)at) + k, last));
@@ -265,7 +329,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
         const uint32_t team = lane / TL, k = lane % TL;
         if (k < kWin) {
 #pragma unroll
-            for (uint32_t i = 0; i < sizeof(w) / 4u; ++i) stage[((I0 + i) * (kW / TL) + team) * kWin + k] = w[i];
+            for (uint32_t i = 0; i < sizeof(w) / 4u; ++i) stage[((I0 + i) * (kW / TL) + team) * kWin + k] = __builtin_bitreverse32(w[i]);
         }
     };
     // the words come from other lanes of the wavefront.  The wait: a window's lanes that store nothing leave their loads unread,
@@ -308,14 +372,14 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
         // and TD * n < 2^32 positions in all; across threads they are added as 64-bit values)
         unsigned long long sum = part;
         for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-        if (lane == 0) s_sum[wave] = sum;
+        if (lane == 0) tail.sum[wave] = sum;
         __syncthreads();
         if (tid == 0) {
             unsigned long long all = 0;
-            for (uint32_t k = 0; k < NW; ++k) all += s_sum[k];
-            if (all != H.n_esc_total) s_bad = 1u;
+            for (uint32_t k = 0; k < NW; ++k) all += tail.sum[k];
+            if (all != H.n_esc_total) tail.bad = 1u;
         }
-        if (big) s_bad = 1u;
+        if (big) tail.bad = 1u;
     }
     __syncthreads();
     const bool ok2 = sc.ok != 0;  // every thread reads the same value, then nobody writes before the barrier
@@ -323,7 +387,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
     if (ok2 && H.n_used == 1) {
         if (tid == 0 && (H.sym_lo != H.sym_hi || sc_len[0] != 0)) sc.ok = 0;
         // length 0: every look-up gives one symbol and moves on by nothing
-        for (uint32_t i = tid; i < lut_n; i += kDecThreads) s_lut[i] = 0x80000000u | ((H.sym_lo - g.R) & 0xFFFu);
+        const uint32_t e = dec_entry<WIDE>(H.sym_lo, 0u, 0u, g.LMAX + 1u, g.R, g.LMAX);
+        for (uint32_t i = tid; i < lut_n; i += kDecThreads) s_lut[i] = e;
     } else if (ok2) {
         if (wave == 0) {
             // first wavefront: every lane derives the same per-length tables, then the symbols are put in
@@ -369,20 +434,20 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
 #pragma unroll
             for (uint32_t l = 1; l <= (uint32_t)kLmaxLimit; ++l)
                 limit[l] = l <= g.LMAX ? (sc.first[l] + sc.cl[l]) << (g.LMAX - l) : 0xFFFFFFFFu;
-            for (uint32_t i0 = tid * 8u; i0 < lut_n; i0 += kDecThreads * 8u) {  // (lut_n >= 16: a multiple of 8)
+            // (the eight: strings that agree in all but their last three bits, an eighth of the table apart each)
+            const uint32_t eighth = lut_n >> 3;
+            for (uint32_t u = tid; u < eighth; u += kDecThreads) {  // (lut_n >= 16: a multiple of 8)
+                const uint32_t i0 = __builtin_bitreverse32(u) >> (32u - g.LMAX);
                 const uint32_t ea = dec_first_code(sc, limit, i0, g.LMAX), la = ea >> 12;
-                uint32_t e[8];
                 if (g.LMAX - la >= 3u) {
 #pragma unroll
-                    for (uint32_t k = 0; k < 8; ++k) e[k] = ea;
+                    for (uint32_t k = 0; k < 8; ++k) sc.one[u + k * eighth] = (uint16_t)ea;
                 } else {
-                    e[0] = ea;
+                    sc.one[u] = (uint16_t)ea;
 #pragma unroll
-                    for (uint32_t k = 1; k < 8; ++k) e[k] = dec_first_code(sc, limit, i0 + k, g.LMAX);
+                    for (uint32_t k = 1; k < 8; ++k)  // (k's bits are the string's last three, in reverse)
+                        sc.one[u + k * eighth] = (uint16_t)dec_first_code(sc, limit, i0 | ((k & 1u) << 2 | (k & 2u) | k >> 2), g.LMAX);
                 }
-                uint4 v;
-                v.x = e[0] | (e[1] << 16); v.y = e[2] | (e[3] << 16); v.z = e[4] | (e[5] << 16); v.w = e[6] | (e[7] << 16);
-                *reinterpret_cast<uint4*>(&sc.one[i0]) = v;
             }
             __syncthreads();  // (uniform: sc.ok was read after a barrier and nothing has written it since)
             for (uint32_t i0 = tid; i0 < lut_n; i0 += kDecThreads * 4u) {  // four strings in flight per thread
@@ -390,15 +455,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
 #pragma unroll
                 for (uint32_t k = 0; k < 4; ++k) e1[k] = sc.one[(i0 + k * kDecThreads) & (lut_n - 1u)];
 #pragma unroll
-                for (uint32_t k = 0; k < 4; ++k)  // what follows the first codeword
-                    e2[k] = sc.one[((i0 + k * kDecThreads) << (e1[k] >> 12)) & (lut_n - 1u)];
+                for (uint32_t k = 0; k < 4; ++k)  // what follows the first codeword (zeros behind the LMAX bits)
+                    e2[k] = sc.one[((i0 + k * kDecThreads) & (lut_n - 1u)) >> (e1[k] >> 12)];
 #pragma unroll
                 for (uint32_t k = 0; k < 4; ++k) {
-                    const uint32_t i = i0 + k * kDecThreads, l1 = e1[k] >> 12, l2 = e2[k] >> 12;
-                    const bool both = l1 + l2 <= g.LMAX && l1 <= 8u;  // the second codeword lies inside the LMAX bits too
-                    const uint32_t q1 = ((e1[k] & 0xFFFu) - g.R) & 0xFFFu, q2 = ((e2[k] & 0xFFFu) - g.R) & 0xFFFu;
-                    if (i < lut_n)
-                        s_lut[i] = both ? ((l1 + l2) << 27) | ((l1 - 1u) << 24) | (q2 << 12) | q1 : 0x80000000u | (l1 << 27) | q1;
+                    const uint32_t i = i0 + k * kDecThreads;
+                    if (i < lut_n) s_lut[i] = dec_entry<WIDE>(e1[k] & 0xFFFu, e1[k] >> 12, e2[k] & 0xFFFu, e2[k] >> 12, g.R, g.LMAX);
                 }
             }
         }
@@ -410,16 +472,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
     bool bad = false;      // something in this wavefront's groups does not add up
     if (valid) {
         const float ebx2 = H.ebx2;
-        const uint32_t lshift = 32u - g.LMAX;
+        const uint32_t lut_mask = (lut_n - 1u) << 2;
+        uint32_t half_high = kHalfHigh;
+        asm("" : "+v"(half_high));  // (a register: an AND-OR takes one other constant at most)
         uint8_t* tab = static_cast<uint8_t*>(outp) + (size_t)t * g.n * g.es;
         const uint32_t* const ref = H.ref_off ? reinterpret_cast<const uint32_t*>(comp + H.ref_off) : nullptr;
         uint32_t* const skipbits = reinterpret_cast<uint32_t*>(s_lut + lut_n) + dec_area_bytes(NW, stage_words, g.K) / 4u + wave * kSkipWords;
         for (uint32_t it = 0; it < iters; ++it) {
             const uint32_t grp = grp_first + it * NW;
             if (grp >= g.G) break;  // whole wavefront
-            // A lane's place in its bit stream: the two words w0, w1 it is decoding from, `c` bits of w0 already used
-            // (0..31), the word after them in `nxt`, fetched ahead from the staging area; na = LDS address of `nxt`, n0 that of
-            // word `wbase` of the chunk.
             if (it != 0) {
                 gh = group_head(grp);
                 gp = group_place(gh);
@@ -442,16 +503,16 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
                 put_window(k32, kr, w);
             }
             staged();
-            const uint32_t n0 = st0 + (linear ? gp.off : lane * kWin) * 4u;
-            const uint32_t na_max = st0 + (stage_words - 1u) * 4u;
-            uint32_t wbase = 0, na = n0, c = 0;
-            // windows: a lane needs a new one when `nxt` is among the last two words (a turn moves at most two words on), unless
-            // its chunk ends in the one it has
-            uint32_t renew_at = (!linear && cw > kWin) ? n0 + (kWin - 2u) * 4u : 0xFFFFFFFFu;
-            auto lds_word = [&](uint32_t a) { return *reinterpret_cast<lds_word_t*>(min(a, na_max)); };
-            auto renew = [&]() {  // the words from `nxt` on, anew, so that `nxt` is the first
-                wbase += (na - n0) >> 2;
-                na = n0;
+            // a lane's place in its bit stream: bit p of the words from LDS address wa on, which is the word before its
+            // chunk's word `wbase`
+            uint32_t wa = st0 + (linear ? gp.off : lane * kWin) * 4u - 4u;
+            asm("" : "+v"(wa));  // (one register: the compiler made two, for the words at wa and those at wa + 4)
+            uint32_t wbase = 0, p = kDecBit0;
+            // windows: a lane needs a new one when a turn could read past the last word, unless its chunk ends in the one it has
+            uint32_t renew_at = (!linear && cw > kWin) ? (kWin - 1u) * 32u : 0xFFFFFFFFu;
+            auto renew = [&]() {  // the words from the first that the next turn reads on, anew
+                wbase += (p >> 5) - 1u;
+                p = (p & 31u) + 32u;
                 const uint32_t left = cw > wbase ? cw - wbase : 0u;
                 uint32_t w[16];
                 if (__ballot(left > 16u) != 0ull) {
@@ -464,19 +525,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
                     put_window(k16, k0, w);
                 }
                 staged();
-                renew_at = left > kWin ? n0 + (kWin - 2u) * 4u : 0xFFFFFFFFu;
+                renew_at = left > kWin ? (kWin - 1u) * 32u : 0xFFFFFFFFu;
             };
-            uint32_t w0 = lds_word(na), w1 = lds_word(na + 4u), nxt = lds_word(na + 8u);
-            na += 8u;
-            const uint32_t base = grp * (kW * g.S) + lane * kV;
-            const uint32_t turns = (min(g.n - grp * (kW * g.S), kW * g.S) + kW * kV - 1u) / (kW * kV);  // (the table can end in this group)
+            const uint32_t gstart = grp * (kW * g.S), in_group = min(g.n - gstart, kW * g.S);  // (the table can end in this group)
+            uint8_t* const gout = tab + (size_t)gstart * g.es;
             // row matching: which rows of this group refer to another row, as a bit per row in LDS (at most 64*S/4 rows)
-            const uint32_t row_lo = (grp * (kW * g.S)) / g.D;
+            const uint32_t row_lo = gstart / g.D;
             // local / D as a multiplication (a division of its own is a third of a turn's instructions): with the reciprocal
             // rounded up it is exact while local * D < 2^32, and local < 64 * S + D
             const uint32_t row_magic = (ref != nullptr && g.D > 1u && g.D <= 32768u) ? 0xFFFFFFFFu / g.D + 1u : 0u;
             if (ref != nullptr) {
-                const uint32_t last_el = min(g.n, (grp + 1u) * (kW * g.S)) - 1u;
+                const uint32_t last_el = gstart + in_group - 1u;
                 const uint32_t n_rows = last_el / g.D - row_lo + 1u;  // <= 64*S/4 because dim % 4 == 0 here
                 for (uint32_t r0 = 0; r0 < n_rows; r0 += 64) {  // uniform trip count
                     const uint32_t r = r0 + lane;
@@ -486,81 +545,75 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
                 }
                 __builtin_amdgcn_wave_barrier();
             }
-            const bool edge = g.n - grp * (kW * g.S) < kW * g.S;  // uniform
-            for (uint32_t j = 0; j < turns; ++j) {
-                const uint32_t idx = base + j * (kW * kV);
-                if (__ballot(na >= renew_at) != 0ull) renew();  // (whole wavefront)
-                bool coded = idx < g.n;
+            // turn j of the group; EDGE: the table ends in it, so a lane can have fewer than four elements, or none
+            auto turn = [&](auto edge, uint32_t j) {
+                constexpr bool EDGE = decltype(edge)::value;
+                const uint32_t el = lane * kV + j * (kW * kV);  // the lane's first element, counted from the group's
+                if (__ballot(p >= renew_at) != 0ull) renew();  // (whole wavefront)
+                bool coded = !EDGE || el < in_group;
                 if (ref != nullptr && coded) {  // a row that refers to another has no bits in the stream; it is copied afterwards
-                    const uint32_t local = idx - row_lo * g.D, r = row_magic ? __umulhi(local, row_magic) : local / g.D;
+                    const uint32_t local = gstart + el - row_lo * g.D, r = row_magic ? __umulhi(local, row_magic) : local / g.D;
                     coded = ((skipbits[r >> 5] >> (r & 31u)) & 1u) == 0u;
                 }
-                if (coded) {
-                    float v4[4];
+                if (!coded) return;
+                const lds_byte_t* const a = reinterpret_cast<const lds_byte_t*>(wa + ((p >> 5) << 2));
+                const uint32_t x0 = lds_word(a, 0u), x1 = lds_word(a, 4u), x2 = lds_word(a, 8u);
+                uint32_t lo = __builtin_amdgcn_alignbit(x1, x0, p), hi = __builtin_amdgcn_alignbit(x2, x1, p);
+                float v4[4];
 #pragma unroll
-                    for (int h2 = 0; h2 < 2; ++h2) {
-                        const uint64_t win = (((uint64_t)w0 << 32) | w1) << c;  // the stream from the lane's place on
-                        const uint32_t e = s_lut[(uint32_t)(win >> 32) >> lshift];
-                        uint32_t adv = (e >> 27) & 15u;
-                        int q2 = (int)(e << 8) >> 20;
-                        if (__ballot((int)e < 0) != 0ull) {  // an entry that answers for one codeword only: the next one by a look-up of its own
-                            const uint32_t e2 = s_lut[(uint32_t)((win << adv) >> 32) >> lshift];
-                            if ((int)e < 0) {
-                                q2 = (int)(e2 << 20) >> 20;
-                                adv += (int)e2 < 0 ? (e2 >> 27) & 15u : ((e2 >> 24) & 7u) + 1u;
-                            }
-                        }
-                        if (!VEC && edge) {  // a turn can reach past the table's end: such a position has no bits
-                            if (idx + (uint32_t)(h2 * 2) + 1u >= g.n) {
-                                const uint32_t l1 = (int)e < 0 ? (e >> 27) & 15u : ((e >> 24) & 7u) + 1u;
-                                adv = idx + (uint32_t)(h2 * 2) < g.n ? l1 : 0u;
-                            }
-                        }
-                        c += adv;
-                        // past the end of w0: move on by a word (`nxt` is read whether or not: same value then)
-                        const bool step = c > 31u;
-                        w0 = step ? w1 : w0;
-                        w1 = step ? nxt : w1;
-                        c &= 31u;
-                        na += step ? 4u : 0u;
-                        nxt = lds_word(na);  // (what lies past the chunk's end is never part of a codeword of its own)
-                        v4[h2 * 2] = (float)((int)(e << 20) >> 20) * ebx2;
-                        v4[h2 * 2 + 1] = (float)q2 * ebx2;
+                for (int h = 0; h < 2; ++h) {
+                    uint32_t e = *reinterpret_cast<const lds_word_t*>(lo & lut_mask);
+                    uint32_t adv = (e >> 27) & 15u;
+                    const uint32_t len1 = EDGE ? dec_len1<WIDE>(e) : 0u;
+                    lo = __builtin_amdgcn_alignbit(hi, lo, adv);
+                    hi >>= adv;
+                    if ((int)e < 0) {  // an entry that answers for one codeword only: the next one by a look-up of its own
+                        const uint32_t f = *reinterpret_cast<const lds_word_t*>(lo & lut_mask), l2 = dec_len1<WIDE>(f);
+                        lo = __builtin_amdgcn_alignbit(hi, lo, l2);
+                        hi >>= l2;
+                        adv += l2;
+                        e = dec_join<WIDE>(e, f);
                     }
-                    // streaming stores: the output is written once and is larger than the caches (four elements at once want
-                    // no more than an element's alignment)
-                    if (VEC || idx + 3u < g.n) {
-                        if constexpr (F16) {
-                            typedef std::conditional_t<VEC, u32x2, u32x2_any> u2v;
-                            u2v o;
-                            o.x = (uint32_t)__half_as_ushort(half_rne(v4[0])) |
-                                  ((uint32_t)__half_as_ushort(half_rne(v4[1])) << 16);
-                            o.y = (uint32_t)__half_as_ushort(half_rne(v4[2])) |
-                                  ((uint32_t)__half_as_ushort(half_rne(v4[3])) << 16);
-                            __builtin_nontemporal_store(o, reinterpret_cast<u2v*>(reinterpret_cast<uint16_t*>(tab) + idx));
-                        } else {
-                            typedef std::conditional_t<VEC, u32x4, u32x4_any> u4v;
-                            u4v o4 = {__float_as_uint(v4[0]), __float_as_uint(v4[1]), __float_as_uint(v4[2]), __float_as_uint(v4[3])};
-                            __builtin_nontemporal_store(o4, reinterpret_cast<u4v*>(reinterpret_cast<float*>(tab) + idx));
-                        }
-                    } else {
-#pragma unroll
-                        for (int v = 0; v < 4; ++v)
-                            if (idx + v < g.n) {
-                                if constexpr (F16) reinterpret_cast<__half*>(tab)[idx + v] = half_rne(v4[v]);
-                                else reinterpret_cast<float*>(tab)[idx + v] = v4[v];
-                            }
+                    if constexpr (EDGE && !VEC) {  // a turn can reach past the table's end: such a position has no bits
+                        if (el + (uint32_t)(h * 2) + 1u >= in_group) adv = el + (uint32_t)(h * 2) < in_group ? len1 : 0u;
                     }
+                    p += adv;
+                    dec_values<WIDE>(e, half_high, ebx2, v4 + h * 2);
                 }
-            }
-            // a chunk's codewords end inside its words: w0 is two words before `nxt`, and c of its bits are used
-            if (__ballot(32u * (wbase + ((na - n0) >> 2) - 2u) + c > 32u * cw) != 0ull) bad = true;
+                // streaming stores: the output is written once and is larger than the caches (four elements at once want
+                // no more than an element's alignment)
+                uint8_t* const o = gout + el * (F16 ? 2u : 4u);
+                if (!EDGE || VEC || el + 3u < in_group) {
+                    if constexpr (F16) {
+                        typedef std::conditional_t<VEC, u32x2, u32x2_any> u2v;
+                        u2v o2;
+                        o2.x = (uint32_t)__half_as_ushort(half_rne(v4[0])) | ((uint32_t)__half_as_ushort(half_rne(v4[1])) << 16);
+                        o2.y = (uint32_t)__half_as_ushort(half_rne(v4[2])) | ((uint32_t)__half_as_ushort(half_rne(v4[3])) << 16);
+                        __builtin_nontemporal_store(o2, reinterpret_cast<u2v*>(o));
+                    } else {
+                        typedef std::conditional_t<VEC, u32x4, u32x4_any> u4v;
+                        u4v o4 = {__float_as_uint(v4[0]), __float_as_uint(v4[1]), __float_as_uint(v4[2]), __float_as_uint(v4[3])};
+                        __builtin_nontemporal_store(o4, reinterpret_cast<u4v*>(o));
+                    }
+                } else {
+#pragma unroll
+                    for (uint32_t v = 0; v < 4; ++v)
+                        if (el + v < in_group) {
+                            if constexpr (F16) reinterpret_cast<__half*>(o)[v] = half_rne(v4[v]);
+                            else reinterpret_cast<float*>(o)[v] = v4[v];
+                        }
+                }
+            };
+            const uint32_t whole = in_group / (kW * kV);
+            for (uint32_t j = 0; j < whole; ++j) turn(std::false_type{}, j);
+            if (in_group > whole * (kW * kV)) turn(std::true_type{}, whole);
+            // a chunk's codewords end inside its words
+            if (__ballot(32u * wbase + p - kDecBit0 > 32u * cw) != 0ull) bad = true;
             if (n_esc != 0u) {  // uniform over the wavefront: verbatim values over the decoded placeholders
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_s_waitcnt(0);  // the wavefront's own stores above are out before the overwrites below
                 const uint32_t* rec = reinterpret_cast<const uint32_t*>(comp + F.off_payload) + gh.goff + total;
-                const uint32_t lo = grp * (kW * g.S);
-                const uint32_t hi = min(g.n, lo + kW * g.S);
+                const uint32_t lo = gstart, hi = gstart + in_group;
                 bool off_range = false;
                 for (uint32_t r = lane; r < n_esc; r += 64) {
                     const uint32_t idx = rec[2u * r], raw = rec[2u * r + 1];
@@ -577,10 +630,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // counted before the work-group says it is done
         }
     }
-    if (bad && lane == 0) s_bad = 1u;
+    if (bad && lane == 0) tail.bad = 1u;
     __syncthreads();
     if (tid == 0) {
-        bool corrupt = !valid || s_bad != 0u;
+        bool corrupt = !valid || tail.bad != 0u;
         // the last work-group of the table: all escapes of the table have been seen
         if (__hip_atomic_fetch_add(&arrived[t], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == wpt) {
             const uint32_t seen = __hip_atomic_exchange(&esc_seen[t], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -648,14 +701,16 @@ hipError_t launch_decompress(const Geom& g, const uint8_t* comp, uint64_t comp_b
         dim3 grid(g.T * wpt), block(64 * nw);
         // a grid that leaves compute units free can have larger staging areas: 6 bits a symbol
         const uint32_t stage = (uint64_t)g.T * wpt <= 256u ? 3072u : kStage;
-        const size_t sm = ((size_t)4 << g.LMAX) + dec_area_bytes(nw, stage, g.K) + (g.lz ? (size_t)nw * kSkipWords * 4 : 0);
+        const size_t sm = ((size_t)4 << g.LMAX) + dec_area_bytes(nw, stage, g.K) + (g.lz ? (size_t)nw * kSkipWords * 4 : 0) + kDecPad + sizeof(DecTail);
         if (prof_on(pl, P_DECODE)) prof_begin(prof, P_DECODE, s);
-#define DLC_DEC2(FF, V, N) hipLaunchKernelGGL((k_decode<FF, V, N>), grid, block, sm, s, g, F, comp, (uint64_t)comp_bytes, w.ctrl, out, wpt, iters, stage, w.dec_esc, w.dec_arrive)
+#define DLC_DEC3(FF, V, W, N) hipLaunchKernelGGL((k_decode<FF, V, W, N>), grid, block, sm, s, g, F, comp, (uint64_t)comp_bytes, w.ctrl, out, wpt, iters, stage, w.dec_esc, w.dec_arrive)
+#define DLC_DEC2(FF, V, N) do { if (g.R > 512u) DLC_DEC3(FF, V, true, N); else DLC_DEC3(FF, V, false, N); } while (0)
 #define DLC_DEC(FF, V) do { if (nw == 8u) DLC_DEC2(FF, V, 8u); else if (nw == 4u) DLC_DEC2(FF, V, 4u); else DLC_DEC2(FF, V, 2u); } while (0)
         if (f16) { if (g.vec) DLC_DEC(true, true); else DLC_DEC(true, false); }
         else { if (g.vec) DLC_DEC(false, true); else DLC_DEC(false, false); }
 #undef DLC_DEC
 #undef DLC_DEC2
+#undef DLC_DEC3
         if (g.lz) {
             const uint32_t bx = std::min<uint32_t>((g.B * (g.D / 4u) + 255u) / 256u, 256u);
             if (f16) hipLaunchKernelGGL(k_row_copy<uint2>, dim3(bx, g.T), dim3(256), 0, s, g, comp, (uint64_t)comp_bytes, w.dtab, out);
@@ -668,18 +723,14 @@ hipError_t launch_decompress(const Geom& g, const uint8_t* comp, uint64_t comp_b
 
 template <uint32_t NW>
 static hipError_t decode_set_attributes() {
-    const int bytes = (4 << kLmaxLimit) + (int)dec_area_bytes(NW, 3072u, 4096u) + (int)(NW * kSkipWords * 4);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_decode<false, false, NW>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_decode<false, true, NW>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_decode<true, false, NW>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_decode<true, true, NW>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    const int bytes = (4 << kLmaxLimit) + (int)dec_area_bytes(NW, 3072u, 4096u) + (int)(NW * kSkipWords * 4) + (int)(kDecPad + sizeof(DecTail));
+    const void* ks[] = {reinterpret_cast<const void*>(k_decode<false, false, false, NW>), reinterpret_cast<const void*>(k_decode<false, true, false, NW>),
+                        reinterpret_cast<const void*>(k_decode<true, false, false, NW>), reinterpret_cast<const void*>(k_decode<true, true, false, NW>),
+                        reinterpret_cast<const void*>(k_decode<false, false, true, NW>), reinterpret_cast<const void*>(k_decode<false, true, true, NW>),
+                        reinterpret_cast<const void*>(k_decode<true, false, true, NW>), reinterpret_cast<const void*>(k_decode<true, true, true, NW>)};
+    hipError_t e = hipSuccess;
+    for (const void* k : ks)
+        if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     return e;
 }
 
