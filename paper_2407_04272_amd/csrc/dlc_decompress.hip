@@ -161,9 +161,10 @@ constexpr uint32_t kSkipWords = 256 * kW / kV / 32;   // row matching: a bit per
 
 struct DecScratch {  // lives in the staging area until the decode table is complete; one[] is followed by sorted[K] and len[K]
     uint32_t ok;
-    uint32_t cl[kLmaxLimit + 2], first[kLmaxLimit + 2], index[kLmaxLimit + 2];
-    alignas(16) uint16_t one[1 << kLmaxLimit];  // len << 12 | symbol of the codeword that the LMAX-bit string starts with whose first bit is bit 0 of the index
-    __device__ uint16_t* sorted() { return reinterpret_cast<uint16_t*>(this + 1); }
+    uint32_t cl[kLmaxLimit + 2], first[kLmaxLimit + 2];
+    uint32_t place[kLmaxLimit + 2];  // of the first symbol of a length in the order, less the first code of that length
+    uint16_t one[1 << kLmaxLimit];  // length and bin (dec_bin) of the codeword that the LMAX-bit string starts with whose first bit is bit 0 of the index
+    __device__ uint16_t* sorted() { return reinterpret_cast<uint16_t*>(this + 1); }  // the symbols' bins in (length, symbol) order
     __device__ uint8_t* len(uint32_t K) { return reinterpret_cast<uint8_t*>(sorted() + K); }
 };
 // bytes behind the decode table: the staging areas (`stage` words) of nw wavefronts, or the scratch where that is larger
@@ -171,40 +172,35 @@ __host__ __device__ constexpr uint32_t dec_area_bytes(uint32_t nw, uint32_t stag
     return nw * stage * 4u > (uint32_t)((sizeof(DecScratch) + 3u * K + 15u) & ~15u) ? nw * stage * 4u : (uint32_t)((sizeof(DecScratch) + 3u * K + 15u) & ~15u);
 }
 
-// (len << 12 | symbol) of the codeword that prefixes the LMAX-bit string i: its length is one more than the number of
-// limits at or below i (limit[l] = first string that no codeword of length <= l prefixes)
-__device__ __forceinline__ uint32_t dec_first_code(DecScratch& sc, const uint32_t (&limit)[kLmaxLimit + 1], uint32_t i,
-                                                   uint32_t LMAX) {
-    uint32_t l = 1;
-#pragma unroll
-    for (uint32_t k = 1; k < (uint32_t)kLmaxLimit; ++k) l += (i >= limit[k]) ? 1u : 0u;
-    const uint32_t c = i >> (LMAX - l);
-    return (l << 12) | sc.sorted()[sc.index[l] + (c - sc.first[l])];
-}
-
 typedef __attribute__((address_space(3))) uint32_t lds_word_t;
 typedef __attribute__((address_space(3))) uint8_t lds_byte_t;
 __device__ __forceinline__ uint32_t lds_word(const lds_byte_t* base, uint32_t off) { return *reinterpret_cast<const lds_word_t*>(base + off); }
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 
-// An entry of the decode table, for the codewords of symbols s1 and s2 (s2 where both fit: `both`), l1 and l2 bits long.
-// WIDE == false (radius up to 512): the bins b = symbol - R as binary16 numbers 1024 + b, of which only the low eleven bits
+// An entry of the decode table, for two codewords, l1 and l2 bits long, of bins b1 and b2 (bin = symbol - R).
+// WIDE == false (radius up to 512): the bins as binary16 numbers 1024 + b, of which only the low eleven bits
 // vary: one AND-OR makes a pair of them, a packed addition takes the 1024 off (exact: integers up to 2048) and one
 // fused multiply-add each makes the product with 2 * bound, converted on the way.
-//   single << 31 | adv << 27 | low bits of 1024 + b2 << 16 | len1 << 11 | low bits of 1024 + b1
-// WIDE (radius 1024 and 2048): the bins as signed 12-bit numbers; len1 has three bits, so a first code of more than 8 stays alone.
-//   single << 31 | adv << 27 | (len1 - 1) << 24 | b2 << 12 | b1
+//   single << 31 | adv << 27 | low bits of 1024 + b2 << 16 | l1 << 11 | low bits of 1024 + b1
+// WIDE (radius 1024 and 2048): the bins as signed 12-bit numbers; l1 has three bits, so a first code of more than 8 stays alone.
+//   single << 31 | adv << 27 | (l1 - 1) << 24 | b2 << 12 | b1
 constexpr uint32_t kHalfLow = 0x07FF07FFu, kHalfHigh = 0x60006000u;
 template <bool WIDE>
-__device__ __forceinline__ uint32_t dec_entry(uint32_t s1, uint32_t l1, uint32_t s2, uint32_t l2, uint32_t R, uint32_t LMAX) {
+__device__ __forceinline__ uint32_t dec_bin(uint32_t sym, uint32_t R) {  // the bits of a bin, as an entry has them
+    const uint32_t t = sym + 1024u - R;
+    if constexpr (WIDE) return (sym - R) & 0xFFFu;
+    else return t < 1024u ? 2u * t - 1024u : t;  // binary16 of t in [512, 1536): 0x6000 + 2 (t - 512), from 1024 on 0x6400 + (t - 1024)
+}
+template <bool WIDE>
+constexpr uint32_t kBinBits = WIDE ? 12u : 11u;  // l << kBinBits | bits of the bin: what one[] holds
+template <bool WIDE>  // of the codewords e1 and e2 (as in one[]); e2 counts if both fit into the LMAX bits
+__device__ __forceinline__ uint32_t dec_entry(uint32_t e1, uint32_t e2, uint32_t LMAX) {
+    const uint32_t l1 = e1 >> kBinBits<WIDE>, l = l1 + (e2 >> kBinBits<WIDE>);
     if constexpr (WIDE) {
-        const uint32_t q1 = (s1 - R) & 0xFFFu, q2 = (s2 - R) & 0xFFFu;
-        return l1 + l2 <= LMAX && l1 <= 8u ? ((l1 + l2) << 27) | ((l1 - 1u) << 24) | (q2 << 12) | q1 : 0x80000000u | (l1 << 27) | q1;
+        const uint32_t b1 = e1 & 0xFFFu;
+        return l <= LMAX && l1 <= 8u ? (l << 27) | ((l1 - 1u) << 24) | (e2 << 12 & 0xFFF000u) | b1 : 0x80000000u | (l1 << 27) | b1;
     } else {
-        // binary16 of t in [512, 1536): 0x6000 + 2 (t - 512) below 1024, 0x6400 + (t - 1024) from there on
-        auto low = [&](uint32_t s) { const uint32_t t = s + 1024u - R; return t < 1024u ? 2u * t - 1024u : t; };
-        const uint32_t e1 = (l1 << 11) | low(s1);
-        return l1 + l2 <= LMAX ? ((l1 + l2) << 27) | (low(s2) << 16) | e1 : 0x80000000u | (l1 << 27) | e1;
+        return l <= LMAX ? (l << 27) | (e2 << 16 & 0x07FF0000u) | e1 : 0x80000000u | (l1 << 27) | e1;
     }
 }
 template <bool WIDE>
@@ -230,6 +226,156 @@ __device__ __forceinline__ void dec_values(uint32_t e, uint32_t half_high, float
         v[1] = __builtin_fmaf((float)b.h.y, ebx2, 0.0f);
     }
 }
+
+// The code lengths of a table from the container, to be asked for before the groups' words.  Symbols that span at most 64: the
+// length of symbol sym_lo + lane, in every wavefront.  A wider span: all lengths to LDS, counted.
+template <uint32_t NT>
+__device__ __forceinline__ uint32_t dec_lengths(const Geom& g, const DecHead& H, const uint8_t* comp, DecScratch& sc, uint32_t tid) {
+    const uint32_t nl = H.sym_hi - H.sym_lo + 1u, lane = tid & 63u;
+    if (!H.ok) return 0u;  // uniform, and so is nl
+    if (nl <= 64u) return lane < nl ? comp[H.cb + lane] : 0u;
+    if (tid == 0) sc.ok = H.n_used == 1u ? 0u : 1u;  // (one symbol spans one)
+    if (tid < kLmaxLimit + 2) sc.cl[tid] = 0;
+    __syncthreads();
+    uint8_t* const sc_len = sc.len(g.K);
+    for (uint32_t i = tid; i < nl; i += NT) {
+        const uint32_t l = comp[H.cb + i];
+        sc_len[i] = (uint8_t)l;
+        if (l > g.LMAX) sc.ok = 0;
+        else if (l) atomicAdd(&sc.cl[l], 1u);
+    }
+    return 0u;
+}
+
+// The decode table of a table's canonical code, by a work-group of NT threads.  `my_len`: what dec_lengths returned.  Where the
+// symbols span at most 64, every wavefront works out counts, first codes and the symbols' order by itself, in scalar
+// registers, and the work-group only meets for the look-ups (a count by LDS atomics, one wavefront's ordering and the limits
+// read back from LDS, the way of a wider span: 7 barriers instead of 3, and 2500 cycles more of a work-group's 18 thousand before the first turn).
+// Returns whether the code is complete and as large as the directory says (the same for every thread; ends with a barrier).
+template <bool WIDE, uint32_t NT>
+__device__ __forceinline__ bool dec_table(const Geom& g, const DecHead& H, uint32_t my_len, uint32_t* lut,
+                                          DecScratch& sc, uint32_t tid) {
+    const uint32_t lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t lut_n = 1u << g.LMAX, nl = H.sym_hi - H.sym_lo + 1u;
+    if (!H.ok) return false;  // uniform
+    uint32_t limit[kLmaxLimit + 1];  // [l]: the first LMAX-bit string that no codeword of at most l bits starts (in scalar registers)
+    bool ok;
+    if (nl <= 64u) {  // uniform
+        uint32_t kraft = 0, code = 0, index = 0, at = 0, place = 0;
+#pragma unroll
+        for (uint32_t l = 1; l <= (uint32_t)kLmaxLimit; ++l) {
+            const uint64_t m = __ballot(my_len == l);
+            const uint32_t c = (uint32_t)__popcll(m);
+            code <<= 1;
+            at = my_len == l ? index + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)) : at;
+            place = lane == l ? index - code : place;
+            code += c;
+            index += c;
+            kraft += l <= g.LMAX ? c << (g.LMAX - l) : 0u;
+            limit[l] = l <= g.LMAX ? code << (g.LMAX - l) : 0xFFFFFFFFu;
+        }
+        if (H.n_used == 1u) ok = nl == 1u && __ballot(my_len != 0u) == 0ull;
+        else ok = kraft == lut_n && index == H.n_used && __ballot(my_len > g.LMAX) == 0ull;
+        if (ok && wave == 0) {
+            if (my_len != 0u) sc.sorted()[at] = (uint16_t)dec_bin<WIDE>(H.sym_lo + lane, g.R);
+            if (lane <= (uint32_t)kLmaxLimit) sc.place[lane] = place;
+        }
+        __syncthreads();
+    } else {
+        uint8_t* const sc_len = sc.len(g.K);
+        __syncthreads();
+        if (wave == 0 && sc.ok != 0u) {
+            // first wavefront: every lane derives the same per-length tables, then the symbols are put in
+            // (length, symbol) order, 64 at a time: a symbol's place is the number of symbols of its length before it
+            uint64_t kraft = 0;
+            uint32_t cnt = 0, code = 0, index = 0;
+            uint32_t fill[kLmaxLimit + 1];
+#pragma unroll
+            for (uint32_t l = 1; l <= (uint32_t)kLmaxLimit; ++l) {
+                const uint32_t c = l <= g.LMAX ? sc.cl[l] : 0u;
+                kraft += l <= g.LMAX ? (uint64_t)c << (g.LMAX - l) : 0ull;
+                cnt += c;
+                code <<= 1;
+                if (lane == 0) { sc.first[l] = code; sc.place[l] = index - code; }
+                fill[l] = index;
+                code += c;
+                index += c;
+            }
+            if (kraft != (1ull << g.LMAX) || cnt != H.n_used) {
+                if (lane == 0) sc.ok = 0;
+            } else {
+                const uint64_t below = (1ull << lane) - 1ull;
+                for (uint32_t base = 0; base < nl; base += 64) {
+                    const uint32_t i = base + lane;
+                    const uint32_t L = i < nl ? sc_len[i] : 0u;
+                    if (__ballot(L != 0u) == 0ull) continue;  // (a stretch of unused symbols: the escape symbol's code can lie far below the others)
+#pragma unroll
+                    for (uint32_t l = 1; l <= (uint32_t)kLmaxLimit; ++l) {
+                        const uint64_t m = __ballot(L == l);
+                        if (L == l) sc.sorted()[fill[l] + (uint32_t)__popcll(m & below)] = (uint16_t)dec_bin<WIDE>(H.sym_lo + i, g.R);
+                        fill[l] += (uint32_t)__popcll(m);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        ok = sc.ok != 0u;
+#pragma unroll
+        for (uint32_t l = 1; l <= (uint32_t)kLmaxLimit; ++l) {
+            const uint32_t past = (uint32_t)__builtin_amdgcn_readfirstlane((int)(sc.first[l] + sc.cl[l]));
+            limit[l] = l <= g.LMAX ? past << (g.LMAX - l) : 0xFFFFFFFFu;
+        }
+    }
+    if (!ok) return false;  // uniform
+    if (H.n_used == 1u) {  // length 0: every look-up gives one symbol and moves on by nothing
+        const uint32_t e = 0x80000000u | dec_bin<WIDE>(H.sym_lo, g.R);
+        for (uint32_t i = tid; i < lut_n; i += NT) lut[i] = e;
+        __syncthreads();
+        return true;
+    }
+    // the codeword that the LMAX-bit string i (its first bit the highest) starts with
+    auto first_code = [&](uint32_t i) {
+        uint32_t l = 1;
+#pragma unroll
+        for (uint32_t k = 1; k < (uint32_t)kLmaxLimit; ++k) l += i >= limit[k] ? 1u : 0u;
+        return (l << kBinBits<WIDE>) | sc.sorted()[(i >> (g.LMAX - l)) + sc.place[l]];
+    };
+    // A thread fills eight strings that agree in all but their last three bits (an eighth of the table apart each, in the
+    // order of reversed strings): all of them start with one codeword when that ends before those bits, which for the
+    // short codes that cover most of the table is the rule, and for whole wavefronts at a time.
+    const uint32_t eighth = lut_n >> 3;  // (lut_n >= 16: a multiple of 8)
+    for (uint32_t k = tid; k < eighth; k += NT) {
+        const uint32_t i0 = k * 8u, u = __builtin_bitreverse32(i0) >> (32u - g.LMAX);
+        const uint32_t ea = first_code(i0);
+        if (g.LMAX - (ea >> kBinBits<WIDE>) >= 3u) {
+#pragma unroll
+            for (uint32_t v = 0; v < 8; ++v) sc.one[u + v * eighth] = (uint16_t)ea;
+        } else {
+            sc.one[u] = (uint16_t)ea;
+#pragma clang loop unroll(disable)
+            for (uint32_t v = 1; v < 8; ++v)  // (v's bits are the string's last three, in reverse)
+                sc.one[u + v * eighth] = (uint16_t)first_code(i0 | ((v & 1u) << 2 | (v & 2u) | v >> 2));
+        }
+    }
+    __syncthreads();
+#pragma clang loop unroll(disable)
+    for (uint32_t i0 = tid; i0 < lut_n; i0 += NT * 4u) {  // four strings in flight per thread
+        uint32_t e1[4], e2[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) e1[k] = sc.one[(i0 + k * NT) & (lut_n - 1u)];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k)  // what follows the first codeword (zeros behind the LMAX bits)
+            e2[k] = sc.one[((i0 + k * NT) & (lut_n - 1u)) >> (e1[k] >> kBinBits<WIDE>)];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) {
+            const uint32_t i = i0 + k * NT;
+            if (i < lut_n) lut[i] = dec_entry<WIDE>(e1[k], e2[k], g.LMAX);
+        }
+    }
+    __syncthreads();  // (the scratch is staging memory from here on)
+    return true;
+}
+
 constexpr uint32_t kDecBit0 = 30;  // `p` at a chunk's first bit
 struct DecTail {
     unsigned long long sum[kDecWaves];
@@ -271,17 +417,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
     gh.cw = 0; gh.goff = 0; gh.gnext = 0;
     if (grp_first < g.G) gh = group_head(grp_first);
     const DecHead H = dec_validate(g, F, comp, comp_bytes, tl);
-    if (tid == 0) { sc.ok = H.ok ? 1u : 0u; tail.bad = 0u; }
-    if (tid < kLmaxLimit + 2) sc.cl[tid] = 0;
-    __syncthreads();
-    const uint32_t nl = H.ok ? H.sym_hi - H.sym_lo + 1u : 0u;
-    uint8_t* const sc_len = sc.len(g.K);
-    for (uint32_t i = tid; i < nl; i += kDecThreads) {
-        const uint32_t l = comp[H.cb + i];
-        sc_len[i] = (uint8_t)l;
-        if (l > g.LMAX) sc.ok = 0;
-        else if (l) atomicAdd(&sc.cl[l], 1u);
-    }
+    if (tid == 0) tail.bad = 0u;
+    const uint32_t my_len = dec_lengths<kDecThreads>(g, H, comp, sc, tid);
     // One group of a wavefront: its words (the chunks', then two per escape) checked against the container.
     struct GroupPlace { bool ok; uint32_t n_esc, total, off; const uint32_t* words; };  // off: the lane's chunk starts there
     auto group_place = [&](const GroupHead& h) {
@@ -346,18 +483,18 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
     constexpr integral_constant<uint32_t, 16> k16{};
     constexpr integral_constant<uint32_t, 32> k32{};
     constexpr integral_constant<uint32_t, kRows> kr{};
-    // the first group's words are on their way while the decode table is made
+    // The first group's words are on their way while the decode table is made.  (The second group's too, in registers of their
+    // own: slower, all work-groups then ask for everything at once.)
+    uint32_t w_first[kRows] = {};
+    auto fetch = [&](const GroupPlace& P) {
+        if (P.total <= stage_words) fetch_group(P, w_first);
+        else fetch_window(k32, k0, P, 0u, w_first);
+    };
     GroupPlace gp;
     gp.ok = false; gp.n_esc = 0; gp.total = 0; gp.off = 0; gp.words = nullptr;
-    uint32_t w_first[kRows];
-#pragma unroll
-    for (uint32_t k = 0; k < kRows; ++k) w_first[k] = 0;
     if (H.ok && grp_first < g.G) {
         gp = group_place(gh);
-        if (gp.ok) {
-            if (gp.total <= stage_words) fetch_group(gp, w_first);
-            else fetch_window(k32, k0, gp, 0u, w_first);
-        }
+        if (gp.ok) fetch(gp);
     }
     // the container as a whole: its escapes are those of its tables (first work-group of the container)
     if (H.ok && tl == 0 && b == 0) {
@@ -381,93 +518,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
         }
         if (big) tail.bad = 1u;
     }
-    __syncthreads();
-    const bool ok2 = sc.ok != 0;  // every thread reads the same value, then nobody writes before the barrier
-    __syncthreads();
-    if (ok2 && H.n_used == 1) {
-        if (tid == 0 && (H.sym_lo != H.sym_hi || sc_len[0] != 0)) sc.ok = 0;
-        // length 0: every look-up gives one symbol and moves on by nothing
-        const uint32_t e = dec_entry<WIDE>(H.sym_lo, 0u, 0u, g.LMAX + 1u, g.R, g.LMAX);
-        for (uint32_t i = tid; i < lut_n; i += kDecThreads) s_lut[i] = e;
-    } else if (ok2) {
-        if (wave == 0) {
-            // first wavefront: every lane derives the same per-length tables, then the symbols are put in
-            // (length, symbol) order, 64 at a time: a symbol's place is the number of symbols of its length before it
-            uint64_t kraft = 0;
-            uint32_t cnt = 0, code = 0, index = 0;
-            uint32_t fill[kLmaxLimit + 1];
-#pragma unroll
-            for (uint32_t l = 1; l <= (uint32_t)kLmaxLimit; ++l) {
-                const uint32_t c = l <= g.LMAX ? sc.cl[l] : 0u;
-                kraft += l <= g.LMAX ? (uint64_t)c << (g.LMAX - l) : 0ull;
-                cnt += c;
-                code <<= 1;
-                if (lane == 0) { sc.first[l] = code; sc.index[l] = index; }
-                fill[l] = index;
-                code += c;
-                index += c;
-            }
-            if (kraft != (1ull << g.LMAX) || cnt != H.n_used) {
-                if (lane == 0) sc.ok = 0;
-            } else {
-                const uint64_t below = (1ull << lane) - 1ull;
-                for (uint32_t base = 0; base < nl; base += 64) {
-                    const uint32_t i = base + lane;
-                    const uint32_t L = i < nl ? sc_len[i] : 0u;
-                    if (__ballot(L != 0u) == 0ull) continue;  // (a stretch of unused symbols: the escape symbol's code can lie far below the others)
-#pragma unroll
-                    for (uint32_t l = 1; l <= (uint32_t)kLmaxLimit; ++l) {
-                        const uint64_t m = __ballot(L == l);
-                        if (L == l) sc.sorted()[fill[l] + (uint32_t)__popcll(m & below)] = (uint16_t)(H.sym_lo + i);
-                        fill[l] += (uint32_t)__popcll(m);
-                    }
-                }
-            }
-        }
-        __syncthreads();
-        if (sc.ok != 0) {
-            // the LMAX-bit string i starts with a codeword of length l iff i < limit[l] and not already
-            // i < limit[l-1]; the limits are the same for every thread (scalar registers).  A thread fills eight
-            // strings in a row: all of them start with one codeword when they agree down to its last bit, which for
-            // the short codes that cover most of the table is the rule.
-            uint32_t limit[kLmaxLimit + 1];
-#pragma unroll
-            for (uint32_t l = 1; l <= (uint32_t)kLmaxLimit; ++l)
-                limit[l] = l <= g.LMAX ? (sc.first[l] + sc.cl[l]) << (g.LMAX - l) : 0xFFFFFFFFu;
-            // (the eight: strings that agree in all but their last three bits, an eighth of the table apart each)
-            const uint32_t eighth = lut_n >> 3;
-            for (uint32_t u = tid; u < eighth; u += kDecThreads) {  // (lut_n >= 16: a multiple of 8)
-                const uint32_t i0 = __builtin_bitreverse32(u) >> (32u - g.LMAX);
-                const uint32_t ea = dec_first_code(sc, limit, i0, g.LMAX), la = ea >> 12;
-                if (g.LMAX - la >= 3u) {
-#pragma unroll
-                    for (uint32_t k = 0; k < 8; ++k) sc.one[u + k * eighth] = (uint16_t)ea;
-                } else {
-                    sc.one[u] = (uint16_t)ea;
-#pragma unroll
-                    for (uint32_t k = 1; k < 8; ++k)  // (k's bits are the string's last three, in reverse)
-                        sc.one[u + k * eighth] = (uint16_t)dec_first_code(sc, limit, i0 | ((k & 1u) << 2 | (k & 2u) | k >> 2), g.LMAX);
-                }
-            }
-            __syncthreads();  // (uniform: sc.ok was read after a barrier and nothing has written it since)
-            for (uint32_t i0 = tid; i0 < lut_n; i0 += kDecThreads * 4u) {  // four strings in flight per thread
-                uint32_t e1[4], e2[4];
-#pragma unroll
-                for (uint32_t k = 0; k < 4; ++k) e1[k] = sc.one[(i0 + k * kDecThreads) & (lut_n - 1u)];
-#pragma unroll
-                for (uint32_t k = 0; k < 4; ++k)  // what follows the first codeword (zeros behind the LMAX bits)
-                    e2[k] = sc.one[((i0 + k * kDecThreads) & (lut_n - 1u)) >> (e1[k] >> 12)];
-#pragma unroll
-                for (uint32_t k = 0; k < 4; ++k) {
-                    const uint32_t i = i0 + k * kDecThreads;
-                    if (i < lut_n) s_lut[i] = dec_entry<WIDE>(e1[k] & 0xFFFu, e1[k] >> 12, e2[k] & 0xFFFu, e2[k] >> 12, g.R, g.LMAX);
-                }
-            }
-        }
-    }
-    __syncthreads();
-    const bool valid = sc.ok != 0;
-    __syncthreads();  // the scratch is staging memory from here on
+    const bool valid = dec_table<WIDE, kDecThreads>(g, H, my_len, s_lut, sc, tid);
     uint32_t my_esc = 0;   // escapes this wavefront has applied (uniform)
     bool bad = false;      // something in this wavefront's groups does not add up
     if (valid) {
@@ -484,6 +535,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
             if (it != 0) {
                 gh = group_head(grp);
                 gp = group_place(gh);
+                if (gp.ok) fetch(gp);
             }
             if (!gp.ok) {
                 bad = true;
@@ -493,10 +545,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
             const bool linear = total <= stage_words;  // uniform
             const uint32_t st0 = (uint32_t)(uintptr_t)stage;
             if (linear) {
-                if (it != 0) fetch_group(gp, w_first);
                 put_group(gp, w_first);
             } else {
-                if (it != 0) fetch_window(k32, k0, gp, 0u, w_first);
                 put_window(k32, k0, w_first);
                 uint32_t w[32u - kRows];
                 fetch_window(k32, kr, gp, 0u, w);
@@ -613,13 +663,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_s_waitcnt(0);  // the wavefront's own stores above are out before the overwrites below
                 const uint32_t* rec = reinterpret_cast<const uint32_t*>(comp + F.off_payload) + gh.goff + total;
-                const uint32_t lo = gstart, hi = gstart + in_group;
                 bool off_range = false;
                 for (uint32_t r = lane; r < n_esc; r += 64) {
-                    const uint32_t idx = rec[2u * r], raw = rec[2u * r + 1];
-                    if (idx < lo || idx >= hi) { off_range = true; continue; }
-                    if constexpr (F16) reinterpret_cast<uint16_t*>(tab)[idx] = (uint16_t)raw;
-                    else reinterpret_cast<uint32_t*>(tab)[idx] = raw;
+                    const uint32_t at = rec[2u * r] - gstart, raw = rec[2u * r + 1];
+                    if (at >= in_group) { off_range = true; continue; }
+                    if constexpr (F16) reinterpret_cast<uint16_t*>(gout)[at] = (uint16_t)raw;
+                    else reinterpret_cast<uint32_t*>(gout)[at] = raw;
                 }
                 if (__ballot(off_range) != 0ull) bad = true;
                 my_esc += n_esc;
@@ -689,14 +738,16 @@ hipError_t launch_decompress(const Geom& g, const uint8_t* comp, uint64_t comp_b
     if (g.lz)  // before the decode kernel: the row-copy kernel follows the references only where they were checked
         hipLaunchKernelGGL(k_dec_refs, dim3(g.T), dim3(256), 0, s, g, F, comp, comp_bytes, w.dtab, w.ctrl);
     {
-        // a work-group decodes `iters` blocks of nw groups of one table, a wavefront each: enough blocks to spread the
-        // cost of its decode table, enough work-groups (a few thousand) to fill the chip whatever the shape, and no
-        // more wavefronts than a table has groups
+        // a work-group decodes `iters` blocks of nw groups of one table, a wavefront each, and no more wavefronts than a table
+        // has groups.  More blocks spread the cost of its decode table, a fifth of its time with one; more work-groups fill the
+        // chip and even out the compute units.  Where the stores bound the whole (fp32), a second round of work-groups fills the
+        // gaps of the first (512 MiB: two rounds 111 us, one of two blocks 117); where they do not, one round is the shorter way
+        // (1024 blocks, half precision: 94 us, now 77; 512 blocks, row matching, where most rows are not stored: 66, now 57)
         // (a small grid takes the wavefronts all the same: they make the decode table sooner)
         const uint32_t nw = (g.G >= 6u || (uint64_t)g.T * g.G <= 512u) ? kDecWaves : (g.G >= 3u ? 4u : 2u);
         const uint32_t bpt = (g.G + nw - 1) / nw;
         const uint64_t blocks = (uint64_t)g.T * bpt;
-        const uint32_t iters = (uint32_t)std::min<uint64_t>(4, std::max<uint64_t>(1, blocks / 2048));
+        const uint32_t iters = (uint32_t)std::min<uint64_t>(4, std::max<uint64_t>(1, blocks / (f16 ? 512u : (g.lz ? 256u : 2048u))));
         const uint32_t wpt = (bpt + iters - 1) / iters;  // work-groups per table
         dim3 grid(g.T * wpt), block(64 * nw);
         // a grid that leaves compute units free can have larger staging areas: 6 bits a symbol
