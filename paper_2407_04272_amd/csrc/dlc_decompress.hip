@@ -377,10 +377,110 @@ __device__ __forceinline__ bool dec_table(const Geom& g, const DecHead& H, uint3
 }
 
 constexpr uint32_t kDecBit0 = 30;  // `p` at a chunk's first bit
+constexpr uint32_t kSplitWaves = 8;  // wavefronts of a work-group that shares a group's chunks
 struct DecTail {
     unsigned long long sum[kDecWaves];
     uint32_t bad, pad;
 };
+
+// the four elements at `el` of a group; EDGE: the table can end among them (four elements at once want no more than an
+// element's alignment).  STREAM: past the caches, as an output larger than they are wants it (stores of whole kilobytes; where
+// a wavefront's lanes are at different turns the caches put the lines together: 208 groups 22.5 us, now 17.6).
+template <bool F16, bool VEC, bool EDGE = true, bool STREAM = false>
+__device__ __forceinline__ void dec_store(uint8_t* gout, uint32_t el, uint32_t in_group, const float (&v4)[4]) {
+    uint8_t* const o = gout + el * (F16 ? 2u : 4u);
+    if (!EDGE || VEC || el + 3u < in_group) {
+        if constexpr (F16) {
+            typedef std::conditional_t<VEC, u32x2, u32x2_any> u2v;
+            u2v o2;
+            o2.x = (uint32_t)__half_as_ushort(half_rne(v4[0])) | ((uint32_t)__half_as_ushort(half_rne(v4[1])) << 16);
+            o2.y = (uint32_t)__half_as_ushort(half_rne(v4[2])) | ((uint32_t)__half_as_ushort(half_rne(v4[3])) << 16);
+            if constexpr (STREAM) __builtin_nontemporal_store(o2, reinterpret_cast<u2v*>(o));
+            else *reinterpret_cast<u2v*>(o) = o2;
+        } else {
+            typedef std::conditional_t<VEC, u32x4, u32x4_any> u4v;
+            u4v o4 = {__float_as_uint(v4[0]), __float_as_uint(v4[1]), __float_as_uint(v4[2]), __float_as_uint(v4[3])};
+            if constexpr (STREAM) __builtin_nontemporal_store(o4, reinterpret_cast<u4v*>(o));
+            else *reinterpret_cast<u4v*>(o) = o4;
+        }
+    } else {
+#pragma unroll
+        for (uint32_t v = 0; v < 4; ++v)
+            if (el + v < in_group) {
+                if constexpr (F16) reinterpret_cast<__half*>(o)[v] = half_rne(v4[v]);
+                else reinterpret_cast<float*>(o)[v] = v4[v];
+            }
+    }
+}
+
+// What a group's decoding starts from sits in the sections whose place the geometry fixes (the host has made sure they lie
+// inside comp_bytes): its loads go out before anything else is known.  gid: the group's number inside the container.
+struct GroupHead { uint32_t cw, goff, gnext; };
+__device__ __forceinline__ GroupHead dec_group_head(const Geom& g, const FixedLayout& F, const uint8_t* comp, uint32_t gid, uint32_t lane) {
+    const uint32_t* const goffs = reinterpret_cast<const uint32_t*>(comp + F.off_group);
+    GroupHead h;
+    h.cw = comp[F.off_chunk + (uint64_t)gid * kW + lane];
+    h.goff = goffs[gid];
+    h.gnext = gid + 1 < g.TD * g.G ? goffs[gid + 1] : 0xFFFFFFFFu;  // (the last group ends where the payload does)
+    return h;
+}
+// A group's words (the chunks', then two per escape) checked against the container.  off: the lane's chunk starts there.
+struct GroupPlace { bool ok; uint32_t n_esc, total, off; const uint32_t* words; };
+__device__ __forceinline__ GroupPlace dec_group_place(const FixedLayout& F, const DecHead& H, const uint8_t* comp, const GroupHead& h) {
+    GroupPlace P;
+    const uint32_t incl = wave_incl_scan(h.cw);
+    P.total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    const uint64_t gend = h.gnext == 0xFFFFFFFFu ? H.words_total : (uint64_t)h.gnext;
+    P.ok = !(gend > H.words_total || (uint64_t)h.goff + P.total > gend || ((gend - h.goff - P.total) & 1ull));
+    P.n_esc = P.ok ? (uint32_t)((gend - h.goff - P.total) >> 1) : 0u;
+    P.words = reinterpret_cast<const uint32_t*>(comp + F.off_payload) + h.goff;
+    P.off = incl - h.cw;
+    return P;
+}
+
+// The container as a whole: its escapes are those of its tables (a container's first work-group, of NW wavefronts).
+template <uint32_t NW>
+__device__ __forceinline__ void dec_check_escapes(const Geom& g, const DecHead& H, const uint8_t* comp, DecTail& tail, uint32_t tid) {
+    uint32_t part = 0;
+    bool big = false;
+    for (uint32_t k = tid; k < g.TD; k += 64u * NW) {
+        const uint32_t e = reinterpret_cast<const uint32_t*>(comp + kHeaderBytes + (uint64_t)kDirBytes * k)[4];
+        big = big || e > g.n;
+        part += e > g.n ? 0u : e;
+    }
+    // (32-bit partial sums per thread cannot wrap: a thread adds at most TD / 512 counts of less than 2^31 each,
+    // and TD * n < 2^32 positions in all; across threads they are added as 64-bit values)
+    unsigned long long sum = part;
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    if ((tid & 63u) == 0) tail.sum[tid >> 6] = sum;
+    __syncthreads();
+    if (tid == 0) {
+        unsigned long long all = 0;
+        for (uint32_t k = 0; k < NW; ++k) all += tail.sum[k];
+        if (all != H.n_esc_total) tail.bad = 1u;
+    }
+    if (big) tail.bad = 1u;
+}
+
+// The end of a work-group, one of wpt of its table.  my_esc: the escapes its wavefront has applied.
+__device__ __forceinline__ void dec_finish(const DecHead& H, bool valid, uint32_t my_esc, uint32_t wpt, Ctrl* ctrl, uint32_t* esc_seen,
+                                           uint32_t* arrived, DecTail& tail, uint32_t tid) {
+    if (my_esc != 0u && (tid & 63u) == 0u) {
+        __hip_atomic_fetch_add(esc_seen, my_esc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // counted before the work-group says it is done
+    }
+    __syncthreads();
+    if (tid == 0) {
+        bool corrupt = !valid || tail.bad != 0u;
+        // the last work-group of the table: all escapes of the table have been seen
+        if (__hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == wpt) {
+            const uint32_t seen = __hip_atomic_exchange(esc_seen, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (valid && seen != H.n_esc) corrupt = true;
+        }
+        if (corrupt) set_status(ctrl, DLC_ECORRUPT);
+    }
+}
 constexpr uint32_t kDecPad = 512;  // bytes behind the staging areas: a damaged chunk runs at most 256 codes of 12 bits past its words' start
 
 template <bool F16, bool VEC, bool WIDE, uint32_t NW>
@@ -399,19 +499,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
     DecScratch& sc = *reinterpret_cast<DecScratch*>(s_lut + lut_n);
     DecTail& tail = *reinterpret_cast<DecTail*>(reinterpret_cast<unsigned char*>(s_lut + lut_n) + dec_area_bytes(NW, stage_words, g.K) +
                                                 (g.lz ? NW * kSkipWords * 4u : 0u) + kDecPad);
-    const uint32_t* const goffs = reinterpret_cast<const uint32_t*>(comp + F.off_group);
-    const uint32_t n_groups = g.TD * g.G;
-    // What a group's decoding starts from sits in the sections whose place the geometry fixes (the host has made
-    // sure they lie inside comp_bytes): the loads of the first group go out before anything else is known.
-    struct GroupHead { uint32_t cw, goff, gnext; };
-    auto group_head = [&](uint32_t grp) {
-        GroupHead h;
-        const uint32_t gid = tl * g.G + grp;  // group number inside the container
-        h.cw = comp[F.off_chunk + (uint64_t)gid * kW + lane];
-        h.goff = goffs[gid];
-        h.gnext = gid + 1 < n_groups ? goffs[gid + 1] : 0xFFFFFFFFu;  // (the last group ends where the payload does)
-        return h;
-    };
+    auto group_head = [&](uint32_t grp) { return dec_group_head(g, F, comp, tl * g.G + grp, lane); };
     const uint32_t grp_first = b * iters * NW + wave;
     GroupHead gh;
     gh.cw = 0; gh.goff = 0; gh.gnext = 0;
@@ -419,19 +507,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
     const DecHead H = dec_validate(g, F, comp, comp_bytes, tl);
     if (tid == 0) tail.bad = 0u;
     const uint32_t my_len = dec_lengths<kDecThreads>(g, H, comp, sc, tid);
-    // One group of a wavefront: its words (the chunks', then two per escape) checked against the container.
-    struct GroupPlace { bool ok; uint32_t n_esc, total, off; const uint32_t* words; };  // off: the lane's chunk starts there
-    auto group_place = [&](const GroupHead& h) {
-        GroupPlace P;
-        const uint32_t incl = wave_incl_scan(h.cw);
-        P.total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-        const uint64_t gend = h.gnext == 0xFFFFFFFFu ? H.words_total : (uint64_t)h.gnext;
-        P.ok = !(gend > H.words_total || (uint64_t)h.goff + P.total > gend || ((gend - h.goff - P.total) & 1ull));
-        P.n_esc = P.ok ? (uint32_t)((gend - h.goff - P.total) >> 1) : 0u;
-        P.words = reinterpret_cast<const uint32_t*>(comp + F.off_payload) + h.goff;
-        P.off = incl - h.cw;
-        return P;
-    };
+    auto group_place = [&](const GroupHead& h) { return dec_group_place(F, H, comp, h); };
     uint32_t* const stage = s_lut + lut_n + wave * stage_words;
     // The first kStage words of the group as they lie, into registers.  Branch-free, all loads in flight together: an
     // index past the group's end reads its last word instead (an empty group the word at its position, which still lies
@@ -496,28 +572,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
         gp = group_place(gh);
         if (gp.ok) fetch(gp);
     }
-    // the container as a whole: its escapes are those of its tables (first work-group of the container)
-    if (H.ok && tl == 0 && b == 0) {
-        uint32_t part = 0;
-        bool big = false;
-        for (uint32_t k = tid; k < g.TD; k += kDecThreads) {
-            const uint32_t e = reinterpret_cast<const uint32_t*>(comp + kHeaderBytes + (uint64_t)kDirBytes * k)[4];
-            big = big || e > g.n;
-            part += e > g.n ? 0u : e;
-        }
-        // (32-bit partial sums per thread cannot wrap: a thread adds at most TD / 512 counts of less than 2^31 each,
-        // and TD * n < 2^32 positions in all; across threads they are added as 64-bit values)
-        unsigned long long sum = part;
-        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-        if (lane == 0) tail.sum[wave] = sum;
-        __syncthreads();
-        if (tid == 0) {
-            unsigned long long all = 0;
-            for (uint32_t k = 0; k < NW; ++k) all += tail.sum[k];
-            if (all != H.n_esc_total) tail.bad = 1u;
-        }
-        if (big) tail.bad = 1u;
-    }
+    if (H.ok && tl == 0 && b == 0) dec_check_escapes<NW>(g, H, comp, tail, tid);
     const bool valid = dec_table<WIDE, kDecThreads>(g, H, my_len, s_lut, sc, tid);
     uint32_t my_esc = 0;   // escapes this wavefront has applied (uniform)
     bool bad = false;      // something in this wavefront's groups does not add up
@@ -630,29 +685,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
                     p += adv;
                     dec_values<WIDE>(e, half_high, ebx2, v4 + h * 2);
                 }
-                // streaming stores: the output is written once and is larger than the caches (four elements at once want
-                // no more than an element's alignment)
-                uint8_t* const o = gout + el * (F16 ? 2u : 4u);
-                if (!EDGE || VEC || el + 3u < in_group) {
-                    if constexpr (F16) {
-                        typedef std::conditional_t<VEC, u32x2, u32x2_any> u2v;
-                        u2v o2;
-                        o2.x = (uint32_t)__half_as_ushort(half_rne(v4[0])) | ((uint32_t)__half_as_ushort(half_rne(v4[1])) << 16);
-                        o2.y = (uint32_t)__half_as_ushort(half_rne(v4[2])) | ((uint32_t)__half_as_ushort(half_rne(v4[3])) << 16);
-                        __builtin_nontemporal_store(o2, reinterpret_cast<u2v*>(o));
-                    } else {
-                        typedef std::conditional_t<VEC, u32x4, u32x4_any> u4v;
-                        u4v o4 = {__float_as_uint(v4[0]), __float_as_uint(v4[1]), __float_as_uint(v4[2]), __float_as_uint(v4[3])};
-                        __builtin_nontemporal_store(o4, reinterpret_cast<u4v*>(o));
-                    }
-                } else {
-#pragma unroll
-                    for (uint32_t v = 0; v < 4; ++v)
-                        if (el + v < in_group) {
-                            if constexpr (F16) reinterpret_cast<__half*>(o)[v] = half_rne(v4[v]);
-                            else reinterpret_cast<float*>(o)[v] = v4[v];
-                        }
-                }
+                dec_store<F16, VEC, EDGE, true>(gout, el, in_group, v4);
             };
             const uint32_t whole = in_group / (kW * kV);
             for (uint32_t j = 0; j < whole; ++j) turn(std::false_type{}, j);
@@ -674,23 +707,234 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
                 my_esc += n_esc;
             }
         }
-        if (my_esc != 0u && lane == 0) {
-            __hip_atomic_fetch_add(&esc_seen[t], my_esc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // counted before the work-group says it is done
+    }
+    if (bad && lane == 0) tail.bad = 1u;
+    dec_finish(H, valid, my_esc, wpt, ctrl, esc_seen + t, arrived + t, tail, tid);
+}
+
+// ------------------------------------------------------------------------------------------------
+// Few groups: a work-group of NW wavefronts for each, and the chunks of the group cut into parts, a wavefront a part (lane l
+// still looks after chunk l).  A group by one wavefront is a chain of 64 turns, 38 of the 57 thousand cycles of 26 tables of
+// 2048 x 64, while most of the chip has nothing to do.
+// Where a part's first codeword starts is not known: a part starts at a word boundary as if one started there, and a
+// Huffman code falls into step by itself after a few codewords (streams of 2.2 to 4.4 bits a symbol, measured over their
+// chunks: of 16 parts in 2 to 4 rounds, of 8 in 2 or 3).  Round by round every part takes its start from the end of the part
+// before and goes through its bits again if that has moved; when no end moves any more every part starts where the one
+// before it ends, the first at the chunk's first bit, so the parts together are the chunk.  One part is right after the first
+// round and one more at least after every round, so there are no more rounds than parts, whatever the code.  Then the
+// codewords counted before a part say which elements it has; of those it writes the turns that start in it.
+// A chunk may have more words than its codewords need (the check is that the last one ends inside them, here as
+// in k_decode), and a damaged one any bits: every loop ends at its bits' end, a codeword being a bit at least.
+// ------------------------------------------------------------------------------------------------
+constexpr uint32_t kSplitTurns = 4;  // turns of a part, at least
+struct SplitLds {
+    uint32_t scratch, stage, ends, tail, end;  // byte offsets; the decode table comes first
+};
+__host__ __device__ inline SplitLds split_lds(const Geom& g, uint32_t nw) {
+    SplitLds L;
+    L.scratch = 4u << g.LMAX;
+    L.stage = L.scratch + (((uint32_t)sizeof(DecScratch) + 3u * g.K + 15u) & ~15u) + 16u;  // (a turn reads the word before a chunk's first)
+    L.ends = L.stage + kW * ((g.S * (uint32_t)kLmaxLimit + 31u) / 32u) * 4u;               // a group's words, all of them
+    L.tail = L.ends + (2u * nw * kW + nw + 2u) * 4u;                                       // two sets of ends, a flag a round
+    L.tail = (L.tail + 15u) & ~15u;
+    L.end = L.tail + (uint32_t)sizeof(DecTail) + kDecPad;
+    return L;
+}
+
+template <bool F16, bool VEC, bool WIDE>
+__global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(Geom g, FixedLayout F, const uint8_t* comp, uint64_t comp_bytes, Ctrl* ctrl, void* outp,
+                                                          SplitLds L, uint32_t* esc_seen, uint32_t* arrived) {
+    constexpr uint32_t NW = kSplitWaves, NT = 64u * NW;
+    static_assert(NW <= kDecWaves, "DecTail's sums");
+    extern __shared__ __align__(16) uint32_t s_lut[];  // (all of the kernel's LDS: the table starts at LDS address 0)
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t t = blockIdx.x / g.G, grp = blockIdx.x - t * g.G;
+    const uint32_t dst = t / g.TD, tl = t - dst * g.TD;
+    comp += (uint64_t)dst * comp_bytes;
+    unsigned char* const lds = reinterpret_cast<unsigned char*>(s_lut);
+    DecScratch& sc = *reinterpret_cast<DecScratch*>(lds + L.scratch);
+    uint32_t* const stage = reinterpret_cast<uint32_t*>(lds + L.stage);
+    uint32_t* const ends = reinterpret_cast<uint32_t*>(lds + L.ends);
+    uint32_t* const moved = ends + 2u * NW * kW;
+    DecTail& tail = *reinterpret_cast<DecTail*>(lds + L.tail);
+    const GroupHead gh = dec_group_head(g, F, comp, tl * g.G + grp, lane);
+    const DecHead H = dec_validate(g, F, comp, comp_bytes, tl);
+    if (tid == 0) tail.bad = 0u;
+    if (tid < NW + 2u) moved[tid] = 0u;
+    const uint32_t my_len = dec_lengths<NT>(g, H, comp, sc, tid);
+    GroupPlace gp;
+    gp.ok = false; gp.n_esc = 0; gp.total = 0; gp.off = 0; gp.words = nullptr;
+    // A chunk may have more words than the longest codes fill; its codewords only reach the first of them, and only
+    // those are staged then: cw of them, from `off` on.
+    uint32_t cw = min(gh.cw, (g.S * (uint32_t)kLmaxLimit + 31u) / 32u), off = 0;
+    if (H.ok) {
+        gp = dec_group_place(F, H, comp, gh);
+        off = gp.off;
+        if (gp.ok && __ballot(cw != gh.cw) == 0ull) {
+            for (uint32_t i = tid; i < gp.total; i += 2u * NT) {  // two loads in flight
+                const uint32_t i2 = min(i + NT, gp.total - 1u), w0 = gp.words[i], w1 = gp.words[i2];
+                stage[i] = __builtin_bitreverse32(w0);
+                stage[i2] = __builtin_bitreverse32(w1);
+            }
+        } else if (gp.ok) {
+            off = wave_incl_scan(cw) - cw;
+            for (uint32_t c = wave; c < kW; c += NW) {
+                const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)cw, (int)c), to = (uint32_t)__builtin_amdgcn_readlane((int)off, (int)c), at = (uint32_t)__builtin_amdgcn_readlane((int)gp.off, (int)c);
+                for (uint32_t i = lane; i < n; i += kW) stage[to + i] = __builtin_bitreverse32(gp.words[at + i]);
+            }
+        }
+    }
+    if (H.ok && tl == 0 && grp == 0) dec_check_escapes<NW>(g, H, comp, tail, tid);
+    const bool valid = dec_table<WIDE, NT>(g, H, my_len, s_lut, sc, tid);  // (its barriers publish the staged words, too)
+    uint32_t my_esc = 0;
+    bool bad = valid && !gp.ok;
+    if (valid && gp.ok) {  // uniform over the work-group
+        const uint32_t lut_mask = ((1u << g.LMAX) - 1u) << 2;
+        uint32_t half_high = kHalfHigh;
+        asm("" : "+v"(half_high));
+        const uint32_t gstart = grp * (kW * g.S), in_group = min(g.n - gstart, kW * g.S);
+        uint8_t* const gout = static_cast<uint8_t*>(outp) + ((size_t)t * g.n + gstart) * g.es;
+        uint32_t wa = (uint32_t)(uintptr_t)(lds_byte_t*)stage + off * 4u - 4u;
+        asm("" : "+v"(wa));
+        struct Window { uint32_t lo, hi; };
+        auto window = [&](uint32_t p) {  // the 64 bits from two before the place p (counted as in k_decode) on
+            const lds_byte_t* const a = reinterpret_cast<const lds_byte_t*>(wa + ((p >> 5) << 2));
+            const uint32_t x0 = lds_word(a, 0u), x1 = lds_word(a, 4u), x2 = lds_word(a, 8u);
+            Window w;
+            w.lo = __builtin_amdgcn_alignbit(x1, x0, p);
+            w.hi = __builtin_amdgcn_alignbit(x2, x1, p);
+            return w;
+        };
+        auto shift = [](Window& w, uint32_t by) {
+            w.lo = __builtin_amdgcn_alignbit(w.hi, w.lo, by);
+            w.hi >>= by;
+        };
+        const uint32_t turns = (in_group + kW * kV - 1u) / (kW * kV);
+        const uint32_t parts = min(NW, max(1u, turns / kSplitTurns)), part = wave;
+        // elements of the lane's chunk
+        const uint32_t whole = in_group / (kW * kV), over = in_group - whole * (kW * kV);
+        const uint32_t n_el = whole * kV + min(kV, over - min(over, lane * kV));
+        const uint32_t n_turns = (n_el + kV - 1u) / kV;
+        uint32_t start = 0, before = 0, count = 0;  // the part's first bit, codewords before it and in it
+        if (H.n_used == 1u) {  // no bits: the turns as they come
+            before = min(n_el, kV * (n_turns * part / parts));
+            count = part + 1u < parts ? kV * (n_turns * (part + 1u) / parts) - before : n_el - before;
+        } else {
+            const uint32_t b0 = cw * part / parts * 32u, b1 = cw * (part + 1u) / parts * 32u;
+            uint32_t stop = b0;
+            // the part's codewords from bit `start` on: those that start before b1 (the last part's are not asked for).  Two at a
+            // time while a pair cannot reach past b1, then one by one.
+            auto run = [&](bool go) {
+                uint32_t x = go ? start : b1, c = 0;
+                while (x + g.LMAX <= b1) {
+                    Window w = window(x + kDecBit0);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const uint32_t e = *reinterpret_cast<const lds_word_t*>(w.lo & lut_mask), adv = (e >> 27) & 15u;
+                        x += adv;
+                        c += 2u + (uint32_t)((int)e >> 31);
+                        shift(w, adv);
+                        if (k < 3 && x + g.LMAX > b1) break;
+                    }
+                }
+                if (x < b1) {  // (fewer than LMAX bits: one window has the codewords)
+                    Window w = window(x + kDecBit0);
+                    do {
+                        const uint32_t l1 = dec_len1<WIDE>(*reinterpret_cast<const lds_word_t*>(w.lo & lut_mask));
+                        x += l1;
+                        c += 1u;
+                        shift(w, l1);
+                    } while (x < b1);
+                }
+                return (c << 16) | x;
+            };
+            start = b0;
+            uint32_t got = part + 1u < parts ? run(true) : start;
+            stop = got & 0xFFFFu;
+            count = got >> 16;
+            uint32_t set = 0;
+            if (part < parts) ends[part * kW + lane] = got;
+            __syncthreads();
+            for (uint32_t round = 0; round <= parts; ++round) {  // uniform over the work-group
+                const uint32_t from = part != 0u && part < parts ? ends[set * (NW * kW) + (part - 1u) * kW + lane] & 0xFFFFu : 0u;
+                const bool again = part < parts && from != start;
+                start = from;
+                if (__ballot(again) != 0ull && part + 1u < parts) {
+                    const uint32_t g2 = run(again);
+                    if (again) got = g2;  // (nothing where the codeword before goes on past this part's end)
+                    if (__ballot((got & 0xFFFFu) != stop) != 0ull && lane == 0) moved[round] = 1u;
+                    stop = got & 0xFFFFu;
+                    count = got >> 16;
+                }
+                set ^= 1u;
+                if (part < parts) ends[set * (NW * kW) + part * kW + lane] = got;
+                __syncthreads();
+                if (moved[round] == 0u) break;
+            }
+            for (uint32_t k = 0; k + 1u < NW; ++k) before += k < min(part, parts) ? ends[set * (NW * kW) + k * kW + lane] >> 16 : 0u;
+            before = min(before, n_el);
+            count = part + 1u < parts ? count : n_el;
+        }
+        // the turns that start in this part
+        const uint32_t j1 = part < parts ? min(n_turns, (before + min(count, n_el) + kV - 1u) / kV) : 0u;
+        uint32_t j = (before + kV - 1u) / kV, p = start + kDecBit0;
+        bool go = j < j1;
+        const bool last = go && j1 == n_turns;  // this part has the chunk's last codeword
+        {  // codewords of a turn that started in the part before
+            Window w = window(p);
+            const uint32_t skip = j * kV - before;
+#pragma unroll
+            for (uint32_t k = 0; k + 1u < kV; ++k) {
+                const uint32_t e = *reinterpret_cast<const lds_word_t*>(w.lo & lut_mask), l1 = dec_len1<WIDE>(e);
+                p += k < skip ? l1 : 0u;
+                shift(w, l1);
+            }
+        }
+        while (__ballot(go) != 0ull) {
+            if (go) {
+                const uint32_t el = lane * kV + j * (kW * kV);
+                Window w = window(p);
+                float v4[4];
+#pragma unroll
+                for (uint32_t h = 0; h < 2u; ++h) {
+                    uint32_t e = *reinterpret_cast<const lds_word_t*>(w.lo & lut_mask);
+                    uint32_t adv = (e >> 27) & 15u;
+                    const uint32_t l1 = VEC ? 0u : dec_len1<WIDE>(e);
+                    shift(w, adv);
+                    if ((int)e < 0) {
+                        const uint32_t f = *reinterpret_cast<const lds_word_t*>(w.lo & lut_mask), l2 = dec_len1<WIDE>(f);
+                        shift(w, l2);
+                        adv += l2;
+                        e = dec_join<WIDE>(e, f);
+                    }
+                    if constexpr (!VEC) {  // a turn can reach past the table's end: such a position has no bits
+                        if (el + h * 2u + 1u >= in_group) adv = el + h * 2u < in_group ? l1 : 0u;
+                    }
+                    p += adv;
+                    dec_values<WIDE>(e, half_high, H.ebx2, v4 + h * 2u);
+                }
+                dec_store<F16, VEC>(gout, el, in_group, v4);
+                ++j;
+                go = j < j1;
+            }
+        }
+        // a chunk's codewords end inside its words
+        if (__ballot(last && p - kDecBit0 > 32u * gh.cw) != 0ull) bad = true;
+        if (gp.n_esc != 0u) {  // uniform over the work-group: verbatim values over the decoded placeholders
+            __syncthreads();   // (all stores of the work-group are out)
+            bool off_range = false;
+            for (uint32_t r = tid; r < gp.n_esc; r += NT) {
+                const uint32_t at = gp.words[gp.total + 2u * r] - gstart, raw = gp.words[gp.total + 2u * r + 1u];
+                if (at >= in_group) { off_range = true; continue; }
+                if constexpr (F16) reinterpret_cast<uint16_t*>(gout)[at] = (uint16_t)raw;
+                else reinterpret_cast<uint32_t*>(gout)[at] = raw;
+            }
+            if (__ballot(off_range) != 0ull) bad = true;
+            if (wave == 0) my_esc = gp.n_esc;
         }
     }
     if (bad && lane == 0) tail.bad = 1u;
-    __syncthreads();
-    if (tid == 0) {
-        bool corrupt = !valid || tail.bad != 0u;
-        // the last work-group of the table: all escapes of the table have been seen
-        if (__hip_atomic_fetch_add(&arrived[t], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == wpt) {
-            const uint32_t seen = __hip_atomic_exchange(&esc_seen[t], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&arrived[t], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (valid && seen != H.n_esc) corrupt = true;
-        }
-        if (corrupt) set_status(ctrl, DLC_ECORRUPT);
-    }
+    dec_finish(H, valid, my_esc, g.G, ctrl, esc_seen + t, arrived + t, tail, tid);
 }
 
 // rows that refer to an earlier row of their table: copies of that row's reconstruction (after the decode kernel).
@@ -754,11 +998,24 @@ hipError_t launch_decompress(const Geom& g, const uint8_t* comp, uint64_t comp_b
         const uint32_t stage = (uint64_t)g.T * wpt <= 256u ? 3072u : kStage;
         const size_t sm = ((size_t)4 << g.LMAX) + dec_area_bytes(nw, stage, g.K) + (g.lz ? (size_t)nw * kSkipWords * 4 : 0) + kDecPad + sizeof(DecTail);
         if (prof_on(pl, P_DECODE)) prof_begin(prof, P_DECODE, s);
+        // Up to two groups a compute unit: a work-group each (us: one group 24, now 15; 208 groups 30.5, now 18; 512 groups of 2.2 and
+        // 4.4 bits a symbol 23.8 and 29.2, now 22.7 and 23.5).  More than the chip holds at once, and a wavefront a
+        // group is the shorter way (720 groups: 24 and 29 against 34 and 37).  Sixteen wavefronts, and parts half as long, are no
+        // faster: they need more rounds.
+        const bool split = !g.lz && g.NG <= 512u;
+        const SplitLds L = split_lds(g, kSplitWaves);
 #define DLC_DEC3(FF, V, W, N) hipLaunchKernelGGL((k_decode<FF, V, W, N>), grid, block, sm, s, g, F, comp, (uint64_t)comp_bytes, w.ctrl, out, wpt, iters, stage, w.dec_esc, w.dec_arrive)
 #define DLC_DEC2(FF, V, N) do { if (g.R > 512u) DLC_DEC3(FF, V, true, N); else DLC_DEC3(FF, V, false, N); } while (0)
 #define DLC_DEC(FF, V) do { if (nw == 8u) DLC_DEC2(FF, V, 8u); else if (nw == 4u) DLC_DEC2(FF, V, 4u); else DLC_DEC2(FF, V, 2u); } while (0)
-        if (f16) { if (g.vec) DLC_DEC(true, true); else DLC_DEC(true, false); }
+#define DLC_SPLIT2(FF, V, W) hipLaunchKernelGGL((k_decode_split<FF, V, W>), dim3(g.NG), dim3(64u * kSplitWaves), L.end, s, g, F, comp, (uint64_t)comp_bytes, w.ctrl, out, L, w.dec_esc, w.dec_arrive)
+#define DLC_SPLIT(FF, V) do { if (g.R > 512u) DLC_SPLIT2(FF, V, true); else DLC_SPLIT2(FF, V, false); } while (0)
+        if (split) {
+            if (f16) { if (g.vec) DLC_SPLIT(true, true); else DLC_SPLIT(true, false); }
+            else { if (g.vec) DLC_SPLIT(false, true); else DLC_SPLIT(false, false); }
+        } else if (f16) { if (g.vec) DLC_DEC(true, true); else DLC_DEC(true, false); }
         else { if (g.vec) DLC_DEC(false, true); else DLC_DEC(false, false); }
+#undef DLC_SPLIT
+#undef DLC_SPLIT2
 #undef DLC_DEC
 #undef DLC_DEC2
 #undef DLC_DEC3
@@ -785,8 +1042,23 @@ static hipError_t decode_set_attributes() {
     return e;
 }
 
+static hipError_t split_set_attributes() {
+    Geom g = {};
+    g.LMAX = kLmaxLimit; g.K = 4096u; g.S = 256u;
+    const int bytes = (int)split_lds(g, kSplitWaves).end;
+    const void* ks[] = {reinterpret_cast<const void*>(k_decode_split<false, false, false>), reinterpret_cast<const void*>(k_decode_split<false, true, false>),
+                        reinterpret_cast<const void*>(k_decode_split<true, false, false>), reinterpret_cast<const void*>(k_decode_split<true, true, false>),
+                        reinterpret_cast<const void*>(k_decode_split<false, false, true>), reinterpret_cast<const void*>(k_decode_split<false, true, true>),
+                        reinterpret_cast<const void*>(k_decode_split<true, false, true>), reinterpret_cast<const void*>(k_decode_split<true, true, true>)};
+    hipError_t e = hipSuccess;
+    for (const void* k : ks)
+        if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    return e;
+}
+
 hipError_t decompress_set_attributes() {
     hipError_t e = decode_set_attributes<8u>();
+    if (e == hipSuccess) e = split_set_attributes();
     if (e == hipSuccess) e = decode_set_attributes<4u>();
     if (e == hipSuccess) e = decode_set_attributes<2u>();
     return e;
