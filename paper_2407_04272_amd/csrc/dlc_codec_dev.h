@@ -189,6 +189,22 @@ __device__ __forceinline__ void hist_block(const uint8_t* base, uint32_t rem, ui
 // ------------------------------------------------------------------------------------------------
 __host__ __device__ constexpr size_t codebook_smem(uint32_t K) { return (size_t)K * (8 + 4 + 4 + 2 + 2 + 2 + 2) + 64 * 4; }
 
+// what another work-group of the same launch may read of a table's codebook goes past the caches
+__device__ __forceinline__ void store_tmeta(TMeta* p, const TMeta& m) {
+    uint64_t* q = reinterpret_cast<uint64_t*>(p);
+    __hip_atomic_store(q, (uint64_t)m.n_used | (uint64_t)m.sym_lo << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(q + 1, (uint64_t)m.sym_hi | (uint64_t)m.n_outliers << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <bool WITHIN>
+__device__ __forceinline__ TMeta load_tmeta(const TMeta* p) {
+    if constexpr (!WITHIN) return *p;
+    const uint64_t* q = reinterpret_cast<const uint64_t*>(p);
+    const uint64_t a = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), b = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    TMeta m;
+    m.n_used = (uint32_t)a; m.sym_lo = (uint32_t)(a >> 32); m.sym_hi = (uint32_t)b; m.n_outliers = (uint32_t)(b >> 32);
+    return m;
+}
+
 struct CodebookShared {
     uint32_t lo, hi, maxlen, codes_done, cl[kLmaxLimit + 2], next[kLmaxLimit + 2];
 };
@@ -382,7 +398,7 @@ __device__ __forceinline__ bool codebook_build_wave(const Geom& g, uint32_t* his
         m.sym_lo = n_used ? lo : 0u;
         m.sym_hi = n_used ? hi : 0u;
         m.n_outliers = n_escape;  // symbol 0 = escape
-        *tmeta_t = m;
+        store_tmeta(tmeta_t, m);
     }
     return true;
 }
@@ -394,10 +410,11 @@ __device__ __forceinline__ bool codebook_build_wave(const Geom& g, uint32_t* his
 // hist_t is read, copied to hist_view_t (inspection) and cleared, so that the next call starts from zero counts.
 // enc_t is written with device-scope stores: other work-groups of a running kernel may read it once they have
 // seen the caller's completion flag.
+// within: another work-group of the same launch reads the lengths, too.
 template <uint32_t NT = 256>
 __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, uint32_t* hist_view_t, uint16_t* enc_t,
                                                uint8_t* lens_t, TMeta* tmeta_t, unsigned char* smem, CodebookShared& sh,
-                                               uint32_t tid, uint32_t carry = 0) {
+                                               uint32_t tid, uint32_t carry = 0, bool within = false) {
     const uint32_t K = g.K;
     uint64_t* key = reinterpret_cast<uint64_t*>(smem);        // [K] sort keys: count << 16 | symbol
     uint32_t* cnt = reinterpret_cast<uint32_t*>(key + K);      // [K] counts
@@ -605,14 +622,15 @@ __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, 
         uint32_t L = len_s[k];
         __hip_atomic_store(&enc_t[k], (uint16_t)(L ? ((L << 12) | nodew[k]) : 0u), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
-        lens_t[k] = (uint8_t)L;
+        if (within) __hip_atomic_store(&lens_t[k], (uint8_t)L, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else lens_t[k] = (uint8_t)L;
     }
     if (tid == 0) {
         TMeta m;
         // an empty histogram cannot come out of the histogram step (every table has an element); should it
         // happen anyway, the symbol range is still a valid one for the kernels that size things from it
         m.n_used = n_used; m.sym_lo = sym_lo; m.sym_hi = sym_hi; m.n_outliers = cnt[0];  // symbol 0 = escape
-        *tmeta_t = m;
+        store_tmeta(tmeta_t, m);
     }
     __syncthreads();
 }
@@ -676,7 +694,7 @@ __device__ __forceinline__ bool codebook_window_wave(const Geom& g, const uint32
         m.sym_lo = n_used ? lo : 0u;
         m.sym_hi = n_used ? hi : 0u;
         m.n_outliers = n_escape;
-        *tmeta_t = m;
+        store_tmeta(tmeta_t, m);
     }
     return true;
 }
@@ -684,8 +702,14 @@ __device__ __forceinline__ bool codebook_window_wave(const Geom& g, const uint32
 // ------------------------------------------------------------------------------------------------
 // offsets of the output: single-pass look-back scan
 // ------------------------------------------------------------------------------------------------
-constexpr uint32_t kFlagAgg = 1, kFlagPrefix = 2;
+constexpr uint32_t kFlagAgg = 1, kFlagPrefix = 2, kFlagReady = 3;  // Ready: nothing for the scan yet (see wg_ready)
 constexpr uint32_t kSpinLimit = 1u << 22;
+
+// Tells the work-groups that finish the containers that this one's table has its codebook in memory (one thread, after a barrier
+// before which every wavefront has waited for its stores).
+__device__ __forceinline__ void wg_ready(uint64_t* state, uint64_t epoch, uint32_t wg) {
+    __hip_atomic_store(&state[wg], epoch << 34 | (uint64_t)kFlagReady << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // Exclusive prefix of `total` over the work-groups before `wg`: single-pass look-back over one record per
 // work-group, 256 records per step (four per lane).  The chain of "wait for a predecessor's prefix" steps across
@@ -713,7 +737,8 @@ __device__ __forceinline__ uint32_t wg_scan(uint64_t* state, uint64_t epoch, uin
                 const int64_t my = pos - (int64_t)(lane * 4u + (uint32_t)k);
                 const uint64_t sv = my >= (int64_t)dom0 ? __hip_atomic_load(&state[my], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
                                                         : (tag | ((uint64_t)kFlagPrefix << 32));
-                const uint32_t flag = (sv >> 34) == epoch ? (uint32_t)(sv >> 32) & 3u : 0u;
+                uint32_t flag = (sv >> 34) == epoch ? (uint32_t)(sv >> 32) & 3u : 0u;
+                flag = flag == kFlagReady ? 0u : flag;
                 if (!has_p) {
                     hole = hole || flag == 0u;
                     sum += flag != 0u ? (uint32_t)sv : 0u;
@@ -735,7 +760,7 @@ __device__ __forceinline__ uint32_t wg_scan(uint64_t* state, uint64_t epoch, uin
             if (pm) break;
             pos -= 256;
         }
-        if (lane == 0)
+        if (lane == 0 && !*dead)
             __hip_atomic_store(&state[wg], tag | ((uint64_t)kFlagPrefix << 32) | (uint32_t)(excl + total),
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }

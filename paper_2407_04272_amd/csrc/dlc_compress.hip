@@ -7,23 +7,24 @@
 #include <algorithm>
 
 #include "dlc_codec_dev.h"
+#include "dlc_finalize.h"
 
 namespace dlc {
 
-void launch_encode_64(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
-                      uint64_t capacity, hipStream_t s);
-void launch_table_64(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
-                     uint64_t capacity, hipStream_t s);
+bool launch_encode_64(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
+                      uint64_t capacity, uint64_t* out_bytes, hipStream_t s);
+bool launch_table_64(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
+                     uint64_t capacity, uint64_t* out_bytes, hipStream_t s);
 hipError_t encode_set_attributes_64();
-void launch_encode_128(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
-                      uint64_t capacity, hipStream_t s);
-void launch_table_128(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
-                     uint64_t capacity, hipStream_t s);
+bool launch_encode_128(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
+                      uint64_t capacity, uint64_t* out_bytes, hipStream_t s);
+bool launch_table_128(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
+                     uint64_t capacity, uint64_t* out_bytes, hipStream_t s);
 hipError_t encode_set_attributes_128();
-void launch_encode_256(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
-                      uint64_t capacity, hipStream_t s);
-void launch_table_256(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
-                     uint64_t capacity, hipStream_t s);
+bool launch_encode_256(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
+                      uint64_t capacity, uint64_t* out_bytes, hipStream_t s);
+bool launch_table_256(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
+                     uint64_t capacity, uint64_t* out_bytes, hipStream_t s);
 hipError_t encode_set_attributes_256();
 void launch_encode_carry_64(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
                             uint64_t capacity, uint32_t bpt, hipStream_t s);
@@ -162,217 +163,6 @@ __global__ __launch_bounds__(256) void k_codebook(Geom g, uint32_t* hist, uint32
 // one of them builds the tree).
 static inline uint32_t codebook_tables_per_wg(const Geom& g) { return g.T >= 512u && g.K >= kWaveAlphabet ? 4u : 1u; }
 static inline size_t codebook_lds(const Geom& g, uint32_t tpw) { return tpw == 4u ? codebook_four_smem(g.K) : codebook_smem(g.K); }
-
-// ------------------------------------------------------------------------------------------------
-// finalize: code-length blocks behind the payload, header, directory, padding, size metadata; clears the
-// per-call control words for the next call.  Every work-group (256 threads, or 1024: finalize_threads) works out where the
-// code-length blocks go (a scan over the tables) and writes the blocks of its share of the tables, a wavefront
-// per table; the first work-group also writes everything else.
-// ------------------------------------------------------------------------------------------------
-__device__ __forceinline__ uint64_t a16(uint64_t x) { return (x + 15ull) & ~15ull; }
-
-// One destination's container, by work-group xi of the xn that share the work (all of NT threads); everything below is
-// that container's.  The tables' word ranges may come from work-groups of the running kernel: they are read past the caches.
-template <uint32_t NT>
-__device__ __forceinline__ void finalize_dest(const Geom& g, const FixedLayout& F, const TMeta* tmeta, const uint8_t* __restrict__ lens,
-                                              const QParam* qp, Ctrl* ctrl, const uint32_t* word_start, const uint32_t* word_end,
-                                              uint8_t* __restrict__ out, uint64_t capacity, uint64_t* out_bytes, uint32_t* esc_count,
-                                              const uint8_t* rm_on, const uint32_t* rm_ref, uint32_t* bsum, uint32_t dst, uint32_t xi,
-                                              uint32_t xn) {
-    constexpr uint32_t NW = NT / 64u;
-    __shared__ uint32_t s_red[NW + 1];
-    __shared__ uint32_t s_abort;
-    __shared__ uint32_t s_cb[NT + 1];   // start of each table's block, relative to the pass's first block
-    __shared__ uint32_t s_lo[NT], s_nl[NT];
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const bool first = xi == 0;
-    const uint32_t T = g.TD;
-    tmeta += (size_t)dst * T;
-    lens += (size_t)dst * T * g.K;
-    qp += (size_t)dst * T;
-    word_start += (size_t)dst * T;
-    word_end += (size_t)dst * T;
-    if (esc_count) esc_count += (size_t)dst * T;
-    out += (uint64_t)dst * capacity;
-    uint64_t* const table_bytes = out_bytes + 1 + (size_t)dst * T;
-    const uint64_t words = __hip_atomic_load(&word_end[T - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint64_t off_cb = a16(F.off_payload + 4ull * words);
-    // an internal failure of the encode kernel spoils every container; one that did not fit spoils only itself, and
-    // the capacity test below fails for it whenever the encode kernel's did.  (The flag is cleared by the last
-    // destination to finish, so every destination's first work-group can still read it.)
-    if (first && bsum) {  // single-pass path: the block sums the next call adds to start at zero (not the ones this call reads)
-        const uint32_t nb = sum_blocks_per_dest(g);
-        for (uint32_t i = tid; i < nb; i += NT) bsum[(size_t)dst * nb + i] = 0u;
-    }
-    const bool aborted = first && (__hip_atomic_load(&ctrl->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kAbortInternal) != 0;
-    uint64_t cb_carry = 0, nout_carry = 0;
-    for (uint32_t base = 0; base < T; base += NT) {
-        const uint32_t t = base + tid;
-        TMeta m;
-        uint32_t cb = 0, no = 0, nl = 0, w0 = 0, w1 = 0, eb_bits = 0;
-        if (t < T) {
-            m = tmeta[t];
-            if (first) {  // (what the directory needs, together with the rest: one latency)
-                w0 = __hip_atomic_load(&word_start[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                w1 = __hip_atomic_load(&word_end[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                eb_bits = qp[t].eb_bits;
-            }
-            if (first && esc_count) {  // single-pass path: the codebook is older than the payload, the escapes were counted by the encode kernel
-                m.n_outliers = esc_count[t];
-                esc_count[t] = 0;
-            }
-            if (m.sym_lo > m.sym_hi || m.sym_hi >= g.K) { m.sym_lo = 0; m.sym_hi = 0; }  // never index outside lens[]
-            nl = m.sym_hi - m.sym_lo + 1u;
-            cb = (nl + 3u) & ~3u;
-            no = m.n_outliers;
-        }
-        uint32_t cb_tot, no_tot;
-        const uint32_t cb_ex = block_excl_scan<(int)NW>(cb, s_red, tid, &cb_tot);
-        __syncthreads();
-        (void)block_excl_scan<(int)NW>(no, s_red, tid, &no_tot);
-        s_cb[tid] = cb_ex;
-        s_lo[tid] = m.sym_lo;
-        s_nl[tid] = nl;
-        if (tid == 0) {
-            s_cb[NT] = cb_tot;
-            // the code-length blocks are the last thing in the container: the capacity check of this pass
-            s_abort = aborted || off_cb + cb_carry + cb_tot > capacity;
-        }
-        __syncthreads();
-        if (s_abort) break;  // uniform
-        const uint32_t nt = min(NT, T - base);
-        // the blocks of this work-group's tables, a wavefront per table, four bytes per lane (the blocks start on
-        // 4-byte boundaries and are padded to them)
-        for (uint32_t lt = xi * NW + wave; lt < nt; lt += xn * NW) {
-            const uint32_t n_l = s_nl[lt];
-            const uint8_t* src = lens + (size_t)(base + lt) * g.K + s_lo[lt];
-            uint32_t* dst = reinterpret_cast<uint32_t*>(out + off_cb + cb_carry + s_cb[lt]);
-            for (uint32_t wd = lane; wd < (n_l + 3u) / 4u; wd += 64) {
-                uint32_t v = 0;
-#pragma unroll
-                for (uint32_t b = 0; b < 4; ++b) {
-                    const uint32_t i = wd * 4u + b;
-                    v |= (i < n_l ? (uint32_t)src[i] : 0u) << (8u * b);
-                }
-                dst[wd] = v;
-            }
-        }
-        if (first && t < T) {
-            uint8_t* d = out + kHeaderBytes + (uint64_t)kDirBytes * t;
-            uint32_t* d32 = reinterpret_cast<uint32_t*>(d);
-            d32[0] = eb_bits; d32[1] = m.n_used; d32[2] = m.sym_lo; d32[3] = m.sym_hi; d32[4] = m.n_outliers;
-            d32[5] = g.G;
-            uint64_t* d64 = reinterpret_cast<uint64_t*>(d + 24);
-            d64[0] = off_cb + cb_carry + cb_ex; d64[1] = 0; d64[2] = w0; d64[3] = (uint64_t)(w1 - w0);
-            table_bytes[t] = 4ull * (uint64_t)(w1 - w0) + cb + (uint64_t)(kW + 4u) * g.G + kDirBytes;
-        }
-        cb_carry += cb_tot;
-        nout_carry += no_tot;
-        __syncthreads();
-    }
-    // row matching: the references of the tables that use it, behind the code-length blocks, each block on a 16-byte
-    // boundary (all blocks are 4*B bytes, so block k starts k * a16(4*B) after the first)
-    uint64_t end_bytes = off_cb + cb_carry;  // where the container ends
-    if (rm_on && !s_abort) {
-        rm_on += (size_t)dst * T;
-        rm_ref += (size_t)dst * T * g.B;
-        const uint64_t rbase = a16(end_bytes), rsz = a16(4ull * g.B);
-        uint32_t n_on = 0;  // tables with references
-        for (uint32_t base = 0; base < T; base += NT) {
-            uint32_t tot;
-            (void)block_excl_scan<(int)NW>((base + tid < T && rm_on[base + tid]) ? 1u : 0u, s_red, tid, &tot);
-            n_on += tot;
-            __syncthreads();
-        }
-        if (n_on) end_bytes = rbase + (uint64_t)(n_on - 1u) * rsz + 4ull * g.B;
-        if (end_bytes > capacity) {  // uniform
-            __syncthreads();
-            if (tid == 0) s_abort = 1;
-            __syncthreads();
-        } else if (n_on) {
-            for (uint64_t i = off_cb + cb_carry + tid; first && i < rbase; i += NT) out[i] = 0;
-            uint32_t on_carry = 0;
-            for (uint32_t base = 0; base < T; base += NT) {
-                const uint32_t t = base + tid;
-                const uint32_t on = (t < T && rm_on[t]) ? 1u : 0u;
-                uint32_t tot;
-                const uint32_t ex = block_excl_scan<(int)NW>(on, s_red, tid, &tot);
-                s_cb[tid] = on ? on_carry + ex : 0xFFFFFFFFu;  // the table's block number
-                __syncthreads();
-                if (first && on) {
-                    uint64_t* d64 = reinterpret_cast<uint64_t*>(out + kHeaderBytes + (uint64_t)kDirBytes * t + 24);
-                    d64[1] = rbase + (uint64_t)(on_carry + ex) * rsz;
-                    table_bytes[t] += 4ull * g.B;
-                }
-                const uint32_t nt = min(NT, T - base);
-                for (uint32_t lt = xi; lt < nt; lt += xn) {  // a work-group per table
-                    const uint32_t k = s_cb[lt];
-                    if (k == 0xFFFFFFFFu) continue;  // uniform
-                    uint32_t* dstw = reinterpret_cast<uint32_t*>(out + rbase + (uint64_t)k * rsz);
-                    const uint32_t* src = rm_ref + (size_t)(base + lt) * g.B;
-                    for (uint32_t r = tid; r < g.B; r += NT) dstw[r] = src[r];
-                    if (k + 1u < n_on)  // padding up to the next block
-                        for (uint32_t r = g.B + tid; r < (uint32_t)(rsz / 4u); r += NT) dstw[r] = 0u;
-                }
-                on_carry += tot;
-                __syncthreads();
-            }
-        }
-    }
-    if (!first) return;
-    uint64_t container_bytes = 0;  // of this destination; 0 = it did not fit
-    if (s_abort) {
-        if (tid == 0 && !aborted) set_status(ctrl, DLC_ECAPACITY);
-        for (uint32_t t = tid; t < T; t += NT) table_bytes[t] = 0;
-        if (esc_count)  // whatever the passes after the failing one have not cleared
-            for (uint32_t t = tid; t < T; t += NT) esc_count[t] = 0;
-    } else {
-        // padding between sections
-        const uint64_t e0 = kHeaderBytes + (uint64_t)kDirBytes * T;
-        for (uint64_t i = e0 + tid; i < F.off_group; i += NT) out[i] = 0;
-        const uint64_t e1 = F.off_group + 4ull * T * g.G;
-        for (uint64_t i = e1 + tid; i < F.off_chunk; i += NT) out[i] = 0;
-        const uint64_t e2 = F.off_payload + 4ull * words;
-        for (uint64_t i = e2 + tid; i < off_cb; i += NT) out[i] = 0;
-        if (tid == 0) {
-            uint32_t* h = reinterpret_cast<uint32_t*>(out);
-            h[H_MAGIC] = kMagic; h[H_VERSION] = kVersion; h[H_DTYPE] = g.dtype; h[H_T] = T; h[H_B] = g.B; h[H_D] = g.D;
-            h[H_R] = g.R; h[H_S] = g.S; h[H_LMAX] = g.LMAX; h[H_W] = kW; h[H_V] = kV; h[H_NG] = T * g.G;
-            uint64_t* q = reinterpret_cast<uint64_t*>(out);
-            q[HQ_NOUT] = nout_carry; q[HQ_WORDS] = words; q[HQ_OFF_GROUP] = F.off_group; q[HQ_OFF_CHUNK] = F.off_chunk;
-            q[HQ_OFF_PAYLOAD] = F.off_payload; q[HQ_OFF_CB] = off_cb;
-            const uint64_t total = end_bytes;
-            q[HQ_TOTAL] = total; q[HQ_TOTAL + 1] = 0; q[HQ_TOTAL + 2] = 0; q[HQ_TOTAL + 3] = 0;
-            container_bytes = total;
-        }
-    }
-    if (tid != 0) return;
-    // sizes: one destination -> out_bytes[0] is its container's size.  Several -> every destination stores its size
-    // behind the per-table entries, and the last one to do so adds them up into out_bytes[0] (0 if any did not fit).
-    // the next call starts with ticket 0 and no abort (the histograms were cleared by the codebook step)
-    if (g.ND == 1) {
-        out_bytes[0] = container_bytes;
-        ctrl->ticket = 0;
-        ctrl->abort = 0;
-    } else {
-        unsigned long long* dest_bytes = reinterpret_cast<unsigned long long*>(out_bytes + 1 + (size_t)g.ND * T);
-        __hip_atomic_store(&dest_bytes[dst], (unsigned long long)container_bytes, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (__hip_atomic_fetch_add(&ctrl->dest_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == g.ND) {
-            unsigned long long sum = 0;
-            bool all = true;
-            for (uint32_t d = 0; d < g.ND; ++d) {
-                const unsigned long long b = __hip_atomic_load(&dest_bytes[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                all = all && b != 0;
-                sum += b;
-            }
-            out_bytes[0] = all ? sum : 0;
-            __hip_atomic_store(&ctrl->dest_done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            ctrl->ticket = 0;
-            __hip_atomic_store(&ctrl->abort, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
-}
 
 template <uint32_t NT>
 __global__ __launch_bounds__(NT) void k_finalize(Geom g, FixedLayout F, const TMeta* tmeta, const uint8_t* __restrict__ lens,
@@ -584,12 +374,16 @@ hipError_t launch_compress(const Geom& g, const void* payload, uint8_t* out, uin
     const bool whole_rounds = (g.T >= 128u && g.T <= 256u) || g.T > 352u;
     const bool fused = !g.lz && (g.G <= 8u || (g.G <= 16u && whole_rounds)) && (g.T <= 256u || g.K <= 1024u);
     const uint32_t tpw = codebook_tables_per_wg(g);
+    // The launch that codes the groups finishes the containers, too, where a work-group has a thread for each of a container's
+    // tables (see finish_container), unless every kernel is to be timed by itself or there are references to copy.
+    uint64_t* const fin = g.lz || prof_on(pl, P_FINALIZE) ? nullptr : out_bytes;
+    bool finished = false;
     if (fused) {
         if (prof_on(pl, P_TABLE)) prof_begin(prof, P_TABLE, s);
         switch (g.S) {
-            case 64: launch_table_64(g, F, payload, w, epoch, out, capacity, s); break;
-            case 128: launch_table_128(g, F, payload, w, epoch, out, capacity, s); break;
-            default: launch_table_256(g, F, payload, w, epoch, out, capacity, s); break;
+            case 64: finished = launch_table_64(g, F, payload, w, epoch, out, capacity, fin, s); break;
+            case 128: finished = launch_table_128(g, F, payload, w, epoch, out, capacity, fin, s); break;
+            default: finished = launch_table_256(g, F, payload, w, epoch, out, capacity, fin, s); break;
         }
         if (prof_on(pl, P_TABLE)) prof_end(prof, P_TABLE, s);
     } else {
@@ -625,20 +419,22 @@ hipError_t launch_compress(const Geom& g, const void* payload, uint8_t* out, uin
         {
             if (prof_on(pl, P_ENCODE)) prof_begin(prof, P_ENCODE, s);
             switch (g.S) {
-                case 64: launch_encode_64(g, F, payload, w, epoch, out, capacity, s); break;
-                case 128: launch_encode_128(g, F, payload, w, epoch, out, capacity, s); break;
-                default: launch_encode_256(g, F, payload, w, epoch, out, capacity, s); break;
+                case 64: finished = launch_encode_64(g, F, payload, w, epoch, out, capacity, fin, s); break;
+                case 128: finished = launch_encode_128(g, F, payload, w, epoch, out, capacity, fin, s); break;
+                default: finished = launch_encode_256(g, F, payload, w, epoch, out, capacity, fin, s); break;
             }
             if (prof_on(pl, P_ENCODE)) prof_end(prof, P_ENCODE, s);
         }
     }
-    if (prof_on(pl, P_FINALIZE)) prof_begin(prof, P_FINALIZE, s);
+    if (!finished) {
+        if (prof_on(pl, P_FINALIZE)) prof_begin(prof, P_FINALIZE, s);
 #define DLC_FIN(N) hipLaunchKernelGGL(k_finalize<N>, finalize_grid(g), dim3(N), 0, s, g, F, w.tmeta, w.lens, w.qp, w.ctrl, w.word_start, \
                                       w.word_end, out, capacity, out_bytes, (uint32_t*)nullptr, g.lz ? (const uint8_t*)w.rm_on : nullptr, \
                                       (const uint32_t*)w.rm_ref, (uint32_t*)nullptr)
-    if (finalize_threads(g) == 256u) DLC_FIN(256); else DLC_FIN(1024);
+        if (finalize_threads(g) == 256u) DLC_FIN(256); else DLC_FIN(1024);
 #undef DLC_FIN
-    if (prof_on(pl, P_FINALIZE)) prof_end(prof, P_FINALIZE, s);
+        if (prof_on(pl, P_FINALIZE)) prof_end(prof, P_FINALIZE, s);
+    }
     if (w.carry != 0)  // the codebook the next call will use: this call's counts (kept as the copy), escape symbol included
         hipLaunchKernelGGL(k_codebook, dim3((g.T + tpw - 1u) / tpw), dim3(256), codebook_lds(g, tpw), s, g, w.hist_view, w.hist_view, w.enc_next,
                            w.lens_next, w.tmeta_next, 1u, tpw);

@@ -4,6 +4,7 @@
 #include <algorithm>
 
 #include "dlc_codec_dev.h"
+#include "dlc_finalize.h"
 
 #define DLC_CAT2(a, b) a##b
 #define DLC_CAT(a, b) DLC_CAT2(a, b)
@@ -428,8 +429,8 @@ __device__ __forceinline__ void build_pairs(uint32_t* pair, const uint16_t* ent,
 template <int S, bool F16, bool VEC, bool LZ, uint32_t NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4)))
 void k_encode(const void* payload, const uint8_t* sym_plane, Geom g, FixedLayout F, const QParam* qp, const uint16_t* enc,
-              const TMeta* tmeta, Ctrl* ctrl, uint64_t* state, uint64_t epoch, uint8_t* out, uint64_t capacity, uint32_t bpt,
-              uint32_t* word_start, uint32_t* word_end, uint32_t cap, uint32_t pair_max) {
+              const TMeta* tmeta, const uint8_t* lens, Ctrl* ctrl, uint64_t* state, uint64_t epoch, uint8_t* out, uint64_t capacity, uint32_t bpt,
+              uint32_t* word_start, uint32_t* word_end, uint64_t* out_bytes, uint32_t xn, uint32_t cap, uint32_t pair_max) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t s_wg, s_lo, s_hi;
     const uint32_t tid = threadIdx.x;
@@ -437,6 +438,10 @@ void k_encode(const void* payload, const uint8_t* sym_plane, Geom g, FixedLayout
     __syncthreads();
     GroupJob J;
     J.wg = __builtin_amdgcn_readfirstlane(s_wg);
+    if (J.wg >= g.T * bpt) {  // uniform; xn for every container
+        finish_container<64u * NW, false>(g, F, tmeta, lens, qp, ctrl, state, epoch, bpt, out, capacity, out_bytes, J.wg - g.T * bpt, xn, *reinterpret_cast<FinLds<64u * NW>*>(smem), tid);
+        return;
+    }
     J.t = J.wg / bpt;
     J.grp = (J.wg % bpt) * NW + __builtin_amdgcn_readfirstlane(tid >> 6);
     // the destination this table belongs to: its container starts `capacity` bytes after the previous one, its
@@ -487,7 +492,7 @@ template <int S, bool F16, bool VEC, uint32_t NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4)))
 void k_table(const void* payload, uint8_t* sym_plane, Geom g, FixedLayout F, const QParam* qp, uint32_t* hist_view, uint16_t* enc,
              uint8_t* lens, TMeta* tmeta, Ctrl* ctrl, uint64_t* state, uint64_t epoch, uint8_t* out, uint64_t capacity,
-             uint32_t* word_start, uint32_t* word_end, uint32_t cap, uint32_t pair_max) {
+             uint32_t* word_start, uint32_t* word_end, uint64_t* out_bytes, uint32_t xn, uint32_t cap, uint32_t pair_max) {
     constexpr uint32_t NT = 64u * NW;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ CodebookShared s_cb;
@@ -507,6 +512,10 @@ void k_table(const void* payload, uint8_t* sym_plane, Geom g, FixedLayout F, con
     __syncthreads();
     GroupJob J;
     J.wg = __builtin_amdgcn_readfirstlane(s_wg);
+    if (J.wg >= g.T) {  // uniform; xn for every container
+        finish_container<NT, true>(g, F, tmeta, lens, qp, ctrl, state, epoch, 1u, out, capacity, out_bytes, J.wg - g.T, xn, *reinterpret_cast<FinLds<NT>*>(smem), tid);
+        return;
+    }
     const uint32_t t = J.wg;  // a work-group per table, in ticket order
     J.t = t;
     J.grp = wave;
@@ -584,12 +593,13 @@ void k_table(const void* payload, uint8_t* sym_plane, Geom g, FixedLayout F, con
             uint32_t idx;
             const uint32_t e = in_window(k, idx) ? ent[idx] : 0u;
             enc_t[k] = (uint16_t)e;
-            lens_t[k] = (uint8_t)(e >> 12);
+            if (out_bytes) __hip_atomic_store(&lens_t[k], (uint8_t)(e >> 12), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else lens_t[k] = (uint8_t)(e >> 12);
         }
     } else {  // many symbols, or symbols outside the window: from the counts in memory
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        codebook_build<NT>(g, view_t, view_t, enc_t, lens_t, tmeta + t, smem, s_cb, tid, 0u);
+        codebook_build<NT>(g, view_t, view_t, enc_t, lens_t, tmeta + t, smem, s_cb, tid, 0u, out_bytes != nullptr);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         for (uint32_t i = tid; i < 256u; i += NT) {
@@ -604,8 +614,10 @@ void k_table(const void* payload, uint8_t* sym_plane, Geom g, FixedLayout F, con
     J.special = n_other != 0u || s_cnt[kWinEsc] != 0u;
     if (J.pairs) {
         build_pairs(reinterpret_cast<uint32_t*>(smem + J.L.pair), ent, J.lo, J.P, tid, NT);
-        __syncthreads();
     }
+    if (out_bytes) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the codebook is out)
+    __syncthreads();
+    if (out_bytes && tid == 0) wg_ready(state, epoch, J.wg);
     encode_groups<S, F16, VEC, false, NW>(J, payload, sym_plane, g, F, qp, enc, ctrl, state, epoch, out + (uint64_t)J.dst * capacity,
                                           capacity, word_start, word_end, smem, tid);
 }
@@ -623,12 +635,15 @@ static inline uint32_t pair_max_for(uint32_t budget, uint32_t nw, uint32_t waves
     return p;
 }
 
+// out_bytes: where the sizes go if the launch is to finish the containers as well; it does if it returns true
 template <uint32_t NW>
-static void DLC_CAT(encode_launch_, DLC_S)(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch,
-                                           uint8_t* out, uint64_t capacity, hipStream_t s) {
+static bool DLC_CAT(encode_launch_, DLC_S)(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch,
+                                           uint8_t* out, uint64_t capacity, uint64_t* out_bytes, hipStream_t s) {
     constexpr int S = DLC_S;
     const uint32_t bpt = (g.G + NW - 1u) / NW;
-    dim3 grid(g.T * bpt), block(64 * NW);
+    if (g.TD > 64u * NW) out_bytes = nullptr;
+    const uint32_t xn = finish_groups(g, 64u * NW);
+    dim3 grid(g.T * bpt + (out_bytes ? g.ND * xn : 0u)), block(64 * NW);
     // sixteen wavefronts a compute unit share its LDS: columns of 4 bits a symbol.  Where the grid leaves room, longer
     // columns (up to the longest code), so that no group is walked twice.
     const uint32_t per_cu = std::min(16u / NW, std::max(1u, (g.T * bpt + 255u) / 256u));
@@ -636,66 +651,74 @@ static void DLC_CAT(encode_launch_, DLC_S)(const Geom& g, const FixedLayout& F, 
     uint32_t cap = (uint32_t)S * 12u / 32u;
     while (cap > (uint32_t)S / 8u && enc_lds(NW, NW, cap, 56u).end > budget) --cap;
     const uint32_t pair_max = pair_max_for(budget, NW, NW, cap);
-    const size_t sm = enc_lds(NW, NW, cap, pair_max).end;
+    size_t sm = enc_lds(NW, NW, cap, pair_max).end;
+    if (out_bytes) sm = std::max(sm, sizeof(FinLds<64u * NW>));
     const bool f16 = g.dtype == DLC_F16;
 #define DLC_ENC(FF, V, LZ)                                                                                            \
-    hipLaunchKernelGGL((k_encode<S, FF, V, LZ, NW>), grid, block, sm, s, payload, w.sym_plane, g, F, w.qp, w.enc, w.tmeta, w.ctrl, w.state, \
-                       epoch, out, capacity, bpt, w.word_start, w.word_end, cap, pair_max)
+    hipLaunchKernelGGL((k_encode<S, FF, V, LZ, NW>), grid, block, sm, s, payload, w.sym_plane, g, F, w.qp, w.enc, w.tmeta, w.lens, w.ctrl, \
+                       w.state, epoch, out, capacity, bpt, w.word_start, w.word_end, out_bytes, xn, cap, pair_max)
     if (g.lz) { if (f16) DLC_ENC(true, true, true); else DLC_ENC(false, true, true); }  // (dim % 4 == 0 there)
     else if (f16) { if (g.vec) DLC_ENC(true, true, false); else DLC_ENC(true, false, false); }
     else { if (g.vec) DLC_ENC(false, true, false); else DLC_ENC(false, false, false); }
 #undef DLC_ENC
+    return out_bytes != nullptr;
 }
 
-void DLC_CAT(launch_encode_, DLC_S)(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch,
-                                    uint8_t* out, uint64_t capacity, hipStream_t s) {
+bool DLC_CAT(launch_encode_, DLC_S)(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch,
+                                    uint8_t* out, uint64_t capacity, uint64_t* out_bytes, hipStream_t s) {
     // four groups a work-group where that spreads a small payload over more compute units
-    if (g.G <= 4u || g.T * ((g.G + 3u) / 4u) <= 512u) DLC_CAT(encode_launch_, DLC_S)<4u>(g, F, payload, w, epoch, out, capacity, s);
-    else DLC_CAT(encode_launch_, DLC_S)<8u>(g, F, payload, w, epoch, out, capacity, s);
+    if (g.G <= 4u || g.T * ((g.G + 3u) / 4u) <= 512u) return DLC_CAT(encode_launch_, DLC_S)<4u>(g, F, payload, w, epoch, out, capacity, out_bytes, s);
+    return DLC_CAT(encode_launch_, DLC_S)<8u>(g, F, payload, w, epoch, out, capacity, out_bytes, s);
 }
 
 template <uint32_t NW>
-static void DLC_CAT(table_launch_, DLC_S)(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch,
-                                          uint8_t* out, uint64_t capacity, uint32_t cap, uint32_t budget, hipStream_t s) {
+static bool DLC_CAT(table_launch_, DLC_S)(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch,
+                                          uint8_t* out, uint64_t capacity, uint64_t* out_bytes, uint32_t cap, uint32_t budget, uint32_t slots, hipStream_t s) {
     constexpr int S = DLC_S;
-    dim3 grid(g.T), block(64 * NW);
+    const uint32_t xn = finish_groups(g, 64u * NW);
+    // `slots` work-groups run at a time.  Those that finish the containers have to run beside the tables': started when the first
+    // tables are done they are late (512 tables of 256 elements 28.2 us, so 30.4), but for one round among several (4096 of 32768: 360, so 354).
+    if (g.TD > 64u * NW || (g.T + g.ND * xn > slots && g.T < 2u * slots)) out_bytes = nullptr;
+    dim3 grid(g.T + (out_bytes ? g.ND * xn : 0u)), block(64 * NW);
     const uint32_t waves = std::min(NW, g.G);
     const uint32_t pair_max = pair_max_for(budget, NW, waves, cap);
     size_t sm = enc_lds(NW, waves, cap, pair_max).end;
     sm = std::max(sm, std::max(hist_lds_bytes(g.K), codebook_smem(g.K)));
+    if (out_bytes) sm = std::max(sm, sizeof(FinLds<64u * NW>));
     const bool f16 = g.dtype == DLC_F16;
 #define DLC_TAB(FF, V)                                                                                                \
     hipLaunchKernelGGL((k_table<S, FF, V, NW>), grid, block, sm, s, payload, w.sym_plane, g, F, w.qp, w.hist_view, w.enc, w.lens, w.tmeta, \
-                       w.ctrl, w.state, epoch, out, capacity, w.word_start, w.word_end, cap, pair_max)
+                       w.ctrl, w.state, epoch, out, capacity, w.word_start, w.word_end, out_bytes, xn, cap, pair_max)
     if (f16) { if (g.vec) DLC_TAB(true, true); else DLC_TAB(true, false); }
     else { if (g.vec) DLC_TAB(false, true); else DLC_TAB(false, false); }
 #undef DLC_TAB
+    return out_bytes != nullptr;
 }
 
-void DLC_CAT(launch_table_, DLC_S)(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch,
-                                   uint8_t* out, uint64_t capacity, hipStream_t s) {
+bool DLC_CAT(launch_table_, DLC_S)(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch,
+                                   uint8_t* out, uint64_t capacity, uint64_t* out_bytes, hipStream_t s) {
     constexpr uint32_t S = DLC_S;
     if (g.T <= 256u) {
         // no more tables than compute units: a work-group has one to itself.  Sixteen wavefronts read a table of more than
         // one unit each; the columns are as long as the LDS allows (12 bits a symbol is the longest code)
         uint32_t cap = S * 12u / 32u;
         while (cap > S / 8u && enc_lds(16u, std::min(16u, g.G), cap, 56u).end > kLdsMax - kTableStatic) --cap;
-        if (g.n <= 16u * kW * kV) DLC_CAT(table_launch_, DLC_S)<4u>(g, F, payload, w, epoch, out, capacity, cap, kLdsMax - kTableStatic, s);
-        else DLC_CAT(table_launch_, DLC_S)<16u>(g, F, payload, w, epoch, out, capacity, cap, kLdsMax - kTableStatic, s);
+        if (g.n <= 16u * kW * kV) return DLC_CAT(table_launch_, DLC_S)<4u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax - kTableStatic, 256u, s);
+        return DLC_CAT(table_launch_, DLC_S)<16u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax - kTableStatic, 256u, s);
     } else if (g.T <= 512u && g.G <= 8u) {
         // two work-groups of eight wavefronts a compute unit, one round of them, with columns as long as that leaves.  (Two
         // wavefronts for tables of one or two groups: 300 tables of one group at ratios of 10 and 4.9 37 and 103 us a call, so 33
         // and 86; of four groups, four wavefronts: 50 and 117, so 51 and 112.)
         uint32_t cap = S * 12u / 32u;
         while (cap > S / 8u && enc_lds(8u, g.G, cap, 40u).end > kLdsMax / 2u - kTableStatic) --cap;
-        DLC_CAT(table_launch_, DLC_S)<8u>(g, F, payload, w, epoch, out, capacity, cap, kLdsMax / 2u - kTableStatic, s);
+        return DLC_CAT(table_launch_, DLC_S)<8u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax / 2u - kTableStatic, 512u, s);
     } else {
         // as many wavefronts as the table has groups, twelve to sixteen a compute unit
         const uint32_t cap = S / 8u;
-        if (g.G <= 2u) DLC_CAT(table_launch_, DLC_S)<2u>(g, F, payload, w, epoch, out, capacity, cap, kLdsMax / 6u - kTableStatic, s);
-        else if (g.G <= 4u) DLC_CAT(table_launch_, DLC_S)<4u>(g, F, payload, w, epoch, out, capacity, cap, kLdsMax / 3u - kTableStatic, s);
-        else if (g.G <= 8u) DLC_CAT(table_launch_, DLC_S)<8u>(g, F, payload, w, epoch, out, capacity, cap, kLdsMax / 2u - kTableStatic, s);
-        else DLC_CAT(table_launch_, DLC_S)<16u>(g, F, payload, w, epoch, out, capacity, cap, kLdsMax - kTableStatic, s);
+        if (g.G <= 2u) return DLC_CAT(table_launch_, DLC_S)<2u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax / 6u - kTableStatic, 1536u, s);
+        if (g.G <= 4u) return DLC_CAT(table_launch_, DLC_S)<4u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax / 3u - kTableStatic, 768u, s);
+        if (g.G <= 8u) return DLC_CAT(table_launch_, DLC_S)<8u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax / 2u - kTableStatic, 512u, s);
+        return DLC_CAT(table_launch_, DLC_S)<16u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax - kTableStatic, 256u, s);
     }
 }
 

@@ -44,7 +44,7 @@ struct Geom {
 };
 
 // per-table results of the codebook step
-struct TMeta {
+struct alignas(16) TMeta {
     uint32_t n_used, sym_lo, sym_hi, n_outliers;
 };
 
