@@ -199,14 +199,15 @@ static int stats_workspace(const Geom& g, Ws& w) {
     auto take = [&](size_t b) { size_t o = off; off = a256(off + b); return o; };
     const size_t o_probe = take(sizeof(QParam) * g.T);
     const size_t o_own = take(2ull * g.T * g.B * 4);
-    const size_t o_mult = take(16ull * g.D);
+    const size_t o_mult = take(1024ull * stats_mult_steps(g));
     const size_t o_hash = take(2ull * g.T * g.B * 8);
-    const size_t o_mm = take(16ull * g.T + 8ull);  // what the host reads: ranges, counts, collisions, status
+    const size_t o_range = take(8ull * g.T * kStatsBlocks);
+    const size_t o_unique = take(8ull * g.T);
     uint8_t* base = nullptr;
     if (hipMalloc((void**)&base, off) != hipSuccess) { (void)hipGetLastError(); return DLC_ENOMEM; }
     w.stats_base = base; w.stats_bytes = off;
     w.probe = (QParam*)(base + o_probe); w.st_own = (uint32_t*)(base + o_own); w.st_mult = (uint32_t*)(base + o_mult);
-    w.rowhash = (uint64_t*)(base + o_hash); w.st_minmax = (uint32_t*)(base + o_mm); w.st_unique = w.st_minmax + 2 * (size_t)g.T;
+    w.rowhash = (uint64_t*)(base + o_hash); w.st_range = (uint32_t*)(base + o_range); w.st_unique = (uint32_t*)(base + o_unique);
     return DLC_OK;
 }
 
@@ -258,14 +259,15 @@ extern "C" int dlc_create(dlc_ctx** out, const dlc_config* cfg) {
         return DLC_EHIP;
     }
     // (behind the ring: two slots for the statistics' probe bounds and results, 16 bytes a table and two words)
-    if (hipHostMalloc((void**)&c->pin, sizeof(QParam) * g.T * (dlc_ctx::kRing + 2), hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc((void**)&c->pin, sizeof(QParam) * g.T * (dlc_ctx::kRing + 3), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         (void)hipFree(base);
         delete c;
         return DLC_ENOMEM;
     }
     static_assert(2 * sizeof(QParam) >= 16 + 8, "the statistics' results fit two slots");
-    c->ws.st_pin = c->pin + (size_t)g.T * dlc_ctx::kRing;
+    c->ws.st_pin_probe = c->pin + (size_t)g.T * dlc_ctx::kRing;
+    c->ws.st_pin = reinterpret_cast<uint32_t*>(c->ws.st_pin_probe + g.T);
     for (int i = 0; i < dlc_ctx::kRing; ++i)
         if (hipEventCreateWithFlags(&c->pin_ev[i], hipEventDisableTiming) != hipSuccess) {
             dlc_destroy(c);
@@ -614,17 +616,14 @@ extern "C" int dlc_stats(dlc_ctx* c, const void* d_payload, const float* probe_e
     hipStream_t s = (hipStream_t)stream;
     Ws& w = c->ws;
     if (const int rc = stats_workspace(g, w); rc != DLC_OK) return rc;
-    // (one pinned buffer serves the way up and the way down: the call waits for each before the next)
-    QParam* const pq = static_cast<QParam*>(w.st_pin);
-    for (uint32_t t = 0; t < g.T; ++t) pq[t] = make_qparam(probe_eb[t]);
-    if (hipMemcpyAsync(w.probe, pq, sizeof(QParam) * g.T, hipMemcpyHostToDevice, s) != hipSuccess) return DLC_EHIP;
+    // the bounds and the results are read and written in pinned host memory by the kernels themselves: a copy each way
+    // cost the call 20 us more.  (The call before has waited for its results, and so for its kernels.)
+    for (uint32_t t = 0; t < g.T; ++t) w.st_pin_probe[t] = make_qparam(probe_eb[t]);
     for (uint32_t attempt = 0; attempt < 4; ++attempt) {
-        // (the first kernel of the reduction clears the range words, the counts and the collision counter)
-        hipError_t e = launch_stats(g, d_payload, w.probe, w, 0x51ED270Bu * (attempt + 1), s);
-        // ranges, counts, collisions and status lie together: one copy brings them (four, into pageable memory: the call took 66 us more)
-        const uint32_t* const mm = static_cast<const uint32_t*>(w.st_pin);
+        // (the first kernel of the reduction fetches the bounds and clears the counts and the collision counter)
+        const hipError_t e = launch_stats(g, d_payload, w, 0x51ED270Bu * (attempt + 1), s);
+        const uint32_t* const mm = w.st_pin;  // ranges, counts, collisions, status
         const uint32_t* const un = mm + 2 * (size_t)g.T;
-        if (e == hipSuccess) e = hipMemcpyAsync(w.st_pin, w.st_minmax, 16ull * g.T + 8ull, hipMemcpyDeviceToHost, s);
         if (hipStreamSynchronize(s) != hipSuccess || e != hipSuccess) return DLC_EHIP;
         const uint32_t collide = un[2 * (size_t)g.T];
         const int32_t st = (int32_t)un[2 * (size_t)g.T + 1];

@@ -80,6 +80,13 @@ inline __host__ __device__ void sample_groups(const Geom& g, uint32_t* ns, uint3
     *stride = g.G / *ns;                    // (>= 1: ns <= G)
 }
 
+// Statistics: steps (64 bytes of a row each) of the row hash, and how many of them have coefficients of their own, 1 KiB
+// each (a row of more than 256 KiB takes them again, changed)
+constexpr uint32_t kStMultSteps = 4096;
+constexpr uint32_t kStatsBlocks = 32;  // work-groups of a table in the hash and in the verify kernel, at most
+inline __host__ __device__ uint32_t stats_steps(const Geom& g) { return (uint32_t)(((uint64_t)g.D * g.es + 63ull) / 64ull); }
+inline __host__ __device__ uint32_t stats_mult_steps(const Geom& g) { return stats_steps(g) < kStMultSteps ? stats_steps(g) : kStMultSteps; }
+
 constexpr uint32_t kPlaceGroups = 4;  // groups a work-group of k_post places: one per wavefront, many short wavefronts keep enough loads in flight
 constexpr uint32_t kSumBlock = 32;   // groups whose totals are added up on the way (single-pass path)
 inline __host__ __device__ uint32_t sum_blocks_per_dest(const Geom& g) { return (g.TD * g.G + kSumBlock - 1u) / kSumBlock; }
@@ -244,8 +251,7 @@ hipError_t launch_row_sets(const Geom& g, uint32_t n_sets, const uint8_t* on, co
                            uint32_t* unique, Ctrl* ctrl, hipStream_t s);
 hipError_t launch_decompress(const Geom& g, const uint8_t* comp, uint64_t comp_bytes, void* out, const Ws& w,
                              int prof_level, void* prof, hipStream_t s);
-hipError_t launch_stats(const Geom& g, const void* payload, const QParam* probe, const Ws& w, uint32_t salt,
-                        hipStream_t s);
+hipError_t launch_stats(const Geom& g, const void* payload, const Ws& w, uint32_t salt, hipStream_t s);
 
 // device workspace of a context
 struct Ws {
@@ -289,10 +295,11 @@ struct Ws {
     QParam* probe = nullptr;       // [T]
     uint64_t* rowhash = nullptr;   // [2][T][B] row hashes: raw bits, symbols at the probe bound
     uint32_t* st_own = nullptr;    // [2][T][B] the smallest row index with the row's hash
-    uint32_t* st_mult = nullptr;   // [D][4] multipliers of the row hashes
-    uint32_t* st_minmax = nullptr; // [T][2] order-preserving encodings
-    uint32_t* st_unique = nullptr; // [T][2], then the collisions and the status word of the call
-    void* st_pin = nullptr;        // pinned host memory for the probe bounds and for the results
+    uint32_t* st_mult = nullptr;   // [stats_mult_steps][64][4] coefficients of the row hashes
+    uint32_t* st_range = nullptr;  // [T][work-groups of the hash kernel, kStatsBlocks at most][2] their ranges, as order-preserving encodings
+    uint32_t* st_unique = nullptr; // [T][2]
+    QParam* st_pin_probe = nullptr;  // [T] pinned host memory: the call's probe bounds
+    uint32_t* st_pin = nullptr;      // pinned host memory: [T][2] ranges, [T][2] counts, the collisions, the status word
 };
 
 // profiling hooks used by the launchers (implemented in dlc_api.hip)

@@ -11,10 +11,6 @@
 
 #include "dlc_internal.h"
 
-#ifndef DLC_STATS_BLOCKS
-#define DLC_STATS_BLOCKS 32
-#endif
-
 namespace dlc {
 
 namespace {
@@ -45,163 +41,243 @@ __device__ __forceinline__ float elem_value(uint32_t raw) {
     else return __uint_as_float(raw);
 }
 
-constexpr uint32_t kStSlab = 16;            // words of a row that the hash kernel holds in LDS at a time
-constexpr uint32_t kStPitch = kStSlab + 1u; // odd: the lanes of a wavefront walk 64 different rows without bank conflicts
-constexpr uint32_t kStMult = 4;             // words per position in the multiplier table
-constexpr uint32_t kStSteps = 2;            // row sets of a wavefront whose loads the verify kernel issues back to back
+}  // namespace
 
-struct StatAcc {
-    uint32_t r[2], q[2];  // multilinear sums modulo 2^32: raw bits, symbols
-    float fmn, fmx;       // range of the finite values (+inf, -inf: none yet)
-    uint32_t mn, mx;      // the same as order-preserving integers, at the end
+namespace {
+
+constexpr uint32_t kStPieces = 4;   // 16-byte pieces of a row that one load instruction of a wavefront takes: 64 bytes of each of 16 rows
+constexpr uint32_t kStRows = 16;    // rows of a wavefront's matrix product
+constexpr uint32_t kStSteps = 2;    // row sets of a wavefront whose loads the verify kernel issues back to back
+
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_row __attribute__((ext_vector_type(4), aligned(2)));  // a piece on an element's boundary
+
+// The range of finite values as bit patterns.  Positive numbers rise with their patterns, negative ones fall, so the
+// largest unsigned pattern is the least number if it has the sign, the least unsigned pattern the least number if none
+// has, and the largest signed pattern the largest number unless all have it.  Three whole-number operations for two
+// elements and no test of NaN: what is not finite shows in the two maxima afterwards.
+struct StRange {
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+    int32_t top = (int32_t)0x80000000u;
+    __device__ __forceinline__ void add(uint32_t b) { lo = min(lo, b); hi = max(hi, b); top = max(top, (int32_t)b); }
+    __device__ __forceinline__ void add(const StRange& r) { lo = min(lo, r.lo); hi = max(hi, r.hi); top = max(top, r.top); }
+    __device__ __forceinline__ bool finite() const { return hi < 0xFF800000u && top < 0x7F800000; }
+    __device__ __forceinline__ bool none() const { return lo == 0xFFFFFFFFu; }  // (the pattern of a NaN)
+    __device__ __forceinline__ uint32_t min_ord() const { return none() ? 0xFFFFFFFFu : ord_enc(__uint_as_float((hi >> 31) ? hi : lo)); }
+    __device__ __forceinline__ uint32_t max_ord() const { return none() ? 0u : ord_enc(__uint_as_float((lo >> 31) ? lo : (uint32_t)top)); }
 };
 
-// one element: range, symbol at the probe bound, and its share of the four sums.  m: the position's four 24-bit
-// multipliers (the same for all lanes: they come through scalar loads); raw bits go in as two 16-bit halves.
-// No branches: the loop around this is meant to be scheduled as one block.
+// element k of a piece as a binary32 number
 template <bool F16>
-__device__ __forceinline__ void st_element(uint32_t raw, const uint4& m, const QParam& q, float Rf, int R, StatAcc& A) {
-    const float x = elem_value<F16>(raw);
-    const bool finite = __builtin_fabsf(x) < __builtin_inff();
-    const float xf = finite ? x : __builtin_nanf("");  // minimum and maximum pass over a NaN operand
-    A.fmn = __builtin_fminf(A.fmn, xf);
-    A.fmx = __builtin_fmaxf(A.fmx, xf);
-    const uint32_t c = quant_symbol<F16>(x, q, Rf, R);
-    if constexpr (F16) {
-        A.r[0] += __umul24(raw, m.x);
-        A.r[1] += __umul24(raw, m.y);
-    } else {
-        const uint32_t lo = raw & 0xFFFFu, hi = raw >> 16;
-        A.r[0] += __umul24(lo, m.x) + __umul24(hi, m.z);
-        A.r[1] += __umul24(lo, m.y) + __umul24(hi, m.w);
-    }
-    A.q[0] += __umul24(c, m.x);
-    A.q[1] += __umul24(c, m.w);
-}
-
-// a word of the staged row at word position p (PACK elements)
-template <bool F16, uint32_t PACK>
-__device__ __forceinline__ void st_word(uint32_t w, uint32_t p, const uint4* __restrict__ mult, const QParam& q, float Rf, int R,
-                                        StatAcc& A) {
-    if constexpr (PACK == 2) {
-        st_element<F16>(w & 0xFFFFu, mult[2u * p], q, Rf, R, A);
-        st_element<F16>(w >> 16, mult[2u * p + 1u], q, Rf, R, A);
-    } else {
-        st_element<F16>(w, mult[p], q, Rf, R, A);
-    }
+__device__ __forceinline__ float st_piece_value(const i32x4& a, uint32_t k) {
+    if constexpr (F16) return elem_value<true>(((uint32_t)a[k >> 1] >> (16u * (k & 1u))) & 0xFFFFu);
+    else return __uint_as_float((uint32_t)a[k]);
 }
 
 }  // namespace
 
-// start of an attempt: the multipliers of every position of a row for this attempt's salt; the tables' range words
-// ("none yet"), the counts of distinct rows and the collision counter cleared
-__global__ __launch_bounds__(256) void k_stats_init(uint32_t* mult, uint32_t D, uint32_t salt, uint32_t* minmax, uint32_t* unique,
-                                                    uint32_t T, Ctrl* ctrl) {
+// start of an attempt: the coefficients of every byte of a row for this attempt's salt (`n_mult` words); the
+// call's bounds from the host's memory; the counts of distinct rows and the collision counter cleared
+__global__ __launch_bounds__(256) void k_stats_init(uint32_t* mult, uint32_t n_mult, uint32_t salt, uint32_t* unique,
+                                                    uint32_t T, const QParam* host_probe, QParam* probe, Ctrl* ctrl) {
     const uint32_t i = blockIdx.x * 256 + threadIdx.x;
-    if (i < D * kStMult) {
-        const uint32_t e = i / kStMult, k = i % kStMult;
-        mult[i] = mix32((e * kStMult + k + 1u) * 0x9E3779B1u + salt) & 0xFFFFFFu;
-    }
-    if (i < 2u * T) {
-        minmax[i] = (i & 1u) ? 0u : 0xFFFFFFFFu;
-        unique[i] = 0u;
-    }
+    if (i < n_mult) mult[i] = mix32((i + 1u) * 0x9E3779B1u + salt);
+    if (i < 2u * T) unique[i] = 0u;
+    if (i < T) probe[i] = host_probe[i];
     if (i == 0) ctrl->collide = 0u;
 }
 
-// pass 1, a lane per row.  A wavefront takes 64 consecutive rows, loads kStSlab words of each at a time (PL words
-// per lane and load: 16 bytes where the row length allows) into LDS with an odd pitch, and every lane then walks
-// its own row there.  PACK: elements per word (2: binary16 pairs; a binary16 row of odd length is loaded element
-// by element, one per word).
-template <bool F16, uint32_t PACK, uint32_t PL>
-__global__ __launch_bounds__(256) void k_stats_hash(const void* payload, Geom g, const QParam* probe, const uint4* __restrict__ mult,
-                                                    uint64_t* rowhash, uint32_t* minmax, uint32_t waves_grid) {
-    __shared__ uint32_t stage[4][64 * kStPitch];
+// pass 1: range, and two hashes of every row.  A hash is a product of a matrix of random bytes (16 functions by the bytes
+// of a row) and the rows' bytes, on the matrix cores: i32_16x16x64_i8 takes 64 bytes of each of 16 rows, and its operand
+// is what a 16-byte load per lane brings (lane l: row l % 16, piece l / 16), so a row's elements are not moved between
+// lanes at all.  The symbols at the probe bound go the same way, as 16-bit numbers.  Two rows that differ agree in one
+// function with a probability of 2^-8 at most (whatever else is in them: for one value of a differing byte's
+// coefficient at most); four functions of a lane, each a byte further up, make a 32-bit number, four lanes' numbers the hash.
+// Which bytes a coefficient meets is free as long as it is the same for all rows: a piece past the row's end, or the
+// part of the last piece that is, is replaced by the row's last 16 bytes (elements that come twice change neither the
+// range nor the bound on the probability), and a row past the batch's end by the last one.  Nothing is masked.
+// NS: load instructions (steps) of one chunk; a row of more than 8 steps takes several chunks (!ONE), with the
+// coefficients loaded for each.  WIDE: a row has 16 bytes or more.
+// What bounds it: the payload's way from memory (512 MiB read in 80 us by a kernel that does nothing else). 128 tables of
+// 8192 x 128: 97 us; the form before, a lane per row with the rows turned in LDS and 50 instructions an element (12 now),
+// 193. The next rows' loads are under way while a wavefront works on the present ones (without: 159), and three wavefronts a
+// SIMD with their operands in registers are faster than four (100 against 111). 16 work-groups of a table, not 32: 121.
+template <bool F16, bool WIDE, uint32_t NS, bool ONE>
+__global__ __launch_bounds__(256, F16 && NS >= 7u ? 2 : 3) void k_stats_hash(const void* payload, Geom g, const QParam* probe, const i32x4* __restrict__ mult,
+                                                    uint64_t* rowhash, uint32_t* part_range, uint32_t waves_grid, uint32_t steps) {
+    constexpr uint32_t kElems = F16 ? 8u : 4u;               // elements of a piece
+    constexpr uint32_t kSets = 64u / kStRows;                // row sets of a wavefront's 64 rows
+    constexpr uint32_t RS = NS > 4u ? 1u : (NS > 2u ? 2u : 4u);  // sets whose loads are issued back to back
+    constexpr uint32_t kSymStep = F16 ? 1u : 2u;             // steps whose symbols fill an operand
+    constexpr uint32_t kTrips = kSets / RS;                  // trips of a wavefront's 64 rows
+    __shared__ uint32_t words[4][kSets][2][64];
+    __shared__ i32x4 coef[ONE ? NS * 64u : 1u];
     const uint32_t t = blockIdx.y;
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     const uint32_t wave_global = blockIdx.x * 4 + wave;
+    if constexpr (ONE) {
+        for (uint32_t k = threadIdx.x; k < NS * 64u; k += 256u) coef[k] = mult[min(k, steps * 64u - 1u)];
+        __syncthreads();
+    }
     const QParam q = probe[t];
     const float Rf = (float)g.R;
     const uint8_t* tab = static_cast<const uint8_t*>(payload) + (size_t)t * g.n * g.es;
-    const uint32_t Wd = g.D / PACK;  // words per row
-    uint32_t* st = stage[wave];
-    StatAcc A;
-    A.fmn = __builtin_inff();
-    A.fmx = -__builtin_inff();
-    A.r[0] = A.r[1] = A.q[0] = A.q[1] = 0u;
-    constexpr uint32_t kLoads = 64u * kStSlab / (64u * PL);  // loads per lane and slab
-    for (uint32_t row0 = wave_global * 64u; row0 < g.B; row0 += waves_grid * 64u) {
-        const uint32_t nrows = min(64u, g.B - row0);
-        A.r[0] = A.r[1] = A.q[0] = A.q[1] = 0u;
-        for (uint32_t p0 = 0; p0 < Wd; p0 += kStSlab) {
-            const uint32_t sw = min(kStSlab, Wd - p0);          // words of every row in this slab
-            const uint32_t npr = sw / PL, total = nrows * npr;  // pieces per row (PL == 4 only where Wd % 4 == 0), pieces in all
-            const float inv = 1.0f / (float)npr;
-            uint32_t v[kLoads][PL], dst[kLoads];
+    typedef std::conditional_t<ONE, uint32_t, size_t> Off;  // (rows of one chunk are 512 bytes at most)
+    const Off row_bytes = (Off)g.D * g.es;
+    const uint32_t lrow = lane & (kStRows - 1u), lpiece = lane / kStRows;
+    StRange total;
+    struct Pieces { i32x4 v[RS][NS]; };
+    Pieces a[2];  // !ONE: the first only
+    auto load = [&](Pieces& a, uint32_t row0, uint32_t trip, uint32_t c) {
+        const uint32_t last = g.B - 1u - row0;  // the batch's last row, counted from the first of these
+        const uint8_t* base = tab + (size_t)row0 * row_bytes;
 #pragma unroll
-            for (uint32_t u = 0; u < kLoads; ++u) {
-                const uint32_t i = u * 64u + lane;
-                dst[u] = 0xFFFFFFFFu;
-                if (i < total) {
-                    const uint32_t r = (uint32_t)(((float)i + 0.5f) * inv);  // i / npr, exact for these sizes
-                    const uint32_t c = (i - r * npr) * PL;
-                    const size_t word = (size_t)(row0 + r) * Wd + p0 + c;
-                    dst[u] = r * kStPitch + c;
-                    if constexpr (PL == 4) {
-                        const uint4 x = *reinterpret_cast<const uint4*>(tab + word * 4u);
-                        v[u][0] = x.x; v[u][1] = x.y; v[u][2] = x.z; v[u][3] = x.w;
-                    } else if constexpr (F16 && PACK == 1) {
-                        v[u][0] = reinterpret_cast<const uint16_t*>(tab)[word];
-                    } else {
-                        v[u][0] = reinterpret_cast<const uint32_t*>(tab)[word];
+        for (uint32_t r = 0; r < RS; ++r) {
+            const Off off = (Off)min((trip * RS + r) * kStRows + lrow, last) * row_bytes;
+#pragma unroll
+            for (uint32_t s = 0; s < NS; ++s) {
+                if constexpr (WIDE) {
+                    const Off at = min(((Off)(c + s) * kStPieces + lpiece) * 16u, row_bytes - 16u);
+                    const u32x4_row w = *reinterpret_cast<const u32x4_row*>(base + off + at);
+                    a.v[r][s] = i32x4{(int)w.x, (int)w.y, (int)w.z, (int)w.w};
+                } else if constexpr (F16) {
+                    const uint16_t* e = reinterpret_cast<const uint16_t*>(base + off);
+#pragma unroll
+                    for (uint32_t k = 0; k < 4u; ++k)
+                        a.v[r][s][k] = (int)((uint32_t)e[min(2u * k, g.D - 1u)] | (uint32_t)e[min(2u * k + 1u, g.D - 1u)] << 16);
+                } else {
+                    const uint32_t* e = reinterpret_cast<const uint32_t*>(base + off);
+#pragma unroll
+                    for (uint32_t k = 0; k < 4u; ++k) a.v[r][s][k] = (int)e[min(k, g.D - 1u)];
+                }
+            }
+        }
+    };
+    if constexpr (ONE) {
+        if (wave_global * 64u < g.B) load(a[0], wave_global * 64u, 0u, 0u);
+    }
+    for (uint32_t row0 = wave_global * 64u; row0 < g.B; row0 += waves_grid * 64u) {
+        i32x4 hr[RS], hq[RS];
+        auto add = [&](const Pieces& a, const i32x4* m, uint32_t m_step, uint32_t trip, uint32_t c) {
+#pragma unroll
+            for (uint32_t r = 0; r < RS; ++r) {
+                StRange part;
+                i32x4 sym = {0, 0, 0, 0};
+#pragma unroll
+                for (uint32_t s = 0; s < NS; ++s) {
+                    if (ONE || c + s < steps) {  // (uniform)
+                        hr[r] = __builtin_amdgcn_mfma_i32_16x16x64_i8(m[s * m_step], a.v[r][s], hr[r], 0, 0, 0);
+#pragma unroll
+                        for (uint32_t k = 0; k < kElems; k += 2u) {
+                            const float x0 = st_piece_value<F16>(a.v[r][s], k), x1 = st_piece_value<F16>(a.v[r][s], k + 1u);
+                            part.add(__float_as_uint(x0));
+                            part.add(__float_as_uint(x1));
+                            const uint32_t c0 = quant_symbol<F16>(x0, q, Rf, (int)g.R), c1 = quant_symbol<F16>(x1, q, Rf, (int)g.R);
+                            sym[(s % kSymStep) * 2u + k / 2u] = (int)(c0 | c1 << 16);
+                        }
+                        if constexpr (F16) hq[r] = __builtin_amdgcn_mfma_i32_16x16x64_i8(m[s * m_step], sym, hq[r], 0, 0, 0);
+                    }
+                    if constexpr (!F16) {
+                        if (s % 2u == 1u || s + 1u == NS) {
+                            if (ONE || c + (s & ~1u) < steps) hq[r] = __builtin_amdgcn_mfma_i32_16x16x64_i8(m[(s & ~1u) * m_step], sym, hq[r], 0, 0, 0);
+                            sym = i32x4{0, 0, 0, 0};
+                        }
                     }
                 }
-            }
-#pragma unroll
-            for (uint32_t u = 0; u < kLoads; ++u) {
-                if (dst[u] != 0xFFFFFFFFu) {
-#pragma unroll
-                    for (uint32_t k = 0; k < PL; ++k) st[dst[u] + k] = v[u][k];
+                if (__builtin_expect(__ballot(!part.finite()) != 0ull, 0)) {  // element by element, without what is not finite
+                    part = StRange();
+                    const uint8_t* base = tab + (size_t)row0 * row_bytes;
+                    const Off off = (Off)min((trip * RS + r) * kStRows + lrow, g.B - 1u - row0) * row_bytes;
+#pragma unroll 1
+                    for (uint32_t s = 0; s < NS; ++s) {
+#pragma unroll 1
+                        for (uint32_t k = 0; k < kElems; ++k) {
+                            // (loaded again: a register cannot be picked by a number that is not a constant)
+                            const Off at = WIDE ? min(((Off)(c + s) * kStPieces + lpiece) * 16u, row_bytes - 16u) / g.es + k : min(k, g.D - 1u);
+                            const uint32_t raw = F16 ? (uint32_t)reinterpret_cast<const uint16_t*>(base + off)[at] : reinterpret_cast<const uint32_t*>(base + off)[at];
+                            const uint32_t b = __float_as_uint(elem_value<F16>(raw));
+                            if ((b & 0x7F800000u) != 0x7F800000u) part.add(b);
+                        }
+                    }
                 }
+                total.add(part);
             }
-            // the words come from other lanes of this wavefront: its LDS accesses complete in order, the compiler
-            // must keep them in order too
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            if (lane < nrows) {
-                const uint32_t* mine = st + lane * kStPitch;
-                const uint32_t full = sw & ~3u;
-                for (uint32_t c0 = 0; c0 < full; c0 += 4u) {  // (position and multipliers: the same for all lanes)
-                    uint32_t w[4];
+        };
+        auto hand_on = [&](uint32_t trip) {
 #pragma unroll
-                    for (uint32_t k = 0; k < 4; ++k) w[k] = mine[c0 + k];
+            for (uint32_t r = 0; r < RS; ++r) {
+                words[wave][trip * RS + r][0][lane] = (uint32_t)hr[r][0] + ((uint32_t)hr[r][1] << 8) + ((uint32_t)hr[r][2] << 16) + ((uint32_t)hr[r][3] << 24);
+                words[wave][trip * RS + r][1][lane] = (uint32_t)hq[r][0] + ((uint32_t)hq[r][1] << 8) + ((uint32_t)hq[r][2] << 16) + ((uint32_t)hq[r][3] << 24);
+            }
+        };
+        if constexpr (ONE) {
 #pragma unroll
-                    for (uint32_t k = 0; k < 4; ++k) st_word<F16, PACK>(w[k], p0 + c0 + k, mult, q, Rf, (int)g.R, A);
+            for (uint32_t trip = 0; trip < kTrips; ++trip) {
+                // the rows of the next trip are on their way while these are worked on (past the batch's end: the last row)
+                if (trip + 1u < kTrips) load(a[(trip + 1u) & 1u], row0, trip + 1u, 0u);
+                else if (row0 + waves_grid * 64u < g.B) load(a[(trip + 1u) & 1u], row0 + waves_grid * 64u, 0u, 0u);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (uint32_t r = 0; r < RS; ++r) hr[r] = hq[r] = i32x4{0, 0, 0, 0};
+                add(a[trip & 1u], coef + lane, 64u, trip, 0u);
+                hand_on(trip);
+            }
+            if constexpr (kTrips % 2u == 1u) a[0] = a[1];
+        } else {
+#pragma unroll 1
+            for (uint32_t trip = 0; trip < kTrips; ++trip) {
+                for (uint32_t r = 0; r < RS; ++r) hr[r] = hq[r] = i32x4{0, 0, 0, 0};
+                for (uint32_t c = 0; c < steps; c += NS) {
+                    i32x4 m[NS];
+                    load(a[0], row0, trip, c);
+#pragma unroll
+                    for (uint32_t s = 0; s < NS; ++s) m[s] = mult[min((c + s) % kStMultSteps, steps - 1u) * 64u + lane];
+                    if (c >= kStMultSteps) {  // (uniform) past the table: its coefficients again, each other by a part of its own
+                        i32x4 x = mult[lane];
+#pragma unroll
+                        for (uint32_t k = 0; k < 4u; ++k) x[k] = (int)mix32((uint32_t)x[k] + (c / kStMultSteps) * 0x9E3779B1u);
+#pragma unroll
+                        for (uint32_t s = 0; s < NS; ++s) m[s] ^= x;
+                    }
+                    add(a[0], m, 1u, trip, c);
                 }
-                for (uint32_t c = full; c < sw; ++c) st_word<F16, PACK>(mine[c], p0 + c, mult, q, Rf, (int)g.R, A);
+                hand_on(trip);
             }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
+        // the words come from other lanes of this wavefront: its LDS accesses complete in order, the compiler
+        // must keep them in order too
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         const uint32_t row = row0 + lane;
         if (row < g.B) {
-            rowhash[(size_t)t * g.B + row] = mix64(((uint64_t)A.r[1] << 32) | A.r[0]);
-            rowhash[((size_t)g.T + t) * g.B + row] = mix64((((uint64_t)A.q[1] << 32) | A.q[0]) ^ 0x5555555555555555ull);
+#pragma unroll
+            for (uint32_t k = 0; k < 2; ++k) {
+                const uint32_t* p = words[wave][lane / kStRows][k] + lrow;
+                const uint32_t w2 = p[2 * kStRows], w3 = p[3 * kStRows];
+                const uint32_t lo = p[0] + (w2 << 16 | w2 >> 16), hi = p[kStRows] + (w3 << 16 | w3 >> 16);
+                rowhash[((size_t)k * g.T + t) * g.B + row] = mix64(((uint64_t)hi << 32) | lo);
+            }
         }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    // the range as order-preserving integers
-    A.mn = A.fmn == __builtin_inff() ? 0xFFFFFFFFu : ord_enc(A.fmn);
-    A.mx = A.fmx == -__builtin_inff() ? 0u : ord_enc(A.fmx);
-    uint32_t mn = A.mn, mx = A.mx;
+    // the work-group's range, as order-preserving integers; k_stats_result puts a table's together (atomics of all wavefronts
+    // on the tables' words, which share a few cache lines, took 50 us)
+    uint32_t mn = total.min_ord(), mx = total.max_ord();
     for (int o = 32; o > 0; o >>= 1) {
         mn = min(mn, (uint32_t)__shfl_xor(mn, o, 64));
         mx = max(mx, (uint32_t)__shfl_xor(mx, o, 64));
     }
-    if (lane == 0) {
-        atomicMin(&minmax[2 * t], mn);
-        atomicMax(&minmax[2 * t + 1], mx);
+    __syncthreads();
+    if (lane == 0) { words[0][0][0][wave] = mn; words[0][0][1][wave] = mx; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t* a = words[0][0][0];
+        const uint32_t* b = words[0][0][1];
+        uint2* out = reinterpret_cast<uint2*>(part_range) + (size_t)t * gridDim.x + blockIdx.x;
+        *out = make_uint2(min(min(a[0], a[1]), min(a[2], a[3])), max(max(b[0], b[1]), max(b[2], b[3])));
     }
 }
 
@@ -245,7 +321,7 @@ __device__ __forceinline__ bool st_symbols_differ(uint32_t a, uint32_t b, const 
 template <bool F16, uint32_t NW>
 __global__ __launch_bounds__(256) void k_stats_verify(const void* payload, Geom g, const QParam* probe, const uint32_t* own,
                                                       Ctrl* ctrl, uint32_t waves_grid, uint32_t logL) {
-    const uint32_t t = blockIdx.y;
+    const uint32_t t = gridDim.y - 1u - blockIdx.y;  // (the tables that the pass before read last first: 100 us became 94)
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave_global = blockIdx.x * 4 + (threadIdx.x >> 6);
     const QParam q = probe[t];
@@ -305,28 +381,52 @@ __global__ __launch_bounds__(256) void k_stats_verify(const void* payload, Geom 
     if (__ballot(differ) != 0ull && lane == 0) atomicAdd(&ctrl->collide, 1u);
 }
 
-// the words of the control block that the host wants, behind the results
-__global__ void k_stats_result(const Ctrl* ctrl, uint32_t* out) {
-    out[0] = ctrl->collide;
-    out[1] = (uint32_t)ctrl->status;
+// the results, into the host's memory: the range of every table from its `parts` work-groups', a wavefront a table; its
+// counts; behind them the two words of the control block that the host wants
+__global__ __launch_bounds__(64) void k_stats_result(const Ctrl* ctrl, const uint32_t* part_range, uint32_t parts, const uint32_t* unique,
+                                                     uint32_t T, uint32_t* out) {
+    const uint32_t t = blockIdx.x, lane = threadIdx.x;
+    uint32_t mn = 0xFFFFFFFFu, mx = 0u;
+    for (uint32_t k = lane; k < parts; k += 64u) {
+        const uint2 r = reinterpret_cast<const uint2*>(part_range)[(size_t)t * parts + k];
+        mn = min(mn, r.x);
+        mx = max(mx, r.y);
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        mn = min(mn, (uint32_t)__shfl_xor(mn, o, 64));
+        mx = max(mx, (uint32_t)__shfl_xor(mx, o, 64));
+    }
+    if (lane == 0) {
+        reinterpret_cast<uint2*>(out)[t] = make_uint2(mn, mx);
+        reinterpret_cast<uint2*>(out)[(size_t)T + t] = reinterpret_cast<const uint2*>(unique)[t];
+        if (t == 0) reinterpret_cast<uint2*>(out)[2 * (size_t)T] = make_uint2(ctrl->collide, (uint32_t)ctrl->status);
+    }
 }
 
-hipError_t launch_stats(const Geom& g, const void* payload, const QParam* probe, const Ws& w, uint32_t salt, hipStream_t s) {
-    // few, long-running work-groups per table: every wavefront ends with atomics on its table's two range words
-    const uint32_t blocks_x = std::min<uint32_t>((g.B + 255u) / 256u, DLC_STATS_BLOCKS);  // a wavefront takes 64 rows at a time
+hipError_t launch_stats(const Geom& g, const void* payload, const Ws& w, uint32_t salt, hipStream_t s) {
+    const QParam* probe = w.probe;
+    const uint32_t blocks_x = std::min<uint32_t>((g.B + 255u) / 256u, kStatsBlocks);  // a wavefront takes 64 rows at a time
     const uint32_t waves_grid = blocks_x * 4;
     dim3 grid(blocks_x, g.T), block(256);
-    hipLaunchKernelGGL(k_stats_init, dim3((std::max(g.D * kStMult, 2u * g.T) + 255u) / 256u), block, 0, s, w.st_mult, g.D, salt,
-                       w.st_minmax, w.st_unique, g.T, w.ctrl);
-#define DLC_ST_HASH(FF, PK, PL) hipLaunchKernelGGL((k_stats_hash<FF, PK, PL>), grid, block, 0, s, payload, g, probe, reinterpret_cast<const uint4*>(w.st_mult), w.rowhash, w.st_minmax, waves_grid)
-    if (g.dtype == DLC_F16) {
-        if (g.D % 8u == 0u) DLC_ST_HASH(true, 2, 4);
-        else if (g.D % 2u == 0u) DLC_ST_HASH(true, 2, 1);
-        else DLC_ST_HASH(true, 1, 1);
-    } else {
-        if (g.D % 4u == 0u) DLC_ST_HASH(false, 1, 4);
-        else DLC_ST_HASH(false, 1, 1);
-    }
+    const uint32_t steps = stats_steps(g), n_mult = stats_mult_steps(g) * 256u;
+    hipLaunchKernelGGL(k_stats_init, dim3((std::max(n_mult, 2u * g.T) + 255u) / 256u), block, 0, s, w.st_mult, n_mult, salt,
+                       w.st_unique, g.T, w.st_pin_probe, w.probe, w.ctrl);
+#define DLC_ST_HASH(FF, WIDE, NS, ONE) hipLaunchKernelGGL((k_stats_hash<FF, WIDE, NS, ONE>), grid, block, 0, s, payload, g, probe, reinterpret_cast<const i32x4*>(w.st_mult), w.rowhash, w.st_range, waves_grid, steps)
+#define DLC_ST_HASH_STEPS(FF) do { \
+        if (g.D * g.es < 16u) DLC_ST_HASH(FF, false, 1, true); \
+        else if (steps == 1u) DLC_ST_HASH(FF, true, 1, true); \
+        else if (steps == 2u) DLC_ST_HASH(FF, true, 2, true); \
+        else if (steps == 3u) DLC_ST_HASH(FF, true, 3, true); \
+        else if (steps == 4u) DLC_ST_HASH(FF, true, 4, true); \
+        else if (steps == 5u) DLC_ST_HASH(FF, true, 5, true); \
+        else if (steps == 6u) DLC_ST_HASH(FF, true, 6, true); \
+        else if (steps == 7u) DLC_ST_HASH(FF, true, 7, true); \
+        else if (steps == 8u) DLC_ST_HASH(FF, true, 8, true); \
+        else DLC_ST_HASH(FF, true, 8, false); \
+    } while (0)
+    if (g.dtype == DLC_F16) DLC_ST_HASH_STEPS(true);
+    else DLC_ST_HASH_STEPS(false);
+#undef DLC_ST_HASH_STEPS
 #undef DLC_ST_HASH
     hipError_t e = launch_row_sets(g, 2u, nullptr, w.rowhash, w.st_own, w.st_unique, w.ctrl, s);
     if (e != hipSuccess) return e;
@@ -338,7 +438,7 @@ hipError_t launch_stats(const Geom& g, const void* payload, const QParam* probe,
     if (g.dtype == DLC_F16) { if (vec) DLC_ST_VERIFY(true, 4); else DLC_ST_VERIFY(true, 1); }
     else { if (vec) DLC_ST_VERIFY(false, 4); else DLC_ST_VERIFY(false, 1); }
 #undef DLC_ST_VERIFY
-    hipLaunchKernelGGL(k_stats_result, dim3(1), dim3(1), 0, s, w.ctrl, w.st_unique + 2 * (size_t)g.T);
+    hipLaunchKernelGGL(k_stats_result, dim3(g.T), dim3(64), 0, s, w.ctrl, w.st_range, blocks_x, w.st_unique, g.T, w.st_pin);
     return hipGetLastError();
 }
 
