@@ -179,50 +179,91 @@ __global__ __launch_bounds__(256) void k_rm_hash(const void* payload, Geom g, co
 }
 
 // the sets: work-group (part, t, set) takes the rows of table t whose hashes' top bits say `part`, puts them into an
-// open-addressing set in LDS (a slot holds a row index; the hash of the row that sits there is read from memory,
-// and only rows with that hash ever replace it, the smaller index winning), and then looks every one of its rows
-// up again: own[row] = the smallest row index with the row's hash.  n_slots (a power of two) is the batch size or
-// more whenever that fits the LDS, so the set cannot fill up; for larger batches a work-group's share of the rows
-// is half the slots or less, and where a set does fill up all the same (hashes that crowd into one share), the rows that
-// found no slot are their own owners (coded rows, for row matching), and ctrl, if given, gets an error (the
-// statistics want exact counts).  rowhash and own: [sets][T][B]; on (optional): tables to skip; unique (optional):
-// [T][sets] counts of the rows that own their hash.
+// open-addressing set in LDS, where the smallest row index of a hash stays, and then looks every one of its rows up again:
+// own[row] = the smallest row index with the row's hash.
+// TAG (batches of kRmTagRows at most): a slot holds the hash's upper 48 bits and the row's index, so that neither way
+// leaves the LDS and the smaller index wins by a minimum of whole slots; the place in the set comes from the lower bits, so
+// rows whose hashes differ meet in one slot only if 48 bits agree and the others lead to neighbouring places (2^-58 for a
+// pair; those who use the owners compare the rows, and treat such a pair as one whose hashes agree).  Otherwise a slot holds
+// an index alone, and the hash of the row that sits there is read from memory.  128 tables of 8192 rows, two sets:
+// 25 us, 45 before (a dependent read of memory for every row on each way); one set of 64 tables 14, before 32.  Of that the
+// strides of every hash's own made 3 (with the next place for all, the longest of 64 lanes' searches is what counts).
+// A table's work-groups differ in y alone: they read the same hashes, and for multiples of eight tables through the same L2.
+// n_slots (a power of two) is the batch size or more whenever that fits the LDS, so the set cannot fill up; for larger
+// batches a work-group's share of the rows is half the slots or less, and where a set does fill up all the same (hashes that
+// crowd into one share), the rows that found no slot are their own owners (coded rows, for row matching), and ctrl, if given,
+// gets an error (the statistics want exact counts).  rowhash and own: [sets][T][B]; on (optional): tables to skip; unique
+// (optional): [T][sets] counts of the rows that own their hash.
+constexpr uint32_t kRmTagRows = 65536;
+template <bool TAG>
 __global__ __launch_bounds__(1024) void k_rm_sets(Geom g, const uint8_t* on, const uint64_t* rowhash, uint32_t* own,
                                                   uint32_t n_slots, uint32_t parts, uint32_t* unique, Ctrl* ctrl) {
-    extern __shared__ __align__(16) uint32_t slot[];
+    typedef std::conditional_t<TAG, unsigned long long, uint32_t> Slot;
+    extern __shared__ __align__(16) uint32_t slot_words[];
     __shared__ uint32_t s_owners;
-    const uint32_t part = blockIdx.x, t = blockIdx.y, set = blockIdx.z, tid = threadIdx.x;
+    const uint32_t part = blockIdx.y, t = blockIdx.x, set = blockIdx.z, tid = threadIdx.x;
     if (on && !on[t]) return;  // uniform
-    constexpr uint32_t kEmpty = 0xFFFFFFFFu;
+    constexpr Slot kEmpty = (Slot)~0ull;  // (as a row's slot: the batch's last possible row, which no later row looks for)
     constexpr uint32_t kBatch = 4;  // hashes a thread loads back to back
-    for (uint32_t k = tid; k < n_slots; k += 1024) slot[k] = kEmpty;
-    if (tid == 0) s_owners = 0u;
-    __syncthreads();
+    constexpr uint64_t kTag = ~(uint64_t)(kRmTagRows - 1u);
     const uint64_t* rh = rowhash + ((size_t)set * g.T + t) * g.B;
     uint32_t* own_t = own + ((size_t)set * g.T + t) * g.B;
-    volatile uint32_t* vslot = slot;
-    for (uint32_t r0 = tid; r0 < g.B; r0 += 1024u * kBatch) {
-        uint64_t h[kBatch];
+    uint64_t h[kBatch];
+    auto load = [&](uint32_t r0) {
 #pragma unroll
         for (uint32_t k = 0; k < kBatch; ++k) h[k] = r0 + k * 1024u < g.B ? rh[r0 + k * 1024u] : 0ull;
+    };
+    load(tid);
+    Slot* slot = reinterpret_cast<Slot*>(slot_words);
+    volatile Slot* vslot = slot;
+    for (uint32_t k = tid; k < n_slots * (uint32_t)sizeof(Slot) / 16u; k += 1024)
+        reinterpret_cast<uint4*>(slot_words)[k] = make_uint4(~0u, ~0u, ~0u, ~0u);
+    if (tid == 0) s_owners = 0u;
+    __syncthreads();
+    auto mine = [&](uint32_t row, uint64_t hash) { return row < g.B && ((uint32_t)(hash >> 52) & (parts - 1u)) == part; };
+    auto place = [&](uint64_t hash) { return (uint32_t)(TAG ? hash : hash >> 20) & (n_slots - 1u); };
+    auto stride = [&](uint64_t hash) { return (uint32_t)(hash >> 32) | 1u; };  // (odd: all places in turn)
+    auto same = [&](Slot cur, uint64_t hash) {  // is the row in this slot one with this hash?
+        if constexpr (TAG) return ((cur ^ hash) & kTag) == 0ull;
+        else return rh[cur] == hash;
+    };
+    for (uint32_t r0 = tid; r0 < g.B; r0 += 1024u * kBatch) {
+        if (r0 != tid) load(r0);
+        // the first place of every row: the reads of a batch together, then the exchanges; what is left goes on by itself
+        Slot me[kBatch], cur[kBatch];
+        bool left[kBatch];
 #pragma unroll
         for (uint32_t k = 0; k < kBatch; ++k) {
             const uint32_t row = r0 + k * 1024u;
-            if (row >= g.B || ((uint32_t)(h[k] >> 52) & (parts - 1u)) != part) continue;
-            uint32_t pos = (uint32_t)(h[k] >> 20) & (n_slots - 1u);
+            left[k] = mine(row, h[k]);
+            me[k] = TAG ? (Slot)((h[k] & kTag) | row) : (Slot)row;
+            cur[k] = vslot[place(h[k])];
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < kBatch; ++k) {
+            if (left[k] && cur[k] == kEmpty) {
+                cur[k] = atomicCAS(&slot[place(h[k])], kEmpty, me[k]);
+                left[k] = cur[k] != kEmpty;
+            }
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < kBatch; ++k) {
+            if (!left[k]) continue;
+            uint32_t pos = place(h[k]);
+            Slot c = cur[k];
             bool placed = false;
             for (uint32_t probe_n = 0; probe_n < n_slots; ++probe_n) {
-                uint32_t cur = vslot[pos];
-                if (cur == kEmpty) {
-                    cur = atomicCAS(&slot[pos], kEmpty, row);
-                    if (cur == kEmpty) { placed = true; break; }
+                if (c == kEmpty) {
+                    c = atomicCAS(&slot[pos], kEmpty, me[k]);
+                    if (c == kEmpty) { placed = true; break; }
                 }
-                if (rh[cur] == h[k]) {
-                    atomicMin(&slot[pos], row);
+                if (same(c, h[k])) {
+                    if (me[k] < c) atomicMin(&slot[pos], me[k]);
                     placed = true;
                     break;
                 }
-                pos = (pos + 1u) & (n_slots - 1u);
+                pos = (pos + stride(h[k])) & (n_slots - 1u);
+                c = vslot[pos];
             }
             if (!placed && ctrl) set_status(ctrl, DLC_ESTATE);
         }
@@ -230,27 +271,31 @@ __global__ __launch_bounds__(1024) void k_rm_sets(Geom g, const uint8_t* on, con
     __syncthreads();
     uint32_t owners = 0;
     for (uint32_t r0 = tid; r0 < g.B; r0 += 1024u * kBatch) {
-        uint64_t h[kBatch];
+        if (g.B > 1024u * kBatch) load(r0);  // (else they are still there)
+        Slot cur[kBatch];
 #pragma unroll
-        for (uint32_t k = 0; k < kBatch; ++k) h[k] = r0 + k * 1024u < g.B ? rh[r0 + k * 1024u] : 0ull;
+        for (uint32_t k = 0; k < kBatch; ++k) cur[k] = vslot[place(h[k])];
 #pragma unroll
         for (uint32_t k = 0; k < kBatch; ++k) {
             const uint32_t row = r0 + k * 1024u;
-            if (row >= g.B || ((uint32_t)(h[k] >> 52) & (parts - 1u)) != part) continue;
+            if (!mine(row, h[k])) continue;
             uint32_t o = row;
-            uint32_t pos = (uint32_t)(h[k] >> 20) & (n_slots - 1u);
-            for (uint32_t probe_n = 0; probe_n < n_slots; ++probe_n) {
-                const uint32_t cur = vslot[pos];
-                if (cur == kEmpty) break;
-                if (cur == row || rh[cur] == h[k]) { o = cur; break; }
-                pos = (pos + 1u) & (n_slots - 1u);
+            uint32_t pos = place(h[k]);
+            Slot c = cur[k];
+            for (uint32_t probe_n = 0; probe_n < n_slots && c != kEmpty; ++probe_n) {
+                if (same(c, h[k])) {
+                    o = (uint32_t)c & (TAG ? kRmTagRows - 1u : 0xFFFFFFFFu);
+                    break;
+                }
+                pos = (pos + stride(h[k])) & (n_slots - 1u);
+                c = vslot[pos];
             }
             own_t[row] = o;
             owners += o == row ? 1u : 0u;
         }
     }
     if (unique) {  // uniform
-        for (int o = 32; o > 0; o >>= 1) owners += (uint32_t)__shfl_xor((int)owners, o, 64);
+        owners = wave_sum(owners);
         if ((tid & 63u) == 0u && owners) atomicAdd(&s_owners, owners);
         __syncthreads();
         if (tid == 0 && s_owners) atomicAdd(&unique[(size_t)t * gridDim.z + set], s_owners);
@@ -441,15 +486,20 @@ void row_match_multipliers(uint32_t* mult, uint32_t n_pieces) {
 
 hipError_t launch_row_sets(const Geom& g, uint32_t n_sets, const uint8_t* on, const uint64_t* rowhash, uint32_t* own,
                            uint32_t* unique, Ctrl* ctrl, hipStream_t s) {
-    // slots for the whole batch, 64 KiB at most; about a thousand work-groups in all (32 per table and set at most),
-    // and more where a batch is large: a work-group's share of the rows is half its slots or less (up to 32 M rows)
+    // slots for the whole batch, 16384 at most; a work-group a compute unit (32 per table and set at most: each reads all the
+    // table's hashes; 64 tables of 8192: 14 us, with two work-groups a compute unit 20), and more where a batch is large:
+    // a work-group's share of the rows is half its slots or less (up to 32 M rows)
     uint32_t n_slots = 64;
     while (n_slots < g.B && n_slots < 16384u) n_slots <<= 1;
     uint32_t parts = 1;
-    while (parts < 32u && parts * g.T * n_sets < 1024u) parts <<= 1;
+    while (parts < 32u && parts * g.T * n_sets < 256u) parts <<= 1;
     while (parts < 4096u && (uint64_t)parts * n_slots < 2ull * g.B) parts <<= 1;
-    hipLaunchKernelGGL(k_rm_sets, dim3(parts, g.T, n_sets), dim3(1024), n_slots * 4u, s, g, on, rowhash, own, n_slots, parts,
-                       unique, ctrl);
+    if (g.B <= kRmTagRows)
+        hipLaunchKernelGGL(k_rm_sets<true>, dim3(g.T, parts, n_sets), dim3(1024), n_slots * 8u, s, g, on, rowhash, own, n_slots, parts,
+                           unique, ctrl);
+    else
+        hipLaunchKernelGGL(k_rm_sets<false>, dim3(g.T, parts, n_sets), dim3(1024), n_slots * 4u, s, g, on, rowhash, own, n_slots, parts,
+                           unique, ctrl);
     return hipGetLastError();
 }
 
@@ -477,7 +527,9 @@ hipError_t launch_row_match(const Geom& g, const void* payload, const Ws& w, hip
 }
 
 hipError_t row_match_set_attributes() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(k_rm_sets), hipFuncAttributeMaxDynamicSharedMemorySize, 16384 * 4);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_rm_sets<true>), hipFuncAttributeMaxDynamicSharedMemorySize, 16384 * 8);
+    if (e != hipSuccess) return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(k_rm_sets<false>), hipFuncAttributeMaxDynamicSharedMemorySize, 16384 * 4);
 }
 
 }  // namespace dlc
