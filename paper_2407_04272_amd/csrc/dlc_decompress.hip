@@ -941,8 +941,10 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(Geom g, Fixed
 // A thread per 16-byte (fp32) / 8-byte (fp16) piece of a row, pieces of a row on neighbouring threads.
 template <typename U>
 __global__ __launch_bounds__(256) void k_row_copy(Geom g, const uint8_t* comp, uint64_t comp_bytes, const DecTable* dtab,
-                                                  void* outp) {
-    const uint32_t t = blockIdx.y;
+                                                  void* outp, uint32_t bx) {
+    uint32_t t, block;
+    table_of_group(bx, &t, &block);
+    if (t >= g.T) return;           // uniform
     const uint32_t dst = t / g.TD;  // the container this table is in
     comp += (uint64_t)dst * comp_bytes;
     const DecTable D = dtab[t];
@@ -953,8 +955,8 @@ __global__ __launch_bounds__(256) void k_row_copy(Geom g, const uint8_t* comp, u
     const uint32_t total = g.B * upr;
     // four pieces a thread has in flight: references first, then the rows they point at (named variables, not an
     // array: the compiler moved an array of vectors into LDS)
-    const uint32_t stride = gridDim.x * 256;
-    for (uint32_t i0 = blockIdx.x * 256 + threadIdx.x; i0 < total; i0 += stride * 4u) {
+    const uint32_t stride = bx * 256;
+    for (uint32_t i0 = block * 256 + threadIdx.x; i0 < total; i0 += stride * 4u) {
         uint32_t row[4], o[4];
 #pragma unroll
         for (uint32_t k = 0; k < 4; ++k) {
@@ -1021,8 +1023,8 @@ hipError_t launch_decompress(const Geom& g, const uint8_t* comp, uint64_t comp_b
 #undef DLC_DEC3
         if (g.lz) {
             const uint32_t bx = std::min<uint32_t>((g.B * (g.D / 4u) + 255u) / 256u, 256u);
-            if (f16) hipLaunchKernelGGL(k_row_copy<uint2>, dim3(bx, g.T), dim3(256), 0, s, g, comp, (uint64_t)comp_bytes, w.dtab, out);
-            else hipLaunchKernelGGL(k_row_copy<uint4>, dim3(bx, g.T), dim3(256), 0, s, g, comp, (uint64_t)comp_bytes, w.dtab, out);
+            if (f16) hipLaunchKernelGGL(k_row_copy<uint2>, dim3(table_grid(g.T, bx)), dim3(256), 0, s, g, comp, (uint64_t)comp_bytes, w.dtab, out, bx);
+            else hipLaunchKernelGGL(k_row_copy<uint4>, dim3(table_grid(g.T, bx)), dim3(256), 0, s, g, comp, (uint64_t)comp_bytes, w.dtab, out, bx);
         }
         if (prof_on(pl, P_DECODE)) prof_end(prof, P_DECODE, s);
     }

@@ -193,6 +193,16 @@ __device__ __forceinline__ uint32_t load4(const void* gbase, uint32_t off, uint3
     }
 }
 
+// Kernels whose work-groups read rows of all parts of their table: the table's `bx` work-groups come one after the other on one
+// XCD (work-groups go to the eight XCDs in turn), so that a row that many refer to is fetched into one L2 and not into
+// eight.  The grid is table_grid(T, bx) work-groups; *t >= T: nothing to do.
+__device__ __forceinline__ void table_of_group(uint32_t bx, uint32_t* t, uint32_t* block) {
+    const uint32_t xcd = blockIdx.x & 7u, k = blockIdx.x >> 3;
+    *t = (k / bx) * 8u + xcd;
+    *block = k % bx;
+}
+inline __host__ uint32_t table_grid(uint32_t T, uint32_t bx) { return (T + 7u) / 8u * 8u * bx; }
+
 // inclusive prefix sum over the 64 lanes (all of them active), in registers: four shifts inside the rows of sixteen
 // lanes, then the rows' sums handed on (six dependent instructions; as six LDS permutes it took 700 cycles)
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {

@@ -73,7 +73,7 @@ __device__ __forceinline__ void rm_add_other(uint64_t id, uint32_t e, uint32_t a
     a[2] += rm_mix32(z ^ 0x5BD1E995u);
 }
 
-constexpr uint32_t kRmSteps = 4;  // row sets of a wavefront whose loads are issued back to back
+constexpr uint32_t kRmSteps = 1;  // row sets of a wavefront whose loads are issued back to back (64 tables of 8192 rows: 26 us, with four 34: fewer wavefronts)
 constexpr uint32_t kRmSlab = 32;   // pieces of a row that pass 1 holds in LDS at a time
 constexpr uint32_t kRmPitch = kRmSlab + 1u;
 
@@ -330,9 +330,11 @@ __global__ __launch_bounds__(256) void k_rm_owner(const void* payload, Geom g, c
                                                   const uint32_t* rowown, const uint64_t* rowhash, uint32_t* ref, uint8_t* sym_plane,
                                                   uint32_t* hist, uint32_t waves_grid, uint32_t logL) {
     extern __shared__ __align__(16) uint32_t lh[];  // what to take off the counts: window [kWinBins + 1][kWinCopies] | exact [K]
-    const uint32_t t = blockIdx.y;
+    uint32_t t, block;
+    table_of_group(waves_grid / 4u, &t, &block);
+    if (t >= g.T) return;  // uniform
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
-    const uint32_t wave_global = blockIdx.x * 4 + (tid >> 6);
+    const uint32_t wave_global = block * 4 + (tid >> 6);
     uint32_t* ref_t = ref + (size_t)t * g.B;
     if (!on[t]) {  // uniform: every row is a coded row
         for (uint32_t row = wave_global * 64 + lane; row < g.B; row += waves_grid * 64) ref_t[row] = row;
@@ -519,7 +521,7 @@ hipError_t launch_row_match(const Geom& g, const void* payload, const Ws& w, hip
         hipError_t e = launch_row_sets(g, 1u, w.rm_on, w.rm_hash, w.rm_own, nullptr, nullptr, s);
         if (e != hipSuccess) return e;
     }
-#define DLC_RM_OWNER(FF, PP) hipLaunchKernelGGL((k_rm_owner<FF, PP>), grid, block, sm, s, payload, g, w.qp, w.rm_on, w.rm_own, w.rm_hash, w.rm_ref, w.sym_plane, w.hist, waves_grid, logL)
+#define DLC_RM_OWNER(FF, PP) hipLaunchKernelGGL((k_rm_owner<FF, PP>), dim3(table_grid(g.T, blocks_x)), block, sm, s, payload, g, w.qp, w.rm_on, w.rm_own, w.rm_hash, w.rm_ref, w.sym_plane, w.hist, waves_grid, logL)
     if (g.dtype == DLC_F16) { if (pw == 4u) DLC_RM_OWNER(true, 4); else DLC_RM_OWNER(true, 1); }
     else { if (pw == 4u) DLC_RM_OWNER(false, 4); else DLC_RM_OWNER(false, 1); }
 #undef DLC_RM_OWNER

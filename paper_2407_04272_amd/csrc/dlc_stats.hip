@@ -47,7 +47,7 @@ namespace {
 
 constexpr uint32_t kStPieces = 4;   // 16-byte pieces of a row that one load instruction of a wavefront takes: 64 bytes of each of 16 rows
 constexpr uint32_t kStRows = 16;    // rows of a wavefront's matrix product
-constexpr uint32_t kStSteps = 2;    // row sets of a wavefront whose loads the verify kernel issues back to back
+constexpr uint32_t kStSteps = 4;    // row sets of a wavefront whose loads the verify kernel issues back to back
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_row __attribute__((ext_vector_type(4), aligned(2)));  // a piece on an element's boundary
@@ -317,66 +317,80 @@ __device__ __forceinline__ bool st_symbols_differ(uint32_t a, uint32_t b, const 
 // pass 2: every row that does not own its hash must equal the owner: in its bits for the raw rows, in its symbols for
 // the quantised rows (only the elements whose bits differ need the quantiser).  A row is the work of a team of
 // 2^logL lanes, the smallest power of two that covers the row's pieces (64 at most: longer rows take several
-// trips); a wavefront works on 64 rows per trip, 64 >> logL at a time.  own: [2][T][B], raw then quantised.
+// trips); a wavefront works on 64 rows per trip: those that do not own their hash are put next to one another, 64 >> logL are
+// compared at a time, kStSteps times with the loads issued back to back.  own: [2][T][B], raw then quantised.
+// What bounds it: two rows read for each of them (128 tables of 8192 x 128, of which 55 % repeat: 590 MB, half of it rows
+// that others refer to as well) in 65 us.  With all 64 rows walked, the idle ones under a condition: 94.
 template <bool F16, uint32_t NW>
 __global__ __launch_bounds__(256) void k_stats_verify(const void* payload, Geom g, const QParam* probe, const uint32_t* own,
                                                       Ctrl* ctrl, uint32_t waves_grid, uint32_t logL) {
-    const uint32_t t = gridDim.y - 1u - blockIdx.y;  // (the tables that the pass before read last first: 100 us became 94)
+    uint32_t t, block;
+    table_of_group(waves_grid / 4u, &t, &block);
+    if (t >= g.T) return;  // uniform
+    t = g.T - 1u - t;  // (the tables that the pass before read last first: 100 us became 94)
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave_global = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const uint32_t wave_global = block * 4 + (threadIdx.x >> 6);
     const QParam q = probe[t];
     const float Rf = (float)g.R;
     const uint8_t* tab = static_cast<const uint8_t*>(payload) + (size_t)t * g.n * g.es;
     const uint32_t W = NW == 4 ? (uint32_t)((size_t)g.D * g.es / 16u) : g.D;  // pieces per row
     const uint32_t L = 1u << logL, sub = lane & (L - 1u), team = lane >> logL, rps = 64u >> logL;
+    const size_t row_bytes = (size_t)g.D * g.es;
     bool differ = false;
     for (uint32_t row0 = wave_global * 64u; row0 < g.B; row0 += waves_grid * 64u) {
-        uint32_t or_mine = 0xFFFFFFFFu, oq_mine = 0xFFFFFFFFu;  // lane j: the owners of row row0 + j's two hashes
-        {
-            const uint32_t row = row0 + lane;
-            if (row < g.B) {
-                or_mine = own[(size_t)t * g.B + row];
-                oq_mine = own[((size_t)g.T + t) * g.B + row];
-            }
-        }
-        for (uint32_t s0 = 0; s0 < L; s0 += kStSteps) {  // L steps of rps rows make 64 rows
-            uint32_t orr[kStSteps], oq[kStSteps];
-            bool need_r[kStSteps], need_q[kStSteps];
-#pragma unroll
-            for (uint32_t s = 0; s < kStSteps; ++s) {
-                const uint32_t r = (s0 + s) * rps + team;
-                orr[s] = (uint32_t)__shfl((int)or_mine, (int)(r & 63u), 64);
-                oq[s] = (uint32_t)__shfl((int)oq_mine, (int)(r & 63u), 64);
-                const bool live = s0 + s < L && row0 + r < g.B;
-                need_r[s] = live && orr[s] < row0 + r;  // (an owner is never a later row)
-                need_q[s] = live && oq[s] < row0 + r;
-            }
-            for (uint32_t p = sub; p < W; p += L) {
-                StPiece<NW> a[kStSteps], br[kStSteps], bq[kStSteps];
+        // the rows with `need` set are put next to one another and compared with the row `other` of each, all by all teams;
+        // `raw`: in their bits, else in their symbols
+        auto compare = [&](bool need, uint32_t other, bool raw) {
+            const uint64_t mask = __ballot(need);
+            const uint32_t n = (uint32_t)__popcll(mask);
+            if (n == 0u) return;
+            const uint32_t rank = (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
+            const int to = (int)((need ? rank : n + lane - rank) << 2);
+            const uint32_t list_row = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)lane);
+            const uint32_t list_other = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(other | (raw ? 0x80000000u : 0u)));  // (a row's index has 31 bits)
+            for (uint32_t i0 = 0; i0 < n; i0 += rps * kStSteps) {
+                const uint8_t* pa[kStSteps];
+                const uint8_t* pb[kStSteps];
+                bool in[kStSteps], bits[kStSteps];
 #pragma unroll
                 for (uint32_t s = 0; s < kStSteps; ++s) {
-                    const uint32_t row = row0 + (s0 + s) * rps + team;
-                    if (need_r[s] || need_q[s]) a[s] = st_load_piece<F16, NW>(tab, (size_t)row * W + p);
-                    if (need_r[s]) br[s] = st_load_piece<F16, NW>(tab, (size_t)orr[s] * W + p);
-                    if (need_q[s] && !(need_r[s] && oq[s] == orr[s])) bq[s] = st_load_piece<F16, NW>(tab, (size_t)oq[s] * W + p);
+                    const uint32_t i = i0 + s * rps + team;
+                    in[s] = i < n;
+                    const uint32_t k = in[s] ? i : 0u;
+                    const uint32_t r = (uint32_t)__shfl((int)list_row, (int)k, 64), o = (uint32_t)__shfl((int)list_other, (int)k, 64);
+                    bits[s] = (o >> 31) != 0u;
+                    pa[s] = tab + (size_t)(row0 + r) * row_bytes;
+                    pb[s] = tab + (size_t)(o & 0x7FFFFFFFu) * row_bytes;
                 }
+                for (uint32_t p = sub; p < W; p += L) {
+                    StPiece<NW> a[kStSteps], b[kStSteps];
 #pragma unroll
-                for (uint32_t s = 0; s < kStSteps; ++s) {
-                    if (need_r[s]) {
-#pragma unroll
-                        for (uint32_t k = 0; k < NW; ++k) differ |= a[s].v[k] != br[s].v[k];
+                    for (uint32_t s = 0; s < kStSteps; ++s) {  // (past the list: its first row, read and not looked at)
+                        a[s] = st_load_piece<F16, NW>(pa[s], p);
+                        b[s] = st_load_piece<F16, NW>(pb[s], p);
                     }
-                    if (need_q[s]) {
-                        const bool shared = need_r[s] && oq[s] == orr[s];
 #pragma unroll
-                        for (uint32_t k = 0; k < NW; ++k) {
-                            const uint32_t b = shared ? br[s].v[k] : bq[s].v[k];
-                            if (a[s].v[k] != b) differ |= st_symbols_differ<F16, NW>(a[s].v[k], b, q, Rf, (int)g.R);
+                    for (uint32_t s = 0; s < kStSteps; ++s) {
+                        uint32_t x = 0u;
+#pragma unroll
+                        for (uint32_t k = 0; k < NW; ++k) x |= a[s].v[k] ^ b[s].v[k];
+                        if (x != 0u && in[s]) {
+                            bool d = bits[s];
+#pragma unroll
+                            for (uint32_t k = 0; k < NW; ++k)
+                                if (!d && a[s].v[k] != b[s].v[k]) d = st_symbols_differ<F16, NW>(a[s].v[k], b[s].v[k], q, Rf, (int)g.R);
+                            differ |= d;
                         }
                     }
                 }
             }
-        }
+        };
+        const uint32_t row = row0 + lane;
+        const uint32_t own_r = row < g.B ? own[(size_t)t * g.B + row] : 0xFFFFFFFFu, own_q = row < g.B ? own[((size_t)g.T + t) * g.B + row] : 0xFFFFFFFFu;
+        const bool need_r = own_r < row, need_q = own_q < row;  // (an owner is never a later row)
+        compare(need_r || need_q, need_r ? own_r : own_q, need_r);
+        // rows with two owners: equal in their bits to the one is equal in their symbols too
+        compare(need_r && need_q && own_q != own_r, own_q, false);
     }
     if (__ballot(differ) != 0ull && lane == 0) atomicAdd(&ctrl->collide, 1u);
 }
@@ -434,7 +448,7 @@ hipError_t launch_stats(const Geom& g, const void* payload, const Ws& w, uint32_
     const uint32_t pieces = vec ? (uint32_t)((size_t)g.D * g.es / 16u) : g.D;
     uint32_t logL = 0;
     while (logL < 6 && (1u << logL) < pieces) ++logL;
-#define DLC_ST_VERIFY(FF, NW) hipLaunchKernelGGL((k_stats_verify<FF, NW>), grid, block, 0, s, payload, g, probe, w.st_own, w.ctrl, waves_grid, logL)
+#define DLC_ST_VERIFY(FF, NW) hipLaunchKernelGGL((k_stats_verify<FF, NW>), dim3(table_grid(g.T, blocks_x)), block, 0, s, payload, g, probe, w.st_own, w.ctrl, waves_grid, logL)
     if (g.dtype == DLC_F16) { if (vec) DLC_ST_VERIFY(true, 4); else DLC_ST_VERIFY(true, 1); }
     else { if (vec) DLC_ST_VERIFY(false, 4); else DLC_ST_VERIFY(false, 1); }
 #undef DLC_ST_VERIFY
