@@ -73,7 +73,6 @@ __device__ __forceinline__ void rm_add_other(uint64_t id, uint32_t e, uint32_t a
     a[2] += rm_mix32(z ^ 0x5BD1E995u);
 }
 
-constexpr uint32_t kRmSteps = 1;  // row sets of a wavefront whose loads are issued back to back (64 tables of 8192 rows: 26 us, with four 34: fewer wavefronts)
 constexpr uint32_t kRmSlab = 32;   // pieces of a row that pass 1 holds in LDS at a time
 constexpr uint32_t kRmPitch = kRmSlab + 1u;
 
@@ -308,8 +307,9 @@ __global__ __launch_bounds__(1024) void k_rm_sets(Geom g, const uint8_t* on, con
 // that nobody compares with are changed: an owner is never such a row.
 // A lane holds a piece of PW words of the plane (16 bytes where the row length allows, else 4); a row is the work
 // of a team of 2^logL lanes, the smallest power of two that covers the row's pieces (64 at most: longer rows take
-// several trips); a wavefront works on 64 rows per trip: 64 >> logL at a time, in 2^logL steps, kRmSteps of them
-// with their loads issued back to back.
+// several trips); a wavefront works on 64 rows per trip: those with an earlier owner are put next to one another, 64 >> logL
+// at a time are compared.  64 tables of 8192 x 128: 24 us; all 64 rows walked, the idle ones under a condition, 26, four sets
+// of them in flight at half the wavefronts 34.
 template <uint32_t PW>
 struct RmPiece { uint32_t v[PW]; };
 
@@ -355,115 +355,99 @@ __global__ __launch_bounds__(256) void k_rm_owner(const void* payload, Geom g, c
     const uint8_t* tab = static_cast<const uint8_t*>(payload) + (size_t)t * g.n * g.es;
     uint32_t* plane = reinterpret_cast<uint32_t*>(sym_plane + (size_t)t * plane_stride(g));
     for (uint32_t row0 = wave_global * 64u; row0 < g.B; row0 += waves_grid * 64u) {
-        uint32_t own_mine = 0xFFFFFFFFu;  // lane j: the owner of row row0 + j's hash
-        {
-            const uint32_t row = row0 + lane;
-            if (row < g.B) own_mine = rowown[(size_t)t * g.B + row];
-        }
-        for (uint32_t s0 = 0; s0 < L; s0 += kRmSteps) {  // L steps of rps rows make 64 rows
-            uint32_t own[kRmSteps];
-            bool need[kRmSteps], differ[kRmSteps];
-            RmPiece<PW> w[kRmSteps];  // the row's piece of the last trip (the only one unless a row has more than 64 pieces)
+        // the rows that have an earlier owner are put next to one another, rps of them are compared at a time
+        const uint32_t row_mine = row0 + lane;
+        const uint32_t own_mine = row_mine < g.B ? rowown[(size_t)t * g.B + row_mine] : 0xFFFFFFFFu;
+        const bool need_mine = own_mine < row_mine;  // (an owner is never a later row)
+        if (row_mine < g.B && !need_mine) ref_t[row_mine] = row_mine;
+        const uint64_t mask = __ballot(need_mine);
+        const uint32_t n = (uint32_t)__popcll(mask), rank = (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
+        const int to = (int)((need_mine ? rank : n + lane - rank) << 2);
+        const uint32_t list_row = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)row_mine);
+        const uint32_t list_own = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)own_mine);
+        for (uint32_t i0 = 0; i0 < n; i0 += rps) {
+            const bool need = i0 + team < n;
+            const uint32_t row = (uint32_t)__shfl((int)list_row, (int)(need ? i0 + team : 0u), 64);
+            uint32_t own = (uint32_t)__shfl((int)list_own, (int)(need ? i0 + team : 0u), 64);
+            bool differ = false;
+            RmPiece<PW> w;  // the row's piece of the last trip (the only one unless a row has more than 64 pieces)
 #pragma unroll
-            for (uint32_t s = 0; s < kRmSteps; ++s) {
-                const uint32_t r = (s0 + s) * rps + team;
-                own[s] = (uint32_t)__shfl((int)own_mine, (int)(r & 63u), 64);
-                need[s] = s0 + s < L && row0 + r < g.B && own[s] < row0 + r;  // (an owner is never a later row)
-                differ[s] = false;
-#pragma unroll
-                for (uint32_t k = 0; k < PW; ++k) w[s].v[k] = 0u;
-            }
+            for (uint32_t k = 0; k < PW; ++k) w.v[k] = 0u;
             for (uint32_t p = sub; p < W; p += L) {
-                RmPiece<PW> b[kRmSteps];
-#pragma unroll
-                for (uint32_t s = 0; s < kRmSteps; ++s) {
-                    const uint32_t row = row0 + (s0 + s) * rps + team;
-                    if (need[s]) {
-                        w[s] = rm_load_piece<PW>(plane, (size_t)row * W + p);
-                        b[s] = rm_load_piece<PW>(plane, (size_t)own[s] * W + p);
-                    } else {
-#pragma unroll
-                        for (uint32_t k = 0; k < PW; ++k) w[s].v[k] = b[s].v[k] = 0u;
-                    }
-                }
-#pragma unroll
-                for (uint32_t s = 0; s < kRmSteps; ++s) {
+                if (need) {
+                    w = rm_load_piece<PW>(plane, (size_t)row * W + p);
+                    const RmPiece<PW> b = rm_load_piece<PW>(plane, (size_t)own * W + p);
                     uint32_t x = 0u;
                     bool other = false;
 #pragma unroll
                     for (uint32_t k = 0; k < PW; ++k) {
-                        x |= w[s].v[k] ^ b[s].v[k];
-                        other = other || rm_has255(w[s].v[k]);
+                        x |= w.v[k] ^ b.v[k];
+                        other = other || rm_has255(w.v[k]);
                     }
-                    if (x != 0u) differ[s] = true;
+                    if (x != 0u) differ = true;
                     else if (other) {  // rare: the elements outside the window, by what they are
-                        const uint32_t row = row0 + (s0 + s) * rps + team;
                         for (uint32_t k = 0; k < PW; ++k) {
                             for (uint32_t v = 0; v < 4; ++v) {
-                                if (((w[s].v[k] >> (8u * v)) & 255u) < kWinEsc) continue;
+                                if (((w.v[k] >> (8u * v)) & 255u) < kWinEsc) continue;
                                 const uint32_t e = (p * PW + k) * 4u + v;
-                                if (rm_identity<F16>(tab, row * g.D + e, q, Rf, (int)g.R) != rm_identity<F16>(tab, own[s] * g.D + e, q, Rf, (int)g.R))
-                                    differ[s] = true;
+                                if (rm_identity<F16>(tab, row * g.D + e, q, Rf, (int)g.R) != rm_identity<F16>(tab, own * g.D + e, q, Rf, (int)g.R))
+                                    differ = true;
                             }
                         }
                     }
                 }
             }
-#pragma unroll
-            for (uint32_t s = 0; s < kRmSteps; ++s) {
-                const uint32_t row = row0 + (s0 + s) * rps + team;
-                bool same = need[s] && (__ballot(differ[s]) & teammask) == 0ull;  // the same for all lanes of a team
-                // A row that is not its hash's owner's equal: two different rows with one hash.  The first earlier row
-                // with the row's content, if there is one, has that hash too: the whole wavefront looks through the
-                // earlier rows with it, one such row at a time (never expected; slow and plain).
-                uint64_t coll = __ballot(need[s] && !same && sub == 0u);
-                while (coll != 0ull) {  // uniform over the wavefront
-                    const uint32_t leader = (uint32_t)__ffsll((unsigned long long)coll) - 1u;
-                    coll &= coll - 1ull;
-                    const uint32_t crow = row0 + (s0 + s) * rps + (leader >> logL);
-                    const uint64_t h = rowhash[(size_t)t * g.B + crow];
-                    uint32_t found = crow;
-                    for (uint32_t j0 = 0; j0 < crow && found == crow; j0 += 64u) {
-                        const uint32_t j = j0 + lane;
-                        uint64_t m = __ballot(j < crow && rowhash[(size_t)t * g.B + j] == h);
-                        while (m != 0ull && found == crow) {
-                            const uint32_t jj = j0 + (uint32_t)__ffsll((unsigned long long)m) - 1u;
-                            m &= m - 1ull;
-                            bool d = false;
-                            for (uint32_t e = lane; e < g.D; e += 64u)
-                                d = d || rm_identity<F16>(tab, crow * g.D + e, q, Rf, (int)g.R) != rm_identity<F16>(tab, jj * g.D + e, q, Rf, (int)g.R);
-                            if (__ballot(d) == 0ull) found = jj;
-                        }
-                    }
-                    if (found != crow && team == (leader >> logL)) {
-                        own[s] = found;
-                        same = true;
+            bool same = need && (__ballot(differ) & teammask) == 0ull;  // the same for all lanes of a team
+            // A row that is not its hash's owner's equal: two different rows with one hash.  The first earlier row
+            // with the row's content, if there is one, has that hash too: the whole wavefront looks through the
+            // earlier rows with it, one such row at a time (never expected; slow and plain).
+            uint64_t coll = __ballot(need && !same && sub == 0u);
+            while (coll != 0ull) {  // uniform over the wavefront
+                const uint32_t leader = (uint32_t)__ffsll((unsigned long long)coll) - 1u;
+                coll &= coll - 1ull;
+                const uint32_t crow = lane_read(row, leader);
+                const uint64_t h = rowhash[(size_t)t * g.B + crow];
+                uint32_t found = crow;
+                for (uint32_t j0 = 0; j0 < crow && found == crow; j0 += 64u) {
+                    const uint32_t j = j0 + lane;
+                    uint64_t m = __ballot(j < crow && rowhash[(size_t)t * g.B + j] == h);
+                    while (m != 0ull && found == crow) {
+                        const uint32_t jj = j0 + (uint32_t)__ffsll((unsigned long long)m) - 1u;
+                        m &= m - 1ull;
+                        bool d = false;
+                        for (uint32_t e = lane; e < g.D; e += 64u)
+                            d = d || rm_identity<F16>(tab, crow * g.D + e, q, Rf, (int)g.R) != rm_identity<F16>(tab, jj * g.D + e, q, Rf, (int)g.R);
+                        if (__ballot(d) == 0ull) found = jj;
                     }
                 }
-                if (sub == 0 && s0 + s < L && row < g.B) ref_t[row] = same ? own[s] : row;
-                if (!same) continue;
-                for (uint32_t p = sub; p < W; p += L) {
-                    const RmPiece<PW> wv = W <= L ? w[s] : rm_load_piece<PW>(plane, (size_t)row * W + p);
+                if (found != crow && team == (leader >> logL)) {
+                    own = found;
+                    same = true;
+                }
+            }
+            if (sub == 0u && need) ref_t[row] = same ? own : row;
+            if (!same) continue;
+            for (uint32_t p = sub; p < W; p += L) {
+                const RmPiece<PW> wv = W <= L ? w : rm_load_piece<PW>(plane, (size_t)row * W + p);
 #pragma unroll
-                    for (uint32_t k = 0; k < PW; ++k) {
-                        if (!rm_has255(wv.v[k])) {
+                for (uint32_t k = 0; k < PW; ++k) {
+                    if (!rm_has255(wv.v[k])) {
 #pragma unroll
-                            for (uint32_t v = 0; v < 4; ++v) atomicSub(&win[((wv.v[k] >> (8u * v)) & 255u) * kWinCopies], 1u);
-                        } else {
-                            for (uint32_t v = 0; v < 4; ++v) {
-                                const uint32_t idx = (wv.v[k] >> (8u * v)) & 255u;
-                                if (idx < kWinEsc) {
-                                    atomicSub(&win[idx * kWinCopies], 1u);
-                                } else {
-                                    const uint64_t id = rm_identity<F16>(tab, row * g.D + (p * PW + k) * 4u + v, q, Rf, (int)g.R);
-                                    atomicSub(&exact[(id >> 32) ? 0u : (uint32_t)id], 1u);
-                                }
+                        for (uint32_t v = 0; v < 4; ++v) atomicSub(&win[((wv.v[k] >> (8u * v)) & 255u) * kWinCopies], 1u);
+                    } else {
+                        for (uint32_t v = 0; v < 4; ++v) {
+                            const uint32_t idx = (wv.v[k] >> (8u * v)) & 255u;
+                            if (idx < kWinEsc) {
+                                atomicSub(&win[idx * kWinCopies], 1u);
+                            } else {
+                                const uint64_t id = rm_identity<F16>(tab, row * g.D + (p * PW + k) * 4u + v, q, Rf, (int)g.R);
+                                atomicSub(&exact[(id >> 32) ? 0u : (uint32_t)id], 1u);
                             }
                         }
                     }
-                    if constexpr (PW == 4) *reinterpret_cast<uint4*>(plane + ((size_t)row * W + p) * 4u) = make_uint4(0xFDFDFDFDu, 0xFDFDFDFDu, 0xFDFDFDFDu, 0xFDFDFDFDu);
-                    else plane[(size_t)row * W + p] = 0xFDFDFDFDu;
                 }
+                if constexpr (PW == 4) *reinterpret_cast<uint4*>(plane + ((size_t)row * W + p) * 4u) = make_uint4(0xFDFDFDFDu, 0xFDFDFDFDu, 0xFDFDFDFDu, 0xFDFDFDFDu);
+                else plane[(size_t)row * W + p] = 0xFDFDFDFDu;
             }
         }
     }
