@@ -486,7 +486,7 @@ void k_encode(const void* payload, const uint8_t* sym_plane, Geom g, FixedLayout
 //   own and nothing waits for another work-group before the scan.  The payload is read once; the symbol plane goes
 //   through the caches.  What bounds it: with few tables the chain of latencies (loads, one wavefront's tree, the
 //   walk: one table of 4096 elements 14 us, where three launches took 61), with many the counting phase (4096 tables of two
-//   groups: 50 of a work-group's 80 us, at twelve wavefronts a compute unit; 220 us, the three launches 283).
+//   groups: 216 us, the three launches 283).
 // ------------------------------------------------------------------------------------------------
 template <int S, bool F16, bool VEC, uint32_t NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4)))
@@ -713,10 +713,13 @@ bool DLC_CAT(launch_table_, DLC_S)(const Geom& g, const FixedLayout& F, const vo
         while (cap > S / 8u && enc_lds(8u, g.G, cap, 40u).end > kLdsMax / 2u - kTableStatic) --cap;
         return DLC_CAT(table_launch_, DLC_S)<8u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax / 2u - kTableStatic, 512u, s);
     } else {
-        // as many wavefronts as the table has groups, twelve to sixteen a compute unit
+        // As many work-groups a compute unit as the LDS holds, sixteen to twenty-four wavefronts.  Twice as many wavefronts as
+        // a table has groups where it has four or fewer: they share the counting (calls with 4096 tables of two groups 223 us
+        // with two wavefronts, 216 with four, 256 with eight; 2048 of one group 101, 93, 113; 1024 of four groups 122 with four,
+        // 112 with eight; of eight groups 176 with eight, 190 with sixteen).
         const uint32_t cap = S / 8u;
-        if (g.G <= 2u) return DLC_CAT(table_launch_, DLC_S)<2u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax / 6u - kTableStatic, 1536u, s);
-        if (g.G <= 4u) return DLC_CAT(table_launch_, DLC_S)<4u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax / 3u - kTableStatic, 768u, s);
+        if (g.G <= 2u) return DLC_CAT(table_launch_, DLC_S)<4u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax / 6u - kTableStatic, 1536u, s);
+        if (g.G <= 4u) return DLC_CAT(table_launch_, DLC_S)<8u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax / 3u - kTableStatic, 768u, s);
         if (g.G <= 8u) return DLC_CAT(table_launch_, DLC_S)<8u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax / 2u - kTableStatic, 512u, s);
         return DLC_CAT(table_launch_, DLC_S)<16u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax - kTableStatic, 256u, s);
     }
@@ -737,8 +740,7 @@ static hipError_t DLC_CAT(encode_attributes_, DLC_S)() {
 
 hipError_t DLC_CAT(encode_set_attributes_, DLC_S)() {
     constexpr int S = DLC_S;
-    hipError_t e = DLC_CAT(encode_attributes_, DLC_S)<2u>();
-    if (e == hipSuccess) e = DLC_CAT(encode_attributes_, DLC_S)<4u>();
+    hipError_t e = DLC_CAT(encode_attributes_, DLC_S)<4u>();
     if (e == hipSuccess) e = DLC_CAT(encode_attributes_, DLC_S)<8u>();
     if (e == hipSuccess) e = DLC_CAT(encode_attributes_, DLC_S)<16u>();
     const void* ks[] = {reinterpret_cast<const void*>(k_encode<S, false, false, false, 8u>), reinterpret_cast<const void*>(k_encode<S, false, true, false, 8u>),
