@@ -616,9 +616,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
             // windows: a lane needs a new one when a turn could read past the last word, unless its chunk ends in the one it has
             uint32_t renew_at = (!linear && cw > kWin) ? (kWin - 1u) * 32u : 0xFFFFFFFFu;
             auto renew = [&]() {  // the words from the first that the next turn reads on, anew
-                wbase += (p >> 5) - 1u;
+                wbase += (p >> 5) - 1u;  // (-1 for a lane that has not taken a bit: its row then starts with the word before its chunk)
                 p = (p & 31u) + 32u;
-                const uint32_t left = cw > wbase ? cw - wbase : 0u;
+                const uint32_t left = (uint32_t)max((int32_t)(cw - wbase), 0);
                 uint32_t w[16];
                 if (__ballot(left > 16u) != 0ull) {
                     fetch_window(k32, k0, gp, wbase, w);

@@ -98,3 +98,33 @@ def test_a_chunk_that_ends_early_is_refused(kind):
         assert ctx.sync_status() == b.ECORRUPT, chunk
     assert ctx.decompress(to_device(good), good.size, rec) == 0 and ctx.sync_status() == 0
     assert np.array_equal(rec.cpu().numpy().view(np.uint32), oracle.decompress(good, x.shape, x.dtype)[1].view(np.uint32))
+
+
+@pytest.mark.parametrize("T,groups,D,refs,wide,narrow,dtype", [
+    (258, 2, 128, 41, 400, 32, np.float32),   # more than 256 work-groups: windows from 1920 words a group on
+    (258, 2, 128, 41, 400, 32, np.float16),
+    (130, 9, 128, 41, 400, 32, np.float32),   # eight groups a work-group, the ninth on its own
+    (5, 3, 64, 36, 1000, 32, np.float32),    # a small grid: windows from 3072 words on
+])
+@pytest.mark.parametrize("side", [0, 1], ids=["first_row", "second_row"])
+def test_lanes_without_bits_until_after_a_new_window(side, T, groups, D, refs, wide, narrow, dtype):
+    """Two or four rows a turn: in every group one of them is a reference for the first `refs` turns, so its lanes have taken
+    no bit when the others need their next window; all their words are still to come."""
+    S, rows = 256, 256 // D  # (64 turns a group)
+    rng = np.random.default_rng(T + wide + side)
+    bins = rng.integers(0, narrow, (T, groups, 64, rows, D)) - narrow // 2
+    bins[:, :, :, side] = rng.integers(0, wide, (T, groups, 64, D)) - wide // 2
+    bins[:, :, :refs, side] = bins[:, :1, :1, side]  # one row of the table again and again
+    x = (bins * (2 * float(EB))).astype(dtype).reshape(T, groups * 64 * rows, D)
+    o = oracle.compress(x, np.full(T, EB, np.float32), 512, S, 12, row_match=True)
+    q = o.data[48:].view(np.uint64)  # escapes, words, then the sections' offsets
+    ng = T * groups
+    starts = o.data[int(q[2]):int(q[2]) + 4 * ng].view(np.uint32).astype(np.int64)
+    words = np.diff(np.append(starts, int(q[1])))
+    chunk = o.data[int(q[3]):int(q[3]) + 64 * ng].reshape(T, groups, rows, 64 // rows)[:, 1:].astype(np.int64)  # (a table's first group has the row itself)
+    late, busy = chunk[:, :, side], np.delete(chunk, side, axis=2).reshape(T, groups - 1, -1)
+    assert words.min() > (1920 if ng > 256 else 3072), words.min()  # windows
+    assert np.all(late.max(-1) > 28)                                # a window and more to come,
+    assert np.all(busy.max(-1) * 32 * refs >= 64 * 896)             # and the others need a new one before the first bit of it,
+    assert busy.max(-1).min() <= 54                                 # in some group without a second one afterwards
+    _check(T, groups * 64 * rows, D, S, dtype, True, x)
