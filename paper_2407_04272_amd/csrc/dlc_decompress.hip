@@ -941,9 +941,9 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(Geom g, Fixed
 // A thread per 16-byte (fp32) / 8-byte (fp16) piece of a row, pieces of a row on neighbouring threads.
 template <typename U>
 __global__ __launch_bounds__(256) void k_row_copy(Geom g, const uint8_t* comp, uint64_t comp_bytes, const DecTable* dtab,
-                                                  void* outp, uint32_t bx) {
+                                                  void* outp, TableOrder order) {
     uint32_t t, block;
-    table_of_group(bx, &t, &block);
+    order.place(&t, &block);
     if (t >= g.T) return;           // uniform
     const uint32_t dst = t / g.TD;  // the container this table is in
     comp += (uint64_t)dst * comp_bytes;
@@ -955,7 +955,7 @@ __global__ __launch_bounds__(256) void k_row_copy(Geom g, const uint8_t* comp, u
     const uint32_t total = g.B * upr;
     // four pieces a thread has in flight: references first, then the rows they point at (named variables, not an
     // array: the compiler moved an array of vectors into LDS)
-    const uint32_t stride = bx * 256;
+    const uint32_t stride = order.bx * 256;
     for (uint32_t i0 = block * 256 + threadIdx.x; i0 < total; i0 += stride * 4u) {
         uint32_t row[4], o[4];
 #pragma unroll
@@ -1022,9 +1022,11 @@ hipError_t launch_decompress(const Geom& g, const uint8_t* comp, uint64_t comp_b
 #undef DLC_DEC2
 #undef DLC_DEC3
         if (g.lz) {
-            const uint32_t bx = std::min<uint32_t>((g.B * (g.D / 4u) + 255u) / 256u, 256u);
-            if (f16) hipLaunchKernelGGL(k_row_copy<uint2>, dim3(table_grid(g.T, bx)), dim3(256), 0, s, g, comp, (uint64_t)comp_bytes, w.dtab, out, bx);
-            else hipLaunchKernelGGL(k_row_copy<uint4>, dim3(table_grid(g.T, bx)), dim3(256), 0, s, g, comp, (uint64_t)comp_bytes, w.dtab, out, bx);
+            // tables apart and one after the other, us: one of 65536 rows 31 and 16; 9, 26, 64 and 128 of 8192 x 128 12.8 and 10.0,
+            // 25.1 and 22.4, 48.5 and 49.4, 100 and 104; 65 and 100, which the XCDs cannot share alike, 51.7 and 50.4, 76.9 and 77.1
+            const TableOrder order(std::min<uint32_t>((g.B * (g.D / 4u) + 255u) / 256u, 256u), g.T >= 64u && g.T % 8u == 0u);
+            if (f16) hipLaunchKernelGGL(k_row_copy<uint2>, dim3(order.groups(g.T)), dim3(256), 0, s, g, comp, (uint64_t)comp_bytes, w.dtab, out, order);
+            else hipLaunchKernelGGL(k_row_copy<uint4>, dim3(order.groups(g.T)), dim3(256), 0, s, g, comp, (uint64_t)comp_bytes, w.dtab, out, order);
         }
         if (prof_on(pl, P_DECODE)) prof_end(prof, P_DECODE, s);
     }

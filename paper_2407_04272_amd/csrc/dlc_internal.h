@@ -193,15 +193,20 @@ __device__ __forceinline__ uint32_t load4(const void* gbase, uint32_t off, uint3
     }
 }
 
-// Kernels whose work-groups read rows of all parts of their table: the table's `bx` work-groups come one after the other on one
-// XCD (work-groups go to the eight XCDs in turn), so that a row that many refer to is fetched into one L2 and not into
-// eight.  The grid is table_grid(T, bx) work-groups; *t >= T: nothing to do.
-__device__ __forceinline__ void table_of_group(uint32_t bx, uint32_t* t, uint32_t* block) {
-    const uint32_t xcd = blockIdx.x & 7u, k = blockIdx.x >> 3;
-    *t = (k / bx) * 8u + xcd;
-    *block = k % bx;
-}
-inline __host__ uint32_t table_grid(uint32_t T, uint32_t bx) { return (T + 7u) / 8u * 8u * bx; }
+// Kernels whose work-groups read rows of all parts of their table.  Apart: the table's `bx` work-groups come one after the other
+// on one XCD (work-groups go to the eight XCDs in turn), so that a row that many refer to is fetched into one L2 and not into
+// eight; it pays where there are tables enough to load all eight alike (figures at the launches).  Else the tables come one
+// after the other, each over the whole chip.  The grid is groups(T) work-groups; *t >= T: nothing to do.
+struct TableOrder {
+    uint32_t bx, log_xcds;
+    inline __host__ TableOrder(uint32_t bx, bool apart) : bx(bx), log_xcds(apart ? 3u : 0u) {}
+    inline __host__ uint32_t groups(uint32_t T) const { return ((T + (1u << log_xcds) - 1u) >> log_xcds << log_xcds) * bx; }
+    __device__ __forceinline__ void place(uint32_t* t, uint32_t* block) const {
+        const uint32_t k = blockIdx.x >> log_xcds;
+        *t = (k / bx << log_xcds) + (blockIdx.x & ((1u << log_xcds) - 1u));
+        *block = k % bx;
+    }
+};
 
 // inclusive prefix sum over the 64 lanes (all of them active), in registers: four shifts inside the rows of sixteen
 // lanes, then the rows' sums handed on (six dependent instructions; as six LDS permutes it took 700 cycles)

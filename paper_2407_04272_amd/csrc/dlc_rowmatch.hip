@@ -328,11 +328,12 @@ __device__ __forceinline__ RmPiece<PW> rm_load_piece(const uint32_t* plane, size
 template <bool F16, uint32_t PW>
 __global__ __launch_bounds__(256) void k_rm_owner(const void* payload, Geom g, const QParam* qp, const uint8_t* on,
                                                   const uint32_t* rowown, const uint64_t* rowhash, uint32_t* ref, uint8_t* sym_plane,
-                                                  uint32_t* hist, uint32_t waves_grid, uint32_t logL) {
+                                                  uint32_t* hist, TableOrder order, uint32_t logL) {
     extern __shared__ __align__(16) uint32_t lh[];  // what to take off the counts: window [kWinBins + 1][kWinCopies] | exact [K]
     uint32_t t, block;
-    table_of_group(waves_grid / 4u, &t, &block);
+    order.place(&t, &block);
     if (t >= g.T) return;  // uniform
+    const uint32_t waves_grid = order.bx * 4u;
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t wave_global = block * 4 + (tid >> 6);
     uint32_t* ref_t = ref + (size_t)t * g.B;
@@ -505,7 +506,10 @@ hipError_t launch_row_match(const Geom& g, const void* payload, const Ws& w, hip
         hipError_t e = launch_row_sets(g, 1u, w.rm_on, w.rm_hash, w.rm_own, nullptr, nullptr, s);
         if (e != hipSuccess) return e;
     }
-#define DLC_RM_OWNER(FF, PP) hipLaunchKernelGGL((k_rm_owner<FF, PP>), dim3(table_grid(g.T, blocks_x)), block, sm, s, payload, g, w.qp, w.rm_on, w.rm_own, w.rm_hash, w.rm_ref, w.sym_plane, w.hist, waves_grid, logL)
+    // tables apart and one after the other, us: one of 65536 rows 74 and 69; 9, 26, 44, 64 and 128 of 8192 x 128 14.1 and 13.4, 17.1
+    // and 16.3, 20.3 both, 24.4 and 25.0, 41.1 and 43.4
+    const TableOrder order(blocks_x, g.T >= 48u);
+#define DLC_RM_OWNER(FF, PP) hipLaunchKernelGGL((k_rm_owner<FF, PP>), dim3(order.groups(g.T)), block, sm, s, payload, g, w.qp, w.rm_on, w.rm_own, w.rm_hash, w.rm_ref, w.sym_plane, w.hist, order, logL)
     if (g.dtype == DLC_F16) { if (pw == 4u) DLC_RM_OWNER(true, 4); else DLC_RM_OWNER(true, 1); }
     else { if (pw == 4u) DLC_RM_OWNER(false, 4); else DLC_RM_OWNER(false, 1); }
 #undef DLC_RM_OWNER

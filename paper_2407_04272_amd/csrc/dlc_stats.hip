@@ -323,11 +323,12 @@ __device__ __forceinline__ bool st_symbols_differ(uint32_t a, uint32_t b, const 
 // that others refer to as well) in 65 us.  With all 64 rows walked, the idle ones under a condition: 94.
 template <bool F16, uint32_t NW>
 __global__ __launch_bounds__(256) void k_stats_verify(const void* payload, Geom g, const QParam* probe, const uint32_t* own,
-                                                      Ctrl* ctrl, uint32_t waves_grid, uint32_t logL) {
+                                                      Ctrl* ctrl, TableOrder order, uint32_t logL) {
     uint32_t t, block;
-    table_of_group(waves_grid / 4u, &t, &block);
+    order.place(&t, &block);
     if (t >= g.T) return;  // uniform
-    t = g.T - 1u - t;  // (the tables that the pass before read last first: 100 us became 94)
+    const uint32_t waves_grid = order.bx * 4u;
+    t = g.T - 1u - t;  // (the tables that the pass before read last first: 128 tables of 8192 x 128 100 us, so 94)
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave_global = block * 4 + (threadIdx.x >> 6);
     const QParam q = probe[t];
@@ -448,7 +449,10 @@ hipError_t launch_stats(const Geom& g, const void* payload, const Ws& w, uint32_
     const uint32_t pieces = vec ? (uint32_t)((size_t)g.D * g.es / 16u) : g.D;
     uint32_t logL = 0;
     while (logL < 6 && (1u << logL) < pieces) ++logL;
-#define DLC_ST_VERIFY(FF, NW) hipLaunchKernelGGL((k_stats_verify<FF, NW>), dim3(table_grid(g.T, blocks_x)), block, 0, s, payload, g, probe, w.st_own, w.ctrl, waves_grid, logL)
+    // tables apart and one after the other, us: one of 65536 rows 49 and 48; 9, 12, 15, 26, 64 and 128 of 8192 x 128 8.8 and 8.4, 9.8
+    // and 9.0, 9.9 and 11.2, 16.5 and 17.8, 32 and 38, 67 and 76
+    const TableOrder order(blocks_x, g.T > 12u);
+#define DLC_ST_VERIFY(FF, NW) hipLaunchKernelGGL((k_stats_verify<FF, NW>), dim3(order.groups(g.T)), block, 0, s, payload, g, probe, w.st_own, w.ctrl, order, logL)
     if (g.dtype == DLC_F16) { if (vec) DLC_ST_VERIFY(true, 4); else DLC_ST_VERIFY(true, 1); }
     else { if (vec) DLC_ST_VERIFY(false, 4); else DLC_ST_VERIFY(false, 1); }
 #undef DLC_ST_VERIFY
