@@ -474,12 +474,13 @@ void row_match_multipliers(uint32_t* mult, uint32_t n_pieces) {
 hipError_t launch_row_sets(const Geom& g, uint32_t n_sets, const uint8_t* on, const uint64_t* rowhash, uint32_t* own,
                            uint32_t* unique, Ctrl* ctrl, hipStream_t s) {
     // slots for the whole batch, 16384 at most; a work-group a compute unit (32 per table and set at most: each reads all the
-    // table's hashes; 64 tables of 8192: 14 us, with two work-groups a compute unit 20), and more where a batch is large:
+    // table's hashes; 64 tables of 8192: 14 us, with two work-groups a compute unit 20; 9, 26 and 65 tables of 16384, whose
+    // sets fill a compute unit's LDS, with the next more: 31, 35 and 41 us, so 19, 21 and 28), and more where a batch is large:
     // a work-group's share of the rows is half its slots or less (up to 32 M rows)
     uint32_t n_slots = 64;
     while (n_slots < g.B && n_slots < 16384u) n_slots <<= 1;
     uint32_t parts = 1;
-    while (parts < 32u && parts * g.T * n_sets < 256u) parts <<= 1;
+    while (parts < 32u && 2u * parts * g.T * n_sets <= 256u) parts <<= 1;
     while (parts < 4096u && (uint64_t)parts * n_slots < 2ull * g.B) parts <<= 1;
     if (g.B <= kRmTagRows)
         hipLaunchKernelGGL(k_rm_sets<true>, dim3(g.T, parts, n_sets), dim3(1024), n_slots * 8u, s, g, on, rowhash, own, n_slots, parts,
