@@ -438,9 +438,11 @@ void k_encode(const void* payload, const uint8_t* sym_plane, Geom g, FixedLayout
     __syncthreads();
     GroupJob J;
     J.wg = __builtin_amdgcn_readfirstlane(s_wg);
-    if (J.wg >= g.T * bpt) {  // uniform; xn for every container
-        finish_container<64u * NW, false>(g, F, tmeta, lens, qp, ctrl, state, epoch, bpt, out, capacity, out_bytes, J.wg - g.T * bpt, xn, *reinterpret_cast<FinLds<64u * NW>*>(smem), tid);
-        return;
+    if constexpr (!LZ) {  // (row matching: the references are copied by a launch of its own)
+        if (J.wg >= g.T * bpt) {  // uniform; xn for every container
+            finish_container<64u * NW, false>(g, F, tmeta, lens, qp, ctrl, state, epoch, bpt, out, capacity, out_bytes, J.wg - g.T * bpt, xn, *reinterpret_cast<FinLds<64u * NW>*>(smem), tid);
+            return;
+        }
     }
     J.t = J.wg / bpt;
     J.grp = (J.wg % bpt) * NW + __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -488,7 +490,7 @@ void k_encode(const void* payload, const uint8_t* sym_plane, Geom g, FixedLayout
 //   walk: one table of 4096 elements 14 us, where three launches took 61), with many the counting phase (4096 tables of two
 //   groups: 216 us, the three launches 283).
 // ------------------------------------------------------------------------------------------------
-template <int S, bool F16, bool VEC, uint32_t NW>
+template <int S, bool F16, bool VEC, uint32_t NW, bool FIN>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4)))
 void k_table(const void* payload, uint8_t* sym_plane, Geom g, FixedLayout F, const QParam* qp, uint32_t* hist_view, uint16_t* enc,
              uint8_t* lens, TMeta* tmeta, Ctrl* ctrl, uint64_t* state, uint64_t epoch, uint8_t* out, uint64_t capacity,
@@ -512,9 +514,11 @@ void k_table(const void* payload, uint8_t* sym_plane, Geom g, FixedLayout F, con
     __syncthreads();
     GroupJob J;
     J.wg = __builtin_amdgcn_readfirstlane(s_wg);
-    if (J.wg >= g.T) {  // uniform; xn for every container
-        finish_container<NT, true>(g, F, tmeta, lens, qp, ctrl, state, epoch, 1u, out, capacity, out_bytes, J.wg - g.T, xn, *reinterpret_cast<FinLds<NT>*>(smem), tid);
-        return;
+    if constexpr (FIN) {
+        if (J.wg >= g.T) {  // uniform; xn for every container
+            finish_container<NT, true>(g, F, tmeta, lens, qp, ctrl, state, epoch, 1u, out, capacity, out_bytes, J.wg - g.T, xn, *reinterpret_cast<FinLds<NT>*>(smem), tid);
+            return;
+        }
     }
     const uint32_t t = J.wg;  // a work-group per table, in ticket order
     J.t = t;
@@ -593,13 +597,13 @@ void k_table(const void* payload, uint8_t* sym_plane, Geom g, FixedLayout F, con
             uint32_t idx;
             const uint32_t e = in_window(k, idx) ? ent[idx] : 0u;
             enc_t[k] = (uint16_t)e;
-            if (out_bytes) __hip_atomic_store(&lens_t[k], (uint8_t)(e >> 12), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if constexpr (FIN) __hip_atomic_store(&lens_t[k], (uint8_t)(e >> 12), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             else lens_t[k] = (uint8_t)(e >> 12);
         }
     } else {  // many symbols, or symbols outside the window: from the counts in memory
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        codebook_build<NT>(g, view_t, view_t, enc_t, lens_t, tmeta + t, smem, s_cb, tid, 0u, out_bytes != nullptr);
+        codebook_build<NT>(g, view_t, view_t, enc_t, lens_t, tmeta + t, smem, s_cb, tid, 0u, FIN);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         for (uint32_t i = tid; i < 256u; i += NT) {
@@ -615,9 +619,9 @@ void k_table(const void* payload, uint8_t* sym_plane, Geom g, FixedLayout F, con
     if (J.pairs) {
         build_pairs(reinterpret_cast<uint32_t*>(smem + J.L.pair), ent, J.lo, J.P, tid, NT);
     }
-    if (out_bytes) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the codebook is out)
+    if constexpr (FIN) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the codebook is out)
     __syncthreads();
-    if (out_bytes && tid == 0) wg_ready(state, epoch, J.wg);
+    if (FIN && tid == 0) wg_ready(state, epoch, J.wg);
     encode_groups<S, F16, VEC, false, NW>(J, payload, sym_plane, g, F, qp, enc, ctrl, state, epoch, out + (uint64_t)J.dst * capacity,
                                           capacity, word_start, word_end, smem, tid);
 }
@@ -673,12 +677,15 @@ bool DLC_CAT(launch_encode_, DLC_S)(const Geom& g, const FixedLayout& F, const v
 
 template <uint32_t NW>
 static bool DLC_CAT(table_launch_, DLC_S)(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch,
-                                          uint8_t* out, uint64_t capacity, uint64_t* out_bytes, uint32_t cap, uint32_t budget, uint32_t slots, hipStream_t s) {
+                                          uint8_t* out, uint64_t capacity, uint64_t* out_bytes, uint32_t cap, uint32_t budget, uint32_t room, hipStream_t s) {
     constexpr int S = DLC_S;
     const uint32_t xn = finish_groups(g, 64u * NW);
-    // `slots` work-groups run at a time.  Those that finish the containers have to run beside the tables': started when the first
-    // tables are done they are late (512 tables of 256 elements 28.2 us, so 30.4), but for one round among several (4096 of 32768: 360, so 354).
-    if (g.TD > 64u * NW || (g.T + g.ND * xn > slots && g.T < 2u * slots)) out_bytes = nullptr;
+    // A launch that is a single round of tables (`room` work-groups run at a time; 0: it may be several): those that finish the
+    // containers have to run beside them, started when the first tables are done they are late (512 tables of 256 elements 28.2
+    // us, so 30.4).  Of several rounds the last is seldom full (eight containers, us, a launch of their own and in this one: 768
+    // tables of four groups 84, 81, 1536 of two 114, 110, 960 of eight 176, 170, 400 of twelve 123, 118; 4096 of two 360, 354).
+    // (A launch without them is an instantiation of its own: with their code in it 520 tables of six groups took 110 us, so 106.)
+    if (g.TD > 64u * NW || (room != 0u && g.T + g.ND * xn > room)) out_bytes = nullptr;
     dim3 grid(g.T + (out_bytes ? g.ND * xn : 0u)), block(64 * NW);
     const uint32_t waves = std::min(NW, g.G);
     const uint32_t pair_max = pair_max_for(budget, NW, waves, cap);
@@ -686,12 +693,14 @@ static bool DLC_CAT(table_launch_, DLC_S)(const Geom& g, const FixedLayout& F, c
     sm = std::max(sm, std::max(hist_lds_bytes(g.K), codebook_smem(g.K)));
     if (out_bytes) sm = std::max(sm, sizeof(FinLds<64u * NW>));
     const bool f16 = g.dtype == DLC_F16;
-#define DLC_TAB(FF, V)                                                                                                \
-    hipLaunchKernelGGL((k_table<S, FF, V, NW>), grid, block, sm, s, payload, w.sym_plane, g, F, w.qp, w.hist_view, w.enc, w.lens, w.tmeta, \
+#define DLC_TAB2(FF, V, FIN)                                                                                          \
+    hipLaunchKernelGGL((k_table<S, FF, V, NW, FIN>), grid, block, sm, s, payload, w.sym_plane, g, F, w.qp, w.hist_view, w.enc, w.lens, w.tmeta, \
                        w.ctrl, w.state, epoch, out, capacity, w.word_start, w.word_end, out_bytes, xn, cap, pair_max)
+#define DLC_TAB(FF, V) do { if (out_bytes) DLC_TAB2(FF, V, true); else DLC_TAB2(FF, V, false); } while (0)
     if (f16) { if (g.vec) DLC_TAB(true, true); else DLC_TAB(true, false); }
     else { if (g.vec) DLC_TAB(false, true); else DLC_TAB(false, false); }
 #undef DLC_TAB
+#undef DLC_TAB2
     return out_bytes != nullptr;
 }
 
@@ -713,24 +722,34 @@ bool DLC_CAT(launch_table_, DLC_S)(const Geom& g, const FixedLayout& F, const vo
         while (cap > S / 8u && enc_lds(8u, g.G, cap, 40u).end > kLdsMax / 2u - kTableStatic) --cap;
         return DLC_CAT(table_launch_, DLC_S)<8u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax / 2u - kTableStatic, 512u, s);
     } else {
-        // As many work-groups a compute unit as the LDS holds, sixteen to twenty-four wavefronts.  Twice as many wavefronts as
-        // a table has groups where it has four or fewer: they share the counting (calls with 4096 tables of two groups 223 us
-        // with two wavefronts, 216 with four, 256 with eight; 2048 of one group 101, 93, 113; 1024 of four groups 122 with four,
-        // 112 with eight; of eight groups 176 with eight, 190 with sixteen).
+        // Several rounds of work-groups, or a chip that smaller ones fill.  A compute unit holds, by registers (91 a lane: five
+        // wavefronts a SIMD) or by LDS, six work-groups of two wavefronts, five of four (three with the LDS of tables of three and
+        // four groups) and two of eight.  Twice as many wavefronts as a table has groups share the counting and take less time a
+        // table, but more tables may then need one more round (us, with fewer and with more wavefronts: 2048 tables of one group 118,
+        // 109, 1400, which six to a compute unit do in one round, 81, 91, 3072, two rounds, 144, 148; 1024 of four groups 129, 118,
+        // 768 90, 104, 1400 154, 160, 2048 221, 218; of three groups 3000 255, 264).
         const uint32_t cap = S / 8u;
-        if (g.G <= 2u) return DLC_CAT(table_launch_, DLC_S)<4u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax / 6u - kTableStatic, 1536u, s);
-        if (g.G <= 4u) return DLC_CAT(table_launch_, DLC_S)<8u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax / 3u - kTableStatic, 768u, s);
-        if (g.G <= 8u) return DLC_CAT(table_launch_, DLC_S)<8u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax / 2u - kTableStatic, 512u, s);
-        return DLC_CAT(table_launch_, DLC_S)<16u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax - kTableStatic, 256u, s);
+        if (g.G <= 2u) {
+            const uint32_t rounds = (g.T + 1535u) / 1536u;
+            if (rounds <= 2u && g.T > rounds * 1536u - 256u) return DLC_CAT(table_launch_, DLC_S)<2u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax / 6u - kTableStatic, 0u, s);
+            return DLC_CAT(table_launch_, DLC_S)<4u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax / 6u - kTableStatic, 0u, s);
+        }
+        if (g.G <= 4u) {
+            if (g.T <= 768u || (g.T > 1024u && (g.T <= 1536u || g.G == 3u)))
+                return DLC_CAT(table_launch_, DLC_S)<4u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax / 3u - kTableStatic, 0u, s);
+            return DLC_CAT(table_launch_, DLC_S)<8u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax / 3u - kTableStatic, 0u, s);
+        }
+        if (g.G <= 8u) return DLC_CAT(table_launch_, DLC_S)<8u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax / 2u - kTableStatic, 0u, s);
+        return DLC_CAT(table_launch_, DLC_S)<16u>(g, F, payload, w, epoch, out, capacity, out_bytes, cap, kLdsMax - kTableStatic, 0u, s);
     }
 }
 
-template <uint32_t NW>
+template <uint32_t NW, bool FIN>
 static hipError_t DLC_CAT(encode_attributes_, DLC_S)() {
     constexpr int S = DLC_S;
     const int bytes = (int)(kLdsMax - kTableStatic);
-    const void* ks[] = {reinterpret_cast<const void*>(k_table<S, false, false, NW>), reinterpret_cast<const void*>(k_table<S, false, true, NW>),
-                        reinterpret_cast<const void*>(k_table<S, true, false, NW>), reinterpret_cast<const void*>(k_table<S, true, true, NW>)};
+    const void* ks[] = {reinterpret_cast<const void*>(k_table<S, false, false, NW, FIN>), reinterpret_cast<const void*>(k_table<S, false, true, NW, FIN>),
+                        reinterpret_cast<const void*>(k_table<S, true, false, NW, FIN>), reinterpret_cast<const void*>(k_table<S, true, true, NW, FIN>)};
     for (const void* k : ks) {
         const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (e != hipSuccess) return e;
@@ -740,9 +759,14 @@ static hipError_t DLC_CAT(encode_attributes_, DLC_S)() {
 
 hipError_t DLC_CAT(encode_set_attributes_, DLC_S)() {
     constexpr int S = DLC_S;
-    hipError_t e = DLC_CAT(encode_attributes_, DLC_S)<4u>();
-    if (e == hipSuccess) e = DLC_CAT(encode_attributes_, DLC_S)<8u>();
-    if (e == hipSuccess) e = DLC_CAT(encode_attributes_, DLC_S)<16u>();
+    hipError_t e = DLC_CAT(encode_attributes_, DLC_S)<2u, false>();
+    if (e == hipSuccess) e = DLC_CAT(encode_attributes_, DLC_S)<2u, true>();
+    if (e == hipSuccess) e = DLC_CAT(encode_attributes_, DLC_S)<4u, false>();
+    if (e == hipSuccess) e = DLC_CAT(encode_attributes_, DLC_S)<4u, true>();
+    if (e == hipSuccess) e = DLC_CAT(encode_attributes_, DLC_S)<8u, false>();
+    if (e == hipSuccess) e = DLC_CAT(encode_attributes_, DLC_S)<8u, true>();
+    if (e == hipSuccess) e = DLC_CAT(encode_attributes_, DLC_S)<16u, false>();
+    if (e == hipSuccess) e = DLC_CAT(encode_attributes_, DLC_S)<16u, true>();
     const void* ks[] = {reinterpret_cast<const void*>(k_encode<S, false, false, false, 8u>), reinterpret_cast<const void*>(k_encode<S, false, true, false, 8u>),
                         reinterpret_cast<const void*>(k_encode<S, true, false, false, 8u>), reinterpret_cast<const void*>(k_encode<S, true, true, false, 8u>),
                         reinterpret_cast<const void*>(k_encode<S, false, true, true, 8u>), reinterpret_cast<const void*>(k_encode<S, true, true, true, 8u>),
