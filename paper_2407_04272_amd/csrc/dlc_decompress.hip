@@ -154,6 +154,7 @@ __global__ __launch_bounds__(256) void k_dec_refs(Geom g, FixedLayout F, const u
 constexpr int kWaitLoads = 0x0F70;                    // s_waitcnt vmcnt(0) and nothing else
 constexpr uint32_t kRows = 30;                        // a wavefront's staging area has at least kRows words a lane (two work-groups share a CU's LDS)
 constexpr uint32_t kStage = kRows * kW;
+constexpr uint32_t kStageOfTwo = 1888;                // the same for a work-group of two wavefronts: five of those share the LDS
 constexpr uint32_t kWin = 29;                         // words of a chunk in a window (odd: the lanes' rows start in different banks)
 constexpr uint32_t kDecWaves = 8;                     // wavefronts per work-group; 4 or 2 for tables of fewer groups (a
                                                       // destination's piece of a table can be two groups: no idle wavefronts)
@@ -481,14 +482,16 @@ __device__ __forceinline__ void dec_finish(const DecHead& H, bool valid, uint32_
         if (corrupt) set_status(ctrl, DLC_ECORRUPT);
     }
 }
-constexpr uint32_t kDecPad = 512;  // bytes behind the staging areas: a damaged chunk runs at most 256 codes of 12 bits past its words' start
+// bytes behind the staging areas: a damaged chunk runs at most 256 codes of 12 bits past its words' start, 392 bytes; DecTail is at the end
+constexpr uint32_t kDecPad = 512;
+static_assert(kDecPad - sizeof(DecTail) >= 392u, "reads past the last chunk");
 
 template <bool F16, bool VEC, bool WIDE, uint32_t NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) void k_decode(Geom g, FixedLayout F, const uint8_t* comp, uint64_t comp_bytes,
                                                         Ctrl* ctrl, void* outp, uint32_t wpt, uint32_t iters, uint32_t stage_words,
                                                         uint32_t* esc_seen, uint32_t* arrived) {
     constexpr uint32_t kDecThreads = 64u * NW;
-    // [1 << LMAX] decode table, NW staging arrays (the scratch before), row matching's bits, padding, DecTail.  All of the kernel's
+    // [1 << LMAX] decode table, NW staging arrays (the scratch before), row matching's bits, padding with DecTail.  All of the kernel's
     // LDS is in this one piece, which therefore starts at LDS address 0: a masked window is a table entry's address as it is
     extern __shared__ __align__(16) uint32_t s_lut[];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -498,7 +501,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
     const uint32_t lut_n = 1u << g.LMAX;
     DecScratch& sc = *reinterpret_cast<DecScratch*>(s_lut + lut_n);
     DecTail& tail = *reinterpret_cast<DecTail*>(reinterpret_cast<unsigned char*>(s_lut + lut_n) + dec_area_bytes(NW, stage_words, g.K) +
-                                                (g.lz ? NW * kSkipWords * 4u : 0u) + kDecPad);
+                                                (g.lz ? NW * kSkipWords * 4u : 0u) + kDecPad - sizeof(DecTail));
     auto group_head = [&](uint32_t grp) { return dec_group_head(g, F, comp, tl * g.G + grp, lane); };
     const uint32_t grp_first = b * iters * NW + wave;
     GroupHead gh;
@@ -522,7 +525,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
     };
     auto put_group = [&](const GroupPlace& P, const uint32_t (&w)[kRows]) {
 #pragma unroll
-        for (uint32_t k = 0; k < kRows; ++k) stage[k * kW + lane] = __builtin_bitreverse32(w[k]);
+        for (uint32_t k = 0; k < kRows; ++k)
+            if (NW != 2u || (k + 1u) * kW <= kStageOfTwo || k * kW + lane < stage_words) stage[k * kW + lane] = __builtin_bitreverse32(w[k]);
         for (uint32_t k = kStage + lane; k < P.total; k += kW) stage[k] = __builtin_bitreverse32(P.words[k]);
     };
     // A window: the words of every chunk from its lane's `from` on (counted inside the chunk), min(TL, kWin) a chunk, by
@@ -997,8 +1001,10 @@ hipError_t launch_decompress(const Geom& g, const uint8_t* comp, uint64_t comp_b
         const uint32_t wpt = (bpt + iters - 1) / iters;  // work-groups per table
         dim3 grid(g.T * wpt), block(64 * nw);
         // a grid that leaves compute units free can have larger staging areas: 6 bits a symbol
-        const uint32_t stage = (uint64_t)g.T * wpt <= 256u ? 3072u : kStage;
-        const size_t sm = ((size_t)4 << g.LMAX) + dec_area_bytes(nw, stage, g.K) + (g.lz ? (size_t)nw * kSkipWords * 4 : 0) + kDecPad + sizeof(DecTail);
+        // (LDS comes in pieces of 1280 bytes: with 1888 words a wavefront, work-groups of two take 25 of the 128, and five fit a
+        // compute unit; 1184 tables of 256 elements, one round of them, 14.9 us, with 1920 words 19.4)
+        const uint32_t stage = (uint64_t)g.T * wpt <= 256u ? 3072u : (nw == 2u ? kStageOfTwo : kStage);
+        const size_t sm = ((size_t)4 << g.LMAX) + dec_area_bytes(nw, stage, g.K) + (g.lz ? (size_t)nw * kSkipWords * 4 : 0) + kDecPad;
         if (prof_on(pl, P_DECODE)) prof_begin(prof, P_DECODE, s);
         // Up to two groups a compute unit: a work-group each (us: one group 24, now 15; 208 groups 30.5, now 18; 512 groups of 2.2 and
         // 4.4 bits a symbol 23.8 and 29.2, now 22.7 and 23.5).  More than the chip holds at once, and a wavefront a
@@ -1035,7 +1041,7 @@ hipError_t launch_decompress(const Geom& g, const uint8_t* comp, uint64_t comp_b
 
 template <uint32_t NW>
 static hipError_t decode_set_attributes() {
-    const int bytes = (4 << kLmaxLimit) + (int)dec_area_bytes(NW, 3072u, 4096u) + (int)(NW * kSkipWords * 4) + (int)(kDecPad + sizeof(DecTail));
+    const int bytes = (4 << kLmaxLimit) + (int)dec_area_bytes(NW, 3072u, 4096u) + (int)(NW * kSkipWords * 4) + (int)kDecPad;
     const void* ks[] = {reinterpret_cast<const void*>(k_decode<false, false, false, NW>), reinterpret_cast<const void*>(k_decode<false, true, false, NW>),
                         reinterpret_cast<const void*>(k_decode<true, false, false, NW>), reinterpret_cast<const void*>(k_decode<true, true, false, NW>),
                         reinterpret_cast<const void*>(k_decode<false, false, true, NW>), reinterpret_cast<const void*>(k_decode<false, true, true, NW>),

@@ -117,7 +117,7 @@ def test_lanes_without_bits_until_after_a_new_window(side, T, groups, D, refs, w
     bins[:, :, :refs, side] = bins[:, :1, :1, side]  # one row of the table again and again
     x = (bins * (2 * float(EB))).astype(dtype).reshape(T, groups * 64 * rows, D)
     o = oracle.compress(x, np.full(T, EB, np.float32), 512, S, 12, row_match=True)
-    q = o.data[48:].view(np.uint64)  # escapes, words, then the sections' offsets
+    q = o.data[48:104].view(np.uint64)  # escapes, words, then the sections' offsets
     ng = T * groups
     starts = o.data[int(q[2]):int(q[2]) + 4 * ng].view(np.uint32).astype(np.int64)
     words = np.diff(np.append(starts, int(q[1])))
@@ -128,3 +128,20 @@ def test_lanes_without_bits_until_after_a_new_window(side, T, groups, D, refs, w
     assert np.all(busy.max(-1) * 32 * refs >= 64 * 896)             # and the others need a new one before the first bit of it,
     assert busy.max(-1).min() <= 54                                 # in some group without a second one afterwards
     _check(T, groups * 64 * rows, D, S, dtype, True, x)
+
+
+@pytest.mark.parametrize("T,B,D,dtype", [(520, 128, 128, np.float32), (270, 251, 128, np.float32), (520, 128, 128, np.float16)])
+def test_groups_around_the_staging_area_of_two_wavefronts(T, B, D, dtype):
+    """One or two groups a table, more than 512 in all, of 1536 to 2020 words: staged as a whole up to 1888."""
+    S = 256
+    rng = np.random.default_rng(T + B)
+    share = np.linspace(0.0, 0.5, T)[:, None, None]  # of elements of sixteen symbols, else of eight
+    bins = np.where(rng.random((T, B, D)) < share, rng.integers(0, 16, (T, B, D)), rng.integers(0, 8, (T, B, D))) - 4
+    x = (bins * (2 * float(EB))).astype(dtype)
+    o = oracle.compress(x, np.full(T, EB, np.float32), 512, S, 12)
+    q = o.data[48:104].view(np.uint64)
+    ng = T * ((B * D + 64 * S - 1) // (64 * S))
+    words = np.diff(np.append(o.data[int(q[2]):int(q[2]) + 4 * ng].view(np.uint32).astype(np.int64), int(q[1])))
+    for lo, hi in ((1536, 1856), (1856, 1888), (1888, 1920), (1920, 2100)):
+        assert np.any((words > lo) & (words <= hi)), (lo, hi, words.min(), words.max())
+    _check(T, B, D, S, dtype, False, x)
