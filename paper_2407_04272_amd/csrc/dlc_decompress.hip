@@ -1009,8 +1009,11 @@ hipError_t launch_decompress(const Geom& g, const uint8_t* comp, uint64_t comp_b
         // Up to two groups a compute unit: a work-group each (us: one group 24, now 15; 208 groups 30.5, now 18; 512 groups of 2.2 and
         // 4.4 bits a symbol 23.8 and 29.2, now 22.7 and 23.5).  More than the chip holds at once, and a wavefront a
         // group is the shorter way (720 groups: 24 and 29 against 34 and 37).  Sixteen wavefronts, and parts half as long, are no
-        // faster: they need more rounds.
-        const bool split = !g.lz && g.NG <= 512u;
+        // faster: they need more rounds.  Nor is it a gain where a group has 16 turns or fewer, for what is split is a chain too
+        // short for the rounds (512 groups of chunks of 64, 2.2 and 6 bits a symbol: 16.1 and 22.2, a wavefront a group 13.1 and
+        // 18.9; 256 tables of 4096 elements 14.0, so 13.3; of 24 and 32 turns 17.2 and 16.2, a wavefront a group 17.8 both).
+        const uint32_t turns = (std::min(g.n, kW * g.S) + kW * kV - 1u) / (kW * kV);
+        const bool split = !g.lz && g.NG <= 512u && turns > 16u;
         const SplitLds L = split_lds(g, kSplitWaves);
 #define DLC_DEC3(FF, V, W, N) hipLaunchKernelGGL((k_decode<FF, V, W, N>), grid, block, sm, s, g, F, comp, (uint64_t)comp_bytes, w.ctrl, out, wpt, iters, stage, w.dec_esc, w.dec_arrive)
 #define DLC_DEC2(FF, V, N) do { if (g.R > 512u) DLC_DEC3(FF, V, true, N); else DLC_DEC3(FF, V, false, N); } while (0)

@@ -120,3 +120,15 @@ def test_words_behind_a_chunks_codewords_do_not_matter(extra):
     rec = torch.full(x.shape, 7.0, dtype=torch.float32, device="cuda")
     assert ctx.decompress(to_device(out), out.size, rec) == 0 and ctx.sync_status() == 0
     assert np.array_equal(rec.cpu().numpy().view(np.uint32), orec.view(np.uint32))
+
+
+@pytest.mark.parametrize("kind", [("fixed", 23), ("gauss", 2), ("gauss", 60), ("steep", 12), ("escapes", 20)], ids=lambda k: f"{k[0]}{k[1]}")
+@pytest.mark.parametrize("T,B,D,S,dtype", [
+    (3, 64, 64, 256, np.float32), (3, 241, 17, 256, np.float32),  # 16 turns (a wavefront a group) and one element more
+    (301, 90, 49, 128, np.float32),   # 18 turns, more than 256 groups
+    (2, 192, 64, 128, np.float16),    # a whole group of chunks of 128, and half of one
+    (512, 65, 64, 128, np.float32), (513, 65, 64, 128, np.float32),  # as many groups as there are parts for, and one more
+])
+def test_groups_of_few_turns(kind, T, B, D, S, dtype):
+    rng = np.random.default_rng(T * 1000 + B)
+    _round_trip((_bins(rng, kind, T * B * D) * (2.0 * float(EB))).astype(dtype).reshape(T, B, D), S)
