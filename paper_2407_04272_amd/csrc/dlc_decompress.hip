@@ -989,22 +989,37 @@ hipError_t launch_decompress(const Geom& g, const uint8_t* comp, uint64_t comp_b
         hipLaunchKernelGGL(k_dec_refs, dim3(g.T), dim3(256), 0, s, g, F, comp, comp_bytes, w.dtab, w.ctrl);
     {
         // a work-group decodes `iters` blocks of nw groups of one table, a wavefront each, and no more wavefronts than a table
-        // has groups.  More blocks spread the cost of its decode table, a fifth of its time with one; more work-groups fill the
-        // chip and even out the compute units.  Where the stores bound the whole (fp32), a second round of work-groups fills the
-        // gaps of the first (512 MiB: two rounds 111 us, one of two blocks 117); where they do not, one round is the shorter way
-        // (1024 blocks, half precision: 94 us, now 77; 512 blocks, row matching, where most rows are not stored: 66, now 57)
-        // (a small grid takes the wavefronts all the same: they make the decode table sooner)
+        // has groups (a small grid, of row matching or of groups of few turns, takes eight all the same: they make the decode table sooner)
         const uint32_t nw = (g.G >= 6u || (uint64_t)g.T * g.G <= 512u) ? kDecWaves : (g.G >= 3u ? 4u : 2u);
         const uint32_t bpt = (g.G + nw - 1) / nw;
-        const uint64_t blocks = (uint64_t)g.T * bpt;
-        const uint32_t iters = (uint32_t)std::min<uint64_t>(4, std::max<uint64_t>(1, blocks / (f16 ? 512u : (g.lz ? 256u : 2048u))));
+        auto lds_bytes = [&](uint32_t stage) { return ((size_t)4 << g.LMAX) + dec_area_bytes(nw, stage, g.K) + (g.lz ? (size_t)nw * kSkipWords * 4 : 0) + kDecPad; };
+        const uint32_t stage_full = nw == 2u ? kStageOfTwo : kStage;  // (of a chip that is full)
+        // More blocks a work-group spread the cost of its decode table; more work-groups fill the chip and even out the compute
+        // units.  Where the stores bound the whole (fp32), that is one block each, and the next work-groups fill the gaps (512
+        // MiB, 1024 blocks: 111 us, with two blocks each 119; 1536 159, 180).  Where they do not (half precision; row matching, where
+        // most rows are not stored), the rounds of work-groups count, each as long as its blocks and its decode table, which takes
+        // 0.7 of a block (0.5 with row matching, whose blocks are the only ones on their compute unit): one to four blocks, as that
+        // is shortest.  Us a call, one block each and this: half precision, 576 and 1024 blocks 74, 65 and 86, 69, 900 76, 76 (by
+        // twos 87); row matching, 512, 640, 768 and 1024 blocks 114, 105, 152, 137, 164, 164 (by threes 187) and 225, 206.
+        uint32_t iters = 1;
+        if (f16 || g.lz) {
+            const uint32_t per_cu = std::min<uint32_t>(16u / nw, 163840u / (uint32_t)((lds_bytes(stage_full) + 1279u) / 1280u * 1280u));
+            const uint64_t room = 256ull * std::max(1u, per_cu);
+            uint64_t least = ~0ull;
+            for (uint32_t k = 1; k <= 4u; ++k) {
+                const uint64_t rounds = ((uint64_t)g.T * ((bpt + k - 1u) / k) + room - 1u) / room, cost = rounds * (10u * k + (g.lz ? 5u : 7u));
+                if (cost < least) { least = cost; iters = k; }
+            }
+        } else {
+            iters = (uint32_t)std::min<uint64_t>(4, std::max<uint64_t>(1, (uint64_t)g.T * bpt / 2048u));
+        }
         const uint32_t wpt = (bpt + iters - 1) / iters;  // work-groups per table
         dim3 grid(g.T * wpt), block(64 * nw);
         // a grid that leaves compute units free can have larger staging areas: 6 bits a symbol
         // (LDS comes in pieces of 1280 bytes: with 1888 words a wavefront, work-groups of two take 25 of the 128, and five fit a
         // compute unit; 1184 tables of 256 elements, one round of them, 14.9 us, with 1920 words 19.4)
-        const uint32_t stage = (uint64_t)g.T * wpt <= 256u ? 3072u : (nw == 2u ? kStageOfTwo : kStage);
-        const size_t sm = ((size_t)4 << g.LMAX) + dec_area_bytes(nw, stage, g.K) + (g.lz ? (size_t)nw * kSkipWords * 4 : 0) + kDecPad;
+        const uint32_t stage = (uint64_t)g.T * wpt <= 256u ? 3072u : stage_full;
+        const size_t sm = lds_bytes(stage);
         if (prof_on(pl, P_DECODE)) prof_begin(prof, P_DECODE, s);
         // Up to two groups a compute unit: a work-group each (us: one group 24, now 15; 208 groups 30.5, now 18; 512 groups of 2.2 and
         // 4.4 bits a symbol 23.8 and 29.2, now 22.7 and 23.5).  More than the chip holds at once, and a wavefront a
