@@ -749,7 +749,7 @@ __device__ __forceinline__ uint32_t wg_scan(uint64_t* state, uint64_t epoch, uin
             const uint32_t first = pm ? (uint32_t)__ffsll((unsigned long long)pm) - 1u : 64u;  // lane of the nearest prefix
             if (__ballot(hole && lane <= first) != 0ull) {  // something nearer than that prefix is not published yet
                 if (++spins > kSpinLimit) {  // never expected; the bound only guarantees termination
-                    if (lane == 0) { set_status(ctrl, DLC_ESTATE); atomicOr(&ctrl->abort, kAbortInternal); }
+                    if (lane == 0) { set_status(ctrl, DLC_ESTATE); atomicOr(&ctrl->abort, 1u); }
                     *dead = true;
                     break;
                 }

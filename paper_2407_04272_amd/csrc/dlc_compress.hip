@@ -254,7 +254,7 @@ __global__ __launch_bounds__(256) void k_post(Geom g, FixedLayout F, const uint3
             __syncthreads();
         }
         if (tid == 0) {  // (clamped; past 2^32 words the format cannot say where a group starts: the call fails)
-            if (all > 0xFFFFFFFFull && xi == 0) { set_status(ctrl, DLC_ECAPACITY); atomicOr(&ctrl->abort, kAbortInternal); }
+            if (all > 0xFFFFFFFFull && xi == 0) { set_status(ctrl, DLC_ECAPACITY); atomicOr(&ctrl->abort, 1u); }
             __hip_atomic_store(&word_end[dst * g.TD + g.TD - 1u], (uint32_t)min(all, 0xFFFFFFFFull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");

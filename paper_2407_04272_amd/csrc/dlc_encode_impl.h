@@ -346,7 +346,7 @@ __device__ __forceinline__ void encode_groups(const GroupJob& J, const void* pay
     for (uint32_t k = 0; k < wave; ++k) excl += s_tot[k];
     bool dead = s_dead != 0u;  // nothing may be written to the container
     if (F.off_payload + 4ull * ((uint64_t)excl + total) > capacity) {
-        if (!dead && lane == 0) { set_status(ctrl, DLC_ECAPACITY); atomicOr(&ctrl->abort, kAbortCapacity); }
+        if (!dead && lane == 0) set_status(ctrl, DLC_ECAPACITY);
         dead = true;
     }
     if (lane == 0) {

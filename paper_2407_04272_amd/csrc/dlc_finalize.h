@@ -106,7 +106,7 @@ __device__ __forceinline__ void finalize_dest(const Geom& g, const FixedLayout& 
         const uint32_t nb = sum_blocks_per_dest(g);
         for (uint32_t i = tid; i < nb; i += NT) bsum[(size_t)dst * nb + i] = 0u;
     }
-    const bool aborted = first && (__hip_atomic_load(&ctrl->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kAbortInternal) != 0;
+    const bool aborted = first && __hip_atomic_load(&ctrl->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
     uint64_t cb_carry = 0, nout_carry = 0;
     for (uint32_t base = 0; base < T; base += NT) {
         const uint32_t t = base + tid;

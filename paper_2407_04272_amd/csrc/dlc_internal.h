@@ -94,16 +94,12 @@ inline __host__ __device__ uint32_t sum_blocks_per_dest(const Geom& g) { return 
 // small control block; `status` is sticky until read by the host, the rest is cleared per call
 struct Ctrl {
     uint32_t ticket;  // ordered work-group ids of the encode kernel
-    uint32_t abort;   // kAbort* bits: why (part of) the call's output is not valid
-    uint32_t dest_done;  // destinations whose container the finalize kernel has finished (zero between calls)
+    uint32_t abort;   // not 0: an internal wait ran out, or the words cannot be numbered: no container of the call is valid
+    uint32_t dest_done;  // destinations whose container is finished (zero between calls)
     uint32_t pad1;
     int32_t status;   // first device-side error
     uint32_t collide; // statistics: a hash match whose rows differ
 };
-
-// Ctrl::abort: a container did not fit its capacity (the finalize kernel finds that out again for the container
-// concerned: other destinations' containers stay valid); an internal wait ran out (nothing of the call is valid)
-constexpr uint32_t kAbortCapacity = 1, kAbortInternal = 2;
 
 struct DecTable {
     uint32_t valid, n_used, sym_lo, n_outliers;
@@ -276,7 +272,7 @@ struct Ws {
     QParam* qp = nullptr;          // [T]
     uint32_t* hist = nullptr;      // [T][K] zero between calls
     uint32_t* hist_view = nullptr; // [T][K] copy of the last call's histogram (inspection)
-    Ctrl* ctrl = nullptr;          // ticket and abort are zero between calls
+    Ctrl* ctrl = nullptr;          // ticket and abort are zero between calls (abort: but after an internal failure)
     TMeta* tmeta = nullptr;        // [T]
     uint16_t* enc = nullptr;       // [T][K]  len << 12 | codeword
     uint8_t* lens = nullptr;       // [T][K]
