@@ -258,7 +258,7 @@ extern "C" int dlc_create(dlc_ctx** out, const dlc_config* cfg) {
         delete c;
         return DLC_EHIP;
     }
-    // (behind the ring: two slots for the statistics' probe bounds and results, 16 bytes a table and two words)
+    // (behind the ring: a slot for the statistics' probe bounds and two for their results, 16 bytes a table and two words)
     if (hipHostMalloc((void**)&c->pin, sizeof(QParam) * g.T * (dlc_ctx::kRing + 3), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         (void)hipFree(base);

@@ -138,8 +138,8 @@ __global__ __launch_bounds__(256) void k_dec_refs(Geom g, FixedLayout F, const u
 // turn and none is moved on under a condition.  `p` counts from 30, from the word before the chunk's first: the
 // window starts two bits before the next codeword, and masked it is a table entry's byte offset as it is.  Measured against
 // two words and a prefetched third in registers, moved on after every look-up, with 12-bit bins converted one by one (75
-// instructions a turn, now 35): 26 tables of 2048 x 64 36.7 us, now 31.0 (a turn of a wavefront 730 cycles, now 600); seven of
-// 2999 x 37 38, now 28; 512 MiB, where the stores bound it, 115.5, now 111.4.
+// instructions a turn, now 35): with a wavefront a group, 26 tables of 2048 x 64 36.7 us, so 31.0 (a turn of a wavefront 730
+// cycles, 600), seven of 2999 x 37 38, so 28 (both are decoded in parts now, see k_decode_split); 512 MiB, where the stores bound it, 115.5, so 111.4.
 //
 // The bit stream words reach the lanes through LDS: the words of a group lie one after the other, so a wavefront copies
 // them as they lie (256 bytes an instruction) and every lane reads its own from where its chunk starts.  A group of more

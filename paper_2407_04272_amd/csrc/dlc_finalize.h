@@ -234,8 +234,8 @@ __device__ __forceinline__ void finalize_dest(const Geom& g, const FixedLayout& 
 // before, or (LATE) when the tables' work-groups say that their codebooks are there; when the last word's place is known, all
 // that is left is to write.  The work-groups with a container's share 0, which write everything but the blocks' other
 // words, are the last: the ticket counter is cleared when nobody can ask for one any more.
-// (A launch of its own costs 4 us whatever it does: one table of 4096 elements 16.4 us a call, now
-// 13.4; 26 tables of 4096 x 64 47.6, now 43.5; 512 MiB 182, now 179.)
+// (A launch of its own costs 4 us whatever it does: one table of 4096 elements 16.6 us a call, so 14.2; 26 tables of 4096 x 64
+// 47.6, so 43.7; 512 MiB 202, so 197.)
 // ------------------------------------------------------------------------------------------------
 constexpr uint32_t kFinishWords = 16;  // words of the code-length blocks a thread has if all symbols are used
 static inline uint32_t finish_groups(const Geom& g, uint32_t nt) { return (g.TD * (g.K / 4u) + nt * kFinishWords - 1u) / (nt * kFinishWords); }

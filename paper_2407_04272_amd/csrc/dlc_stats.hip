@@ -91,8 +91,10 @@ __global__ __launch_bounds__(256) void k_stats_init(uint32_t* mult, uint32_t n_m
 // of a row) and the rows' bytes, on the matrix cores: i32_16x16x64_i8 takes 64 bytes of each of 16 rows, and its operand
 // is what a 16-byte load per lane brings (lane l: row l % 16, piece l / 16), so a row's elements are not moved between
 // lanes at all.  The symbols at the probe bound go the same way, as 16-bit numbers.  Two rows that differ agree in one
-// function with a probability of 2^-8 at most (whatever else is in them: for one value of a differing byte's
-// coefficient at most); four functions of a lane, each a byte further up, make a 32-bit number, four lanes' numbers the hash.
+// function with a probability of 2^-8 at most (whatever else is in them: for one value of a differing byte's coefficient at
+// most; in rows of up to 256 KiB, whose coefficients are all their own).  Four functions of a lane, each a byte further up, make
+// a 32-bit number, in which they agree with 2^-25 at most (a byte that differs by 128, as the sign of an element does, leaves
+// its lowest seven bits as they are), four lanes' numbers the hash.  The counts do not hang on it: rows are compared afterwards.
 // Which bytes a coefficient meets is free as long as it is the same for all rows: a piece past the row's end, or the
 // part of the last piece that is, is replaced by the row's last 16 bytes (elements that come twice change neither the
 // range nor the bound on the probability), and a row past the batch's end by the last one.  Nothing is masked.

@@ -30,7 +30,7 @@ def _payload(rng, shape, wide):
     (250, 40, 16, 256, 1, True), (254, 20, 16, 256, 1, False), (256, 20, 16, 256, 1, False),  # as many work-groups as run at a time, and more
     (9, 300, 64, 256, 1, True), (253, 129, 128, 64, 1, False),  # sixteen
     (300, 70, 16, 256, 1, True), (500, 33, 8, 64, 1, False), (512, 33, 8, 64, 1, False),  # eight
-    (33, 20, 16, 64, 24, False), (128, 17, 8, 64, 17, True), (128, 17, 8, 64, 26, False),  # two; several containers, more than run at a time
+    (33, 20, 16, 64, 24, False), (128, 17, 8, 64, 17, True), (128, 17, 8, 64, 26, False),  # four; several containers, more than run at a time
     (5, 1100, 64, 64, 1, True), (70, 610, 32, 64, 1, True), (300, 610, 32, 64, 1, False), (20, 610, 32, 64, 3, True),  # three launches
 ])
 def test_same_bytes(T, B, D, S, nd, wide):
