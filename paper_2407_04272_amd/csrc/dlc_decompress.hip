@@ -925,7 +925,8 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(Geom g, Fixed
         // a chunk's codewords end inside its words
         if (__ballot(last && p - kDecBit0 > 32u * gh.cw) != 0ull) bad = true;
         if (gp.n_esc != 0u) {  // uniform over the work-group: verbatim values over the decoded placeholders
-            __syncthreads();   // (all stores of the work-group are out)
+            __builtin_amdgcn_s_waitcnt(kWaitLoads);  // (stores count as well: all of the work-group's are out behind the barrier,
+            __syncthreads();                         // which waits for none by itself)
             bool off_range = false;
             for (uint32_t r = tid; r < gp.n_esc; r += NT) {
                 const uint32_t at = gp.words[gp.total + 2u * r] - gstart, raw = gp.words[gp.total + 2u * r + 1u];
