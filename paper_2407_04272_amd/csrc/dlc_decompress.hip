@@ -1048,8 +1048,11 @@ hipError_t launch_decompress(const Geom& g, const uint8_t* comp, uint64_t comp_b
 #undef DLC_DEC3
         if (g.lz) {
             // tables apart and one after the other, us: one of 65536 rows 31 and 16; 9, 26, 64 and 128 of 8192 x 128 12.8 and 10.0,
-            // 25.1 and 22.4, 48.5 and 49.4, 100 and 104; 65 and 100, which the XCDs cannot share alike, 51.7 and 50.4, 76.9 and 77.1
-            const TableOrder order(std::min<uint32_t>((g.B * (g.D / 4u) + 255u) / 256u, 256u), g.T >= 64u && g.T % 8u == 0u);
+            // 25.1 and 22.4, 48.5 and 49.4, 100 and 104; 65 and 100, which the XCDs cannot share alike, 51.7 and 50.4, 76.9 and 77.1.
+            // The call with 300 of 2048 x 128 165.5 and 167.8.  Tables whose work-groups an XCD runs all at once are as well there,
+            // where most of what they read was written: the call with one of 300 x 16 20.4 and 21.2, with 100 of 2048 x 64 50.3 and 51.4.
+            const uint32_t bx = std::min<uint32_t>((g.B * (g.D / 4u) + 255u) / 256u, 256u);
+            const TableOrder order(bx, bx < 256u || g.T % 8u == 0u || g.T > 128u);
             if (f16) hipLaunchKernelGGL(k_row_copy<uint2>, dim3(order.groups(g.T)), dim3(256), 0, s, g, comp, (uint64_t)comp_bytes, w.dtab, out, order);
             else hipLaunchKernelGGL(k_row_copy<uint4>, dim3(order.groups(g.T)), dim3(256), 0, s, g, comp, (uint64_t)comp_bytes, w.dtab, out, order);
         }

@@ -452,8 +452,9 @@ hipError_t launch_stats(const Geom& g, const void* payload, const Ws& w, uint32_
     uint32_t logL = 0;
     while (logL < 6 && (1u << logL) < pieces) ++logL;
     // tables apart and one after the other, us: one of 65536 rows 49 and 48; 9, 12, 15, 26, 64 and 128 of 8192 x 128 8.8 and 8.4, 9.8
-    // and 9.0, 9.9 and 11.2, 16.5 and 17.8, 32 and 38, 67 and 76
-    const TableOrder order(blocks_x, g.T > 12u);
+    // and 9.0, 9.9 and 11.2, 16.5 and 17.8, 32 and 38, 67 and 76; of few rows it is all the same or better apart (the call with five
+    // of 2048 x 64 38.8 and 39.8)
+    const TableOrder order(blocks_x, g.T > 12u || blocks_x <= 8u);
 #define DLC_ST_VERIFY(FF, NW) hipLaunchKernelGGL((k_stats_verify<FF, NW>), dim3(order.groups(g.T)), block, 0, s, payload, g, probe, w.st_own, w.ctrl, order, logL)
     if (g.dtype == DLC_F16) { if (vec) DLC_ST_VERIFY(true, 4); else DLC_ST_VERIFY(true, 1); }
     else { if (vec) DLC_ST_VERIFY(false, 4); else DLC_ST_VERIFY(false, 1); }

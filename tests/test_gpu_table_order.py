@@ -8,10 +8,10 @@ from gpu_util import DeviceRun, to_device
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("T", [1, 7, 8, 12, 13, 16, 47, 48, 49, 63, 64, 65, 72, 73])
-def test_every_table_once(T):
+@pytest.mark.parametrize("T,B,D", [(T, 300, 16) for T in (1, 7, 8, 12, 13, 16, 47, 48, 49, 64, 73)] +  # two work-groups a table, five in the copy
+                         [(T, 2085, 128) for T in (1, 8, 9, 12, 13, 17)])                          # nine, and as many as the copy has
+def test_every_table_once(T, B, D):
     from paper_2407_04272_amd import binding as b
-    B, D = 300, 16  # (two work-groups a table in the row kernels, five in the copy)
     rng = np.random.default_rng(T)
     x = (rng.standard_normal((T, 90, D)) * 0.1).astype(np.float32)
     x = np.take_along_axis(x, rng.integers(0, 90, (T, B, 1)), axis=1)
