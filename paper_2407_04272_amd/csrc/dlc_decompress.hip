@@ -76,48 +76,6 @@ __device__ __forceinline__ DecHead dec_validate(const Geom& g, const FixedLayout
 }
 
 // ------------------------------------------------------------------------------------------------
-// Row matching only: one work-group per table checks that every reference points back, at a row that is coded,
-// and leaves the verdict (and where the references are) for the row-copy kernel.
-// ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_dec_refs(Geom g, FixedLayout F, const uint8_t* comp, uint64_t comp_bytes,
-                                                  DecTable* dtab, Ctrl* ctrl) {
-    __shared__ uint32_t s_ok;
-    const uint32_t tid = threadIdx.x, t = blockIdx.x;
-    const uint32_t dst = t / g.TD, tl = t - dst * g.TD;
-    comp += (uint64_t)dst * comp_bytes;
-    const DecHead H = dec_validate(g, F, comp, comp_bytes, tl);
-    if (tid == 0) s_ok = H.ok ? 1u : 0u;
-    __syncthreads();
-    if (H.ok && H.ref_off != 0) {
-        const uint32_t* ref = reinterpret_cast<const uint32_t*>(comp + H.ref_off);
-        for (uint32_t r0 = tid; r0 < g.B; r0 += 256u * 4u) {  // four rows in flight per thread
-            uint32_t o[4], oo[4];
-#pragma unroll
-            for (uint32_t k = 0; k < 4; ++k) {
-                const uint32_t r = r0 + k * 256u;
-                o[k] = r < g.B ? ref[r] : 0u;
-            }
-#pragma unroll
-            for (uint32_t k = 0; k < 4; ++k) {
-                const uint32_t r = r0 + k * 256u;
-                oo[k] = (r < g.B && o[k] <= r) ? ref[o[k]] : 0xFFFFFFFFu;
-            }
-#pragma unroll
-            for (uint32_t k = 0; k < 4; ++k)
-                if (r0 + k * 256u < g.B && oo[k] != o[k]) s_ok = 0;  // (a reference forward left oo at "no row")
-        }
-    }
-    __syncthreads();
-    if (tid == 0) {
-        DecTable D;
-        D.valid = s_ok; D.n_used = H.n_used; D.sym_lo = H.sym_lo; D.n_outliers = H.n_esc; D.ebx2 = H.ebx2; D.pad = 0;
-        D.ref_off = H.ref_off;
-        dtab[t] = D;
-        if (!s_ok) set_status(ctrl, DLC_ECORRUPT);
-    }
-}
-
-// ------------------------------------------------------------------------------------------------
 // chunk-parallel decode.  A work-group belongs to one table: it checks the container's header and the table's
 // directory entry, rebuilds the canonical code from the stored lengths into an LDS decode table, and then decodes
 // `iters` consecutive blocks of NW groups (NW = wavefronts of the work-group), one wavefront per group, lane l walking chunk l.  Each lane keeps
@@ -154,7 +112,8 @@ __global__ __launch_bounds__(256) void k_dec_refs(Geom g, FixedLayout F, const u
 constexpr int kWaitLoads = 0x0F70;                    // s_waitcnt vmcnt(0) and nothing else
 constexpr uint32_t kRows = 30;                        // a wavefront's staging area has at least kRows words a lane (two work-groups share a CU's LDS)
 constexpr uint32_t kStage = kRows * kW;
-constexpr uint32_t kStageOfTwo = 1888;                // the same for a work-group of two wavefronts: five of those share the LDS
+constexpr uint32_t kStageSmall = 1888;                // the same for a work-group of two wavefronts (five of those share the LDS) and with row
+                                                      // matching, whose bits need LDS as well
 constexpr uint32_t kWin = 29;                         // words of a chunk in a window (odd: the lanes' rows start in different banks)
 constexpr uint32_t kDecWaves = 8;                     // wavefronts per work-group; 4 or 2 for tables of fewer groups (a
                                                       // destination's piece of a table can be two groups: no idle wavefronts)
@@ -463,9 +422,11 @@ __device__ __forceinline__ void dec_check_escapes(const Geom& g, const DecHead& 
     if (big) tail.bad = 1u;
 }
 
-// The end of a work-group, one of wpt of its table.  my_esc: the escapes its wavefront has applied.
+// The end of a work-group, one of wpt of its table.  my_esc: the escapes its wavefront has applied.  dtab (row matching): gets
+// the table's references where every work-group of the table has found its part in order, for the kernel that copies rows.
+constexpr uint32_t kTableBad = 0x80000000u;  // in the count of arrivals (of less than 2^31 work-groups)
 __device__ __forceinline__ void dec_finish(const DecHead& H, bool valid, uint32_t my_esc, uint32_t wpt, Ctrl* ctrl, uint32_t* esc_seen,
-                                           uint32_t* arrived, DecTail& tail, uint32_t tid) {
+                                           uint32_t* arrived, DecTable* dtab, DecTail& tail, uint32_t tid) {
     if (my_esc != 0u && (tid & 63u) == 0u) {
         __hip_atomic_fetch_add(esc_seen, my_esc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // counted before the work-group says it is done
@@ -473,11 +434,17 @@ __device__ __forceinline__ void dec_finish(const DecHead& H, bool valid, uint32_
     __syncthreads();
     if (tid == 0) {
         bool corrupt = !valid || tail.bad != 0u;
+        if (corrupt && dtab) {
+            __hip_atomic_fetch_or(arrived, kTableBad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the same)
+        }
         // the last work-group of the table: all escapes of the table have been seen
-        if (__hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == wpt) {
+        const uint32_t before = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((before & ~kTableBad) + 1u == wpt) {
             const uint32_t seen = __hip_atomic_exchange(esc_seen, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (valid && seen != H.n_esc) corrupt = true;
+            if (dtab) dtab->ref_off = corrupt || (before & kTableBad) ? 0ull : H.ref_off;
         }
         if (corrupt) set_status(ctrl, DLC_ECORRUPT);
     }
@@ -486,10 +453,10 @@ __device__ __forceinline__ void dec_finish(const DecHead& H, bool valid, uint32_
 constexpr uint32_t kDecPad = 512;
 static_assert(kDecPad - sizeof(DecTail) >= 392u, "reads past the last chunk");
 
-template <bool F16, bool VEC, bool WIDE, uint32_t NW>
+template <bool F16, bool VEC, bool WIDE, uint32_t NW, bool LZ>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) void k_decode(Geom g, FixedLayout F, const uint8_t* comp, uint64_t comp_bytes,
                                                         Ctrl* ctrl, void* outp, uint32_t wpt, uint32_t iters, uint32_t stage_words,
-                                                        uint32_t* esc_seen, uint32_t* arrived) {
+                                                        uint32_t* esc_seen, uint32_t* arrived, DecTable* dtab) {
     constexpr uint32_t kDecThreads = 64u * NW;
     // [1 << LMAX] decode table, NW staging arrays (the scratch before), row matching's bits, padding with DecTail.  All of the kernel's
     // LDS is in this one piece, which therefore starts at LDS address 0: a masked window is a table entry's address as it is
@@ -501,7 +468,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
     const uint32_t lut_n = 1u << g.LMAX;
     DecScratch& sc = *reinterpret_cast<DecScratch*>(s_lut + lut_n);
     DecTail& tail = *reinterpret_cast<DecTail*>(reinterpret_cast<unsigned char*>(s_lut + lut_n) + dec_area_bytes(NW, stage_words, g.K) +
-                                                (g.lz ? NW * kSkipWords * 4u : 0u) + kDecPad - sizeof(DecTail));
+                                                (LZ ? NW * kSkipWords * 4u : 0u) + kDecPad - sizeof(DecTail));
     auto group_head = [&](uint32_t grp) { return dec_group_head(g, F, comp, tl * g.G + grp, lane); };
     const uint32_t grp_first = b * iters * NW + wave;
     GroupHead gh;
@@ -526,7 +493,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
     auto put_group = [&](const GroupPlace& P, const uint32_t (&w)[kRows]) {
 #pragma unroll
         for (uint32_t k = 0; k < kRows; ++k)
-            if (NW != 2u || (k + 1u) * kW <= kStageOfTwo || k * kW + lane < stage_words) stage[k * kW + lane] = __builtin_bitreverse32(w[k]);
+            if ((NW != 2u && !LZ) || (k + 1u) * kW <= kStageSmall || k * kW + lane < stage_words) stage[k * kW + lane] = __builtin_bitreverse32(w[k]);
         for (uint32_t k = kStage + lane; k < P.total; k += kW) stage[k] = __builtin_bitreverse32(P.words[k]);
     };
     // A window: the words of every chunk from its lane's `from` on (counted inside the chunk), min(TL, kWin) a chunk, by
@@ -577,17 +544,49 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
         if (gp.ok) fetch(gp);
     }
     if (H.ok && tl == 0 && b == 0) dec_check_escapes<NW>(g, H, comp, tail, tid);
-    const bool valid = dec_table<WIDE, kDecThreads>(g, H, my_len, s_lut, sc, tid);
     uint32_t my_esc = 0;   // escapes this wavefront has applied (uniform)
     bool bad = false;      // something in this wavefront's groups does not add up
+    // row matching: which rows of a group refer to another row, as a bit per row in LDS (at most 64*S/4 rows), and whether
+    // every reference points back, at a row that is coded
+    const uint32_t* const ref = LZ && H.ok && H.ref_off ? reinterpret_cast<const uint32_t*>(comp + H.ref_off) : nullptr;
+    uint32_t* const skipbits = reinterpret_cast<uint32_t*>(s_lut + lut_n) + dec_area_bytes(NW, stage_words, g.K) / 4u + wave * kSkipWords;
+    auto mark_rows = [&](uint32_t grp) {
+        const uint32_t gstart = grp * (kW * g.S), row_lo = gstart / g.D, last_el = gstart + min(g.n - gstart, kW * g.S) - 1u;
+        const uint32_t n_rows = last_el / g.D - row_lo + 1u;  // <= 64*S/4 because dim % 4 == 0 here
+        for (uint32_t r0 = 0; r0 < n_rows; r0 += 128u) {  // uniform trip count; two rows of a lane in flight
+            uint32_t o[2], oo[2];
+#pragma unroll
+            for (uint32_t k = 0; k < 2u; ++k) o[k] = ref[row_lo + min(r0 + k * 64u + lane, n_rows - 1u)];
+#pragma unroll
+            for (uint32_t k = 0; k < 2u; ++k) {
+                const uint32_t row = row_lo + min(r0 + k * 64u + lane, n_rows - 1u);
+                oo[k] = ref[min(o[k], row)];
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < 2u; ++k) {
+                const uint32_t row = row_lo + min(r0 + k * 64u + lane, n_rows - 1u);
+                bad |= o[k] > row || oo[k] != o[k];
+                const uint64_t m = __ballot(o[k] != row);
+                if (lane == 0 && r0 + k * 64u < n_rows) { skipbits[r0 / 32u + 2u * k] = (uint32_t)m; skipbits[r0 / 32u + 2u * k + 1u] = (uint32_t)(m >> 32); }
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+    // Past the caches where nearly all of the output comes from here; where many rows are copies (of the last 64, a quarter or more)
+    // the rows they are copied from stay in the caches for that.
+    bool stream = true;
+    if (LZ && ref != nullptr && grp_first < g.G) {
+        const uint32_t row = g.B - 1u - min(lane, g.B - 1u), o = ref[row];
+        mark_rows(grp_first);
+        stream = __popcll(__ballot(o != row)) < 16;
+    }
+    const bool valid = dec_table<WIDE, kDecThreads>(g, H, my_len, s_lut, sc, tid);
     if (valid) {
         const float ebx2 = H.ebx2;
         const uint32_t lut_mask = (lut_n - 1u) << 2;
         uint32_t half_high = kHalfHigh;
         asm("" : "+v"(half_high));  // (a register: an AND-OR takes one other constant at most)
         uint8_t* tab = static_cast<uint8_t*>(outp) + (size_t)t * g.n * g.es;
-        const uint32_t* const ref = H.ref_off ? reinterpret_cast<const uint32_t*>(comp + H.ref_off) : nullptr;
-        uint32_t* const skipbits = reinterpret_cast<uint32_t*>(s_lut + lut_n) + dec_area_bytes(NW, stage_words, g.K) / 4u + wave * kSkipWords;
         for (uint32_t it = 0; it < iters; ++it) {
             const uint32_t grp = grp_first + it * NW;
             if (grp >= g.G) break;  // whole wavefront
@@ -595,6 +594,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
                 gh = group_head(grp);
                 gp = group_place(gh);
                 if (gp.ok) fetch(gp);
+                if (LZ && ref != nullptr) mark_rows(grp);
             }
             if (!gp.ok) {
                 bad = true;
@@ -638,29 +638,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
             };
             const uint32_t gstart = grp * (kW * g.S), in_group = min(g.n - gstart, kW * g.S);  // (the table can end in this group)
             uint8_t* const gout = tab + (size_t)gstart * g.es;
-            // row matching: which rows of this group refer to another row, as a bit per row in LDS (at most 64*S/4 rows)
             const uint32_t row_lo = gstart / g.D;
             // local / D as a multiplication (a division of its own is a third of a turn's instructions): with the reciprocal
             // rounded up it is exact while local * D < 2^32, and local < 64 * S + D
             const uint32_t row_magic = (ref != nullptr && g.D > 1u && g.D <= 32768u) ? 0xFFFFFFFFu / g.D + 1u : 0u;
-            if (ref != nullptr) {
-                const uint32_t last_el = gstart + in_group - 1u;
-                const uint32_t n_rows = last_el / g.D - row_lo + 1u;  // <= 64*S/4 because dim % 4 == 0 here
-                for (uint32_t r0 = 0; r0 < n_rows; r0 += 64) {  // uniform trip count
-                    const uint32_t r = r0 + lane;
-                    const bool refers = r < n_rows && ref[row_lo + r] != row_lo + r;
-                    const uint64_t m = __ballot(refers);
-                    if (lane == 0) { skipbits[r0 / 32u] = (uint32_t)m; skipbits[r0 / 32u + 1u] = (uint32_t)(m >> 32); }
-                }
-                __builtin_amdgcn_wave_barrier();
-            }
             // turn j of the group; EDGE: the table ends in it, so a lane can have fewer than four elements, or none
-            auto turn = [&](auto edge, uint32_t j) {
+            auto turn = [&](auto edge, auto past, uint32_t j) {
                 constexpr bool EDGE = decltype(edge)::value;
                 const uint32_t el = lane * kV + j * (kW * kV);  // the lane's first element, counted from the group's
                 if (__ballot(p >= renew_at) != 0ull) renew();  // (whole wavefront)
                 bool coded = !EDGE || el < in_group;
-                if (ref != nullptr && coded) {  // a row that refers to another has no bits in the stream; it is copied afterwards
+                if (LZ && ref != nullptr && coded) {  // a row that refers to another has no bits in the stream; it is copied afterwards
                     const uint32_t local = gstart + el - row_lo * g.D, r = row_magic ? __umulhi(local, row_magic) : local / g.D;
                     coded = ((skipbits[r >> 5] >> (r & 31u)) & 1u) == 0u;
                 }
@@ -689,11 +677,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
                     p += adv;
                     dec_values<WIDE>(e, half_high, ebx2, v4 + h * 2);
                 }
-                dec_store<F16, VEC, EDGE, true>(gout, el, in_group, v4);
+                dec_store<F16, VEC, EDGE, decltype(past)::value>(gout, el, in_group, v4);
             };
             const uint32_t whole = in_group / (kW * kV);
-            for (uint32_t j = 0; j < whole; ++j) turn(std::false_type{}, j);
-            if (in_group > whole * (kW * kV)) turn(std::true_type{}, whole);
+            if (!LZ || stream) {  // uniform
+                for (uint32_t j = 0; j < whole; ++j) turn(std::false_type{}, std::true_type{}, j);
+            } else {
+                for (uint32_t j = 0; j < whole; ++j) turn(std::false_type{}, std::false_type{}, j);
+            }
+            if (in_group > whole * (kW * kV)) turn(std::true_type{}, std::false_type{}, whole);
             // a chunk's codewords end inside its words
             if (__ballot(32u * wbase + p - kDecBit0 > 32u * cw) != 0ull) bad = true;
             if (n_esc != 0u) {  // uniform over the wavefront: verbatim values over the decoded placeholders
@@ -712,8 +704,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
             }
         }
     }
-    if (bad && lane == 0) tail.bad = 1u;
-    dec_finish(H, valid, my_esc, wpt, ctrl, esc_seen + t, arrived + t, tail, tid);
+    if (__ballot(bad) != 0ull && lane == 0) tail.bad = 1u;
+    dec_finish(H, valid, my_esc, wpt, ctrl, esc_seen + t, arrived + t, LZ ? dtab + t : nullptr, tail, tid);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -939,11 +931,13 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(Geom g, Fixed
         }
     }
     if (bad && lane == 0) tail.bad = 1u;
-    dec_finish(H, valid, my_esc, g.G, ctrl, esc_seen + t, arrived + t, tail, tid);
+    dec_finish(H, valid, my_esc, g.G, ctrl, esc_seen + t, arrived + t, nullptr, tail, tid);
 }
 
 // rows that refer to an earlier row of their table: copies of that row's reconstruction (after the decode kernel).
-// A thread per 16-byte (fp32) / 8-byte (fp16) piece of a row, pieces of a row on neighbouring threads.
+// A thread per 16-byte (fp32) / 8-byte (fp16) piece of a row, pieces of a row on neighbouring threads.  What bounds it: the writes
+// (64 tables of 8192 x 128, 62 % of the rows, 166 MB, in 29 us: 5.7 TB/s).  They go past the caches, so that the rows they are copied
+// from, which the decode kernel left there, stay: 46 us with both the other way round, when every row came from memory.
 template <typename U>
 __global__ __launch_bounds__(256) void k_row_copy(Geom g, const uint8_t* comp, uint64_t comp_bytes, const DecTable* dtab,
                                                   void* outp, TableOrder order) {
@@ -952,9 +946,9 @@ __global__ __launch_bounds__(256) void k_row_copy(Geom g, const uint8_t* comp, u
     if (t >= g.T) return;           // uniform
     const uint32_t dst = t / g.TD;  // the container this table is in
     comp += (uint64_t)dst * comp_bytes;
-    const DecTable D = dtab[t];
-    if (!D.valid || D.ref_off == 0) return;  // uniform
-    const uint32_t* ref = reinterpret_cast<const uint32_t*>(comp + D.ref_off);
+    const uint64_t ref_off = dtab[t].ref_off;
+    if (ref_off == 0) return;  // uniform
+    const uint32_t* ref = reinterpret_cast<const uint32_t*>(comp + ref_off);
     U* tab = reinterpret_cast<U*>(static_cast<uint8_t*>(outp) + (size_t)t * g.n * g.es);
     const uint32_t upr = g.D / 4u;  // pieces per row (four elements each; dim % 4 == 0)
     const uint32_t total = g.B * upr;
@@ -975,10 +969,10 @@ __global__ __launch_bounds__(256) void k_row_copy(Geom g, const uint8_t* comp, u
         if (o[1] != row[1]) v1 = tab[src(1)];
         if (o[2] != row[2]) v2 = tab[src(2)];
         if (o[3] != row[3]) v3 = tab[src(3)];
-        if (o[0] != row[0]) tab[(size_t)i0] = v0;
-        if (o[1] != row[1]) tab[(size_t)i0 + stride] = v1;
-        if (o[2] != row[2]) tab[(size_t)i0 + 2u * stride] = v2;
-        if (o[3] != row[3]) tab[(size_t)i0 + 3u * stride] = v3;
+        if (o[0] != row[0]) __builtin_nontemporal_store(v0, &tab[(size_t)i0]);
+        if (o[1] != row[1]) __builtin_nontemporal_store(v1, &tab[(size_t)i0 + stride]);
+        if (o[2] != row[2]) __builtin_nontemporal_store(v2, &tab[(size_t)i0 + 2u * stride]);
+        if (o[3] != row[3]) __builtin_nontemporal_store(v3, &tab[(size_t)i0 + 3u * stride]);
     }
 }
 
@@ -986,29 +980,27 @@ hipError_t launch_decompress(const Geom& g, const uint8_t* comp, uint64_t comp_b
                              void* prof, hipStream_t s) {
     const bool f16 = g.dtype == DLC_F16;
     const FixedLayout F = fixed_layout(g);
-    if (g.lz)  // before the decode kernel: the row-copy kernel follows the references only where they were checked
-        hipLaunchKernelGGL(k_dec_refs, dim3(g.T), dim3(256), 0, s, g, F, comp, comp_bytes, w.dtab, w.ctrl);
     {
         // a work-group decodes `iters` blocks of nw groups of one table, a wavefront each, and no more wavefronts than a table
         // has groups (a small grid, of row matching or of groups of few turns, takes eight all the same: they make the decode table sooner)
         const uint32_t nw = (g.G >= 6u || (uint64_t)g.T * g.G <= 512u) ? kDecWaves : (g.G >= 3u ? 4u : 2u);
         const uint32_t bpt = (g.G + nw - 1) / nw;
         auto lds_bytes = [&](uint32_t stage) { return ((size_t)4 << g.LMAX) + dec_area_bytes(nw, stage, g.K) + (g.lz ? (size_t)nw * kSkipWords * 4 : 0) + kDecPad; };
-        const uint32_t stage_full = nw == 2u ? kStageOfTwo : kStage;  // (of a chip that is full)
+        const uint32_t stage_full = nw == 2u || g.lz ? kStageSmall : kStage;  // (of a chip that is full)
         // More blocks a work-group spread the cost of its decode table; more work-groups fill the chip and even out the compute
         // units.  Where the stores bound the whole (fp32), that is one block each, and the next work-groups fill the gaps (512
-        // MiB, 1024 blocks: 111 us, with two blocks each 119; 1536 159, 180).  Where they do not (half precision; row matching, where
-        // most rows are not stored), the rounds of work-groups count, each as long as its blocks and its decode table, which takes
-        // 0.7 of a block (0.5 with row matching, whose blocks are the only ones on their compute unit): one to four blocks, as that
-        // is shortest.  Us a call, one block each and this: half precision, 576 and 1024 blocks 74, 65 and 86, 69, 900 76, 76 (by
-        // twos 87); row matching, 512, 640, 768 and 1024 blocks 114, 105, 152, 137, 164, 164 (by threes 187) and 225, 206.
+        // MiB, 1024 blocks: 111 us, with two blocks each 119; 1536 159, 180).  Where they do not (half precision), the rounds of
+        // work-groups count, each as long as its blocks and its decode table, which takes 0.7 of a block: one to four blocks, as
+        // that is shortest.  Us a call, one block each and this: half precision, 576 and 1024 blocks 74, 65 and 86, 69, 900 76, 76
+        // (by twos 87).  (fp32 with row matching lies between the two: 560, 640, 768 and 1200 blocks, where half of the rows and
+        // more are copies 95, 94, 102 and 163, by this rule 90, 88, 97 and 154; where nearly none are 103, 110, 118 and 177 against 108, 116, 124 and 187.)
         uint32_t iters = 1;
-        if (f16 || g.lz) {
+        if (f16) {
             const uint32_t per_cu = std::min<uint32_t>(16u / nw, 163840u / (uint32_t)((lds_bytes(stage_full) + 1279u) / 1280u * 1280u));
             const uint64_t room = 256ull * std::max(1u, per_cu);
             uint64_t least = ~0ull;
             for (uint32_t k = 1; k <= 4u; ++k) {
-                const uint64_t rounds = ((uint64_t)g.T * ((bpt + k - 1u) / k) + room - 1u) / room, cost = rounds * (10u * k + (g.lz ? 5u : 7u));
+                const uint64_t rounds = ((uint64_t)g.T * ((bpt + k - 1u) / k) + room - 1u) / room, cost = rounds * (10u * k + 7u);
                 if (cost < least) { least = cost; iters = k; }
             }
         } else {
@@ -1031,30 +1023,31 @@ hipError_t launch_decompress(const Geom& g, const uint8_t* comp, uint64_t comp_b
         const uint32_t turns = (std::min(g.n, kW * g.S) + kW * kV - 1u) / (kW * kV);
         const bool split = !g.lz && g.NG <= 512u && turns > 16u;
         const SplitLds L = split_lds(g, kSplitWaves);
-#define DLC_DEC3(FF, V, W, N) hipLaunchKernelGGL((k_decode<FF, V, W, N>), grid, block, sm, s, g, F, comp, (uint64_t)comp_bytes, w.ctrl, out, wpt, iters, stage, w.dec_esc, w.dec_arrive)
-#define DLC_DEC2(FF, V, N) do { if (g.R > 512u) DLC_DEC3(FF, V, true, N); else DLC_DEC3(FF, V, false, N); } while (0)
-#define DLC_DEC(FF, V) do { if (nw == 8u) DLC_DEC2(FF, V, 8u); else if (nw == 4u) DLC_DEC2(FF, V, 4u); else DLC_DEC2(FF, V, 2u); } while (0)
+#define DLC_DEC3(FF, V, W, N, LZ) hipLaunchKernelGGL((k_decode<FF, V, W, N, LZ>), grid, block, sm, s, g, F, comp, (uint64_t)comp_bytes, w.ctrl, out, wpt, iters, stage, w.dec_esc, w.dec_arrive, w.dtab)
+#define DLC_DEC2(FF, V, N, LZ) do { if (g.R > 512u) DLC_DEC3(FF, V, true, N, LZ); else DLC_DEC3(FF, V, false, N, LZ); } while (0)
+#define DLC_DEC(FF, V, LZ) do { if (nw == 8u) DLC_DEC2(FF, V, 8u, LZ); else if (nw == 4u) DLC_DEC2(FF, V, 4u, LZ); else DLC_DEC2(FF, V, 2u, LZ); } while (0)
 #define DLC_SPLIT2(FF, V, W) hipLaunchKernelGGL((k_decode_split<FF, V, W>), dim3(g.NG), dim3(64u * kSplitWaves), L.end, s, g, F, comp, (uint64_t)comp_bytes, w.ctrl, out, L, w.dec_esc, w.dec_arrive)
 #define DLC_SPLIT(FF, V) do { if (g.R > 512u) DLC_SPLIT2(FF, V, true); else DLC_SPLIT2(FF, V, false); } while (0)
         if (split) {
             if (f16) { if (g.vec) DLC_SPLIT(true, true); else DLC_SPLIT(true, false); }
             else { if (g.vec) DLC_SPLIT(false, true); else DLC_SPLIT(false, false); }
-        } else if (f16) { if (g.vec) DLC_DEC(true, true); else DLC_DEC(true, false); }
-        else { if (g.vec) DLC_DEC(false, true); else DLC_DEC(false, false); }
+        } else if (g.lz) { if (f16) DLC_DEC(true, true, true); else DLC_DEC(false, true, true); }  // (dim % 4 == 0 there)
+        else if (f16) { if (g.vec) DLC_DEC(true, true, false); else DLC_DEC(true, false, false); }
+        else { if (g.vec) DLC_DEC(false, true, false); else DLC_DEC(false, false, false); }
 #undef DLC_SPLIT
 #undef DLC_SPLIT2
 #undef DLC_DEC
 #undef DLC_DEC2
 #undef DLC_DEC3
         if (g.lz) {
-            // tables apart and one after the other, us: one of 65536 rows 31 and 16; 9, 26, 64 and 128 of 8192 x 128 12.8 and 10.0,
-            // 25.1 and 22.4, 48.5 and 49.4, 100 and 104; 65 and 100, which the XCDs cannot share alike, 51.7 and 50.4, 76.9 and 77.1.
-            // The call with 300 of 2048 x 128 165.5 and 167.8.  Tables whose work-groups an XCD runs all at once are as well there,
-            // where most of what they read was written: the call with one of 300 x 16 20.4 and 21.2, with 100 of 2048 x 64 50.3 and 51.4.
+            // tables apart and one after the other, us a call: one of 65536 rows 56.0 and 43.3; 9, 26, 64, 65, 100 and 128 of 8192 x
+            // 128 40.7 and 39.4, 48.9 and 49.8, 67.6 and 74.4, 90.8 and 95.5, 112.5 and 120.2, 125.1 and 135.2; 300 of 2048 x 128 125.6
+            // and 126.0.  Tables whose work-groups an XCD runs all at once are as well there, where most of what they read was
+            // written: one of 300 x 16 18.8 and 19.9, 100 of 2048 x 64 47.2 and 47.6.
             const uint32_t bx = std::min<uint32_t>((g.B * (g.D / 4u) + 255u) / 256u, 256u);
-            const TableOrder order(bx, bx < 256u || g.T % 8u == 0u || g.T > 128u);
-            if (f16) hipLaunchKernelGGL(k_row_copy<uint2>, dim3(order.groups(g.T)), dim3(256), 0, s, g, comp, (uint64_t)comp_bytes, w.dtab, out, order);
-            else hipLaunchKernelGGL(k_row_copy<uint4>, dim3(order.groups(g.T)), dim3(256), 0, s, g, comp, (uint64_t)comp_bytes, w.dtab, out, order);
+            const TableOrder order(bx, bx < 256u || g.T % 8u == 0u || g.T > 16u);
+            if (f16) hipLaunchKernelGGL(k_row_copy<u32x2>, dim3(order.groups(g.T)), dim3(256), 0, s, g, comp, (uint64_t)comp_bytes, w.dtab, out, order);
+            else hipLaunchKernelGGL(k_row_copy<u32x4>, dim3(order.groups(g.T)), dim3(256), 0, s, g, comp, (uint64_t)comp_bytes, w.dtab, out, order);
         }
         if (prof_on(pl, P_DECODE)) prof_end(prof, P_DECODE, s);
     }
@@ -1064,10 +1057,12 @@ hipError_t launch_decompress(const Geom& g, const uint8_t* comp, uint64_t comp_b
 template <uint32_t NW>
 static hipError_t decode_set_attributes() {
     const int bytes = (4 << kLmaxLimit) + (int)dec_area_bytes(NW, 3072u, 4096u) + (int)(NW * kSkipWords * 4) + (int)kDecPad;
-    const void* ks[] = {reinterpret_cast<const void*>(k_decode<false, false, false, NW>), reinterpret_cast<const void*>(k_decode<false, true, false, NW>),
-                        reinterpret_cast<const void*>(k_decode<true, false, false, NW>), reinterpret_cast<const void*>(k_decode<true, true, false, NW>),
-                        reinterpret_cast<const void*>(k_decode<false, false, true, NW>), reinterpret_cast<const void*>(k_decode<false, true, true, NW>),
-                        reinterpret_cast<const void*>(k_decode<true, false, true, NW>), reinterpret_cast<const void*>(k_decode<true, true, true, NW>)};
+    const void* ks[] = {reinterpret_cast<const void*>(k_decode<false, false, false, NW, false>), reinterpret_cast<const void*>(k_decode<false, false, true, NW, false>),
+                        reinterpret_cast<const void*>(k_decode<false, true, false, NW, false>), reinterpret_cast<const void*>(k_decode<false, true, true, NW, false>),
+                        reinterpret_cast<const void*>(k_decode<true, false, false, NW, false>), reinterpret_cast<const void*>(k_decode<true, false, true, NW, false>),
+                        reinterpret_cast<const void*>(k_decode<true, true, false, NW, false>), reinterpret_cast<const void*>(k_decode<true, true, true, NW, false>),
+                        reinterpret_cast<const void*>(k_decode<false, true, false, NW, true>), reinterpret_cast<const void*>(k_decode<false, true, true, NW, true>),
+                        reinterpret_cast<const void*>(k_decode<true, true, false, NW, true>), reinterpret_cast<const void*>(k_decode<true, true, true, NW, true>)};
     hipError_t e = hipSuccess;
     for (const void* k : ks)
         if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);

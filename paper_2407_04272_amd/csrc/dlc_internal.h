@@ -102,10 +102,7 @@ struct Ctrl {
 };
 
 struct DecTable {
-    uint32_t valid, n_used, sym_lo, n_outliers;
-    float ebx2;
-    uint32_t pad;
-    uint64_t ref_off;  // row matching: byte offset of the table's u32 ref[B] in its container, 0 = none
+    uint64_t ref_off;  // row matching: byte offset of the table's u32 ref[B] in its container, 0: none, or not in order
 };
 
 // ---- device helpers -----------------------------------------------------------------------------
@@ -297,7 +294,7 @@ struct Ws {
     uint32_t* bsum = nullptr;      // [ND][ceil(TD*G / kSumBlock)] words of every block of groups (this call's)
     uint32_t* bsum_next = nullptr; // the next call's, cleared while this call's are read; the two change places after every call
     // decompress
-    DecTable* dtab = nullptr;      // [T] row matching: what the reference check found
+    DecTable* dtab = nullptr;      // [T] row matching: the references that the decode kernel has found in order
     uint32_t* dec_esc = nullptr;   // [T] escapes the decode kernel has applied; zero between calls
     uint32_t* dec_arrive = nullptr;  // [T] work-groups of the decode kernel that are done with the table; zero between calls
     // statistics (allocated on first use)

@@ -127,6 +127,43 @@ def test_damaged_references_are_rejected_on_the_gpu():
     assert plain.sync_status() == b.ECORRUPT
 
 
+@pytest.mark.parametrize("dtype,rows", [(np.float32, 200), (np.float32, 100000), (np.float16, 200), (np.float16, 100000)])
+def test_references_of_many_work_groups(dtype, rows):
+    """Tables of more groups than a work-group decodes, with many repeated rows (decoded through the caches) and with few (past
+    them): the reconstruction is the oracle's; one bad reference, wherever it is, spoils its own table alone."""
+    import torch
+    from paper_2407_04272_amd import binding as b
+    import container_reader as cr
+    T, B, D, S = 3, 1500, 96, 64                           # 36 groups: rows lie across their ends
+    x = _lookups(T, B, D, 17, rows=rows, dtype=dtype)
+    x[:, -1] = x[:, 2]
+    x[:, 700] = x[:, 2]
+    ebs = np.full(T, 2e-3 if dtype == np.float32 else 4e-3, np.float32) * (1 + np.arange(T, dtype=np.float32))
+    ctx, d, out, data, sizes = _compress(x, ebs, S)
+    assert np.array_equal(data, oracle.compress(x, ebs, R, S, 12, row_match=True).data)
+    u = np.uint32 if dtype == np.float32 else np.uint16
+    _, orec = oracle.decompress(data, x.shape, dtype)
+    own = np.arange(B)
+    refers = [np.nonzero(t.ref != own)[0] for t in cr.parse(data).tables]
+    assert all(len(r) * 4 > B for r in refers) == (rows == 200)
+    ref_off = cr.parse(data).tables[1].ref_off
+    last, mid = B - 1, 700
+    for row, value in ((None, 0), (last, mid), (mid, mid + 1), (0, 1), (last, B), (mid, 0x80000000)):
+        bad = data.copy()                                  # (a reference to a row that refers itself; forward; past the table)
+        if row is not None:
+            bad[ref_off + 4 * row:ref_off + 4 * row + 4] = np.frombuffer(np.uint32(value).tobytes(), np.uint8)
+        comp = to_device(np.concatenate([bad, np.zeros(16, np.uint8)]))
+        rec = torch.full_like(d, 7.0)
+        assert ctx.decompress(comp, bad.size, rec) == 0
+        assert ctx.sync_status() == (0 if row is None else b.ECORRUPT), (row, value)
+        r = rec.cpu().numpy()
+        for t in range(T):
+            if row is None or t != 1:
+                assert np.array_equal(r[t].view(u), orec[t].view(u)), (row, value, t)
+        if row is not None:
+            assert np.all(r[1][refers[1][refers[1] != row]] == 7.0), (row, value)
+
+
 def test_random_shapes_rows_and_statistics():
     """A seeded sweep over row lengths (every team size and load width of the row kernels), batch sizes and both
     element types: references, containers, reconstructions and the statistics' distinct-row counts against the
