@@ -226,61 +226,69 @@ __device__ __forceinline__ uint32_t lane_next(uint32_t v, uint32_t last) {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)last, (int)v, 0x130 /* wave_shl:1 */, 0xF, 0xF, false);
 }
 
-// The whole tree of a table with at most 64 used symbols, built by one wavefront in registers (`par`: 128 bytes of LDS for
-// turning children into parents at the end): lane i holds used symbol i (symbol order) on entry.  The merge keeps leaves and merged nodes in ONE list in lane
-// order, rising by weight: a step takes the two at the front off, moves the list up by two lanes and puts their sum
-// behind everything that is not heavier.  That is the two-queue merge's order, ties included: the leaves are in the
-// list from the start, so a leaf comes before every node of its weight, and of two nodes of one weight the older one
-// comes first.  What bounds a step is its chain of dependent instructions, and no lane number in it depends on an
-// earlier step (two queues with their heads read by computed lane numbers, the first form of this loop, took 345
-// cycles a step; k_codebook for 26 tables of 17 to 51 symbols: 23 us, now 13).  Depths come from pointer jumping.  Lengths
-// above LM are limited as described above.  Returns the code length of the symbol the lane came in with.  2 <= n <= 64.
+// The whole tree of a table with at most 64 used symbols and less than 2^30 elements, built by one wavefront in registers (`par`:
+// 256 bytes of LDS for the nodes above the others): lane i holds used symbol i (symbol order) on entry.  The merge keeps leaves
+// and merged nodes in ONE list in lane order, rising by weight: a step takes the two at the front off, moves the list up by two
+// lanes and puts their sum behind everything that is not heavier.  That is the two-queue merge's order, ties included: a weight
+// stands above two bits, 0 for a leaf and 1 for a merged node, so a leaf comes before every node of its weight, and of two nodes of
+// one weight the older one comes first.  The list holds nothing else: leaves and nodes leave it in their own orders, so how many
+// nodes every step took, which are the low two bits of the sum it made, says what is above what.
+// What bounds a step is its chain of dependent instructions, and no lane number in it depends on an earlier step (two queues with
+// their heads read by computed lane numbers, the first form of this loop, took 345 cycles a step, the numbers of what was merged
+// carried along in a second list 150).  Depths come from pointer jumping.  Lengths above LM are limited as described above.
+// Returns the code length of the symbol the lane came in with.  2 <= n <= 64.
+constexpr uint32_t kWaveElements = 1u << 30;  // tables of fewer elements
 __device__ __forceinline__ uint32_t wave_huffman_lengths(uint32_t n, uint32_t LM, uint32_t cnt, uint32_t lane, uint8_t* par) {
     const uint32_t kInf = 0xFFFFFFFFu;
-    // position in (count, symbol) order
+    // position in (count, symbol) order (lanes past n - 1, four at a time at most, have the largest keys)
     uint32_t rank = 0;
-    for (uint32_t j0 = 0; j0 < n; j0 += 4u) {
+    if (__ballot(lane < n && cnt >= 1u << 26) == 0ull) {  // the rule: count and lane are one number
+        const uint32_t key = lane < n ? cnt << 6 | lane : kInf;
+        for (uint32_t j0 = 0; j0 < n; j0 += 4u) {
 #pragma unroll
-        for (uint32_t u = 0; u < 4u; ++u) {  // (lanes past n - 1, four at a time at most, do not count)
-            const uint32_t j = j0 + u, cj = lane_read(cnt, j & 63u);
-            rank += (j < n && (cj < cnt || (cj == cnt && j < lane))) ? 1u : 0u;
+            for (uint32_t u = 0; u < 4u; ++u) rank += lane_read(key, j0 + u) < key ? 1u : 0u;
         }
+    } else {
+        const uint64_t key = (uint64_t)cnt << 32 | lane;
+#pragma clang loop unroll(disable)
+        for (uint32_t j = 0; j < n; ++j) rank += ((uint64_t)lane_read(cnt, j) << 32 | j) < key ? 1u : 0u;
     }
     if (lane >= n) rank = lane;  // idle lanes keep their place
     // the sorted sequence: every lane sends its count to the lane of its rank
     const uint32_t sent = (uint32_t)__builtin_amdgcn_ds_permute((int)(rank << 2), (int)cnt);
-    uint32_t w = lane < n ? sent : kInf;  // weights (a sum of all counts is less than 2^31: kInf is heavier than any)
-    uint32_t id = lane;                   // leaf at sorted position id, or 64 + k: merged node k
-    uint32_t kids = 0;                    // lane k: the two that node k was made of
-    for (uint32_t k = 0; k + 1 < n; ++k) {
-        const uint32_t sum = lane_read(w, 0) + lane_read(w, 1);
-        const uint32_t a = lane_read(id, 0), b = lane_read(id, 1);
-        const uint32_t w1 = lane_next(w, kInf), i1 = lane_next(id, 0u);
-        const uint32_t w2 = lane_next(w1, kInf), i2 = lane_next(i1, 0u);
-        const bool before = w2 <= sum;      // stays in front of the sum: it moves up by two lanes
-        const bool here = w1 <= sum;        // (the one in front of it does, or there is none) the sum's place
-        w = before ? w2 : (here ? sum : w1);
-        id = before ? i2 : (here ? 64u + k : i1);
-        kids = lane == k ? (a | (b << 8)) : kids;
+    uint32_t w = lane < n ? sent << 2 : kInf;  // (a sum of all counts is less than 2^30: kInf is heavier than any)
+    uint32_t w1 = kInf, w2 = kInf;             // the list a lane further on, and two (the last lane keeps what it has)
+    uint32_t sums = 0, steps = 0;              // of all steps, the latest in lane 0
+    for (; steps + 1u < n; steps += 4u) {      // (steps past the last, three at most, are of no consequence)
+#pragma unroll
+        for (uint32_t u = 0; u < 4u; ++u) {
+            w1 = lane_next(w, w1);
+            w2 = lane_next(w1, w2);
+            const uint32_t both = w + w1;
+            const uint32_t sum = lane_read((both & ~3u) | 1u, 0);
+            sums = (uint32_t)__builtin_amdgcn_update_dpp((int)both, (int)sums, 0x138 /* wave_shr:1 */, 0xF, 0xF, false);
+            w = min(max(w1, sum), w2);  // not heavier than the sum: it moves up by two lanes; the sum's place; else by one
+        }
     }
+    const uint32_t made = (uint32_t)__shfl((int)sums, (int)((steps - 1u - lane) & 63u), 64);  // lane k: the sum of step k
+    // step k took nodes [nodes_to - took, nodes_to), and leaves that make them two
+    const uint32_t took = lane + 1u < n ? made & 3u : 0u, nodes_to = wave_incl_scan(took), node = nodes_to - took, leaf = 2u * lane - node;
     if (lane + 1u < n) {
-        par[kids & 127u] = (uint8_t)lane;
-        par[kids >> 8] = (uint8_t)lane;
+        // (one address for each of the two: leaves from 0, nodes from 128 on)
+        par[took == 2u ? 128u + node : leaf] = (uint8_t)lane;
+        par[took == 0u ? leaf + 1u : (took == 1u ? 128u + node : 129u + node)] = (uint8_t)lane;
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     // the node above the leaf at sorted position `lane`; above node `lane` (idle lanes: anything)
-    const uint32_t vpl = par[lane] & 63u, vpn = par[64u + lane] & 63u;
-    // depth of every merged node (lane k = node k, the root is node n-2)
+    const uint32_t vpl = par[lane] & 63u, vpn = par[128u + lane] & 63u;
+    // depth of every merged node (lane k = node k, the root is node n-2), above the node it is counted from
     const uint32_t root = n - 2u;
-    uint32_t p = (lane < root) ? vpn : lane;
-    uint32_t d = (lane < root) ? 1u : 0u;
-    for (int r = 0; r < 6 && __ballot(lane < root && p != root) != 0ull; ++r) {  // (until every node has reached the root)
-        const uint32_t dd = __shfl(d, p, 64), pp = __shfl(p, p, 64);
-        d += dd;
-        p = pp;
-    }
+    uint32_t at = lane < root ? vpn | 1u << 8 : lane;
+    for (int r = 0; r < 6 && __ballot(lane < root && (at & 255u) != root) != 0ull; ++r)  // (until every node has reached the root)
+        at = (at & ~255u) + (uint32_t)__shfl((int)at, (int)(at & 255u), 64);
+    const uint32_t d = at >> 8;
     uint32_t len = lane < n ? __shfl(d, vpl, 64) + 1u : 0u;  // of the leaf at sorted position `lane`
     if (__ballot(len > LM) != 0ull) {
         // cut to LM, then repair the Kraft sum: a code of length LM pairs up with a code taken from the deepest
@@ -346,6 +354,7 @@ __device__ __forceinline__ bool codebook_build_wave(const Geom& g, uint32_t* his
                                                     uint8_t* lens_t, TMeta* tmeta_t, unsigned char* wsm, uint32_t lane,
                                                     uint32_t carry) {
     const uint32_t K = g.K;
+    if (g.n >= kWaveElements) return false;  // uniform
     uint64_t* key = reinterpret_cast<uint64_t*>(wsm);            // [64] count << 16 | symbol of the used symbols, symbol order
     uint16_t* ent = reinterpret_cast<uint16_t*>(wsm + 512);      // [K] len << 12 | codeword
     const uint64_t below = (1ull << lane) - 1ull;
@@ -466,7 +475,8 @@ __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, 
     const uint32_t sym_lo = n_used ? (uint32_t)(key[0] & 0xFFFFu) : 0u;
     const uint32_t sym_hi = n_used ? (uint32_t)(key[n_used - 1] & 0xFFFFu) : 0u;
 
-    if (n_used >= 2 && n_used <= 64) {
+    const bool by_wave = n_used <= 64u && g.n < kWaveElements;  // uniform
+    if (n_used >= 2 && by_wave) {
         if (wave == 0) {
             const uint64_t kv = lane < n_used ? key[lane] : ~0ull;  // lane i: the i-th used symbol
             const uint32_t sym = (uint32_t)(kv & 0xFFFFu);
@@ -476,7 +486,7 @@ __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, 
             if (lane == 0) sh.codes_done = 1;
         }
         __syncthreads();
-    } else if (n_used > 64) {
+    } else if (n_used >= 2) {
         const uint32_t n_escape = cnt[0];  // (cnt[] is scratch from here on:
         __syncthreads();                   //  once every thread has read this)
         if (n_used <= NT) {
