@@ -226,27 +226,31 @@ __device__ __forceinline__ uint32_t lane_next(uint32_t v, uint32_t last) {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)last, (int)v, 0x130 /* wave_shl:1 */, 0xF, 0xF, false);
 }
 
-// The whole tree of a table with at most 64 used symbols and less than 2^30 elements, built by one wavefront in registers (`par`:
-// 256 bytes of LDS for the nodes above the others): lane i holds used symbol i (symbol order) on entry.  The merge keeps leaves
-// and merged nodes in ONE list in lane order, rising by weight: a step takes the two at the front off, moves the list up by two
-// lanes and puts their sum behind everything that is not heavier.  That is the two-queue merge's order, ties included: a weight
-// stands above two bits, 0 for a leaf and 1 for a merged node, so a leaf comes before every node of its weight, and of two nodes of
-// one weight the older one comes first.  The list holds nothing else: leaves and nodes leave it in their own orders, so how many
-// nodes every step took, which are the low two bits of the sum it made, says what is above what.
-// What bounds a step is its chain of dependent instructions, and no lane number in it depends on an earlier step (two queues with
-// their heads read by computed lane numbers, the first form of this loop, took 345 cycles a step, the numbers of what was merged
-// carried along in a second list 150).  Depths come from pointer jumping.  Lengths above LM are limited as described above.
+// The whole tree of a table with at most 64 used symbols and less than 2^30 elements, built by one wavefront in registers: lane i
+// holds used symbol i (symbol order) on entry.  The merge keeps leaves and merged nodes in ONE list in lane order, rising by
+// weight: a step takes the two at the front off, moves the list up by two lanes and puts their sum behind everything that is not
+// heavier.  That is the two-queue merge's order, ties included: a weight stands above two bits, 0 for a leaf and 1 for a merged
+// node, so a leaf comes before every node of its weight, and of two nodes of one weight the older one comes first.  The list holds
+// nothing else: leaves and nodes leave it in their own orders, so how many nodes every step took, which are the low two bits of the
+// sum it made, says what is below what.  Nodes of one depth are steps next to one another, and so are the leaves they took: from the
+// root down, a level is where the first node of the level above it starts to take.
+// What bounds it is one wavefront's chains of dependent instructions (about seven cycles each): with 41 symbols 40 steps of 45 cycles
+// (two queues with their heads read by computed lane numbers took 345, the numbers of what was merged carried along in a second list
+// 150), the sort 1100, 13 levels 1000.  Lengths above LM are limited as described above.
 // Returns the code length of the symbol the lane came in with.  2 <= n <= 64.
 constexpr uint32_t kWaveElements = 1u << 30;  // tables of fewer elements
-__device__ __forceinline__ uint32_t wave_huffman_lengths(uint32_t n, uint32_t LM, uint32_t cnt, uint32_t lane, uint8_t* par) {
+__device__ __forceinline__ uint32_t wave_huffman_lengths(uint32_t n, uint32_t LM, uint32_t cnt, uint32_t lane) {
     const uint32_t kInf = 0xFFFFFFFFu;
-    // position in (count, symbol) order (lanes past n - 1, four at a time at most, have the largest keys)
+    // position in (count, symbol) order (lanes past n - 1, eight at a time at most, have the largest keys)
     uint32_t rank = 0;
     if (__ballot(lane < n && cnt >= 1u << 26) == 0ull) {  // the rule: count and lane are one number
         const uint32_t key = lane < n ? cnt << 6 | lane : kInf;
-        for (uint32_t j0 = 0; j0 < n; j0 += 4u) {
 #pragma unroll
-            for (uint32_t u = 0; u < 4u; ++u) rank += lane_read(key, j0 + u) < key ? 1u : 0u;
+        for (uint32_t j0 = 0; j0 < 64u; j0 += 8u) {
+            if (j0 < n) {  // uniform
+#pragma unroll
+                for (uint32_t u = 0; u < 8u; ++u) rank += lane_read(key, j0 + u) < key ? 1u : 0u;
+            }
         }
     } else {
         const uint64_t key = (uint64_t)cnt << 32 | lane;
@@ -265,31 +269,25 @@ __device__ __forceinline__ uint32_t wave_huffman_lengths(uint32_t n, uint32_t LM
             w1 = lane_next(w, w1);
             w2 = lane_next(w1, w2);
             const uint32_t both = w + w1;
-            const uint32_t sum = lane_read((both & ~3u) | 1u, 0);
+            uint32_t node = (both & ~3u) | 1u;
+            asm("" : "+v"(node));  // (one vector instruction, not two scalar ones behind the lane read)
+            const uint32_t sum = lane_read(node, 0);
             sums = (uint32_t)__builtin_amdgcn_update_dpp((int)both, (int)sums, 0x138 /* wave_shr:1 */, 0xF, 0xF, false);
-            w = min(max(w1, sum), w2);  // not heavier than the sum: it moves up by two lanes; the sum's place; else by one
+            // not heavier than the sum: it moves up by two lanes; the sum's place; else by one (the median of the three)
+            w = max(min(w1, sum), min(max(w1, sum), w2));
         }
     }
     const uint32_t made = (uint32_t)__shfl((int)sums, (int)((steps - 1u - lane) & 63u), 64);  // lane k: the sum of step k
-    // step k took nodes [nodes_to - took, nodes_to), and leaves that make them two
-    const uint32_t took = lane + 1u < n ? made & 3u : 0u, nodes_to = wave_incl_scan(took), node = nodes_to - took, leaf = 2u * lane - node;
-    if (lane + 1u < n) {
-        // (one address for each of the two: leaves from 0, nodes from 128 on)
-        par[took == 2u ? 128u + node : leaf] = (uint8_t)lane;
-        par[took == 0u ? leaf + 1u : (took == 1u ? 128u + node : 129u + node)] = (uint8_t)lane;
+    // nodes that the steps before step `lane` took; twice as many things less those are leaves
+    const uint32_t took = lane + 1u < n ? made & 3u : 0u, nodes = wave_incl_scan(took) - took;
+    uint32_t len = 1u, first = n - 2u;  // of the leaf at sorted position `lane`; the first node of a level (the root: alone)
+    for (;;) {
+        const uint32_t below = lane_read(nodes, first);
+        len += lane < 2u * first - below ? 1u : 0u;
+        if (first == 0u) break;  // (its level is the last, or it takes nodes before itself)
+        first = below;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // the node above the leaf at sorted position `lane`; above node `lane` (idle lanes: anything)
-    const uint32_t vpl = par[lane] & 63u, vpn = par[128u + lane] & 63u;
-    // depth of every merged node (lane k = node k, the root is node n-2), above the node it is counted from
-    const uint32_t root = n - 2u;
-    uint32_t at = lane < root ? vpn | 1u << 8 : lane;
-    for (int r = 0; r < 6 && __ballot(lane < root && (at & 255u) != root) != 0ull; ++r)  // (until every node has reached the root)
-        at = (at & ~255u) + (uint32_t)__shfl((int)at, (int)(at & 255u), 64);
-    const uint32_t d = at >> 8;
-    uint32_t len = lane < n ? __shfl(d, vpl, 64) + 1u : 0u;  // of the leaf at sorted position `lane`
+    len = lane < n ? len : 0u;
     if (__ballot(len > LM) != 0ull) {
         // cut to LM, then repair the Kraft sum: a code of length LM pairs up with a code taken from the deepest
         // shorter level, one unit at a time.  Lane L of clv holds the number of codes of length L.
@@ -325,13 +323,14 @@ __device__ __forceinline__ uint32_t wave_huffman_lengths(uint32_t n, uint32_t LM
 }
 
 // canonical codeword of every lane's symbol (the lanes are in symbol order; length 0: not used): the first code of each
-// length, then the rank among the symbols of that length.  below: the lanes before this one.
-__device__ __forceinline__ uint32_t wave_canonical_code(uint32_t len, uint32_t LM, uint64_t below) {
+// length, then the rank among the symbols of that length
+__device__ __forceinline__ uint32_t wave_canonical_code(uint32_t len) {
     uint32_t code = 0, mine = 0;
-    for (uint32_t L = 1; L <= LM; ++L) {
+#pragma unroll
+    for (uint32_t L = 1; L <= (uint32_t)kLmaxLimit; ++L) {
         code <<= 1;
         const uint64_t same = __ballot(len == L);
-        mine = (len == L) ? code + (uint32_t)__popcll(same & below) : mine;
+        mine = len == L ? __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, code)) : mine;
         code += (uint32_t)__popcll(same);
     }
     return mine;
@@ -389,10 +388,9 @@ __device__ __forceinline__ bool codebook_build_wave(const Geom& g, uint32_t* his
     const uint64_t kv = lane < n_used ? key[lane] : ~0ull;  // lane i: the i-th used symbol
     const uint32_t sym = (uint32_t)(kv & 0xFFFFu);
     const uint32_t lo = lane_read(sym, 0), hi = lane_read(sym, n_used ? n_used - 1u : 0u);
-    __builtin_amdgcn_wave_barrier();  // (the keys' memory is used again)
     if (n_used >= 2u) {
-        const uint32_t len = wave_huffman_lengths(n_used, g.LMAX, (uint32_t)(kv >> 16), lane, reinterpret_cast<uint8_t*>(key));
-        const uint32_t mine_code = wave_canonical_code(len, g.LMAX, below);
+        const uint32_t len = wave_huffman_lengths(n_used, g.LMAX, (uint32_t)(kv >> 16), lane);
+        const uint32_t mine_code = wave_canonical_code(len);
         if (lane < n_used) ent[sym] = (uint16_t)((len << 12) | mine_code);
     }
     __builtin_amdgcn_wave_barrier();
@@ -480,8 +478,8 @@ __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, 
         if (wave == 0) {
             const uint64_t kv = lane < n_used ? key[lane] : ~0ull;  // lane i: the i-th used symbol
             const uint32_t sym = (uint32_t)(kv & 0xFFFFu);
-            const uint32_t len = wave_huffman_lengths(n_used, g.LMAX, (uint32_t)(kv >> 16), lane, reinterpret_cast<uint8_t*>(scratch));
-            const uint32_t mine_code = wave_canonical_code(len, g.LMAX, (1ull << lane) - 1ull);
+            const uint32_t len = wave_huffman_lengths(n_used, g.LMAX, (uint32_t)(kv >> 16), lane);
+            const uint32_t mine_code = wave_canonical_code(len);
             if (lane < n_used) { len_s[sym] = (uint16_t)len; nodew[sym] = mine_code; }
             if (lane == 0) sh.codes_done = 1;
         }
@@ -692,8 +690,8 @@ __device__ __forceinline__ bool codebook_window_wave(const Geom& g, const uint32
     const uint64_t kv = lane < n_used ? key[lane] : ~0ull;  // lane i: the i-th used symbol
     const uint32_t idx = (uint32_t)(kv & 0xFFFFu);
     if (n_used >= 2u) {
-        const uint32_t len = wave_huffman_lengths(n_used, g.LMAX, (uint32_t)(kv >> 16), lane, reinterpret_cast<uint8_t*>(key));
-        const uint32_t code = wave_canonical_code(len, g.LMAX, below);
+        const uint32_t len = wave_huffman_lengths(n_used, g.LMAX, (uint32_t)(kv >> 16), lane);
+        const uint32_t code = wave_canonical_code(len);
         if (lane < n_used) ent[idx] = (uint16_t)((len << 12) | code);
     }
     const uint32_t sym = idx == kWinEsc ? 0u : win_lo + idx;
