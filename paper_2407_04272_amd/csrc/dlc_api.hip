@@ -145,6 +145,7 @@ static size_t carve(const Geom& g, uint8_t* base, Ws* w) {
     uint8_t* enc = take(2 * (size_t)g.T * g.K);
     uint8_t* lens = take((size_t)g.T * g.K);
     uint8_t* state = take(8 * (size_t)g.NG);
+    uint8_t* ready = take(4 * (size_t)g.T);
     uint8_t* ws0 = take(4 * (size_t)g.T);
     uint8_t* ws1 = take(4 * (size_t)g.T);
     uint8_t* plane = g.sample ? nullptr : take((size_t)g.NG * kW * g.S);  // (with a sampled codebook every call is a single pass)
@@ -172,7 +173,7 @@ static size_t carve(const Geom& g, uint8_t* base, Ws* w) {
         w->qp = (QParam*)qp;
         w->hist = (uint32_t*)hist; w->hist_view = (uint32_t*)hview; w->ctrl = (Ctrl*)ctrl;
         w->tmeta = (TMeta*)tmeta;
-        w->enc = (uint16_t*)enc; w->lens = lens; w->state = (uint64_t*)state;
+        w->enc = (uint16_t*)enc; w->lens = lens; w->state = (uint64_t*)state; w->ready = (uint32_t*)ready;
         w->word_start = (uint32_t*)ws0; w->word_end = (uint32_t*)ws1;
         w->sym_plane = plane;
         w->esc_count = (uint32_t*)escc;
@@ -401,10 +402,11 @@ extern "C" int dlc_compress(dlc_ctx* c, const void* d_payload, void* d_out, size
         return hipGetLastError() == hipSuccess ? DLC_ECAPACITY : DLC_EHIP;
     }
     c->epoch += 1;
-    if (c->epoch >= (1ull << 30)) {  // look-back records carry a 30-bit call counter
+    if (c->epoch >= (1ull << 30)) {  // look-back records carry a 30-bit call counter (and what they say of a codebook as much)
         const size_t n = c->g.NG;
         hipLaunchKernelGGL(k_zero_words, dim3((unsigned)std::min<size_t>((n + 255) / 256, 4096)), dim3(256), 0, (hipStream_t)stream,
                            c->ws.state, n);
+        hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(256), 0, (hipStream_t)stream, (uint64_t*)c->ws.ready, ((size_t)c->g.T + 1) / 2);
         if (hipGetLastError() != hipSuccess) return DLC_EHIP;
         c->epoch = 1;
     }

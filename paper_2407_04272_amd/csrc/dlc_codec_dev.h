@@ -664,26 +664,27 @@ __device__ __forceinline__ void codebook_build_four(const Geom& g, uint32_t t0, 
 }
 
 // The codebook of a table whose counts lie in LDS by window index (cnt[254]: the escapes), when it has at most 64 used
-// symbols, all of them inside the window; by ONE wavefront.  key: LDS for 64 keys; ent[256] (LDS, zeroed before): gets
-// len << 12 | codeword by window index.  Returns false, with ent untouched, when there are more than 64 used symbols.
+// symbols, all of them inside the window; by ONE wavefront.  key: LDS for 64 keys and one that is nobody's; ent[256] (LDS): gets
+// len << 12 | codeword by window index.  Returns false, with *tm untouched, when there are more than 64 used symbols.
 __device__ __forceinline__ bool codebook_window_wave(const Geom& g, const uint32_t* cnt, uint64_t* key, uint16_t* ent,
-                                                     TMeta* tmeta_t, uint32_t lane) {
+                                                     TMeta* tm, uint32_t lane) {
     const uint32_t win_lo = win_lo_of(g.R);
     const uint64_t below = (1ull << lane) - 1ull;
     const uint32_t n_escape = (uint32_t)__builtin_amdgcn_readfirstlane((int)cnt[kWinEsc]);
     uint32_t n_used = n_escape ? 1u : 0u;  // the escape is symbol 0: the first in symbol order
-    if (n_escape && lane == 0) key[0] = ((uint64_t)n_escape << 16) | kWinEsc;
     uint32_t cv[4];
 #pragma unroll
     for (uint32_t i = 0; i < 4; ++i) cv[i] = i * 64u + lane < kWinEsc ? cnt[i * 64u + lane] : 0u;
+    key[n_escape && lane == 0 ? 0u : 64u] = ((uint64_t)n_escape << 16) | kWinEsc;
 #pragma unroll
     for (uint32_t i = 0; i < 4; ++i) {
         const uint64_t m = __ballot(cv[i] != 0u);
         const uint32_t at = n_used + (uint32_t)__popcll(m & below);
-        if (cv[i] != 0u && at < 64u) key[at] = ((uint64_t)cv[i] << 16) | (i * 64u + lane);
+        key[cv[i] != 0u ? min(at, 64u) : 64u] = ((uint64_t)cv[i] << 16) | (i * 64u + lane);
         n_used += (uint32_t)__popcll(m);
     }
     if (n_used > 64u) return false;  // uniform
+    reinterpret_cast<uint64_t*>(ent)[lane] = 0ull;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -702,7 +703,7 @@ __device__ __forceinline__ bool codebook_window_wave(const Geom& g, const uint32
         m.sym_lo = n_used ? lo : 0u;
         m.sym_hi = n_used ? hi : 0u;
         m.n_outliers = n_escape;
-        store_tmeta(tmeta_t, m);
+        *tm = m;
     }
     return true;
 }
@@ -710,13 +711,13 @@ __device__ __forceinline__ bool codebook_window_wave(const Geom& g, const uint32
 // ------------------------------------------------------------------------------------------------
 // offsets of the output: single-pass look-back scan
 // ------------------------------------------------------------------------------------------------
-constexpr uint32_t kFlagAgg = 1, kFlagPrefix = 2, kFlagReady = 3;  // Ready: nothing for the scan yet (see wg_ready)
+constexpr uint32_t kFlagAgg = 1, kFlagPrefix = 2;
 constexpr uint32_t kSpinLimit = 1u << 22;
 
-// Tells the work-groups that finish the containers that this one's table has its codebook in memory (one thread, after a barrier
-// before which every wavefront has waited for its stores).
-__device__ __forceinline__ void wg_ready(uint64_t* state, uint64_t epoch, uint32_t wg) {
-    __hip_atomic_store(&state[wg], epoch << 34 | (uint64_t)kFlagReady << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Tells other work-groups of the launch that a table has its codebook in memory (one thread, after every wavefront that stored some
+// of it has waited for its stores).
+__device__ __forceinline__ void table_ready(uint32_t* ready, uint64_t epoch, uint32_t t) {
+    __hip_atomic_store(&ready[t], (uint32_t)epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Exclusive prefix of `total` over the work-groups before `wg`: single-pass look-back over one record per
@@ -745,8 +746,7 @@ __device__ __forceinline__ uint32_t wg_scan(uint64_t* state, uint64_t epoch, uin
                 const int64_t my = pos - (int64_t)(lane * 4u + (uint32_t)k);
                 const uint64_t sv = my >= (int64_t)dom0 ? __hip_atomic_load(&state[my], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
                                                         : (tag | ((uint64_t)kFlagPrefix << 32));
-                uint32_t flag = (sv >> 34) == epoch ? (uint32_t)(sv >> 32) & 3u : 0u;
-                flag = flag == kFlagReady ? 0u : flag;
+                const uint32_t flag = (sv >> 34) == epoch ? (uint32_t)(sv >> 32) & 3u : 0u;
                 if (!has_p) {
                     hole = hole || flag == 0u;
                     sum += flag != 0u ? (uint32_t)sv : 0u;

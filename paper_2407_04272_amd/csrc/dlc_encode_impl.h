@@ -365,13 +365,16 @@ __device__ __forceinline__ void encode_groups(const GroupJob& J, const void* pay
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
     // the columns' words to their places; they are the words from `first` on of their chunks.
-    // A team of lanes copies a chunk, a word a lane (as many lanes as a chunk has words at 4 bits a symbol; the
-    // teams' chunks lie so far apart that no two lanes meet in a bank)
+    // A team of lanes copies a chunk, a word a lane: as many lanes as a chunk has words at 4 bits a symbol, a half or a quarter of
+    // them where all chunks are as short (the teams' chunks lie so far apart that no two lanes meet in a bank).  (A table of 4096
+    // elements, chunks of 8 words: 1.9 us with teams of 32 lanes.)
     auto copy = [&](uint32_t first) {
         in_order();
-        constexpr uint32_t TL = (uint32_t)S / 8u;
-        const uint32_t team = lane / TL, k0 = lane % TL;
         const uint32_t n_here = nw > first ? min(nw - first, cap) : 0u;
+        uint32_t log_tl = S == 256 ? 5u : (S == 128 ? 4u : 3u);  // (S / 8)
+        if (S > 64 && __ballot(n_here > (uint32_t)S / 16u) == 0ull) --log_tl;
+        if (S > 128 && __ballot(n_here > (uint32_t)S / 32u) == 0ull) --log_tl;
+        const uint32_t TL = 1u << log_tl, team = lane >> log_tl, k0 = lane & (TL - 1u);
         const uint32_t mine = ((lane_off + first) << 8) | n_here;
         for (uint32_t k = 0; __ballot(n_here > k) != 0ull; k += TL) {  // uniform
             const uint32_t* const rl = rows + min(k + k0 + 1u, cap + 1u) * kColPitch;
@@ -440,7 +443,7 @@ void k_encode(const void* payload, const uint8_t* sym_plane, Geom g, FixedLayout
     J.wg = __builtin_amdgcn_readfirstlane(s_wg);
     if constexpr (!LZ) {  // (row matching: the references are copied by a launch of its own)
         if (J.wg >= g.T * bpt) {  // uniform; xn for every container
-            finish_container<64u * NW, false>(g, F, tmeta, lens, qp, ctrl, state, epoch, bpt, out, capacity, out_bytes, J.wg - g.T * bpt, xn, *reinterpret_cast<FinLds<64u * NW>*>(smem), tid);
+            finish_container<64u * NW, false>(g, F, tmeta, lens, qp, ctrl, state, (const uint32_t*)nullptr, epoch, bpt, out, capacity, out_bytes, J.wg - g.T * bpt, xn, *reinterpret_cast<FinLds<64u * NW>*>(smem), tid);
             return;
         }
     }
@@ -493,16 +496,17 @@ void k_encode(const void* payload, const uint8_t* sym_plane, Geom g, FixedLayout
 template <int S, bool F16, bool VEC, uint32_t NW, bool FIN>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4)))
 void k_table(const void* payload, uint8_t* sym_plane, Geom g, FixedLayout F, const QParam* qp, uint32_t* hist_view, uint16_t* enc,
-             uint8_t* lens, TMeta* tmeta, Ctrl* ctrl, uint64_t* state, uint64_t epoch, uint8_t* out, uint64_t capacity,
+             uint8_t* lens, TMeta* tmeta, Ctrl* ctrl, uint64_t* state, uint32_t* ready, uint64_t epoch, uint8_t* out, uint64_t capacity,
              uint32_t* word_start, uint32_t* word_end, uint64_t* out_bytes, uint32_t xn, uint32_t cap, uint32_t pair_max) {
     constexpr uint32_t NT = 64u * NW;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ CodebookShared s_cb;
     __shared__ uint32_t s_cnt[256];
-    __shared__ uint64_t s_key[64];
-    __shared__ uint32_t s_wg, s_lo, s_hi, s_fast;
+    __shared__ uint64_t s_key[65];
+    __shared__ TMeta s_tm;
+    __shared__ uint32_t s_wg, s_lo, s_hi, s_fast, s_out;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (tid == 0) { s_wg = atomicAdd(&ctrl->ticket, 1u); s_lo = 255u; s_hi = 0u; s_fast = 0u; }
+    if (tid == 0) { s_wg = atomicAdd(&ctrl->ticket, 1u); s_lo = 255u; s_hi = 0u; s_fast = 0u; s_out = 0u; }
     // counts: window rows and exact counts, as in the histogram kernel
     uint32_t* const lh = reinterpret_cast<uint32_t*>(smem);
     const uint32_t* const exact = lh + (kWinBins + 1u) * kWinCopies;
@@ -516,7 +520,7 @@ void k_table(const void* payload, uint8_t* sym_plane, Geom g, FixedLayout F, con
     J.wg = __builtin_amdgcn_readfirstlane(s_wg);
     if constexpr (FIN) {
         if (J.wg >= g.T) {  // uniform; xn for every container
-            finish_container<NT, true>(g, F, tmeta, lens, qp, ctrl, state, epoch, 1u, out, capacity, out_bytes, J.wg - g.T, xn, *reinterpret_cast<FinLds<NT>*>(smem), tid);
+            finish_container<NT, true>(g, F, tmeta, lens, qp, ctrl, state, ready, epoch, 1u, out, capacity, out_bytes, J.wg - g.T, xn, *reinterpret_cast<FinLds<NT>*>(smem), tid);
             return;
         }
     }
@@ -578,29 +582,43 @@ void k_table(const void* payload, uint8_t* sym_plane, Geom g, FixedLayout F, con
         idx = k == 0u ? kWinEsc : k - win_lo;
         return k == 0u || (k >= win_lo && idx < kWinEsc);
     };
-    for (uint32_t k = tid; k < g.K; k += NT) {  // the table's counts (inspection, and the codebook of the next call where it is carried)
-        uint32_t idx;
-        const uint32_t s = (in_window(k, idx) ? s_cnt[idx] : 0u) + exact[k];
-        __hip_atomic_store(&view_t[k], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();  // (the counts are dead in LDS from here on, but for s_cnt)
+    // A table's counts (inspection, and the codebook of the next call where it is carried), codewords and lengths by `nt` threads.
+    // (No element outside the window: the exact counts are zero.)
+    auto put_counts = [&](uint32_t first, uint32_t nt) {
+        for (uint32_t k = first; k < g.K; k += nt) {
+            uint32_t idx;
+            const uint32_t s = (in_window(k, idx) ? s_cnt[idx] : 0u) + (n_other != 0u ? exact[k] : 0u);
+            __hip_atomic_store(&view_t[k], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    };
     uint16_t* const ent = reinterpret_cast<uint16_t*>(smem + J.L.ent);
-    for (uint32_t i = tid; i < 256u; i += NT) ent[i] = 0;
-    __syncthreads();
-    if (n_other == 0u && wave == 0) {
-        const bool done = codebook_window_wave(g, s_cnt, s_key, ent, tmeta + t, lane);
-        if (lane == 0) s_fast = done ? 1u : 0u;
-    }
-    __syncthreads();
-    if (s_fast) {  // uniform
-        for (uint32_t k = tid; k < g.K; k += NT) {
+    auto put_codes = [&](uint32_t first, uint32_t nt) {
+        for (uint32_t k = first; k < g.K; k += nt) {
             uint32_t idx;
             const uint32_t e = in_window(k, idx) ? ent[idx] : 0u;
             enc_t[k] = (uint16_t)e;
             if constexpr (FIN) __hip_atomic_store(&lens_t[k], (uint8_t)(e >> 12), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             else lens_t[k] = (uint8_t)(e >> 12);
         }
+        if (first == 0u) store_tmeta(tmeta + t, s_tm);
+    };
+    if (n_other == 0u) {  // uniform
+        if (wave == 0) {
+            const bool done = codebook_window_wave(g, s_cnt, s_key, ent, &s_tm, lane);
+            if (lane == 0) s_fast = done ? 1u : 0u;
+        }
+        __syncthreads();
+    }
+    // Wavefronts without a group put what nobody in the work-group reads into memory while the others code theirs (with one group of
+    // 4096 elements that and the wait for it were 1.3 us of the work-group's 13)
+    const bool fast = s_fast != 0u, apart = fast && g.G < NW;
+    if (fast) {  // uniform
+        if (!apart) {
+            put_counts(tid, NT);
+            put_codes(tid, NT);
+        }
     } else {  // many symbols, or symbols outside the window: from the counts in memory
+        put_counts(tid, NT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         codebook_build<NT>(g, view_t, view_t, enc_t, lens_t, tmeta + t, smem, s_cb, tid, 0u, FIN);
@@ -619,9 +637,18 @@ void k_table(const void* payload, uint8_t* sym_plane, Geom g, FixedLayout F, con
     if (J.pairs) {
         build_pairs(reinterpret_cast<uint32_t*>(smem + J.L.pair), ent, J.lo, J.P, tid, NT);
     }
-    if constexpr (FIN) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the codebook is out)
+    if (FIN && !apart) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the codebook is out)
     __syncthreads();
-    if (FIN && tid == 0) wg_ready(state, epoch, J.wg);
+    if (!apart) {
+        if (FIN && tid == 0) table_ready(ready, epoch, t);
+    } else if (wave >= g.G) {
+        put_counts(tid - 64u * g.G, NT - 64u * g.G);
+        put_codes(tid - 64u * g.G, NT - 64u * g.G);
+        if constexpr (FIN) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (lane == 0 && atomicAdd(&s_out, 1u) + 1u == NW - g.G) table_ready(ready, epoch, t);  // the last of them
+        }
+    }
     encode_groups<S, F16, VEC, false, NW>(J, payload, sym_plane, g, F, qp, enc, ctrl, state, epoch, out + (uint64_t)J.dst * capacity,
                                           capacity, word_start, word_end, smem, tid);
 }
@@ -695,7 +722,7 @@ static bool DLC_CAT(table_launch_, DLC_S)(const Geom& g, const FixedLayout& F, c
     const bool f16 = g.dtype == DLC_F16;
 #define DLC_TAB2(FF, V, FIN)                                                                                          \
     hipLaunchKernelGGL((k_table<S, FF, V, NW, FIN>), grid, block, sm, s, payload, w.sym_plane, g, F, w.qp, w.hist_view, w.enc, w.lens, w.tmeta, \
-                       w.ctrl, w.state, epoch, out, capacity, w.word_start, w.word_end, out_bytes, xn, cap, pair_max)
+                       w.ctrl, w.state, w.ready, epoch, out, capacity, w.word_start, w.word_end, out_bytes, xn, cap, pair_max)
 #define DLC_TAB(FF, V) do { if (out_bytes) DLC_TAB2(FF, V, true); else DLC_TAB2(FF, V, false); } while (0)
     if (f16) { if (g.vec) DLC_TAB(true, true); else DLC_TAB(true, false); }
     else { if (g.vec) DLC_TAB(false, true); else DLC_TAB(false, false); }

@@ -252,7 +252,7 @@ struct FinLds {
 
 template <uint32_t NT, bool LATE>
 __device__ __forceinline__ void finish_container(const Geom& g, const FixedLayout& F, const TMeta* tmeta, const uint8_t* lens, const QParam* qp,
-                                                 Ctrl* ctrl, const uint64_t* state, uint64_t epoch, uint32_t bpt, uint8_t* out, uint64_t capacity,
+                                                 Ctrl* ctrl, const uint64_t* state, const uint32_t* ready, uint64_t epoch, uint32_t bpt, uint8_t* out, uint64_t capacity,
                                                  uint64_t* out_bytes, uint32_t f, uint32_t xn, FinLds<NT>& L, uint32_t tid) {
     const uint32_t xi = xn - 1u - f / g.ND, dst = f % g.ND, T = g.TD;  // number f of the ND * xn: the shares 0 are the last
     const bool first = xi == 0u;  // uniform
@@ -262,13 +262,8 @@ __device__ __forceinline__ void finish_container(const Geom& g, const FixedLayou
     state += (size_t)dst * T * bpt;
     uint64_t* const table_bytes = out_bytes + 1 + (size_t)dst * T;
     if (tid == 0) L.dead = 0u;
-    // the record of work-group `wg` of this container once its flag is `least` or more (3: codebook there, see wg_ready)
-    auto wait = [&](uint32_t wg, bool prefix) {
-        uint64_t sv;
-        for (uint32_t spins = 0;; ++spins) {
-            sv = __hip_atomic_load(&state[wg], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint32_t flag = (sv >> 34) == epoch ? (uint32_t)(sv >> 32) & 3u : 0u;
-            if (prefix ? flag == kFlagPrefix : flag != 0u) break;
+    auto wait = [&](auto there) {
+        for (uint32_t spins = 0; !there(); ++spins) {
             if (spins > 2u * kSpinLimit) {  // never expected; the bound only guarantees termination
                 set_status(ctrl, DLC_ESTATE);
                 L.dead = 1u;
@@ -277,12 +272,20 @@ __device__ __forceinline__ void finish_container(const Geom& g, const FixedLayou
             __builtin_amdgcn_s_sleep(1);
         }
         asm volatile("" ::: "memory");  // (what the record vouches for is read after it)
+    };
+    auto codebook_there = [&] { return __hip_atomic_load(&ready[(size_t)dst * T + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)epoch; };
+    auto prefix = [&](uint32_t wg) {  // of work-group `wg` of this container
+        uint64_t sv;
+        wait([&] {
+            sv = __hip_atomic_load(&state[wg], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return (sv >> 34) == epoch && ((uint32_t)(sv >> 32) & 3u) == kFlagPrefix;
+        });
         return (uint32_t)sv;
     };
     TMeta m;
     uint32_t nl = 0, cb = 0;
     if (tid < T) {
-        if constexpr (LATE) (void)wait(tid, false);
+        if constexpr (LATE) wait(codebook_there);
         m = load_tmeta<LATE>(tmeta + tid);
         if (m.sym_lo > m.sym_hi || m.sym_hi >= g.K) { m.sym_lo = 0; m.sym_hi = 0; }  // never index outside lens[]
         nl = m.sym_hi - m.sym_lo + 1u;
@@ -314,9 +317,9 @@ __device__ __forceinline__ void finish_container(const Geom& g, const FixedLayou
     const uint32_t eb_bits = first && tid < T ? qp[(size_t)dst * T + tid].eb_bits : 0u;
     // the words' places
     if (first) {
-        if (tid < T) L.end[tid] = wait((tid + 1u) * bpt - 1u, true);
+        if (tid < T) L.end[tid] = prefix((tid + 1u) * bpt - 1u);
     } else if (tid == 0) {
-        L.end[T - 1u] = wait(T * bpt - 1u, true);
+        L.end[T - 1u] = prefix(T * bpt - 1u);
     }
     __syncthreads();
     const uint64_t words = L.end[T - 1u], off_cb = a16(F.off_payload + 4ull * words);
