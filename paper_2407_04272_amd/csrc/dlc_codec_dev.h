@@ -187,7 +187,7 @@ __device__ __forceinline__ void hist_block(const uint8_t* base, uint32_t rem, ui
 //   canonical codewords in (length, symbol) order.  One used symbol: length 0.
 //   smem: codebook_smem(K) bytes, 16-byte aligned.  Ends with a barrier; results are in global memory.
 // ------------------------------------------------------------------------------------------------
-__host__ __device__ constexpr size_t codebook_smem(uint32_t K) { return (size_t)K * (8 + 4 + 4 + 2 + 2 + 2 + 2) + 64 * 4; }
+__host__ __device__ constexpr size_t codebook_smem(uint32_t K) { return (size_t)K * (8 + 4 + 4 + 2) + 64 * 4; }
 
 // what another work-group of the same launch may read of a table's codebook goes past the caches
 __device__ __forceinline__ void store_tmeta(TMeta* p, const TMeta& m) {
@@ -206,7 +206,7 @@ __device__ __forceinline__ TMeta load_tmeta(const TMeta* p) {
 }
 
 struct CodebookShared {
-    uint32_t lo, hi, maxlen, codes_done, cl[kLmaxLimit + 2], next[kLmaxLimit + 2];
+    uint32_t first[kLmaxLimit + 2], more[kLmaxLimit + 2];  // by length: the first codeword; leaves of that length and shorter
 };
 
 __device__ __forceinline__ uint32_t lane_get(uint32_t v, uint32_t l) {
@@ -224,6 +224,23 @@ __device__ __forceinline__ uint32_t lane_read(uint32_t v, uint32_t l) {
 // the next lane's value; the last lane gets `last`
 __device__ __forceinline__ uint32_t lane_next(uint32_t v, uint32_t last) {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)last, (int)v, 0x130 /* wave_shl:1 */, 0xF, 0xF, false);
+}
+
+// Lane L of clv: how many codes have length L, 1 <= L <= LM, those that were longer cut to LM.  The Kraft sum is repaired: a code of
+// length LM pairs up with a code taken from the deepest shorter level, one unit at a time.
+__device__ __forceinline__ uint32_t wave_limit_lengths(uint32_t clv, uint32_t LM, uint32_t lane) {
+    uint32_t kraft = wave_sum(lane >= 1u && lane <= LM ? clv << (LM - lane) : 0u);  // in units of 2^-LM (K codes of length 1 at most: 2^23)
+    while (kraft > 1u << LM && lane_get(clv, LM) > 0u) {
+        const uint64_t shorter = __ballot(clv > 0u && lane >= 1u && lane < LM);
+        clv = lane_put(clv, LM, lane_get(clv, LM) - 1u, lane);
+        if (shorter) {
+            const uint32_t Ld = 63u - (uint32_t)__builtin_clzll(shorter);
+            clv = lane_put(clv, Ld, lane_get(clv, Ld) - 1u, lane);
+            clv = lane_put(clv, Ld + 1u, lane_get(clv, Ld + 1u) + 2u, lane);
+        }
+        kraft -= 1u;
+    }
+    return clv;
 }
 
 // The whole tree of a table with at most 64 used symbols and less than 2^30 elements, built by one wavefront in registers: lane i
@@ -289,26 +306,10 @@ __device__ __forceinline__ uint32_t wave_huffman_lengths(uint32_t n, uint32_t LM
     }
     len = lane < n ? len : 0u;
     if (__ballot(len > LM) != 0ull) {
-        // cut to LM, then repair the Kraft sum: a code of length LM pairs up with a code taken from the deepest
-        // shorter level, one unit at a time.  Lane L of clv holds the number of codes of length L.
         const uint32_t lc = min(len, LM);
         uint32_t clv = 0;
-        uint64_t kraft = 0;  // in units of 2^-LM
-        for (uint32_t L = 1; L <= LM; ++L) {
-            const uint32_t c = (uint32_t)__popcll(__ballot(lane < n && lc == L));
-            clv = lane_put(clv, L, c, lane);
-            kraft += (uint64_t)c << (LM - L);
-        }
-        while (kraft > (1ull << LM) && lane_get(clv, LM) > 0u) {
-            const uint64_t shorter = __ballot(clv > 0u && lane >= 1u && lane < LM);
-            clv = lane_put(clv, LM, lane_get(clv, LM) - 1u, lane);
-            if (shorter) {
-                const uint32_t Ld = 63u - (uint32_t)__builtin_clzll(shorter);
-                clv = lane_put(clv, Ld, lane_get(clv, Ld) - 1u, lane);
-                clv = lane_put(clv, Ld + 1u, lane_get(clv, Ld + 1u) + 2u, lane);
-            }
-            kraft -= 1;
-        }
+        for (uint32_t L = 1; L <= LM; ++L) clv = lane_put(clv, L, (uint32_t)__popcll(__ballot(lane < n && lc == L)), lane);
+        clv = wave_limit_lengths(clv, LM, lane);
         // lengths are handed out most frequent leaf first (the leaves are sorted by rising count)
         const uint32_t back = n - 1u - lane;
         uint32_t acc = 0, nl = 1;
@@ -426,10 +427,7 @@ __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, 
     uint64_t* key = reinterpret_cast<uint64_t*>(smem);        // [K] sort keys: count << 16 | symbol
     uint32_t* cnt = reinterpret_cast<uint32_t*>(key + K);      // [K] counts
     uint32_t* nodew = cnt + K;                                 // [K] merged-node weights, later codewords
-    uint16_t* parent_leaf = reinterpret_cast<uint16_t*>(nodew + K);  // [K] parent of a leaf, later its length
-    uint16_t* parent_node = parent_leaf + K;                   // [K]
-    uint16_t* depth_node = parent_node + K;                    // [K]
-    uint16_t* len_s = depth_node + K;                          // [K] code length per symbol
+    uint16_t* len_s = reinterpret_cast<uint16_t*>(nodew + K);  // [K] code length per symbol
     uint32_t* scratch = reinterpret_cast<uint32_t*>(len_s + K);  // [64]
     const uint32_t lane = tid & 63u, wave = tid >> 6;
 
@@ -458,8 +456,6 @@ __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, 
         len_s[k] = 0;
         mine += cnt[k] != 0;
     }
-    if (tid == 0) { sh.maxlen = 0; sh.codes_done = 0; }
-    if (tid < kLmaxLimit + 2) sh.cl[tid] = 0;
     // compaction offsets of the used symbols (symbol order); the barriers inside also publish cnt[]
     uint32_t n_used;
     const uint32_t my_off = block_excl_scan<(int)(NT / 64u)>(mine, scratch, tid, &n_used);
@@ -481,7 +477,6 @@ __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, 
             const uint32_t len = wave_huffman_lengths(n_used, g.LMAX, (uint32_t)(kv >> 16), lane);
             const uint32_t mine_code = wave_canonical_code(len);
             if (lane < n_used) { len_s[sym] = (uint16_t)len; nodew[sym] = mine_code; }
-            if (lane == 0) sh.codes_done = 1;
         }
         __syncthreads();
     } else if (n_used >= 2) {
@@ -495,6 +490,7 @@ __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, 
             uint32_t rank = 0;
             if (tid < n_used) {
                 mykey = key[tid];
+#pragma unroll 8
                 for (uint32_t j = 0; j < n_used; ++j) rank += key[j] < mykey ? 1u : 0u;
                 tmp[rank] = mykey;
             }
@@ -520,111 +516,84 @@ __device__ __forceinline__ void codebook_build(const Geom& g, uint32_t* hist_t, 
                 }
             }
         }
-        if (tid == 0) {
-            const uint32_t n = n_used;
-            uint32_t a = 0, bq = 0;  // heads of the leaf queue and of the merged-node queue
-            for (uint32_t k = 0; k + 1 < n; ++k) {
-                uint32_t sum = 0;
-                for (int pick = 0; pick < 2; ++pick) {
-                    bool take_leaf;
-                    if (a >= n) take_leaf = false;
-                    else if (bq >= k) take_leaf = true;
-                    else take_leaf = (uint32_t)(key[a] >> 16) <= nodew[bq];
-                    if (take_leaf) { sum += (uint32_t)(key[a] >> 16); parent_leaf[a] = (uint16_t)k; ++a; }
-                    else { sum += nodew[bq]; parent_node[bq] = (uint16_t)k; ++bq; }
-                }
-                nodew[k] = sum;
+        // The merge, by one wavefront: 64 leaves and 64 nodes from the heads of the two queues on are in its lanes (the next ones
+        // are fetched when fewer than two are left), a step reads two of each and takes the lightest, a leaf where they are alike.
+        // What a step found (heads) goes to LDS, 64 steps at a time.  (By one thread, with the queues in LDS, a step was 0.3 us of
+        // dependent LDS reads, and depths, limits and codewords took as long again: 26 tables of 4096 x 64 with 83, 170 and 420
+        // symbols 72, 106 and 291 us a call, now 63, 87 and 241.)
+        uint32_t* const heads = cnt;  // [n_used - 1] leaf << 16 | node
+        if (wave == 0) {
+            const uint32_t n = n_used, kInf = 0xFFFFFFFFu;
+            uint32_t leaf = 0, node = 0, leaf0 = 0, node0 = 0;  // heads, and what lane 0 holds
+            auto leaves = [&] { return leaf + lane < n ? (uint32_t)(key[leaf + lane] >> 16) : kInf; };
+            uint32_t L = leaves(), N = kInf, seen = 0;
+            for (uint32_t k = 0; k + 1u < n; ++k) {
+                if (leaf - leaf0 > 62u) { leaf0 = leaf; L = leaves(); }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (nodes that one lane has stored, read by others)
+                if (node - node0 > 62u) { node0 = node; N = node + lane < k ? nodew[node + lane] : kInf; }
+                const uint32_t l0 = lane_read(L, leaf - leaf0), l1 = lane_read(L, leaf - leaf0 + 1u);
+                const uint32_t n0 = lane_read(N, node - node0), n1 = lane_read(N, node - node0 + 1u);
+                const uint32_t took = l1 <= n0 ? 0u : (n1 < l0 ? 2u : 1u);  // nodes
+                const uint32_t sum = took == 0u ? l0 + l1 : (took == 2u ? n0 + n1 : l0 + n0);
+                seen = lane == (k & 63u) ? leaf << 16 | node : seen;
+                if ((k & 63u) == 63u) heads[k - 63u + lane] = seen;
+                if (lane == 0) nodew[k] = sum;
+                N = lane == k - node0 ? sum : N;
+                node += took;
+                leaf += 2u - took;
             }
+            const uint32_t done = (n - 1u) & ~63u;
+            if (lane < n - 1u - done) heads[done + lane] = seen;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            // level by level from the root down (see wave_huffman_lengths): lane L counts the leaves of length L
+            const uint32_t LM = g.LMAX;
+            uint32_t clv = 0, above = n, first = n - 2u, length = 1;
+            bool longer = false;
+            for (;;) {
+                const uint32_t at = (uint32_t)__builtin_amdgcn_readfirstlane((int)heads[first]);
+                clv += lane == min(length, LM) ? above - (at >> 16) : 0u;
+                longer = longer || length > LM;
+                above = at >> 16;
+                if (first == 0u) break;
+                first = at & 0xFFFFu;
+                ++length;
+            }
+            if (longer) clv = wave_limit_lengths(clv, LM, lane);
+            const uint32_t upto = wave_incl_scan(clv);
+            uint32_t code = 0, first_code = 0;
+            for (uint32_t l = 1; l <= LM; ++l) {
+                code <<= 1;
+                first_code = lane == l ? code : first_code;
+                code += lane_read(clv, l);
+            }
+            if (lane <= LM) { sh.more[lane] = upto; sh.first[lane] = first_code; }
         }
         __syncthreads();
-        {
-            // depth of every merged node by pointer jumping (the root, node n - 2, points at itself at distance 0):
-            // after round r a node knows its 2^r-th ancestor and the distance to it.  Two buffers of packed
-            // (distance << 16 | ancestor) words, in cnt[] and nodew[], which are both free here.
-            const uint32_t root = n_used - 2u;
-            uint32_t* cur = cnt;
-            uint32_t* nxt = nodew;
-            for (uint32_t k = tid; k + 1 < n_used; k += NT) cur[k] = k == root ? root : ((1u << 16) | parent_node[k]);
-            __syncthreads();
-            for (uint32_t span = 1; span < n_used; span <<= 1) {  // uniform trip count
-                for (uint32_t k = tid; k + 1 < n_used; k += NT) {
-                    const uint32_t me = cur[k], up = cur[me & 0xFFFFu];
-                    nxt[k] = ((me >> 16) + (up >> 16)) << 16 | (up & 0xFFFFu);
-                }
-                __syncthreads();
-                uint32_t* sw = cur; cur = nxt; nxt = sw;
-            }
-            for (uint32_t k = tid; k + 1 < n_used; k += NT) depth_node[k] = (uint16_t)(cur[k] >> 16);
-            __syncthreads();
-            if (tid == 0) cnt[0] = n_escape;  // read again at the end (nothing below writes cnt[])
+        for (uint32_t i = tid; i < n_used; i += NT) {  // lengths are handed out most frequent leaf first (the leaves are sorted by rising count)
+            const uint32_t rank = n_used - 1u - i;
+            uint32_t l = 1;
+            while (l < g.LMAX && rank >= sh.more[l]) ++l;
+            len_s[(uint32_t)(key[i] & 0xFFFFu)] = (uint16_t)l;
         }
-        // leaf depths; parent_leaf[] is reused to hold the depth of leaf i (sorted order)
-        uint32_t local_max = 0;
-        for (uint32_t i = tid; i < n_used; i += NT) {
-            const uint32_t d = depth_node[parent_leaf[i]] + 1u;
-            parent_leaf[i] = (uint16_t)d;
-            local_max = max(local_max, d);
-        }
-        if (local_max) atomicMax(&sh.maxlen, local_max);
         __syncthreads();
-    }
-    if (n_used >= 2) {
-        if (sh.maxlen > g.LMAX) {
-            for (uint32_t i = tid; i < n_used; i += NT) atomicAdd(&sh.cl[min((uint32_t)parent_leaf[i], g.LMAX)], 1u);
-            __syncthreads();
-            if (tid == 0) {
-                const uint32_t LM = g.LMAX;
-                uint64_t kraft = 0;
-                for (uint32_t L = 1; L <= LM; ++L) kraft += (uint64_t)sh.cl[L] << (LM - L);
-                while (kraft > (1ull << LM) && sh.cl[LM] > 0) {
-                    sh.cl[LM] -= 1;
-                    for (uint32_t L = LM - 1; L >= 1; --L)
-                        if (sh.cl[L]) { sh.cl[L] -= 1; sh.cl[L + 1] += 2; break; }
-                    kraft -= 1;
+        if (wave == 0) {  // a symbol's codeword: the first of its length and one for every smaller symbol of that length
+            uint32_t next[kLmaxLimit + 1];
+#pragma unroll
+            for (uint32_t l = 1; l <= (uint32_t)kLmaxLimit; ++l) next[l] = l <= g.LMAX ? (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.first[l]) : 0u;
+            for (uint32_t s0 = sym_lo; s0 <= sym_hi; s0 += 64u) {
+                const uint32_t l_mine = s0 + lane <= sym_hi ? len_s[s0 + lane] : 0u;
+                uint32_t mine_code = 0;
+#pragma unroll
+                for (uint32_t l = 1; l <= (uint32_t)kLmaxLimit; ++l) {
+                    const uint64_t same = __ballot(l_mine == l);
+                    mine_code = l_mine == l ? __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, next[l])) : mine_code;
+                    next[l] += (uint32_t)__popcll(same);
                 }
-                // next[L] = number of leaves (counted from the most frequent) with length < L
-                uint32_t acc = 0;
-                for (uint32_t L = 1; L <= LM; ++L) { sh.next[L] = acc; acc += sh.cl[L]; }
-                sh.next[LM + 1] = acc;
+                if (l_mine != 0u) nodew[s0 + lane] = mine_code;
             }
-            __syncthreads();
-            for (uint32_t i = tid; i < n_used; i += NT) {
-                const uint32_t rank = n_used - 1u - i;  // 0 = most frequent (leaves are sorted by rising count)
-                uint32_t L = 1;
-                while (L < g.LMAX && rank >= sh.next[L + 1]) ++L;
-                parent_leaf[i] = (uint16_t)L;
-            }
-            __syncthreads();
-            if (tid < kLmaxLimit + 2) sh.cl[tid] = 0;
-            __syncthreads();
         }
-        if (!sh.codes_done) {  // uniform
-            for (uint32_t i = tid; i < n_used; i += NT) len_s[(uint32_t)(key[i] & 0xFFFFu)] = parent_leaf[i];
-            __syncthreads();
-            // codewords
-            for (uint32_t k = k0; k < k1; ++k)
-                if (len_s[k]) atomicAdd(&sh.cl[len_s[k]], 1u);
-            __syncthreads();
-            if (tid == 0) {
-                uint32_t code = 0;
-                for (uint32_t L = 1; L <= g.LMAX; ++L) {
-                    code <<= 1;
-                    sh.next[L] = code;
-                    code += sh.cl[L];
-                }
-            }
-            __syncthreads();
-            // a symbol's codeword: the first code of its length plus the number of smaller symbols of that length
-            for (uint32_t k = sym_lo + tid; k <= sym_hi; k += NT) {
-                const uint32_t L = len_s[k];
-                if (L) {
-                    uint32_t r = 0;
-                    for (uint32_t j = sym_lo; j < k; ++j) r += len_s[j] == L ? 1u : 0u;
-                    nodew[k] = sh.next[L] + r;
-                }
-            }
-            __syncthreads();
-        }
+        if (tid == 0) cnt[0] = n_escape;  // read again at the end
+        __syncthreads();
     }
     for (uint32_t k = k0; k < k1; ++k) {
         uint32_t L = len_s[k];

@@ -1,4 +1,4 @@
-"""Codebooks of up to 64 used symbols, which one wavefront builds, at the counts where the order of merging is decided by ties or the
+"""Codebooks of up to 64 used symbols, which one wavefront builds in registers, and of more, at the counts where the order of merging is decided by ties or the
 code lengths run into the limit: lengths and codewords against the oracle's, by symbol."""
 import numpy as np
 import pytest
@@ -24,7 +24,7 @@ def _counts(rng, kind, n, total):
 
 
 KINDS = ["equal", "two values", "falling", "doubling", "fibonacci", "bell", "steps", "random"]
-USED = [1, 2, 3, 4, 5, 7, 8, 9, 31, 32, 33, 62, 63, 64, 65]
+USED = [1, 2, 3, 4, 5, 7, 8, 9, 31, 32, 33, 62, 63, 64, 65, 66, 100, 127, 128, 129, 130, 193, 400]
 
 
 @pytest.mark.parametrize("lmax", [10, 12])
@@ -40,7 +40,7 @@ def test_codebooks_of_every_shape(B, lmax):
     hists = []
     for t, (kind, n) in enumerate(cases):
         c = _counts(rng, kind, n, B * D)
-        bins = np.sort(rng.choice(np.arange(-100, 100), n, replace=False))
+        bins = np.sort(rng.choice(np.arange(-220, 220), n, replace=False))
         c = c[rng.permutation(n)]
         x[t] = rng.permutation(np.repeat(bins, c)).astype(np.float32) * (2 * EB)
         h = np.zeros(2 * R, np.uint64)
