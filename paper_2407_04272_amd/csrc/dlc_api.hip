@@ -146,6 +146,7 @@ static size_t carve(const Geom& g, uint8_t* base, Ws* w) {
     uint8_t* lens = take((size_t)g.T * g.K);
     uint8_t* state = take(8 * (size_t)g.NG);
     uint8_t* ready = take(4 * (size_t)g.T);
+    uint8_t* arrived = take(4 * (size_t)g.T);
     uint8_t* ws0 = take(4 * (size_t)g.T);
     uint8_t* ws1 = take(4 * (size_t)g.T);
     uint8_t* plane = g.sample ? nullptr : take((size_t)g.NG * kW * g.S);  // (with a sampled codebook every call is a single pass)
@@ -173,7 +174,7 @@ static size_t carve(const Geom& g, uint8_t* base, Ws* w) {
         w->qp = (QParam*)qp;
         w->hist = (uint32_t*)hist; w->hist_view = (uint32_t*)hview; w->ctrl = (Ctrl*)ctrl;
         w->tmeta = (TMeta*)tmeta;
-        w->enc = (uint16_t*)enc; w->lens = lens; w->state = (uint64_t*)state; w->ready = (uint32_t*)ready;
+        w->enc = (uint16_t*)enc; w->lens = lens; w->state = (uint64_t*)state; w->ready = (uint32_t*)ready; w->arrived = (uint32_t*)arrived;
         w->word_start = (uint32_t*)ws0; w->word_end = (uint32_t*)ws1;
         w->sym_plane = plane;
         w->esc_count = (uint32_t*)escc;

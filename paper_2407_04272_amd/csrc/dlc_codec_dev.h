@@ -100,7 +100,15 @@ struct HistLoads {
     }
 };
 
-template <bool F16, bool VEC, bool FULL, bool LZ, bool PLANE = true>
+// PLANE: kNoPlane, kPlane, or kPlaneThrough: past the caches, for other work-groups of the launch
+enum PlaneStore { kNoPlane, kPlane, kPlaneThrough };
+template <PlaneStore PLANE>
+__device__ __forceinline__ void plane_store(uint32_t* p, uint32_t v) {
+    if constexpr (PLANE == kPlaneThrough) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else if constexpr (PLANE == kPlane) *p = v;
+}
+
+template <bool F16, bool VEC, bool FULL, bool LZ, PlaneStore PLANE = kPlane>
 __device__ __forceinline__ void hist_count(const HistLoads<F16, VEC, FULL>& D, uint32_t n_units, uint32_t lane, const QParam& q,
                                            const HistC& H, uint32_t* plane) {
     constexpr uint32_t kBins = LZ ? kWinSkip : kWinEsc;  // window indices that stand for a symbol
@@ -132,8 +140,8 @@ __device__ __forceinline__ void hist_count(const HistLoads<F16, VEC, FULL>& D, u
                 lds_count((sl[v] << 6) + rows);
             }
             static_assert(kWinCopies * 4u == 64u, "a row of the window");
-            if constexpr (PLANE)
-                plane[u * kW + lane] = __builtin_amdgcn_perm(sl[1], sl[0], 0x0C0C0400u) | __builtin_amdgcn_perm(sl[3], sl[2], 0x04000C0Cu);
+            if constexpr (PLANE != kNoPlane)
+                plane_store<PLANE>(plane + u * kW + lane, __builtin_amdgcn_perm(sl[1], sl[0], 0x0C0C0400u) | __builtin_amdgcn_perm(sl[3], sl[2], 0x04000C0Cu));
             continue;
         }
         uint32_t w[4];
@@ -164,18 +172,66 @@ __device__ __forceinline__ void hist_count(const HistLoads<F16, VEC, FULL>& D, u
                 if (sl[v] == kWinBins && w[v] != kPastEnd) lds_count(H.exact + (w[v] + H.win_lo) * 4u);
         }
         // the window indices of these four elements, for the encode kernel (a unit of this wavefront only)
-        if constexpr (PLANE) {
-            if (FULL || u < n_units) plane[u * kW + lane] = sl[0] | (sl[1] << 8) | (sl[2] << 16) | (sl[3] << 24);
+        if constexpr (PLANE != kNoPlane) {
+            if (FULL || u < n_units) plane_store<PLANE>(plane + u * kW + lane, sl[0] | (sl[1] << 8) | (sl[2] << 16) | (sl[3] << 24));
         }
     }
 }
 
-template <bool F16, bool VEC, bool FULL, bool LZ, bool PLANE = true>
+template <bool F16, bool VEC, bool FULL, bool LZ, PlaneStore PLANE = kPlane>
 __device__ __forceinline__ void hist_block(const uint8_t* base, uint32_t rem, uint32_t n_units, uint32_t lane, const QParam& q,
                                            const HistC& H, uint32_t* plane) {
     HistLoads<F16, VEC, FULL> D;
     D.load(base, rem, n_units, lane);
     hist_count<F16, VEC, FULL, LZ, PLANE>(D, n_units, lane, q, H, plane);
+}
+
+// The units [u0, u1) of a table (u0 a multiple of kHistBlk, and u1 if the table does not end there) by a work-group of NW wavefronts: a block of
+// units at a time, the loads of the next two on their way while one is counted (memory takes 3 us to answer when all compute
+// units ask, and there are few wavefronts); then the block that the table ends in.
+template <bool F16, bool VEC, uint32_t NW, PlaneStore PLANE>
+__device__ __forceinline__ void hist_units(const uint8_t* tab, uint8_t* plane_t, const Geom& g, uint32_t u0, uint32_t u1, uint32_t wave,
+                                           uint32_t lane, const QParam& q, const HistC& H) {
+    const uint32_t whole = min(u1, g.n / (kW * kV));  // units that lie inside the table
+    auto first_of = [&](uint32_t u) { return tab + (size_t)u * (kW * kV) * g.es; };
+    auto plane_of = [&](uint32_t u) { return reinterpret_cast<uint32_t*>(plane_t + u * (kW * kV)); };
+    uint32_t u = u0 + wave * kHistBlk;
+    constexpr uint32_t kStep = NW * kHistBlk;
+    HistLoads<F16, VEC, true> A, B, C;
+    auto have = [&](uint32_t v) { return v + kHistBlk <= whole; };  // uniform over the wavefront
+    if (have(u)) A.load(first_of(u), 0u, kHistBlk, lane);
+    if (have(u + kStep)) B.load(first_of(u + kStep), 0u, kHistBlk, lane);
+    auto turn = [&](HistLoads<F16, VEC, true>& now, HistLoads<F16, VEC, true>& later) {
+        if (!have(u)) return false;
+        if (have(u + 2u * kStep)) later.load(first_of(u + 2u * kStep), 0u, kHistBlk, lane);
+        hist_count<F16, VEC, true, false, PLANE>(now, kHistBlk, lane, q, H, plane_of(u));
+        u += kStep;
+        return true;
+    };
+    while (turn(A, C) && turn(B, A) && turn(C, B)) {}
+    if (u < u1)
+        hist_block<F16, VEC, false, false, PLANE>(first_of(u), g.n - u * (kW * kV), min(kHistBlk, u1 - u), lane, q, H, plane_of(u));
+}
+
+// a table's counts in LDS (window rows, then the exact counts), added to those in memory by NT threads: the copies of a row (skewed
+// start: the threads of a wavefront read different banks) plus the exact counts
+template <bool LZ, uint32_t NT>
+__device__ __forceinline__ void hist_merge(const uint32_t* lh, const Geom& g, uint32_t* hist_t, uint32_t tid) {
+    const uint32_t* exact = lh + (kWinBins + 1u) * kWinCopies;
+    const uint32_t win_lo = win_lo_of(g.R);
+    for (uint32_t k = tid; k < g.K; k += NT) {
+        uint32_t s = exact[k];
+        const uint32_t w = k - win_lo;
+        if (w < (LZ ? kWinSkip : kWinEsc)) {
+            const uint32_t* row = lh + w * kWinCopies;
+            for (uint32_t c = 0; c < kWinCopies; ++c) s += row[(c + tid) & (kWinCopies - 1u)];
+        }
+        if (k == 0u) {  // the escapes
+            const uint32_t* row = lh + kWinEsc * kWinCopies;
+            for (uint32_t c = 0; c < kWinCopies; ++c) s += row[c];
+        }
+        if (s) atomicAdd(&hist_t[k], s);
+    }
 }
 
 // ------------------------------------------------------------------------------------------------

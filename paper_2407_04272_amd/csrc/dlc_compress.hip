@@ -15,16 +15,22 @@ bool launch_encode_64(const Geom& g, const FixedLayout& F, const void* payload, 
                       uint64_t capacity, uint64_t* out_bytes, hipStream_t s);
 bool launch_table_64(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
                      uint64_t capacity, uint64_t* out_bytes, hipStream_t s);
+bool launch_flow_64(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
+                    uint64_t capacity, uint64_t* out_bytes, hipStream_t s);
 hipError_t encode_set_attributes_64();
 bool launch_encode_128(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
                       uint64_t capacity, uint64_t* out_bytes, hipStream_t s);
 bool launch_table_128(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
                      uint64_t capacity, uint64_t* out_bytes, hipStream_t s);
+bool launch_flow_128(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
+                    uint64_t capacity, uint64_t* out_bytes, hipStream_t s);
 hipError_t encode_set_attributes_128();
 bool launch_encode_256(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
                       uint64_t capacity, uint64_t* out_bytes, hipStream_t s);
 bool launch_table_256(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
                      uint64_t capacity, uint64_t* out_bytes, hipStream_t s);
+bool launch_flow_256(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
+                    uint64_t capacity, uint64_t* out_bytes, hipStream_t s);
 hipError_t encode_set_attributes_256();
 void launch_encode_carry_64(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch, uint8_t* out,
                             uint64_t capacity, uint32_t bpt, hipStream_t s);
@@ -82,7 +88,6 @@ __global__ __launch_bounds__(256) void k_hist(const void* payload, Geom g, const
     const uint32_t upg = sa.upg, gstride = sa.gstride;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t lds0 = (uint32_t)(uintptr_t)lh;
-    const uint32_t win_lo = win_lo_of(g.R);
     const uint32_t n_words = (kWinBins + 1u) * kWinCopies + g.K;
     const uint64_t total_units = (uint64_t)g.T * U;
     // this wavefront's units [w0, w1) and the work-group's [g0, g1), as global unit numbers
@@ -117,27 +122,12 @@ __global__ __launch_bounds__(256) void k_hist(const void* payload, Geom g, const
                 const uint32_t rem = g.n - first;
                 const uint32_t n_units = min(kHistBlk, ue - u);
                 uint32_t* plane = SAMPLE ? nullptr : reinterpret_cast<uint32_t*>(sym_plane + (size_t)t * plane_stride(g) + first);
-                if (n_units == kHistBlk && rem >= kHistBlk * kW * kV) hist_block<F16, VEC, true, LZ, !SAMPLE>(base, rem, n_units, lane, q, H, plane);
-                else hist_block<F16, VEC, false, LZ, !SAMPLE>(base, rem, n_units, lane, q, H, plane);
+                if (n_units == kHistBlk && rem >= kHistBlk * kW * kV) hist_block<F16, VEC, true, LZ, SAMPLE ? kNoPlane : kPlane>(base, rem, n_units, lane, q, H, plane);
+                else hist_block<F16, VEC, false, LZ, SAMPLE ? kNoPlane : kPlane>(base, rem, n_units, lane, q, H, plane);
             }
         }
         __syncthreads();
-        // merge: the window rows (sum of the copies, skewed start so that the threads of a wavefront read different
-        // banks) plus the exact counts
-        const uint32_t* exact = lh + (kWinBins + 1u) * kWinCopies;
-        for (uint32_t k = tid; k < g.K; k += 256) {
-            uint32_t s = exact[k];
-            const uint32_t w = k - win_lo;
-            if (w < (LZ ? kWinSkip : kWinEsc)) {
-                const uint32_t* row = lh + w * kWinCopies;
-                for (uint32_t c = 0; c < kWinCopies; ++c) s += row[(c + tid) & (kWinCopies - 1u)];
-            }
-            if (k == 0u) {  // the escapes
-                const uint32_t* row = lh + kWinEsc * kWinCopies;
-                for (uint32_t c = 0; c < kWinCopies; ++c) s += row[c];
-            }
-            if (s) atomicAdd(&hist[(size_t)t * g.K + k], s);
-        }
+        hist_merge<LZ, 256>(lh, g, hist + (size_t)t * g.K, tid);
         __syncthreads();
     }
 }
@@ -361,17 +351,26 @@ hipError_t launch_compress(const Geom& g, const void* payload, uint8_t* out, uin
         }
         return hipGetLastError();
     }
-    // Small tables go from payload to coded groups in one launch, a work-group per table.  Up to eight groups that is the
+    // Larger tables go from payload to coded groups in one launch as well, a table being the work of many work-groups (k_flow), where
+    // the payload is so large that the coding of some tables has the counting of others beside it: then memory works all the time.
+    // Where it is not, the waits for counts and codebooks inside the launch are longer than the gaps between three launches (us, three
+    // launches and one: 65536 units 47.5 and 53, 65536 of 16 tables in chunks of 64 symbols 50 and 54; 75000 56 and 54, 106496 66
+    // and 62, 163840 78 and 75, 262144 106 and 100, 307200 of 300 tables 126 and 112, 524288 184 and 171; in half precision 65536 66
+    // and 71, 75000 81 and 78, 524288 205 and 188).  When every kernel is to be timed by itself the launches stay apart.
+    const uint64_t units = (uint64_t)g.T * ((g.n + kW * kV - 1u) / (kW * kV));
+    const bool flow = !g.lz && units >= 72000u && !prof_on(pl, P_HIST);
+    // Small tables: a work-group per table.  Up to eight groups that is the
     // shorter way whatever the number of tables (one launch for three; 26 tables of eight groups: 35.6 us a call against
     // 36.3, one of one group 17.6 against 24.8).  From nine to sixteen groups, what a work-group has wavefronts for, a
     // work-group has a compute unit to itself, and it is the shorter way where there are tables enough to keep the compute units
     // busy (128 tables of sixteen groups: 65 us against 75; 64: 57 against 51; 26: 53 against 40), but not where a second
     // round of work-groups is nearly empty, and less so the longer the codes are (at ratios of 10 and 5.9: 257 tables of
     // twelve groups 110 and 197 us against 98 and 153; 300: 113 and 202 against 109 and 168; 350: 118 and 205 against 121 and
-    // 184; 400: 124 and 211 against 132 and 197; 512: 142 and 229 against 159 and 344).  Row matching needs every row's
+    // 184; 400: 124 and 211 against 132 and 197; 512: 142 and 229 against 159 and 344), and not in several rounds of larger tables
+    // where k_flow does it (400 of sixteen groups 148 and 141, in half precision 196 and 176; of nine 94 and 96, of twelve in chunks of 64 symbols 52 and 62).  Row matching needs every row's
     // symbols before it knows the counts: it keeps the launches apart, and so do many tables
     // of a large alphabet, whose scratch memory would leave a compute unit one work-group at a time.
-    const bool whole_rounds = (g.T >= 128u && g.T <= 256u) || g.T > 352u;
+    const bool whole_rounds = (g.T >= 128u && g.T <= 256u) || (g.T > 352u && !(flow && g.n >= 200000u));
     const bool fused = !g.lz && (g.G <= 8u || (g.G <= 16u && whole_rounds)) && (g.T <= 256u || g.K <= 1024u);
     const uint32_t tpw = codebook_tables_per_wg(g);
     // The launch that codes the groups finishes the containers, too, where a work-group has a thread for each of a container's
@@ -386,6 +385,14 @@ hipError_t launch_compress(const Geom& g, const void* payload, uint8_t* out, uin
             default: finished = launch_table_256(g, F, payload, w, epoch, out, capacity, fin, s); break;
         }
         if (prof_on(pl, P_TABLE)) prof_end(prof, P_TABLE, s);
+    } else if (flow) {
+        if (prof_on(pl, P_ENCODE)) prof_begin(prof, P_ENCODE, s);
+        switch (g.S) {
+            case 64: finished = launch_flow_64(g, F, payload, w, epoch, out, capacity, fin, s); break;
+            case 128: finished = launch_flow_128(g, F, payload, w, epoch, out, capacity, fin, s); break;
+            default: finished = launch_flow_256(g, F, payload, w, epoch, out, capacity, fin, s); break;
+        }
+        if (prof_on(pl, P_ENCODE)) prof_end(prof, P_ENCODE, s);
     } else {
         // histogram
         {

@@ -429,6 +429,56 @@ __device__ __forceinline__ void build_pairs(uint32_t* pair, const uint16_t* ent,
 // ------------------------------------------------------------------------------------------------
 // groups of tables of any size, from the symbol plane, with the codebooks in memory
 // ------------------------------------------------------------------------------------------------
+// The `per` (NW at most) groups from J.wg % bpt * per on of table J.wg / bpt.  WITHIN: the codebook and the plane come from other work-groups of this launch
+// (of the plane nothing has been read before, so there is nothing old of it in a cache; the codebook's lines hold other tables' too).
+template <int S, bool F16, bool VEC, bool LZ, uint32_t NW, bool WITHIN>
+__device__ __forceinline__ void encode_item(GroupJob& J, const void* payload, const uint8_t* sym_plane, const Geom& g, const FixedLayout& F,
+                                            const QParam* qp, const uint16_t* enc, const TMeta* tmeta, Ctrl* ctrl, uint64_t* state, uint64_t epoch,
+                                            uint8_t* out, uint64_t capacity, uint32_t bpt, uint32_t per, uint32_t* word_start, uint32_t* word_end,
+                                            uint32_t cap, uint32_t pair_max, uint32_t* s_lo, uint32_t* s_hi, unsigned char* smem, uint32_t tid) {
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    J.t = J.wg / bpt;
+    J.grp = wave < per ? (J.wg % bpt) * per + wave : g.G;
+    // the destination this table belongs to: its container starts `capacity` bytes after the previous one, its
+    // groups are numbered and its words are placed from 0, so the scan over work-groups starts anew at its first
+    J.dst = J.t / g.TD;
+    J.tl = J.t - J.dst * g.TD;
+    J.dom0 = J.dst * g.TD * bpt;
+    J.cap = cap;
+    J.lds0 = (uint32_t)(uintptr_t)smem;
+    J.L = enc_lds(NW, per, cap, pair_max);
+    const uint32_t win_lo = win_lo_of(g.R);
+    const uint16_t* enc_t = enc + (size_t)J.t * g.K;
+    uint16_t* ent = reinterpret_cast<uint16_t*>(smem + J.L.ent);
+    const TMeta tm = load_tmeta<WITHIN>(tmeta + J.t);
+    for (uint32_t i = tid; i < 256u; i += 64u * NW) {
+        // (index 254 is the escape, symbol 0; with row matching index 253 marks an element of a row that is stored as
+        // a reference: no bits)
+        const uint32_t c = win_lo + i;
+        const bool sym = i < win_bins(LZ ? 1u : 0u) && c < g.K;
+        uint32_t e = 0u;
+        if (i == kWinEsc || sym) {
+            const uint16_t* p = enc_t + (i == kWinEsc ? 0u : c);
+            e = WITHIN ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
+        }
+        ent[i] = (uint16_t)e;
+        // the span of the used symbols inside the window (a table with one used symbol has a code of length 0 for it)
+        if (sym && c != 0u && (e != 0u || (tm.n_used == 1u && c == tm.sym_lo))) { atomicMin(s_lo, i); atomicMax(s_hi, i); }
+    }
+    __syncthreads();
+    J.lo = min(*s_lo, *s_hi);
+    J.P = *s_hi - J.lo + 1u;
+    J.pairs = J.P <= pair_max;
+    J.special = tm.n_outliers != 0u || (tm.n_used == 1u && tm.sym_lo == 0u) || (tm.sym_lo != 0u && tm.sym_lo < win_lo) ||
+                tm.sym_hi >= win_lo + win_bins(LZ ? 1u : 0u);
+    if (J.pairs) {
+        build_pairs(reinterpret_cast<uint32_t*>(smem + J.L.pair), ent, J.lo, J.P, tid, 64u * NW);
+        __syncthreads();
+    }
+    encode_groups<S, F16, VEC, LZ, NW>(J, payload, sym_plane, g, F, qp, enc, ctrl, state, epoch, out + (uint64_t)J.dst * capacity,
+                                       capacity, word_start, word_end, smem, tid);
+}
+
 template <int S, bool F16, bool VEC, bool LZ, uint32_t NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4)))
 void k_encode(const void* payload, const uint8_t* sym_plane, Geom g, FixedLayout F, const QParam* qp, const uint16_t* enc,
@@ -447,42 +497,117 @@ void k_encode(const void* payload, const uint8_t* sym_plane, Geom g, FixedLayout
             return;
         }
     }
-    J.t = J.wg / bpt;
-    J.grp = (J.wg % bpt) * NW + __builtin_amdgcn_readfirstlane(tid >> 6);
-    // the destination this table belongs to: its container starts `capacity` bytes after the previous one, its
-    // groups are numbered and its words are placed from 0, so the scan over work-groups starts anew at its first
-    J.dst = J.t / g.TD;
-    J.tl = J.t - J.dst * g.TD;
-    J.dom0 = J.dst * g.TD * bpt;
-    J.cap = cap;
-    J.lds0 = (uint32_t)(uintptr_t)smem;
-    J.L = enc_lds(NW, NW, cap, pair_max);
-    const uint32_t win_lo = win_lo_of(g.R);
-    const uint16_t* enc_t = enc + (size_t)J.t * g.K;
-    uint16_t* ent = reinterpret_cast<uint16_t*>(smem + J.L.ent);
-    const TMeta tm = tmeta[J.t];
-    for (uint32_t i = tid; i < 256u; i += 64u * NW) {
-        // (index 254 is the escape, symbol 0; with row matching index 253 marks an element of a row that is stored as
-        // a reference: no bits)
-        const uint32_t c = win_lo + i;
-        const bool sym = i < win_bins(LZ ? 1u : 0u) && c < g.K;
-        const uint32_t e = i == kWinEsc ? enc_t[0] : (sym ? enc_t[c] : 0u);
-        ent[i] = (uint16_t)e;
-        // the span of the used symbols inside the window (a table with one used symbol has a code of length 0 for it)
-        if (sym && c != 0u && (e != 0u || (tm.n_used == 1u && c == tm.sym_lo))) { atomicMin(&s_lo, i); atomicMax(&s_hi, i); }
+    encode_item<S, F16, VEC, LZ, NW, false>(J, payload, sym_plane, g, F, qp, enc, tmeta, ctrl, state, epoch, out, capacity, bpt, NW, word_start, word_end,
+                                            cap, pair_max, &s_lo, &s_hi, smem, tid);
+}
+
+// ------------------------------------------------------------------------------------------------
+// tables of more groups than one work-group takes: quantise, count, codebook, encode in one launch
+//   Work-groups take tickets in the order in which they start.  Of every table there are `cpt` tickets to count a share of it (plane out, past
+//   the caches; counts added to the table's), the last of which to finish builds the codebook, and `ept` to code `gpe` groups each, which
+//   wait for that.  The tickets to code a table come `lag` tables after those to count it, so the codebook is there when they start;
+//   whoever is waited for has an earlier ticket and waits for nobody (counting) or for still earlier ones (the scan).
+//   What bounds it: memory (512 MiB: payload read, plane out and in, words out, 850 MB in the 150 us until the last table is
+//   counted), then the last tables' chain of codebook 6, tables 2, walk 9, scan 4 and copy 3 us.  Three launches, each of which ends with
+//   a part of the chip, took 184 us where this takes 171; 300 tables of 262144 elements 126, so 112.
+// ------------------------------------------------------------------------------------------------
+struct FlowPlan {
+    uint32_t cpt, units;  // tickets to count a table, units each (a multiple of kHistBlk)
+    uint32_t ept, gpe;    // tickets to code a table, groups each
+    uint32_t lag;         // tables counted before the first is coded
+};
+constexpr uint32_t kFlowWaves = 8;
+
+template <int S, bool F16, bool VEC>
+__global__ __launch_bounds__(64 * kFlowWaves) __attribute__((amdgpu_waves_per_eu(4)))
+void k_flow(const void* payload, uint8_t* sym_plane, Geom g, FixedLayout F, const QParam* qp, uint32_t* hist, uint32_t* hist_view, uint16_t* enc,
+            uint8_t* lens, TMeta* tmeta, Ctrl* ctrl, uint64_t* state, uint32_t* ready, uint32_t* arrived, uint64_t epoch, uint8_t* out, uint64_t capacity,
+            FlowPlan P, uint32_t* word_start, uint32_t* word_end, uint64_t* out_bytes, uint32_t xn, uint32_t cap, uint32_t pair_max) {
+    constexpr uint32_t NW = kFlowWaves, NT = 64u * NW;
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ CodebookShared s_cb;
+    __shared__ uint32_t s_ticket, s_lo, s_hi, s_go;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid == 0) { s_ticket = atomicAdd(&ctrl->ticket, 1u); s_lo = 255u; s_hi = 0u; }
+    __syncthreads();
+    const uint32_t ticket = __builtin_amdgcn_readfirstlane(s_ticket);
+    // ticket -> what to do: the first `lag` tables' counting; a table's counting and the coding of the table `lag` before it; the last tables' coding
+    uint32_t t, r;
+    bool count = true;
+    {
+        const uint32_t head = P.lag * P.cpt, per = P.cpt + P.ept, body = (g.T - P.lag) * per;
+        if (ticket < head) {
+            t = ticket / P.cpt;
+            r = ticket - t * P.cpt;
+        } else if (ticket - head < body) {
+            const uint32_t i = ticket - head, k = i / per;
+            r = i - k * per;
+            count = r < P.cpt;
+            t = count ? P.lag + k : k;
+            r = count ? r : r - P.cpt;
+        } else {
+            const uint32_t i = ticket - head - body;
+            t = i / P.ept;
+            r = i - t * P.ept;
+            t += g.T - P.lag;
+            count = false;
+        }
+    }
+    if (t >= g.T) {  // uniform; xn for every container
+        finish_container<NT, true>(g, F, tmeta, lens, qp, ctrl, state, ready, epoch, P.ept, out, capacity, out_bytes, ticket - g.T * (P.cpt + P.ept), xn, *reinterpret_cast<FinLds<NT>*>(smem), tid);
+        return;
+    }
+    if (count) {
+        uint32_t* const lh = reinterpret_cast<uint32_t*>(smem);
+        {
+            uint4* z = reinterpret_cast<uint4*>(lh);
+            const uint32_t n4 = ((kWinBins + 1u) * kWinCopies + g.K + 3u) / 4u;
+            for (uint32_t k = tid; k < n4; k += NT) z[k] = make_uint4(0, 0, 0, 0);
+        }
+        __syncthreads();
+        {
+            const QParam q = qp[t];
+            const HistC H = hist_consts<false>(g, q, (uint32_t)(uintptr_t)smem, lane);
+            const uint32_t U = (g.n + kW * kV - 1u) / (kW * kV), u0 = r * P.units;
+            hist_units<F16, VEC, NW, kPlaneThrough>(static_cast<const uint8_t*>(payload) + (size_t)t * g.n * g.es, sym_plane + (size_t)t * plane_stride(g), g,
+                                                    u0, min(U, u0 + P.units), wave, lane, q, H);
+        }
+        __syncthreads();
+        hist_merge<false, NT>(lh, g, hist + (size_t)t * g.K, tid);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this work-group's plane and counts are in memory
+        __syncthreads();
+        if (tid == 0) {
+            const bool last = __hip_atomic_fetch_add(&arrived[t], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == P.cpt;
+            if (last) __hip_atomic_store(&arrived[t], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s_go = last ? 1u : 0u;
+        }
+        __syncthreads();
+        if (s_go == 0u) return;  // uniform
+        codebook_build<NT>(g, hist + (size_t)t * g.K, hist_view + (size_t)t * g.K, enc + (size_t)t * g.K, lens + (size_t)t * g.K, tmeta + t, smem, s_cb, tid, 0u, true);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) table_ready(ready, epoch, t);
+        return;
+    }
+    if (tid == 0) {
+        bool there = true;
+        for (uint32_t spins = 0; __hip_atomic_load(&ready[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != (uint32_t)epoch; ++spins) {
+            if (spins > kSpinLimit) {  // never expected; the bound only guarantees termination
+                set_status(ctrl, DLC_ESTATE);
+                atomicOr(&ctrl->abort, 1u);
+                there = false;
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+        s_go = there ? 1u : 0u;
     }
     __syncthreads();
-    J.lo = min(s_lo, s_hi);
-    J.P = s_hi - J.lo + 1u;
-    J.pairs = J.P <= pair_max;
-    J.special = tm.n_outliers != 0u || (tm.n_used == 1u && tm.sym_lo == 0u) || (tm.sym_lo != 0u && tm.sym_lo < win_lo) ||
-                tm.sym_hi >= win_lo + win_bins(LZ ? 1u : 0u);
-    if (J.pairs) {
-        build_pairs(reinterpret_cast<uint32_t*>(smem + J.L.pair), ent, J.lo, J.P, tid, 64u * NW);
-        __syncthreads();
-    }
-    encode_groups<S, F16, VEC, LZ, NW>(J, payload, sym_plane, g, F, qp, enc, ctrl, state, epoch, out + (uint64_t)J.dst * capacity,
-                                       capacity, word_start, word_end, smem, tid);
+    if (s_go == 0u) return;  // uniform (those behind find no record of this one and give up as well)
+    GroupJob J;
+    J.wg = t * P.ept + r;
+    encode_item<S, F16, VEC, false, NW, true>(J, payload, sym_plane, g, F, qp, enc, tmeta, ctrl, state, epoch, out, capacity, P.ept, P.gpe, word_start, word_end,
+                                              cap, pair_max, &s_lo, &s_hi, smem, tid);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -538,28 +663,7 @@ void k_table(const void* payload, uint8_t* sym_plane, Geom g, FixedLayout F, con
         const HistC H = hist_consts<false>(g, q, J.lds0, lane);
         const uint8_t* tab = static_cast<const uint8_t*>(payload) + (size_t)t * g.n * g.es;
         uint8_t* plane_t = sym_plane + (size_t)t * plane_stride(g);
-        const uint32_t U = (g.n + kW * kV - 1u) / (kW * kV);  // units of 256 elements, a block of four at a time
-        const uint32_t whole = g.n / (kW * kV);               // units that lie inside the table
-        auto first_of = [&](uint32_t u) { return tab + (size_t)u * (kW * kV) * g.es; };
-        auto plane_of = [&](uint32_t u) { return reinterpret_cast<uint32_t*>(plane_t + u * (kW * kV)); };
-        // whole blocks, the loads of the next two on their way while one is counted (memory takes 3 us to answer when all
-        // compute units ask, and there are few wavefronts); then the block that the table ends in
-        uint32_t u = wave * kHistBlk;
-        constexpr uint32_t kStep = NW * kHistBlk;
-        HistLoads<F16, VEC, true> A, B, C;
-        auto have = [&](uint32_t v) { return v + kHistBlk <= whole; };  // uniform over the wavefront
-        if (have(u)) A.load(first_of(u), 0u, kHistBlk, lane);
-        if (have(u + kStep)) B.load(first_of(u + kStep), 0u, kHistBlk, lane);
-        auto turn = [&](HistLoads<F16, VEC, true>& now, HistLoads<F16, VEC, true>& later) {
-            if (!have(u)) return false;
-            if (have(u + 2u * kStep)) later.load(first_of(u + 2u * kStep), 0u, kHistBlk, lane);
-            hist_count<F16, VEC, true, false>(now, kHistBlk, lane, q, H, plane_of(u));
-            u += kStep;
-            return true;
-        };
-        while (turn(A, C) && turn(B, A) && turn(C, B)) {}
-        if (u < U)
-            hist_block<F16, VEC, false, false>(first_of(u), g.n - u * (kW * kV), min(kHistBlk, U - u), lane, q, H, plane_of(u));
+        hist_units<F16, VEC, NW, kPlane>(tab, plane_t, g, 0u, (g.n + kW * kV - 1u) / (kW * kV), wave, lane, q, H);
     }
     __syncthreads();
     for (uint32_t r = tid; r < 256u; r += NT) {  // the copies of a row (skewed start: different banks)
@@ -702,6 +806,44 @@ bool DLC_CAT(launch_encode_, DLC_S)(const Geom& g, const FixedLayout& F, const v
     return DLC_CAT(encode_launch_, DLC_S)<8u>(g, F, payload, w, epoch, out, capacity, out_bytes, s);
 }
 
+// Counting, codebooks and coding in one launch (out_bytes as above)
+bool DLC_CAT(launch_flow_, DLC_S)(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch,
+                                  uint8_t* out, uint64_t capacity, uint64_t* out_bytes, hipStream_t s) {
+    constexpr int S = DLC_S;
+    constexpr uint32_t NW = kFlowWaves;
+    if (g.TD > 64u * NW) out_bytes = nullptr;
+    const uint32_t xn = finish_groups(g, 64u * NW);
+    FlowPlan P;
+    // Shares of a table alike, 1024 in all, two rounds of the work-groups that run at a time, so that what a share costs
+    // besides its loads (3 us: counters cleared, counts added) is little; no larger than 256 KiB of fp32 where memory bounds the
+    // counting (512 MiB by 128, 256 and 512 units 175, 171 and 177 us), 512 units where it does not (half precision 241, 208 and 188).
+    const uint32_t U = (g.n + kW * kV - 1u) / (kW * kV), most = g.dtype == DLC_F16 ? 512u : 256u;
+    const uint32_t want = (uint32_t)std::min<uint64_t>(most, std::max<uint64_t>(64u, (uint64_t)g.T * U / 1024u));
+    const uint32_t shares = (U + want - 1u) / want;
+    P.units = ((U + shares - 1u) / shares + kHistBlk - 1u) / kHistBlk * kHistBlk;
+    P.cpt = (U + P.units - 1u) / P.units;
+    P.gpe = NW;
+    P.ept = (g.G + P.gpe - 1u) / P.gpe;
+    // as many shares ahead as to have a table counted when its coding starts, with all of the work-groups between at work (512 MiB,
+    // 600, 1000 and 1600 shares: 176, 171 and 172 us)
+    P.lag = std::min(g.T, (1024u + P.cpt - 1u) / P.cpt);
+    const uint32_t n_wg = g.T * (P.cpt + P.ept) + (out_bytes ? g.ND * xn : 0u);
+    const uint32_t budget = kLdsMax / 2u - kTableStatic;
+    uint32_t cap = (uint32_t)S * 12u / 32u;
+    while (cap > (uint32_t)S / 8u && enc_lds(NW, P.gpe, cap, 60u).end > budget) --cap;
+    const uint32_t pair_max = pair_max_for(budget, NW, P.gpe, cap);
+    size_t sm = std::max((size_t)enc_lds(NW, P.gpe, cap, pair_max).end, std::max(hist_lds_bytes(g.K), codebook_smem(g.K)));
+    if (out_bytes) sm = std::max(sm, sizeof(FinLds<64u * NW>));
+    const bool f16 = g.dtype == DLC_F16;
+#define DLC_FLOW(FF, V)                                                                                               \
+    hipLaunchKernelGGL((k_flow<S, FF, V>), dim3(n_wg), dim3(64u * NW), sm, s, payload, w.sym_plane, g, F, w.qp, w.hist, w.hist_view, w.enc, w.lens, \
+                       w.tmeta, w.ctrl, w.state, w.ready, w.arrived, epoch, out, capacity, P, w.word_start, w.word_end, out_bytes, xn, cap, pair_max)
+    if (f16) { if (g.vec) DLC_FLOW(true, true); else DLC_FLOW(true, false); }
+    else { if (g.vec) DLC_FLOW(false, true); else DLC_FLOW(false, false); }
+#undef DLC_FLOW
+    return out_bytes != nullptr;
+}
+
 template <uint32_t NW>
 static bool DLC_CAT(table_launch_, DLC_S)(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch,
                                           uint8_t* out, uint64_t capacity, uint64_t* out_bytes, uint32_t cap, uint32_t budget, uint32_t room, hipStream_t s) {
@@ -802,6 +944,10 @@ hipError_t DLC_CAT(encode_set_attributes_, DLC_S)() {
                         reinterpret_cast<const void*>(k_encode<S, false, true, true, 4u>), reinterpret_cast<const void*>(k_encode<S, true, true, true, 4u>)};
     for (const void* k : ks)
         if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kEncLdsMax);
+    const void* fs[] = {reinterpret_cast<const void*>(k_flow<S, false, false>), reinterpret_cast<const void*>(k_flow<S, false, true>),
+                        reinterpret_cast<const void*>(k_flow<S, true, false>), reinterpret_cast<const void*>(k_flow<S, true, true>)};
+    for (const void* k : fs)
+        if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLdsMax - kTableStatic));
     return e;
 }
 

@@ -275,6 +275,7 @@ struct Ws {
     uint8_t* lens = nullptr;       // [T][K]
     uint64_t* state = nullptr;     // [NG] look-back records
     uint32_t* ready = nullptr;     // [T] the call whose codebook of the table is in memory
+    uint32_t* arrived = nullptr;   // [T] shares of the table that have been counted; zero between calls
     uint32_t* word_start = nullptr;  // [T]
     uint32_t* word_end = nullptr;    // [T]
     uint8_t* sym_plane = nullptr;  // [T][G*64*S] window index of every element (255: see the element itself)

@@ -1,0 +1,127 @@
+"""Payloads so large that counting, codebooks and coding of their tables share one launch (k_flow): containers and reconstructions
+against the oracle, byte for byte, over its remainders (shares of a table, groups a ticket, the table's end) and its neighbours'
+paths (several containers, more tables than a work-group has threads, a carried codebook's first call)."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import to_device
+
+pytestmark = pytest.mark.gpu
+
+UNIT = 256
+
+
+def _payload(rng, T, B, D, dtype, wide):
+    sigma = 10.0 ** rng.uniform(-2.5, -1.0, (T, 1, 1)).astype(np.float32)
+    rows = (rng.standard_normal((T, 64, D), dtype=np.float32) * sigma)
+    x = np.take_along_axis(rows, rng.integers(0, 64, (T, B, 1)), axis=1)
+    x += rng.standard_normal((T, 1, D), dtype=np.float32) * sigma * 0.1
+    x = x.astype(dtype)
+    x.reshape(-1)[::100003] = 3e4                # an escape in some groups
+    rel = np.where(np.arange(T) % 4 == 3, 0.004 if wide else 0.01, 0.05)
+    eb = ((np.quantile(x.reshape(T, -1)[:, ::97].astype(np.float32), 0.999, axis=1) * 2) * rel).astype(np.float32)
+    x[T // 2] = x[T // 2, 0, 0]                  # one symbol throughout
+    return x, np.maximum(eb, np.float32(1e-4))
+
+
+CASES = [  # T, B, D, S, dtype, destinations, radius
+    (26, 11300, 64, 256, np.float32, 1, 512),    # 45 groups and a part of one
+    (1, 150001, 125, 256, np.float32, 1, 512),   # one table off the 16-byte grid, its end inside a unit
+    (35, 5001, 111, 128, np.float32, 1, 512),
+    (19, 16385, 64, 64, np.float32, 1, 2048),    # an alphabet of 4096 symbols
+    (560, 1100, 64, 64, np.float16, 1, 512),     # more tables than a work-group has threads: the container by a launch of its own
+    (23, 10001, 96, 128, np.float16, 1, 128),
+    (9, 1700, 333, 256, np.float32, 4, 512),     # four containers
+]
+
+
+@pytest.mark.parametrize("T,B,D,S,dtype,nd,R", CASES)
+def test_containers_match_the_oracle(T, B, D, S, dtype, nd, R):
+    import torch
+    from paper_2407_04272_amd import binding as b
+    assert T * nd * ((B * D + UNIT - 1) // UNIT) >= 72000
+    rng = np.random.default_rng(T + B)
+    cfg = b.make_config(b.F16 if dtype == np.float16 else b.F32, T, B, D, R, S, 12, 0, num_dest=nd)
+    ctx = b.Context(cfg)
+    cap = b.dlc_compress_bound(cfg)
+    stride = (cap // nd) & ~255 if nd > 1 else cap
+    out = torch.full((cap + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+    sizes = torch.zeros(1 + nd * T + (nd if nd > 1 else 0), dtype=torch.int64, device="cuda")
+    for call in range(2):  # (the second call finds what the first has left in the workspace)
+        print("flow", T, B, D, S, np.dtype(dtype).name, nd, call, flush=True)
+        pieces, ebs = zip(*[_payload(rng, T, B, D, dtype, call == 1) for _ in range(nd)])
+        ctx.set_error_bounds(eb=ebs[0])
+        d = to_device(np.stack(pieces) if nd > 1 else pieces[0])
+        assert ctx.compress(d, out, sizes, capacity=cap) == 0 and ctx.sync_status() == 0
+        h = out.cpu().numpy()
+        assert np.all(h[cap:] == 0xA5)
+        sz = sizes.cpu().numpy().astype(np.uint64)
+        for k in range(nd):
+            o = oracle.compress(pieces[k], ebs[0], R, S, 12, want_hist=True)
+            assert o.rc == 0
+            n = o.data.size
+            assert np.array_equal(h[k * stride:k * stride + n], o.data), (call, k)
+            assert np.array_equal(sz[1 + k * T:1 + (k + 1) * T], o.sizes[1:]), (call, k)
+            assert np.array_equal(ctx.read_histogram().reshape(nd, T, -1)[k], o.hist), (call, k)
+        if nd == 1:
+            assert int(sz[0]) == n
+            rec = torch.full_like(d, 7.0)
+            assert ctx.decompress(out, n, rec) == 0 and ctx.sync_status() == 0
+            rc, orec = oracle.decompress(o.data, pieces[0].shape, dtype)
+            u = np.uint32 if dtype == np.float32 else np.uint16
+            assert rc == 0 and np.array_equal(rec.cpu().numpy().view(u), orec.view(u))
+
+
+def test_capacity_and_two_streams():
+    """A container that does not fit fails alone, also while another context's launch of the same kind runs beside it."""
+    import torch
+    from paper_2407_04272_amd import binding as b
+    T, B, D, S = 20, 15000, 64, 256
+    rng = np.random.default_rng(3)
+    x, eb = _payload(rng, T, B, D, np.float32, False)
+    o = oracle.compress(x, eb, 512, S, 12)
+    d = to_device(x)
+    cfg = b.make_config(b.F32, T, B, D, 512, S, 12)
+    room = [b.dlc_compress_bound(cfg), o.data.size - 4, o.data.size]
+    ctxs = [b.Context(cfg) for _ in room]
+    outs = [torch.full((r + 64,), 0xA5, dtype=torch.uint8, device="cuda") for r in room]
+    sizes = [torch.zeros(1 + T, dtype=torch.int64, device="cuda") for _ in room]
+    streams = [torch.cuda.Stream() for _ in room]
+    torch.cuda.synchronize()
+    for call in range(3):
+        for c, s in zip(ctxs, streams):
+            c.set_error_bounds(eb=eb, stream=s)
+        for c, s, q, z, r in zip(ctxs, streams, outs, sizes, room):
+            assert c.compress(d, q, z, capacity=r, stream=s) == 0
+        status = [c.sync_status(stream=s) for c, s in zip(ctxs, streams)]
+        assert status == [0, b.ECAPACITY, 0], call
+        for k, (q, z, r) in enumerate(zip(outs, sizes, room)):
+            h = q.cpu().numpy()
+            assert np.all(h[r:] == 0xA5)
+            if k != 1:
+                assert int(z[0]) == o.data.size and np.array_equal(h[:o.data.size], o.data), call
+            else:
+                assert int(z[0]) == 0
+
+
+def test_first_call_of_a_carried_chain():
+    """The first call under new bounds builds its own codebook, and its counts are the next call's."""
+    import torch
+    from paper_2407_04272_amd import binding as b
+    T, B, D, S = 18, 8300, 128, 256
+    rng = np.random.default_rng(4)
+    cfg = b.make_config(b.F32, T, B, D, 512, S, 12, b.FLAG_CARRY_CODEBOOK)
+    ctx = b.Context(cfg)
+    out = torch.empty(b.dlc_compress_bound(cfg), dtype=torch.uint8, device="cuda")
+    sizes = torch.zeros(1 + T, dtype=torch.int64, device="cuda")
+    prev, eb = None, None
+    for call in range(2):
+        x, e = _payload(rng, T, B, D, np.float32, False)
+        eb = e if eb is None else eb
+        ctx.set_error_bounds(eb=eb)
+        assert ctx.compress(to_device(x), out, sizes) == 0 and ctx.sync_status() == 0
+        o = oracle.compress(x, eb, 512, S, 12, carry_hist=prev, want_hist=True)
+        n = o.data.size
+        assert int(sizes[0]) == n and np.array_equal(out[:n].cpu().numpy(), o.data), call
+        prev = o.hist
