@@ -44,10 +44,11 @@ constexpr uint32_t kCarryCopyBytes = (kCarryRows + 7u) * kCarryRowBytes;  // a c
 static_assert(kCarryCopies * 65536u > 4u * 64u * 256u && 4u * 64u * 256u / kCarryCopies < 65536u, "a count must fit 16 bits");
 constexpr uint32_t kCarryRecs = 128;  // escapes a wavefront remembers in LDS (offsets in the group); a group with more walks its elements again
 
-// LDS staging of a wavefront, [row][lane]: row 0 takes the stores made before a chunk's first word is complete, row
+// LDS staging of a wavefront, a column a lane: row 0 takes the stores made before a chunk's first word is complete, row
 // k + 1 holds word k of the lane's chunk, the last row takes what does not fit (a group with such a chunk is walked
-// again, straight to memory)
-__host__ __device__ constexpr uint32_t carry_stage_words(uint32_t cap) { return (cap + 2u) * kW; }
+// on from a state kept where no column could be full yet, for the next words).  Words of one column lie in different banks.
+constexpr uint32_t kCarryPitch = kW + 1u;
+__host__ __device__ constexpr uint32_t carry_stage_words(uint32_t cap) { return (cap + 2u) * kCarryPitch; }
 
 // A SIMD serves the oldest of its wavefronts first, so of the four work-groups that share a compute unit the one
 // launched first runs ahead and the last one trails (lifetimes 89, 93, 98, 103 us by launch order on an MI355X), and
@@ -81,7 +82,6 @@ struct CarryEnv {
     uint16_t* recs;        // LDS: where in the group the wavefront has met escapes, kCarryRecs at most
     uint32_t sp_base;      // LDS address of this lane's column of the staging rows
     uint32_t row_max;      // the last staging row
-    uint32_t* dst;         // second walk of a group that did not fit its staging rows: the lane's chunk in memory
     uint32_t rank;         // which of the work-groups sharing a compute unit this one is, by launch order (0..3)
     uint32_t count;        // 0: nobody wants this call's counts (the codebook is not carried to the next call)
 };
@@ -97,18 +97,13 @@ struct CarryState {
 __device__ __forceinline__ void carry_flush(const CarryEnv& E, const CarryState& S) {
     const uint32_t row = min(S.nbt >> 5, E.row_max);
     const uint32_t word = __builtin_amdgcn_alignbit((uint32_t)(S.acc >> 32), (uint32_t)S.acc, S.nbt);  // (shift: nbt mod 32)
-    *reinterpret_cast<lds_u32*>(E.sp_base + row * (kW * 4u)) = word;
+    *reinterpret_cast<lds_u32*>(E.sp_base + __umul24(row, kCarryPitch * 4u)) = word;
 }
 
-// the same for a walk that writes a chunk straight to memory (the chunks' places are known by then): a word goes
-// out once, when it is complete (S.nrec counts the words written: the second walk keeps no records)
-__device__ __forceinline__ void carry_flush_mem(const CarryEnv& E, CarryState& S) {
-    const uint32_t k = S.nbt >> 5;
-    if (k != S.nrec) {
-        E.dst[k - 1u] = __builtin_amdgcn_alignbit((uint32_t)(S.acc >> 32), (uint32_t)S.acc, S.nbt);
-        S.nrec = k;
-    }
-}
+struct CarryMark {  // a walk's state before turn j (a multiple of a trip's turns)
+    uint64_t acc;
+    uint32_t nbt, j;
+};
 
 // codeword and length of an element the table had no answer for, with the quantiser's own arithmetic: a symbol
 // outside the window or without a code in the carried codebook, an escape, a position past the end of the table.
@@ -138,8 +133,7 @@ __device__ __forceinline__ void carry_slow_entry(const CarryEnv& E, float x, boo
 }
 
 // One block of kCarryBlk units already loaded: quantise, count, look up, append.
-// REWALK: the group is walked a second time because a chunk did not fit its staging rows; nothing is counted or
-// recorded again, and the words go to memory.
+// REWALK: the group is walked on for the words that did not fit its staging rows; nothing is counted or recorded again.
 template <bool F16, bool FULL, bool REWALK>
 __device__ __forceinline__ void carry_block(const CarryEnv& E, const float (&x)[kCarryBlk][4], const uint32_t (&valid)[kCarryBlk],
                                             uint32_t jb, CarryState& S) {
@@ -231,15 +225,15 @@ __device__ __forceinline__ void carry_block(const CarryEnv& E, const float (&x)[
             // the rule: the four codewords as one piece of at most 32 bits
             S.acc = (S.acc << L) | ((c01 << l23) | c23);
             S.nbt += L;
-            if constexpr (REWALK) carry_flush_mem(E, S); else carry_flush(E, S);
+            carry_flush(E, S);
         } else {
             // two pieces of at most 24 bits
             S.acc = (S.acc << l01) | c01;
             S.nbt += l01;
-            if constexpr (REWALK) carry_flush_mem(E, S); else carry_flush(E, S);
+            carry_flush(E, S);
             S.acc = (S.acc << l23) | c23;
             S.nbt += l23;
-            if constexpr (REWALK) carry_flush_mem(E, S); else carry_flush(E, S);
+            carry_flush(E, S);
         }
     }
 }
@@ -252,11 +246,12 @@ __device__ __forceinline__ void carry_load(const CarryEnv& E, uint32_t jb, float
         valid[u] = load4<F16, VEC, FULL>(E.gbase, E.lane * kV + (jb + u) * (kW * kV), FULL ? 0xFFFFFFFFu : E.rem, x[u], raw);
 }
 
-// One walk over a group: lane l codes chunk l (at turn j the four elements group_base + j*256 + 4*l .. +3).  The
-// loads of the next kCarryLoad turns are issued before the current ones are worked on; those of the first turns
-// (xa, va) are already on their way when the walk starts.
+// One walk over a group, from turn `from` on (a multiple of a trip's 2 * kCarryLoad turns): lane l codes chunk l (at turn j the four
+// elements group_base + j*256 + 4*l .. +3).  The loads of the next kCarryLoad turns are issued before the current ones are worked on;
+// those of the first turns (xa, va) are already on their way when the walk starts.  Returns its state at the first trip before
+// which a chunk had more than `limit` bits, or at its end.
 template <int S, bool F16, bool VEC, bool FULL, bool REWALK = false>
-__device__ __forceinline__ void carry_walk(const CarryEnv& E, CarryState& St, float (&xa)[kCarryLoad][4], uint32_t (&va)[kCarryLoad]) {
+__device__ __forceinline__ CarryMark carry_walk(const CarryEnv& E, CarryState& St, float (&xa)[kCarryLoad][4], uint32_t (&va)[kCarryLoad], uint32_t from, int limit) {
     constexpr uint32_t N = (uint32_t)S / kV;  // turns of a whole group; the table can end in this one
     const uint32_t n_turns = FULL ? N : min(N, ((E.rem + kW * kV - 1u) / (kW * kV) + 2u * kCarryLoad - 1u) & ~(2u * kCarryLoad - 1u));
     static_assert(N % (2 * kCarryLoad) == 0 && kCarryLoad % kCarryBlk == 0, "two load blocks per trip, whole work blocks per load block");
@@ -264,8 +259,16 @@ __device__ __forceinline__ void carry_walk(const CarryEnv& E, CarryState& St, fl
     typedef const uint32_t (&VBlk)[kCarryBlk];
     float xb[kCarryLoad][4];
     uint32_t vb[kCarryLoad];
-    for (uint32_t jb = 0; jb < n_turns; jb += 2 * kCarryLoad) {
+    CarryMark M;
+    M.j = 0xFFFFFFFFu;
+    for (uint32_t jb = from; jb < n_turns; jb += 2 * kCarryLoad) {
         set_wave_priority(jb / (2 * kCarryLoad) + E.rank);
+        if (__ballot((int)St.nbt > limit) != 0ull) {  // uniform
+            M.acc = St.acc;
+            M.nbt = St.nbt;
+            M.j = jb;
+            limit = 0x7FFFFFFF;
+        }
         carry_load<F16, VEC, FULL>(E, jb + kCarryLoad, xb, vb);
 #pragma unroll
         for (uint32_t k = 0; k < kCarryLoad; k += kCarryBlk)
@@ -275,6 +278,12 @@ __device__ __forceinline__ void carry_walk(const CarryEnv& E, CarryState& St, fl
         for (uint32_t k = 0; k < kCarryLoad; k += kCarryBlk)
             carry_block<F16, FULL, REWALK>(E, reinterpret_cast<XBlk>(xb[k]), reinterpret_cast<VBlk>(vb[k]), jb + kCarryLoad + k, St);
     }
+    if (M.j == 0xFFFFFFFFu) {
+        M.acc = St.acc;
+        M.nbt = St.nbt;
+        M.j = n_turns;
+    }
+    return M;
 }
 
 // escape records of one group under a carried codebook: as emit_escapes, but a symbol without a code is one too
@@ -463,12 +472,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 
         CarryState St;
         St.acc = 0; St.nbt = 0; St.esc = 0; St.nrec = 0;
+        CarryMark M;
+        M.acc = 0; M.nbt = 0; M.j = 0;
+        // a state marked below this many bits (in the trip before it, a trip's bits more) has no word of the next pass behind it
+        constexpr int kLimit = (int)(CAP * 32u - 2u * kCarryLoad * kV * (uint32_t)kLmaxLimit);
+        auto last_word = [&](const CarryState& St) {  // the chunk's last, partly filled word
+            if (St.nbt & 31u)
+                *reinterpret_cast<lds_u32*>(E.sp_base + __umul24(min((St.nbt >> 5) + 1u, E.row_max), kCarryPitch * 4u)) = (uint32_t)St.acc << (32u - (St.nbt & 31u));
+        };
         if (active) {
-            if (full) carry_walk<S, F16, VEC, true>(E, St, xa, va);
-            else carry_walk<S, F16, VEC, false>(E, St, xa, va);
-            if (St.nbt & 31u)  // the chunk's last, partly filled word
-                *reinterpret_cast<lds_u32*>(E.sp_base + min((St.nbt >> 5) + 1u, E.row_max) * (kW * 4u)) =
-                    (uint32_t)St.acc << (32u - (St.nbt & 31u));
+            if (full) M = carry_walk<S, F16, VEC, true>(E, St, xa, va, 0u, kLimit);
+            else M = carry_walk<S, F16, VEC, false>(E, St, xa, va, 0u, kLimit);
+            last_word(St);
         }
         // the next item's first elements: on their way while this item is written out
         auto ask_for_next = [&]() {
@@ -495,7 +510,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         if (active && !spilled) {
             uint32_t wb[CAP];
 #pragma unroll
-            for (uint32_t k = 0; k < CAP; ++k) wb[k] = *reinterpret_cast<lds_u32*>(E.sp_base + (k + 1u) * (kW * 4u));
+            for (uint32_t k = 0; k < CAP; ++k) wb[k] = *reinterpret_cast<lds_u32*>(E.sp_base + (k + 1u) * (kCarryPitch * 4u));
             __builtin_amdgcn_wave_barrier();
             const uint32_t lin = (uint32_t)(uintptr_t)stage + lane_off * 4u;
 #pragma unroll
@@ -516,21 +531,44 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             if (!spilled) {
                 for (uint32_t k = lane; k < chunk_total; k += 64) gw[k] = stage[k];
             } else {
-                // A chunk of the group has more words than its staging rows: the group is walked again, the same way
-                // but for the counts and the records, and every lane writes its chunk's words to memory as they get
-                // complete (4 bytes a lane and 64 lines an instruction: the slow way out, for payloads that take more
-                // than 4 bits per symbol).  The loads of the next item, already on their way, are asked for again.
-                E.dst = gw + lane_off;
-                CarryState Sr;
-                Sr.acc = 0; Sr.nbt = 0; Sr.esc = 0; Sr.nrec = 0;
-                if (full) {
-                    carry_load<F16, VEC, true>(E, 0, xa, va);
-                    carry_walk<S, F16, VEC, true, true>(E, Sr, xa, va);
-                } else {
-                    carry_load<F16, VEC, false>(E, 0, xa, va);
-                    carry_walk<S, F16, VEC, false, true>(E, Sr, xa, va);
+                // A chunk of the group has more words than its staging rows: the columns go to their places as they are, a team of
+                // lanes a chunk, and the group is walked on for every further CAP words (no counts, no records).  The loads of the next
+                // item, already on their way, are asked for again.  (Walked again from the start, every lane storing its words as they got
+                // complete, 64 lines an instruction: 512 MiB at 4.6 bits a symbol 420 us a call.)
+                auto copy = [&](uint32_t first) {
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (the columns are other lanes')
+                    const uint32_t team = lane / CAP, k0 = lane % CAP, n_here = nw > first ? min(nw - first, CAP) : 0u;
+                    const uint32_t mine = ((lane_off + first) << 8) | n_here;
+                    const uint32_t* const rl = stage + (k0 + 1u) * kCarryPitch;
+#pragma clang loop unroll(disable)
+                    for (uint32_t c0 = 0; c0 < CAP; c0 += 4u) {  // four chunks in flight
+                        uint32_t oc[4], v[4];
+#pragma unroll
+                        for (uint32_t u = 0; u < 4u; ++u) {
+                            const uint32_t c = c0 + u + team * CAP;
+                            oc[u] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(c * 4u), (int)mine);
+                            v[u] = rl[c];
+                        }
+#pragma unroll
+                        for (uint32_t u = 0; u < 4u; ++u)
+                            if (k0 < (oc[u] & 255u)) gw[(oc[u] >> 8) + k0] = v[u];
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                };
+                copy(0u);
+                for (uint32_t first = CAP; __ballot(nw > first) != 0ull; first += CAP) {  // uniform
+                    CarryState Sr;
+                    Sr.acc = M.acc; Sr.nbt = M.nbt - CAP * 32u; Sr.esc = 0; Sr.nrec = 0;  // (what is counted from the pass's first word on may be below zero)
+                    if (full) {
+                        if (M.j < (uint32_t)S / kV) carry_load<F16, VEC, true>(E, M.j, xa, va);
+                        M = carry_walk<S, F16, VEC, true, true>(E, Sr, xa, va, M.j, kLimit);
+                    } else {
+                        carry_load<F16, VEC, false>(E, M.j, xa, va);
+                        M = carry_walk<S, F16, VEC, false, true>(E, Sr, xa, va, M.j, kLimit);
+                    }
+                    last_word(Sr);
+                    copy(first);
                 }
-                if (Sr.nbt & 31u) E.dst[Sr.nbt >> 5] = (uint32_t)Sr.acc << (32u - (Sr.nbt & 31u));
                 ask_for_next();
             }
             if (n_esc != 0u) {  // uniform over the wavefront
