@@ -83,7 +83,6 @@ struct CarryEnv {
     uint32_t sp_base;      // LDS address of this lane's column of the staging rows
     uint32_t row_max;      // the last staging row
     uint32_t rank;         // which of the work-groups sharing a compute unit this one is, by launch order (0..3)
-    uint32_t count;        // 0: nobody wants this call's counts (the codebook is not carried to the next call)
 };
 
 struct CarryState {
@@ -134,7 +133,7 @@ __device__ __forceinline__ void carry_slow_entry(const CarryEnv& E, float x, boo
 
 // One block of kCarryBlk units already loaded: quantise, count, look up, append.
 // REWALK: the group is walked on for the words that did not fit its staging rows; nothing is counted or recorded again.
-template <bool F16, bool FULL, bool REWALK>
+template <bool F16, bool FULL, bool REWALK, bool COUNT>
 __device__ __forceinline__ void carry_block(const CarryEnv& E, const float (&x)[kCarryBlk][4], const uint32_t (&valid)[kCarryBlk],
                                             uint32_t jb, CarryState& S) {
     uint32_t a[kCarryBlk][4];
@@ -160,12 +159,14 @@ __device__ __forceinline__ void carry_block(const CarryEnv& E, const float (&x)[
         }
     // all look-ups, then all counts: the look-ups must not queue behind the (slower) atomic updates, whose results
     // nobody waits for
-    uint32_t len[kCarryBlk][4], code[kCarryBlk][4];
+    // COUNT: length and codeword out of the row's word.  Else the row's word as it is, codeword << 8 | length: a shift takes its
+    // amount from the low five bits, so a sum of lengths is a sum of words (seven instructions less for four elements).
+    uint32_t len[kCarryBlk][4], code[kCarryBlk][4];  // no answer from the table: length 0
 #pragma unroll
     for (uint32_t u = 0; u < kCarryBlk; ++u)
 #pragma unroll
         for (int v = 0; v < 4; ++v) code[u][v] = *reinterpret_cast<lds_u32*>(a[u][v]);
-    if (!REWALK && E.count != 0u) {  // (uniform: with a sampled codebook nobody reads the counts, and the walk is 4 us shorter without them)
+    if constexpr (COUNT && !REWALK) {
 #pragma unroll
         for (uint32_t u = 0; u < kCarryBlk; ++u)
 #pragma unroll
@@ -176,8 +177,8 @@ __device__ __forceinline__ void carry_block(const CarryEnv& E, const float (&x)[
     for (uint32_t u = 0; u < kCarryBlk; ++u)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            len[u][v] = (code[u][v] >> 12) & 15u;
-            code[u][v] &= 0xFFFu;
+            len[u][v] = COUNT ? (code[u][v] >> 12) & 15u : code[u][v];
+            code[u][v] = COUNT ? code[u][v] & 0xFFFu : code[u][v] >> 8;
         }
     if (__ballot(!sure) != 0ull) {
         // one block in ten or so: the bound test again, with the quantiser's own two roundings; an element that fails
@@ -201,7 +202,7 @@ __device__ __forceinline__ void carry_block(const CarryEnv& E, const float (&x)[
             for (int v = 0; v < 4; ++v) {
                 if (len[u][v] != 0u) continue;
                 bool is_esc;
-                carry_slow_entry<F16>(E, x[u][v], FULL || ((valid[u] >> v) & 1u), a[u][v], len[u][v], code[u][v], is_esc, !REWALK && E.count != 0u);
+                carry_slow_entry<F16>(E, x[u][v], FULL || ((valid[u] >> v) & 1u), a[u][v], len[u][v], code[u][v], is_esc, COUNT && !REWALK);
                 if (is_esc && !REWALK) { ++S.esc; em |= 1u << v; }
             }
             // the records of these escapes, in element order (the walk meets the elements of a group in
@@ -219,20 +220,20 @@ __device__ __forceinline__ void carry_block(const CarryEnv& E, const float (&x)[
                 S.nrec += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
             }
         }
-        const uint32_t l01 = len[u][0] + len[u][1], l23 = len[u][2] + len[u][3], L = l01 + l23;
-        const uint32_t c01 = (code[u][0] << len[u][1]) | code[u][1], c23 = (code[u][2] << len[u][3]) | code[u][3];
+        const uint32_t l01 = len[u][0] + len[u][1], l23 = len[u][2] + len[u][3], L = COUNT ? l01 + l23 : (l01 + l23) & 63u;
+        const uint32_t c01 = (code[u][0] << (len[u][1] & 31u)) | code[u][1], c23 = (code[u][2] << (len[u][3] & 31u)) | code[u][3];
         if (__ballot(L > 32u) == 0ull) {
             // the rule: the four codewords as one piece of at most 32 bits
-            S.acc = (S.acc << L) | ((c01 << l23) | c23);
+            S.acc = (S.acc << L) | ((c01 << (l23 & 31u)) | c23);
             S.nbt += L;
             carry_flush(E, S);
         } else {
             // two pieces of at most 24 bits
-            S.acc = (S.acc << l01) | c01;
-            S.nbt += l01;
+            S.acc = (S.acc << (l01 & 31u)) | c01;
+            S.nbt += l01 & 31u;
             carry_flush(E, S);
-            S.acc = (S.acc << l23) | c23;
-            S.nbt += l23;
+            S.acc = (S.acc << (l23 & 31u)) | c23;
+            S.nbt += l23 & 31u;
             carry_flush(E, S);
         }
     }
@@ -250,7 +251,7 @@ __device__ __forceinline__ void carry_load(const CarryEnv& E, uint32_t jb, float
 // elements group_base + j*256 + 4*l .. +3).  The loads of the next kCarryLoad turns are issued before the current ones are worked on;
 // those of the first turns (xa, va) are already on their way when the walk starts.  Returns its state at the first trip before
 // which a chunk had more than `limit` bits, or at its end.
-template <int S, bool F16, bool VEC, bool FULL, bool REWALK = false>
+template <int S, bool F16, bool VEC, bool FULL, bool COUNT, bool REWALK = false>
 __device__ __forceinline__ CarryMark carry_walk(const CarryEnv& E, CarryState& St, float (&xa)[kCarryLoad][4], uint32_t (&va)[kCarryLoad], uint32_t from, int limit) {
     constexpr uint32_t N = (uint32_t)S / kV;  // turns of a whole group; the table can end in this one
     const uint32_t n_turns = FULL ? N : min(N, ((E.rem + kW * kV - 1u) / (kW * kV) + 2u * kCarryLoad - 1u) & ~(2u * kCarryLoad - 1u));
@@ -272,11 +273,11 @@ __device__ __forceinline__ CarryMark carry_walk(const CarryEnv& E, CarryState& S
         carry_load<F16, VEC, FULL>(E, jb + kCarryLoad, xb, vb);
 #pragma unroll
         for (uint32_t k = 0; k < kCarryLoad; k += kCarryBlk)
-            carry_block<F16, FULL, REWALK>(E, reinterpret_cast<XBlk>(xa[k]), reinterpret_cast<VBlk>(va[k]), jb + k, St);
+            carry_block<F16, FULL, REWALK, COUNT>(E, reinterpret_cast<XBlk>(xa[k]), reinterpret_cast<VBlk>(va[k]), jb + k, St);
         if (jb + 2 * kCarryLoad < n_turns) carry_load<F16, VEC, FULL>(E, jb + 2 * kCarryLoad, xa, va);
 #pragma unroll
         for (uint32_t k = 0; k < kCarryLoad; k += kCarryBlk)
-            carry_block<F16, FULL, REWALK>(E, reinterpret_cast<XBlk>(xb[k]), reinterpret_cast<VBlk>(vb[k]), jb + kCarryLoad + k, St);
+            carry_block<F16, FULL, REWALK, COUNT>(E, reinterpret_cast<XBlk>(xb[k]), reinterpret_cast<VBlk>(vb[k]), jb + kCarryLoad + k, St);
     }
     if (M.j == 0xFFFFFFFFu) {
         M.acc = St.acc;
@@ -323,11 +324,12 @@ __device__ __forceinline__ void carry_emit_escapes(uint32_t* rec, uint32_t lane,
 // follows (k_post) puts them where the sums of the groups' totals say.  The grid is sized to what the chip holds at
 // once, so the set-up of a work-group is paid once, the code table stays in LDS while the items are of one table,
 // and the first loads of an item are on their way while the item before it is being written out.
-template <int S, bool F16, bool VEC>
+// COUNT: this call's symbols are counted, for the next call's codebook (not where it comes from a sample: the walk is shorter without).
+template <int S, bool F16, bool VEC, bool COUNT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_encode_carry(const void* payload, Geom g, FixedLayout F, const QParam* qp,
                                                       const uint16_t* enc, uint8_t* out, uint64_t capacity, uint32_t bpt,
                                                       uint32_t* hist, uint32_t* esc_count, uint32_t* slots, uint64_t slot_words,
-                                                      uint32_t* gtot, uint32_t* bsum, uint32_t ipw, uint32_t n_items, uint32_t count) {
+                                                      uint32_t* gtot, uint32_t* bsum, uint32_t ipw, uint32_t n_items) {
     constexpr uint32_t CAP = (uint32_t)S / 8u;          // words of LDS per chunk: room for 4 bits per symbol
     constexpr uint32_t kStageWords = carry_stage_words(CAP);  // per wavefront
     constexpr uint32_t kGroupEls = kW * (uint32_t)S;
@@ -354,7 +356,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     E.recs = s_recs + wave * kCarryRecs;
     E.sp_base = (uint32_t)(uintptr_t)stage + lane * 4u;
     E.row_max = CAP + 1u;
-    E.count = count;
     E.rank = min(3u, blockIdx.x / ((gridDim.x + 3u) / 4u));  // (the grid is four work-groups per compute unit, handed out in rounds)
     // which group of which table an item gives this wavefront (grp >= G: none)
     auto where = [&](uint32_t item, uint32_t& t, uint32_t& grp) {
@@ -379,7 +380,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     // this call's histogram of a table, for the next call's codebook: the window rows (sum of the copies; everything
     // else went to memory directly); the counts start again at zero
     auto merge_counts = [&](uint32_t t) {
-        if (tid < kCarryRows - 2u) {
+        if (COUNT && tid < kCarryRows - 2u) {
             uint32_t s = 0;
             for (uint32_t c = 0; c < kCarryCopies; ++c) {
                 uint32_t& w = s_tab[c * (kCarryCopyBytes / 4u) + tid + 1u];
@@ -387,17 +388,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                 w &= 0xFFFFu;
             }
             const uint32_t sym = win_lo + tid;
-            if (s && sym < g.K && count) atomicAdd(&hist[(size_t)t * g.K + sym], s);
+            if (s && sym < g.K) atomicAdd(&hist[(size_t)t * g.K + sym], s);
         }
     };
+    // a row of the code table: with counts (length << 12 | codeword, the count above), without as the walk wants it
+    auto row_word = [](uint32_t e) { return COUNT ? e : (e & 0xFFFu) << 8 | (e >> 12); };
     // the same for a wavefront's own table (tables of few groups)
     uint32_t* const tab_w = s_tab + wave * (kCarryCopyBytes / 4u);
     auto merge_counts_wave = [&](uint32_t t) {
-        for (uint32_t r = lane; r < kCarryRows - 2u; r += 64) {
+        if constexpr (COUNT) for (uint32_t r = lane; r < kCarryRows - 2u; r += 64) {
             const uint32_t w = tab_w[r + 1u];
             tab_w[r + 1u] = w & 0xFFFFu;
             const uint32_t sym = win_lo + r;
-            if ((w >> 16) && sym < g.K && count) atomicAdd(&hist[(size_t)t * g.K + sym], w >> 16);
+            if ((w >> 16) && sym < g.K) atomicAdd(&hist[(size_t)t * g.K + sym], w >> 16);
         }
     };
     // the first item's first elements are asked for before anything else: their way from memory is the longest
@@ -422,12 +425,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                 if (cur_t != 0xFFFFFFFFu) merge_counts_wave(cur_t);
                 for (uint32_t row = lane; row < kCarryRows; row += 64) {
                     const uint32_t c = win_lo + row - 1u;
-                    tab_w[row] = (row >= 1u && row <= kCarryRows - 2u && c < g.K && c != 0u) ? enc_t[c] : 0u;
+                    tab_w[row] = row_word((row >= 1u && row <= kCarryRows - 2u && c < g.K && c != 0u) ? enc_t[c] : 0u);
                 }
                 __builtin_amdgcn_wave_barrier();
                 cur_t = t;
                 since_merge = 0;
-            } else if (active && since_merge == 3u) {
+            } else if (COUNT && active && since_merge == 3u) {
                 merge_counts_wave(cur_t);
                 __builtin_amdgcn_wave_barrier();
                 since_merge = 0;
@@ -444,12 +447,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                 const uint32_t row = k % kCarryRows;
                 const uint32_t c = win_lo + row - 1u;
                 const uint32_t e = (row >= 1u && row <= kCarryRows - 2u && c < g.K && c != 0u) ? enc_t[c] : 0u;
-                s_tab[(k / kCarryRows) * (kCarryCopyBytes / 4u) + row] = e;  // (length 0: no code; count 0)
+                s_tab[(k / kCarryRows) * (kCarryCopyBytes / 4u) + row] = row_word(e);  // (length 0: no code; count 0)
             }
             __syncthreads();
             cur_t = t;
             since_merge = 0;
-        } else if (since_merge == 3u) {  // (a copy's count of a row has 16 bits: three items of 16384 elements a copy fit)
+        } else if (COUNT && since_merge == 3u) {  // (a copy's count of a row has 16 bits: three items of 16384 elements a copy fit)
             __syncthreads();
             merge_counts(cur_t);
             __syncthreads();
@@ -481,8 +484,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                 *reinterpret_cast<lds_u32*>(E.sp_base + __umul24(min((St.nbt >> 5) + 1u, E.row_max), kCarryPitch * 4u)) = (uint32_t)St.acc << (32u - (St.nbt & 31u));
         };
         if (active) {
-            if (full) M = carry_walk<S, F16, VEC, true>(E, St, xa, va, 0u, kLimit);
-            else M = carry_walk<S, F16, VEC, false>(E, St, xa, va, 0u, kLimit);
+            if (full) M = carry_walk<S, F16, VEC, true, COUNT>(E, St, xa, va, 0u, kLimit);
+            else M = carry_walk<S, F16, VEC, false, COUNT>(E, St, xa, va, 0u, kLimit);
             last_word(St);
         }
         // the next item's first elements: on their way while this item is written out
@@ -561,10 +564,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                     Sr.acc = M.acc; Sr.nbt = M.nbt - CAP * 32u; Sr.esc = 0; Sr.nrec = 0;  // (what is counted from the pass's first word on may be below zero)
                     if (full) {
                         if (M.j < (uint32_t)S / kV) carry_load<F16, VEC, true>(E, M.j, xa, va);
-                        M = carry_walk<S, F16, VEC, true, true>(E, Sr, xa, va, M.j, kLimit);
+                        M = carry_walk<S, F16, VEC, true, COUNT, true>(E, Sr, xa, va, M.j, kLimit);
                     } else {
                         carry_load<F16, VEC, false>(E, M.j, xa, va);
-                        M = carry_walk<S, F16, VEC, false, true>(E, Sr, xa, va, M.j, kLimit);
+                        M = carry_walk<S, F16, VEC, false, COUNT, true>(E, Sr, xa, va, M.j, kLimit);
                     }
                     last_word(Sr);
                     copy(first);
@@ -620,11 +623,13 @@ void DLC_CAT(launch_encode_carry_, DLC_S)(const Geom& g, const FixedLayout& F, c
     const uint32_t ipw = (n_items + DLC_CAT(carry_resident_, DLC_S)() - 1u) / DLC_CAT(carry_resident_, DLC_S)();
     dim3 grid((n_items + ipw - 1u) / ipw), block(256);
     const bool f16 = g.dtype == DLC_F16;
-#define DLC_ENC(FF, V)                                                                                                 \
-    hipLaunchKernelGGL((k_encode_carry<S, FF, V>), grid, block, 0, s, payload, g, F, w.qp, w.enc, out, capacity, bpt, w.hist, \
-                       w.esc_count, w.slots, (uint64_t)carry_slot_words(g), w.gtot, w.bsum, ipw, n_items, w.sample != 0 ? 0u : 1u)
+#define DLC_ENC2(FF, V, COUNT)                                                                                         \
+    hipLaunchKernelGGL((k_encode_carry<S, FF, V, COUNT>), grid, block, 0, s, payload, g, F, w.qp, w.enc, out, capacity, bpt, w.hist, \
+                       w.esc_count, w.slots, (uint64_t)carry_slot_words(g), w.gtot, w.bsum, ipw, n_items)
+#define DLC_ENC(FF, V) do { if (w.sample != 0) DLC_ENC2(FF, V, false); else DLC_ENC2(FF, V, true); } while (0)
     if (f16) { if (g.vec) DLC_ENC(true, true); else DLC_ENC(true, false); }
     else { if (g.vec) DLC_ENC(false, true); else DLC_ENC(false, false); }
+#undef DLC_ENC2
 #undef DLC_ENC
 }
 
