@@ -422,9 +422,10 @@ __device__ __forceinline__ void dec_check_escapes(const Geom& g, const DecHead& 
     if (big) tail.bad = 1u;
 }
 
-// The end of a work-group, one of wpt of its table.  my_esc: the escapes its wavefront has applied.  dtab (row matching): gets
+// The end of a work-group, one of wpt of its table.  my_esc: the escapes its wavefront has applied.  dtab (LZ: row matching): gets
 // the table's references where every work-group of the table has found its part in order, for the kernel that copies rows.
 constexpr uint32_t kTableBad = 0x80000000u;  // in the count of arrivals (of less than 2^31 work-groups)
+template <bool LZ>
 __device__ __forceinline__ void dec_finish(const DecHead& H, bool valid, uint32_t my_esc, uint32_t wpt, Ctrl* ctrl, uint32_t* esc_seen,
                                            uint32_t* arrived, DecTable* dtab, DecTail& tail, uint32_t tid) {
     if (my_esc != 0u && (tid & 63u) == 0u) {
@@ -434,17 +435,17 @@ __device__ __forceinline__ void dec_finish(const DecHead& H, bool valid, uint32_
     __syncthreads();
     if (tid == 0) {
         bool corrupt = !valid || tail.bad != 0u;
-        if (corrupt && dtab) {
+        if (LZ && corrupt) {
             __hip_atomic_fetch_or(arrived, kTableBad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the same)
         }
         // the last work-group of the table: all escapes of the table have been seen
         const uint32_t before = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if ((before & ~kTableBad) + 1u == wpt) {
+        if ((LZ ? before & ~kTableBad : before) + 1u == wpt) {
             const uint32_t seen = __hip_atomic_exchange(esc_seen, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (valid && seen != H.n_esc) corrupt = true;
-            if (dtab) dtab->ref_off = corrupt || (before & kTableBad) ? 0ull : H.ref_off;
+            if constexpr (LZ) dtab->ref_off = corrupt || (before & kTableBad) ? 0ull : H.ref_off;
         }
         if (corrupt) set_status(ctrl, DLC_ECORRUPT);
     }
@@ -685,7 +686,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
             } else {
                 for (uint32_t j = 0; j < whole; ++j) turn(std::false_type{}, std::false_type{}, j);
             }
-            if (in_group > whole * (kW * kV)) turn(std::true_type{}, std::false_type{}, whole);
+            if (in_group > whole * (kW * kV)) turn(std::true_type{}, std::bool_constant<!LZ>{}, whole);
             // a chunk's codewords end inside its words
             if (__ballot(32u * wbase + p - kDecBit0 > 32u * cw) != 0ull) bad = true;
             if (n_esc != 0u) {  // uniform over the wavefront: verbatim values over the decoded placeholders
@@ -705,7 +706,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
         }
     }
     if (__ballot(bad) != 0ull && lane == 0) tail.bad = 1u;
-    dec_finish(H, valid, my_esc, wpt, ctrl, esc_seen + t, arrived + t, LZ ? dtab + t : nullptr, tail, tid);
+    dec_finish<LZ>(H, valid, my_esc, wpt, ctrl, esc_seen + t, arrived + t, LZ ? dtab + t : nullptr, tail, tid);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -931,7 +932,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void k_decode_split(Geom g, Fixed
         }
     }
     if (bad && lane == 0) tail.bad = 1u;
-    dec_finish(H, valid, my_esc, g.G, ctrl, esc_seen + t, arrived + t, nullptr, tail, tid);
+    dec_finish<false>(H, valid, my_esc, g.G, ctrl, esc_seen + t, arrived + t, nullptr, tail, tid);
 }
 
 // rows that refer to an earlier row of their table: copies of that row's reconstruction (after the decode kernel).
