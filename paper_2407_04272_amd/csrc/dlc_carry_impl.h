@@ -99,6 +99,10 @@ __device__ __forceinline__ void carry_flush(const CarryEnv& E, const CarryState&
     *reinterpret_cast<lds_u32*>(E.sp_base + __umul24(row, kCarryPitch * 4u)) = word;
 }
 
+// trips from one test for a mark to the next: two where a group has many (512 MiB that need no mark 132.0 us a call with a test every
+// trip, 131.4; of 4.6 bits a symbol 178, 189)
+template <int S>
+constexpr uint32_t kMarkTrips = S == 256 ? 2u : 1u;
 struct CarryMark {  // a walk's state before turn j (a multiple of a trip's turns)
     uint64_t acc;
     uint32_t nbt, j;
@@ -249,8 +253,8 @@ __device__ __forceinline__ void carry_load(const CarryEnv& E, uint32_t jb, float
 
 // One walk over a group, from turn `from` on (a multiple of a trip's 2 * kCarryLoad turns): lane l codes chunk l (at turn j the four
 // elements group_base + j*256 + 4*l .. +3).  The loads of the next kCarryLoad turns are issued before the current ones are worked on;
-// those of the first turns (xa, va) are already on their way when the walk starts.  Returns its state at the first trip before
-// which a chunk had more than `limit` bits, or at its end.
+// those of the first turns (xa, va) are already on their way when the walk starts.  Returns its state at the first trip (of every
+// kMarkTrips<S>) before which a chunk had more than `limit` bits, or at its end.
 template <int S, bool F16, bool VEC, bool FULL, bool COUNT, bool REWALK = false>
 __device__ __forceinline__ CarryMark carry_walk(const CarryEnv& E, CarryState& St, float (&xa)[kCarryLoad][4], uint32_t (&va)[kCarryLoad], uint32_t from, int limit) {
     constexpr uint32_t N = (uint32_t)S / kV;  // turns of a whole group; the table can end in this one
@@ -264,7 +268,7 @@ __device__ __forceinline__ CarryMark carry_walk(const CarryEnv& E, CarryState& S
     M.j = 0xFFFFFFFFu;
     for (uint32_t jb = from; jb < n_turns; jb += 2 * kCarryLoad) {
         set_wave_priority(jb / (2 * kCarryLoad) + E.rank);
-        if (__ballot((int)St.nbt > limit) != 0ull) {  // uniform
+        if ((jb & (kMarkTrips<S> * 2u * kCarryLoad - 1u)) == 0u && __ballot((int)St.nbt > limit) != 0ull) {  // uniform
             M.acc = St.acc;
             M.nbt = St.nbt;
             M.j = jb;
@@ -477,8 +481,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         St.acc = 0; St.nbt = 0; St.esc = 0; St.nrec = 0;
         CarryMark M;
         M.acc = 0; M.nbt = 0; M.j = 0;
-        // a state marked below this many bits (in the trip before it, a trip's bits more) has no word of the next pass behind it
-        constexpr int kLimit = (int)(CAP * 32u - 2u * kCarryLoad * kV * (uint32_t)kLmaxLimit);
+        // a state marked below this many bits (in the trips before it, their bits more) has no word of the next pass behind it
+        constexpr int kLimit = (int)(CAP * 32u - kMarkTrips<S> * 2u * kCarryLoad * kV * (uint32_t)kLmaxLimit);
         auto last_word = [&](const CarryState& St) {  // the chunk's last, partly filled word
             if (St.nbt & 31u)
                 *reinterpret_cast<lds_u32*>(E.sp_base + __umul24(min((St.nbt >> 5) + 1u, E.row_max), kCarryPitch * 4u)) = (uint32_t)St.acc << (32u - (St.nbt & 31u));
