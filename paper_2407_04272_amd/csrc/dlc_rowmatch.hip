@@ -73,6 +73,11 @@ __device__ __forceinline__ void rm_add_other(uint64_t id, uint32_t e, uint32_t a
     a[2] += rm_mix32(z ^ 0x5BD1E995u);
 }
 
+// the hash from the three sums
+__device__ __forceinline__ uint64_t rm_finish(const uint32_t a[3]) {
+    return rm_mix64((((uint64_t)a[1] << 32) | a[0]) + (uint64_t)a[2] * 0x9E3779B97F4A7C15ull);
+}
+
 constexpr uint32_t kRmSlab = 32;   // pieces of a row that pass 1 holds in LDS at a time
 constexpr uint32_t kRmPitch = kRmSlab + 1u;
 
@@ -173,7 +178,104 @@ __global__ __launch_bounds__(256) void k_rm_hash(const void* payload, Geom g, co
         }
         const uint32_t row = row0 + lane;
         if (row < g.B)
-            rowhash[(size_t)t * g.B + row] = rm_mix64((((uint64_t)a[1] << 32) | a[0]) + (uint64_t)a[2] * 0x9E3779B97F4A7C15ull);
+            rowhash[(size_t)t * g.B + row] = rm_finish(a);
+    }
+}
+
+// The same hash for rows of 256 elements and more that are whole 16-byte pieces (of four words): a row is the work of a team
+// of 2^logL lanes, a piece each, as it lies in memory; where a row has 64 pieces or fewer, a lane's position in it never changes
+// and the multipliers of its piece stay in registers.  Nothing goes through LDS, and the team adds its sums up (modulo 2^32).
+// A lane a row leaves the chip empty where rows are few and long: a wavefront then walks 64 of them alone.  Whole calls, lane
+// per row and team, us: 16 tables of 2048 rows of 1024 250 and 153, of 2048 x 2048 (26 tables) 461 and 254 (both with the
+// compare kernel's finer split), 16 of 8192 x 256 144 and 125.  Rows of 128 and fewer, of which there are many, gain nothing (64
+// tables of 8192 x 128: 21 us either way, of which the plane's way from memory is 12): they keep a lane each.
+constexpr uint32_t kRmBlk = 4;  // pieces a lane has in flight
+
+// the sum over the team's lanes, in all of them
+__device__ __forceinline__ uint32_t rm_team_sum(uint32_t v, uint32_t logL) {
+#define DLC_RM_ADD(c) v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, c, 0xF, 0xF, true)
+    if (logL > 0u) DLC_RM_ADD(0xB1);   // the neighbour
+    if (logL > 1u) DLC_RM_ADD(0x4E);   // the other pair of four
+    if (logL > 2u) DLC_RM_ADD(0x141);  // the other four of eight
+    if (logL > 3u) DLC_RM_ADD(0x140);  // the other eight of sixteen
+#undef DLC_RM_ADD
+    if (logL > 4u) v += (uint32_t)__shfl_xor((int)v, 16, 64);
+    if (logL > 5u) v += (uint32_t)__shfl_xor((int)v, 32, 64);
+    return v;
+}
+
+// LONG: rows of more than 64 pieces, 64 at a time (the multipliers with them)
+template <bool F16, bool LONG>
+__global__ __launch_bounds__(256) void k_rm_hash_team(const void* payload, Geom g, const QParam* qp, const uint8_t* on,
+                                                      uint64_t* rowhash, const uint8_t* sym_plane,
+                                                      const uint32_t* __restrict__ mult, uint32_t logL) {
+    const uint32_t t = blockIdx.y;
+    if (!on[t]) return;  // uniform
+    const uint32_t lane = threadIdx.x & 63u, L = 1u << logL, sub = lane & (L - 1u), team = lane >> logL, rps = 64u >> logL;
+    const uint32_t W = g.D / 16u;
+    const QParam q = qp[t];
+    const float Rf = (float)g.R;
+    const uint8_t* tab = static_cast<const uint8_t*>(payload) + (size_t)t * g.n * g.es;
+    const uint4* plane = reinterpret_cast<const uint4*>(sym_plane + (size_t)t * plane_stride(g));
+    uint64_t* const out = rowhash + (size_t)t * g.B;
+    uint4 m03[4];
+    uint2 m45[4];
+    auto load_mult = [&](uint32_t piece) {
+        const uint32_t* m = mult + 32u * min(piece, W - 1u);  // (a lane past the row's end holds zeroes and adds nothing)
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) {
+            m03[k] = *reinterpret_cast<const uint4*>(m + 8u * k);
+            m45[k] = *reinterpret_cast<const uint2*>(m + 8u * k + 4u);
+        }
+    };
+    if constexpr (!LONG) load_mult(sub);
+    const uint32_t step = kRmBlk * rps;  // rows a wavefront does at a time
+    const uint32_t waves = gridDim.x * 4u, wave = blockIdx.x * 4u + (threadIdx.x >> 6);
+    for (uint32_t row0 = wave * step; row0 < g.B; row0 += waves * step) {
+        uint32_t a[kRmBlk][3];
+#pragma unroll
+        for (uint32_t u = 0; u < kRmBlk; ++u) a[u][0] = a[u][1] = a[u][2] = 0u;
+        for (uint32_t p0 = 0; p0 < (LONG ? W : 1u); p0 += 64u) {
+            const uint32_t p = p0 + sub;
+            uint4 v[kRmBlk];
+#pragma unroll
+            for (uint32_t u = 0; u < kRmBlk; ++u) {
+                const uint32_t row = row0 + u * rps + team;
+                v[u] = row < g.B && p < W ? plane[(size_t)row * W + p] : make_uint4(0u, 0u, 0u, 0u);
+            }
+            if constexpr (LONG) load_mult(p);
+#pragma unroll
+            for (uint32_t u = 0; u < kRmBlk; ++u) {
+                const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+                bool other = false;
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k) {
+                    rm_add_piece(w[k], m03[k], m45[k], a[u]);
+                    other = other || rm_has255(w[k]);
+                }
+                if (other) {  // rare
+                    const uint32_t row = row0 + u * rps + team;
+                    for (uint32_t k = 0; k < 4; ++k) {
+                        for (uint32_t b = 0; b < 4; ++b) {
+                            if (((w[k] >> (8u * b)) & 255u) < kWinEsc) continue;
+                            const uint32_t e = (p * 4u + k) * 4u + b;
+                            rm_add_other(rm_identity<F16>(tab, row * g.D + e, q, Rf, (int)g.R), e, a[u]);
+                        }
+                    }
+                }
+            }
+        }
+        uint32_t mine[3] = {0u, 0u, 0u};
+#pragma unroll
+        for (uint32_t u = 0; u < kRmBlk; ++u) {
+#pragma unroll
+            for (uint32_t i = 0; i < 3; ++i) {
+                a[u][i] = rm_team_sum(a[u][i], logL);
+                if (sub == u) mine[i] = a[u][i];
+            }
+        }
+        const uint32_t row = row0 + sub * rps + team;  // (a team has kRmBlk lanes or more)
+        if (sub < kRmBlk && row < g.B) out[row] = rm_finish(mine);
     }
 }
 
@@ -309,7 +411,7 @@ __global__ __launch_bounds__(1024) void k_rm_sets(Geom g, const uint8_t* on, con
 // of a team of 2^logL lanes, the smallest power of two that covers the row's pieces (64 at most: longer rows take
 // several trips); a wavefront works on 64 rows per trip: those with an earlier owner are put next to one another, 64 >> logL
 // at a time are compared.  64 tables of 8192 x 128: 24 us; all 64 rows walked, the idle ones under a condition, 26, four sets
-// of them in flight at half the wavefronts 34.
+// of them in flight at half the wavefronts 34.  (rows: 64, or fewer where that leaves too few wavefronts, see launch_row_match)
 template <uint32_t PW>
 struct RmPiece { uint32_t v[PW]; };
 
@@ -328,7 +430,7 @@ __device__ __forceinline__ RmPiece<PW> rm_load_piece(const uint32_t* plane, size
 template <bool F16, uint32_t PW>
 __global__ __launch_bounds__(256) void k_rm_owner(const void* payload, Geom g, const QParam* qp, const uint8_t* on,
                                                   const uint32_t* rowown, const uint64_t* rowhash, uint32_t* ref, uint8_t* sym_plane,
-                                                  uint32_t* hist, TableOrder order, uint32_t logL) {
+                                                  uint32_t* hist, TableOrder order, uint32_t logL, uint32_t rows) {
     extern __shared__ __align__(16) uint32_t lh[];  // what to take off the counts: window [kWinBins + 1][kWinCopies] | exact [K]
     uint32_t t, block;
     order.place(&t, &block);
@@ -355,12 +457,13 @@ __global__ __launch_bounds__(256) void k_rm_owner(const void* payload, Geom g, c
     const float Rf = (float)g.R;
     const uint8_t* tab = static_cast<const uint8_t*>(payload) + (size_t)t * g.n * g.es;
     uint32_t* plane = reinterpret_cast<uint32_t*>(sym_plane + (size_t)t * plane_stride(g));
-    for (uint32_t row0 = wave_global * 64u; row0 < g.B; row0 += waves_grid * 64u) {
+    for (uint32_t row0 = wave_global * rows; row0 < g.B; row0 += waves_grid * rows) {
         // the rows that have an earlier owner are put next to one another, rps of them are compared at a time
         const uint32_t row_mine = row0 + lane;
-        const uint32_t own_mine = row_mine < g.B ? rowown[(size_t)t * g.B + row_mine] : 0xFFFFFFFFu;
+        const uint32_t end = min(g.B, row0 + rows);
+        const uint32_t own_mine = row_mine < end ? rowown[(size_t)t * g.B + row_mine] : 0xFFFFFFFFu;
         const bool need_mine = own_mine < row_mine;  // (an owner is never a later row)
-        if (row_mine < g.B && !need_mine) ref_t[row_mine] = row_mine;
+        if (row_mine < end && !need_mine) ref_t[row_mine] = row_mine;
         const uint64_t mask = __ballot(need_mine);
         const uint32_t n = (uint32_t)__popcll(mask), rank = (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
         const int to = (int)((need_mine ? rank : n + lane - rank) << 2);
@@ -491,26 +594,49 @@ hipError_t launch_row_sets(const Geom& g, uint32_t n_sets, const uint8_t* on, co
     return hipGetLastError();
 }
 
+// work-groups of four wavefronts a table, `rows` rows at a time each: 32 at most where there are tables enough, else as many as
+// a thousand work-groups need (whole calls, us, with 32 for all and with this: one table of 65536 x 128 221 and 143, of 300000 x
+// 64 682 and 447)
+static uint32_t row_blocks(const Geom& g, uint32_t rows) {
+    return std::min<uint32_t>((g.B + 4u * rows - 1u) / (4u * rows), std::max<uint32_t>(32u, 1024u / g.T));
+}
+
 hipError_t launch_row_match(const Geom& g, const void* payload, const Ws& w, hipStream_t s) {
     const uint32_t pw = g.D % 16u == 0u ? 4u : 1u;  // words of the plane per lane in pass 2
     uint32_t logL = 0;
     while (logL < 6 && (1u << logL) < g.D / (4u * pw)) ++logL;
-    const uint32_t blocks_x = std::min<uint32_t>((g.B + 255u) / 256u, 32u);  // a wavefront takes 64 rows at a time
-    const uint32_t waves_grid = blocks_x * 4;
     const size_t sm = hist_lds_bytes(g.K);
-    dim3 grid(blocks_x, g.T), block(256);
-    if (g.dtype == DLC_F16)
-        hipLaunchKernelGGL(k_rm_hash<true>, grid, block, 0, s, payload, g, w.qp, w.rm_on, w.rm_hash, w.sym_plane, w.rm_mult, waves_grid);
-    else
-        hipLaunchKernelGGL(k_rm_hash<false>, grid, block, 0, s, payload, g, w.qp, w.rm_on, w.rm_hash, w.sym_plane, w.rm_mult, waves_grid);
+    const dim3 block(256);
+    if (pw == 4u && g.D >= 256u) {
+        const uint32_t trips = (uint32_t)((((uint64_t)g.B << logL) + 64u * kRmBlk - 1u) / (64u * kRmBlk));  // of a wavefront
+        const dim3 grid((trips + 7u) / 8u, g.T);  // two each
+#define DLC_RM_HASH(FF, LL) hipLaunchKernelGGL((k_rm_hash_team<FF, LL>), grid, block, 0, s, payload, g, w.qp, w.rm_on, w.rm_hash, w.sym_plane, w.rm_mult, logL)
+        if (g.D > 1024u) { if (g.dtype == DLC_F16) DLC_RM_HASH(true, true); else DLC_RM_HASH(false, true); }
+        else { if (g.dtype == DLC_F16) DLC_RM_HASH(true, false); else DLC_RM_HASH(false, false); }
+#undef DLC_RM_HASH
+    } else {
+        const dim3 grid(row_blocks(g, 64u), g.T);
+        const uint32_t waves_grid = grid.x * 4u;
+        if (g.dtype == DLC_F16)
+            hipLaunchKernelGGL(k_rm_hash<true>, grid, block, 0, s, payload, g, w.qp, w.rm_on, w.rm_hash, w.sym_plane, w.rm_mult, waves_grid);
+        else
+            hipLaunchKernelGGL(k_rm_hash<false>, grid, block, 0, s, payload, g, w.qp, w.rm_on, w.rm_hash, w.sym_plane, w.rm_mult, waves_grid);
+    }
     {
         hipError_t e = launch_row_sets(g, 1u, w.rm_on, w.rm_hash, w.rm_own, nullptr, nullptr, s);
         if (e != hipSuccess) return e;
     }
+    // A wavefront takes 64 rows at a time, fewer (but a row a team) where there would be less than eight wavefronts a compute unit,
+    // or sixteen where a row takes a wavefront's time.  Whole calls, us, at 64 rows and at this rule's: one table of 8192 x 128 64
+    // and 60, 9 of them 83 and 80, 26 of 512 x 64 48.4 and 46.4, 4 of 1024 x 512 75 and 56, 16 of 2048 x 1024 153 and 116; four
+    // thousand wavefronts for short rows too: one of 65536 x 128 149 instead of 143.
+    uint32_t rows = 64u;
+    const uint32_t lim = g.D >= 256u ? 4096u : 2048u;
+    while (rows > 8u && rows > (64u >> logL) && (uint64_t)g.T * g.B < (uint64_t)lim * rows) rows /= 2u;
     // tables apart and one after the other, us: one of 65536 rows 74 and 69; 9, 26, 44, 64 and 128 of 8192 x 128 14.1 and 13.4, 17.1
     // and 16.3, 20.3 both, 24.4 and 25.0, 41.1 and 43.4
-    const TableOrder order(blocks_x, g.T >= 48u);
-#define DLC_RM_OWNER(FF, PP) hipLaunchKernelGGL((k_rm_owner<FF, PP>), dim3(order.groups(g.T)), block, sm, s, payload, g, w.qp, w.rm_on, w.rm_own, w.rm_hash, w.rm_ref, w.sym_plane, w.hist, order, logL)
+    const TableOrder order(row_blocks(g, rows), g.T >= 48u);
+#define DLC_RM_OWNER(FF, PP) hipLaunchKernelGGL((k_rm_owner<FF, PP>), dim3(order.groups(g.T)), block, sm, s, payload, g, w.qp, w.rm_on, w.rm_own, w.rm_hash, w.rm_ref, w.sym_plane, w.hist, order, logL, rows)
     if (g.dtype == DLC_F16) { if (pw == 4u) DLC_RM_OWNER(true, 4); else DLC_RM_OWNER(true, 1); }
     else { if (pw == 4u) DLC_RM_OWNER(false, 4); else DLC_RM_OWNER(false, 1); }
 #undef DLC_RM_OWNER

@@ -276,6 +276,31 @@ def test_rows_with_equal_hashes_still_get_the_first_occurrence(dtype):
         assert rc == 0 and np.array_equal(rec.cpu().numpy().view(u), orec.view(u))
 
 
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+@pytest.mark.parametrize("T,B,D", [(2, 9, 256), (1, 131, 272), (3, 70, 1008), (1, 65, 1024), (1, 37, 1040), (2, 21, 2064),
+                                   (1, 8300, 64), (1, 1, 512)])
+def test_long_rows_and_few_rows(T, B, D, dtype):
+    """Rows that are the work of a team of lanes (one piece a lane, the last lanes without one, several pieces a lane) and
+    batches whose rows are spread over more wavefronts: references and container are the oracle's."""
+    print("long rows", T, B, D, np.dtype(dtype).name, flush=True)
+    x = _lookups(T, B, D, B + D, rows=max(2, B // 3), dtype=dtype)
+    if B > 4:
+        big = 1e9 if dtype == np.float32 else 6e4
+        x[0, 1, D - 1] = big
+        x[0, 2] = x[0, 1]                       # a repeated row with an escape in its last element
+        x[0, 3] = x[0, 1]
+        x[0, 3, D - 1] = -big                   # the escape's raw bits differ: not a repeat
+        x[0, 4, 0] += 1
+    ebs = np.full(T, 1e-3 if dtype == np.float32 else 4e-3, np.float32)
+    ctx, d, out, data, sizes = _compress(x, ebs, 64)
+    refs = ctx.read_row_refs()
+    for t in range(T):
+        s_t, _ = oracle.quantize(x[t:t + 1], float(ebs[t]), R)
+        assert np.array_equal(refs[t], first_occurrence(x[t:t + 1], s_t)[0]), t
+    o = oracle.compress(x, ebs, R, 64, 12, row_match=True)
+    assert o.rc == 0 and np.array_equal(sizes, o.sizes) and np.array_equal(data, o.data)
+
+
 def test_more_escapes_in_a_group_than_the_encoder_remembers():
     """More than 128 escapes in one group, many of them in rows that are stored as references: the records are those
     of the coded rows only (the encoder's second look at such a group goes by the symbol plane, where an element of a
