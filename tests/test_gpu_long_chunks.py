@@ -145,3 +145,41 @@ def test_groups_around_the_staging_area_of_two_wavefronts(T, B, D, dtype):
     for lo, hi in ((1536, 1856), (1856, 1888), (1888, 1920), (1920, 2100)):
         assert np.any((words > lo) & (words <= hi)), (lo, hi, words.min(), words.max())
     _check(T, B, D, S, dtype, False, x)
+
+
+@pytest.mark.parametrize("kind", KINDS, ids=_ids)
+@pytest.mark.parametrize("flag", ["carried", "sampled"])
+@pytest.mark.parametrize("T,B,D,S,dtype", [
+    (3, 700, 100, 256, np.float32),   # five groups a table, the last ragged
+    (2, 1500, 37, 128, np.float32),   # n % 4 == 0 with an odd row length
+    (3, 333, 41, 64, np.float32),     # n % 4 != 0: scalar loads
+    (2, 700, 100, 256, np.float16),
+    (2, 333, 41, 128, np.float16),
+])
+def test_single_pass(kind, flag, T, B, D, S, dtype):
+    """Groups of more words than a column holds on the single-pass path: walked on from a mark, once and several times."""
+    import torch
+    from paper_2407_04272_amd import binding as b
+    if dtype == np.float16 and kind[0] == "escapes":
+        kind = (kind[0], kind[1] / 10)
+    print("single pass", flag, kind, T, B, D, S, np.dtype(dtype).name, flush=True)
+    x = _payload(np.random.default_rng(int(T + 31 * S + kind[1])), kind, (T, B, D)).astype(dtype)
+    ebs = np.full(T, EB, np.float32)
+    cfg = b.make_config(b.F16 if dtype == np.float16 else b.F32, T, B, D, 512, S, 12, b.FLAG_CARRY_CODEBOOK if flag == "carried" else b.FLAG_SAMPLE_CODEBOOK)
+    ctx = b.Context(cfg)
+    ctx.set_error_bounds(eb=ebs)
+    cap = b.dlc_compress_bound(cfg)
+    out = torch.full((cap + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+    sizes = torch.zeros(1 + T, dtype=torch.int64, device="cuda")
+    d = to_device(x)
+    prev = None
+    for call in range(3):
+        assert ctx.compress(d, out, sizes, capacity=cap) == 0 and ctx.sync_status() == 0
+        h, n = out.cpu().numpy(), int(sizes[0])
+        assert np.all(h[cap:] == 0xA5)
+        if flag == "carried":
+            o = oracle.compress(x, ebs, 512, S, 12, carry_hist=prev, want_hist=True)
+            prev = o.hist
+        else:
+            o = oracle.compress(x, ebs, 512, S, 12, sample_codebook=True)
+        assert o.rc == 0 and n == o.data.size and np.array_equal(h[:n], o.data), call
