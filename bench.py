@@ -12,6 +12,7 @@ through compress AND decompress per second of step time.
 from __future__ import annotations
 
 import argparse
+import gc
 import json
 import os
 import sys
@@ -177,12 +178,14 @@ def main():
     algo_bytes = payload_bytes * (1.0 + 1.0 / cr)  # read s + write s/CR per element (and the reverse)
     kern = {k: (ms / n if n else 0.0) for k, (ms, n) in prof.items()}          # timed region
     kern_all = {k: (ms / n if n else 0.0) for k, (ms, n) in prof_all.items()}  # pre-pass, every kernel
-    # dominant kernel = the one with the largest average duration; its duration comes from the timed region when it is
-    # one of the kernels timed there (the dominant kernel of a direction is), else from the pre-pass
-    timed_kernels = [k for k in kern_all if kern_all[k] > 0]
+    # dominant kernel = the one with the largest average duration, by the timed region where a kernel is timed there (the
+    # dominant kernel of a direction is; k_encode is there the launch that also counts and builds the codebooks), else by the
+    # pre-pass
+    known = {k: kern[k] if kern.get(k, 0) > 0 else v for k, v in kern_all.items()}
+    timed_kernels = [k for k in known if known[k] > 0]
     if timed_kernels:
-        dom = max(timed_kernels, key=lambda k: kern_all[k])
-        dom_ms = kern[dom] if kern.get(dom, 0) > 0 else kern_all[dom]
+        dom = max(timed_kernels, key=lambda k: known[k])
+        dom_ms = known[dom]
     else:
         dom, dom_ms = "dlc_compress (all kernels)", comp_ms
     # priced with the path's algorithmic bytes per element, s(1 + 1/CR), times the elements a launch processes (all of
@@ -213,9 +216,9 @@ def main():
         "stats_ms": round(stats_ms, 3), "stats_GBps": round(payload_bytes / stats_ms / 1e6, 2),
         "kernel_ms": {k: round(v, 4) for k, v in kern.items() if v > 0},
         "kernel_ms_all": {k: round(v, 4) for k, v in kern_all.items() if v > 0},
-        # (events around every kernel keep the containers' end in a launch of its own, k_finalize; the timed step has it inside
-        # the launch that codes the groups)
-        "kernel_ms_all_note": "each kernel timed by itself, outside the timed region; k_finalize is part of the encode launch there",
+        # (events around every kernel keep counting, codebooks, coding and the containers' end in launches of their own; the timed
+        # step has them in one, whose time kernel_ms gives under k_encode)
+        "kernel_ms_all_note": "each kernel timed by itself, outside the timed region; k_hist, k_codebook and k_finalize are part of the k_encode launch there",
         "roofline": {"bound": "hbm", "kernel": dom, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": traffic,
                      # what the target is stated on: a whole call of each direction (all its kernels), same bytes
@@ -568,6 +571,8 @@ def _run_schedule(b, torch, np, W, dev, S, iterations=200):
         ev = [[torch.cuda.Event(enable_timing=True) for _ in range(6)] for _ in range(iterations)]
         comp_bytes = 0
         worst = 0.0
+        gc.collect()
+        gc.disable()  # (a collection of 45 ms between an event and the call it times would be the call's)
         for it in range(iterations):
             fwd, bwd = gen.step()
             if it == 0:
@@ -596,6 +601,7 @@ def _run_schedule(b, torch, np, W, dev, S, iterations=200):
             e[5].record()
             if comp_bytes_f is not None:
                 comp_bytes += comp_bytes_f + int(sizes[0].item())
+        gc.enable()
         torch.cuda.synchronize()
         assert cf.sync_status() == 0 and cb.sync_status() == 0
         c_ms = sum(e[0].elapsed_time(e[1]) + e[3].elapsed_time(e[4]) for e in ev)
