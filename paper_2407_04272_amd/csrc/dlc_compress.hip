@@ -287,6 +287,7 @@ __global__ __launch_bounds__(256) void k_post(Geom g, FixedLayout F, const uint3
     }
 }
 
+// (with row matching: for more references than the coding launch copies, see encode_launch)
 // work-groups of the finalize kernel: sixteen wavefronts each, four where a container has at most 256 tables (they start
 // sooner and a scan is shorter: 5.3 us -> 4.0), but for row matching, where a work-group copies a table's references (10 us
 // with sixteen, 13.6 with four)
@@ -374,8 +375,8 @@ hipError_t launch_compress(const Geom& g, const void* payload, uint8_t* out, uin
     const bool fused = !g.lz && (g.G <= 8u || (g.G <= 16u && whole_rounds)) && (g.T <= 256u || g.K <= 1024u);
     const uint32_t tpw = codebook_tables_per_wg(g);
     // The launch that codes the groups finishes the containers, too, where a work-group has a thread for each of a container's
-    // tables (see finish_container), unless every kernel is to be timed by itself or there are references to copy.
-    uint64_t* const fin = g.lz || prof_on(pl, P_FINALIZE) ? nullptr : out_bytes;
+    // tables (see finish_container), unless every kernel is to be timed by itself or there are very many references to copy.
+    uint64_t* const fin = prof_on(pl, P_FINALIZE) ? nullptr : out_bytes;
     bool finished = false;
     if (fused) {
         if (prof_on(pl, P_TABLE)) prof_begin(prof, P_TABLE, s);

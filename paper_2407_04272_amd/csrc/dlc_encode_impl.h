@@ -483,7 +483,8 @@ template <int S, bool F16, bool VEC, bool LZ, uint32_t NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4)))
 void k_encode(const void* payload, const uint8_t* sym_plane, Geom g, FixedLayout F, const QParam* qp, const uint16_t* enc,
               const TMeta* tmeta, const uint8_t* lens, Ctrl* ctrl, uint64_t* state, uint64_t epoch, uint8_t* out, uint64_t capacity, uint32_t bpt,
-              uint32_t* word_start, uint32_t* word_end, uint64_t* out_bytes, uint32_t xn, uint32_t cap, uint32_t pair_max) {
+              uint32_t* word_start, uint32_t* word_end, uint64_t* out_bytes, uint32_t xn, uint32_t cap, uint32_t pair_max, const uint8_t* rm_on,
+              const uint32_t* rm_ref) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t s_wg, s_lo, s_hi;
     const uint32_t tid = threadIdx.x;
@@ -491,11 +492,9 @@ void k_encode(const void* payload, const uint8_t* sym_plane, Geom g, FixedLayout
     __syncthreads();
     GroupJob J;
     J.wg = __builtin_amdgcn_readfirstlane(s_wg);
-    if constexpr (!LZ) {  // (row matching: the references are copied by a launch of its own)
-        if (J.wg >= g.T * bpt) {  // uniform; xn for every container
-            finish_container<64u * NW, false>(g, F, tmeta, lens, qp, ctrl, state, (const uint32_t*)nullptr, epoch, bpt, out, capacity, out_bytes, J.wg - g.T * bpt, xn, *reinterpret_cast<FinLds<64u * NW>*>(smem), tid);
-            return;
-        }
+    if (J.wg >= g.T * bpt) {  // uniform; xn for every container
+        finish_container<64u * NW, false, LZ>(g, F, tmeta, lens, qp, ctrl, state, (const uint32_t*)nullptr, epoch, bpt, out, capacity, out_bytes, J.wg - g.T * bpt, xn, *reinterpret_cast<FinLds<64u * NW>*>(smem), tid, rm_on, rm_ref);
+        return;
     }
     encode_item<S, F16, VEC, LZ, NW, false>(J, payload, sym_plane, g, F, qp, enc, tmeta, ctrl, state, epoch, out, capacity, bpt, NW, word_start, word_end,
                                             cap, pair_max, &s_lo, &s_hi, smem, tid);
@@ -770,14 +769,19 @@ static inline uint32_t pair_max_for(uint32_t budget, uint32_t nw, uint32_t waves
     return p;
 }
 
+constexpr uint32_t kFinishMost = 128;  // work-groups a container that copy its references
+
 // out_bytes: where the sizes go if the launch is to finish the containers as well; it does if it returns true
 template <uint32_t NW>
 static bool DLC_CAT(encode_launch_, DLC_S)(const Geom& g, const FixedLayout& F, const void* payload, const Ws& w, uint64_t epoch,
                                            uint8_t* out, uint64_t capacity, uint64_t* out_bytes, hipStream_t s) {
     constexpr int S = DLC_S;
     const uint32_t bpt = (g.G + NW - 1u) / NW;
-    if (g.TD > 64u * NW) out_bytes = nullptr;
-    const uint32_t xn = finish_groups(g, 64u * NW);
+    uint32_t xn = finish_groups(g, 64u * NW);
+    if (g.lz) xn = std::max(xn, std::min<uint32_t>(kFinishMost, (uint32_t)(((uint64_t)g.TD * g.B + 64u * NW * kFinishRefs - 1u) / (64u * NW * kFinishRefs))));
+    // (With row matching up to as many references as so many work-groups load at once; more in a launch of their own: with 64
+    // work-groups that go round again 64 tables of 16384 x 32 138 us instead of 134, with 128 135, 128 of 8192 x 128 279 and 275.)
+    if (g.TD > 64u * NW || (g.lz && (uint64_t)g.TD * g.B > (uint64_t)kFinishMost * 64u * NW * kFinishRefs)) out_bytes = nullptr;
     dim3 grid(g.T * bpt + (out_bytes ? g.ND * xn : 0u)), block(64 * NW);
     // sixteen wavefronts a compute unit share its LDS: columns of 4 bits a symbol.  Where the grid leaves room, longer
     // columns (up to the longest code), so that no group is walked twice.
@@ -791,7 +795,7 @@ static bool DLC_CAT(encode_launch_, DLC_S)(const Geom& g, const FixedLayout& F, 
     const bool f16 = g.dtype == DLC_F16;
 #define DLC_ENC(FF, V, LZ)                                                                                            \
     hipLaunchKernelGGL((k_encode<S, FF, V, LZ, NW>), grid, block, sm, s, payload, w.sym_plane, g, F, w.qp, w.enc, w.tmeta, w.lens, w.ctrl, \
-                       w.state, epoch, out, capacity, bpt, w.word_start, w.word_end, out_bytes, xn, cap, pair_max)
+                       w.state, epoch, out, capacity, bpt, w.word_start, w.word_end, out_bytes, xn, cap, pair_max, w.rm_on, w.rm_ref)
     if (g.lz) { if (f16) DLC_ENC(true, true, true); else DLC_ENC(false, true, true); }  // (dim % 4 == 0 there)
     else if (f16) { if (g.vec) DLC_ENC(true, true, false); else DLC_ENC(true, false, false); }
     else { if (g.vec) DLC_ENC(false, true, false); else DLC_ENC(false, false, false); }

@@ -228,14 +228,15 @@ __device__ __forceinline__ void finalize_dest(const Geom& g, const FixedLayout& 
 }
 
 // ------------------------------------------------------------------------------------------------
-// The same from inside the kernel that codes the groups (at most as many tables a container as a work-group has threads; no
-// row matching), by `xn` work-groups more for every container.  They have the last of the tickets, so everybody they wait for
+// The same from inside the kernel that codes the groups (at most as many tables a container as a work-group has threads),
+// by `xn` work-groups more for every container.  They have the last of the tickets, so everybody they wait for
 // is running already.  They have the code-length blocks' words in LDS before the groups are coded: from the launch
 // before, or (LATE) when the tables' work-groups say that their codebooks are there; when the last word's place is known, all
 // that is left is to write.  The work-groups with a container's share 0, which write everything but the blocks' other
 // words, are the last: the ticket counter is cleared when nobody can ask for one any more.
 // (A launch of its own costs 4 us whatever it does: one table of 4096 elements 16.6 us a call, so 14.2; 26 tables of 4096 x 64
-// 47.6, so 43.7; 512 MiB 202, so 197.)
+// 47.6, so 43.7; 512 MiB 202, so 197.  With row matching, where that launch copies the references as well: 3 tables of 1000 x 64
+// 47.2, so 43.4, one of 65536 x 128, whose references one work-group copied, 143, so 124, 64 of 8192 x 128 170.5, so 166.4.)
 // ------------------------------------------------------------------------------------------------
 constexpr uint32_t kFinishWords = 16;  // words of the code-length blocks a thread has if all symbols are used
 static inline uint32_t finish_groups(const Geom& g, uint32_t nt) { return (g.TD * (g.K / 4u) + nt * kFinishWords - 1u) / (nt * kFinishWords); }
@@ -248,12 +249,16 @@ struct FinLds {
     uint32_t span[NT];  // lowest symbol | symbols in the block << 12
     uint32_t end[NT];   // the tables' last words
     uint32_t word[NT * kFinishWords];  // this work-group's share of the blocks
+    uint32_t refs[NT];  // row matching: the tables with references
 };
 
-template <uint32_t NT, bool LATE>
+constexpr uint32_t kFinishRefs = 16;  // references a thread loads back to back
+
+template <uint32_t NT, bool LATE, bool LZ = false>
 __device__ __forceinline__ void finish_container(const Geom& g, const FixedLayout& F, const TMeta* tmeta, const uint8_t* lens, const QParam* qp,
                                                  Ctrl* ctrl, const uint64_t* state, const uint32_t* ready, uint64_t epoch, uint32_t bpt, uint8_t* out, uint64_t capacity,
-                                                 uint64_t* out_bytes, uint32_t f, uint32_t xn, FinLds<NT>& L, uint32_t tid) {
+                                                 uint64_t* out_bytes, uint32_t f, uint32_t xn, FinLds<NT>& L, uint32_t tid,
+                                                 const uint8_t* rm_on = nullptr, const uint32_t* rm_ref = nullptr) {
     const uint32_t xi = xn - 1u - f / g.ND, dst = f % g.ND, T = g.TD;  // number f of the ND * xn: the shares 0 are the last
     const bool first = xi == 0u;  // uniform
     tmeta += (size_t)dst * T;
@@ -314,6 +319,28 @@ __device__ __forceinline__ void finish_container(const Geom& g, const FixedLayou
         }
         L.word[i - w_lo] = c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24);
     }
+    // row matching: the references of the tables that use it, behind the code-length blocks, each table's on a 16-byte boundary: a
+    // share of all of them, in place of the padding zeroes.  The first are loaded before the last word's place is known.
+    uint32_t on = 0, on_ex = 0, n_on = 0, r_lo = 0, r_hi = 0, rv[LZ ? kFinishRefs : 1u];
+    const uint32_t pitch = (g.B + 3u) & ~3u;  // words from one table's references to the next's
+    auto load_refs = [&](uint32_t i0) {
+#pragma unroll
+        for (uint32_t u = 0; u < (LZ ? kFinishRefs : 0u); ++u) {
+            const uint32_t i = i0 + u * NT + tid, k = i / pitch, r = i - k * pitch;
+            rv[u] = i < r_hi && r < g.B ? rm_ref[((size_t)dst * T + L.refs[k]) * g.B + r] : 0u;
+        }
+    };
+    if constexpr (LZ) {
+        on = tid < T && rm_on[(size_t)dst * T + tid] ? 1u : 0u;
+        __syncthreads();
+        on_ex = block_excl_scan<(int)(NT / 64u)>(on, L.red, tid, &n_on);
+        if (on) L.refs[on_ex] = tid;
+        __syncthreads();
+        const uint32_t all = n_on ? (n_on - 1u) * pitch + g.B : 0u, part = (all + xn - 1u) / xn;
+        r_lo = min(all, xi * part);
+        r_hi = min(all, r_lo + part);
+        load_refs(r_lo);
+    }
     const uint32_t eb_bits = first && tid < T ? qp[(size_t)dst * T + tid].eb_bits : 0u;
     // the words' places
     if (first) {
@@ -324,7 +351,17 @@ __device__ __forceinline__ void finish_container(const Geom& g, const FixedLayou
     __syncthreads();
     const uint64_t words = L.end[T - 1u], off_cb = a16(F.off_payload + 4ull * words);
     // (a container that did not fit spoils only itself: the test below fails for it whenever the groups' did)
-    const bool fits = L.dead == 0u && off_cb + cb_tot <= capacity;
+    const uint64_t off_ref = a16(off_cb + cb_tot), end = n_on ? off_ref + 4ull * ((uint64_t)(n_on - 1u) * pitch + g.B) : off_cb + cb_tot;
+    const bool fits = L.dead == 0u && end <= capacity;
+    if (LZ && fits) {
+        uint32_t* const refs = reinterpret_cast<uint32_t*>(out + off_ref);
+        for (uint32_t i0 = r_lo; i0 < r_hi; i0 += NT * kFinishRefs) {
+            if (i0 != r_lo) load_refs(i0);
+#pragma unroll
+            for (uint32_t u = 0; u < (LZ ? kFinishRefs : 0u); ++u)
+                if (i0 + u * NT + tid < r_hi) refs[i0 + u * NT + tid] = rv[u];
+        }
+    }
     if (fits) {
         uint32_t* const blocks = reinterpret_cast<uint32_t*>(out + off_cb);
         for (uint32_t i = w_lo + tid; i < w_hi; i += NT) blocks[i] = L.word[i - w_lo];
@@ -332,12 +369,20 @@ __device__ __forceinline__ void finish_container(const Geom& g, const FixedLayou
     if (!first) return;
     if (fits) {
         if (tid < T) finish_table(g, out, tid, m, eb_bits, off_cb + cb_ex, cb, tid ? L.end[tid - 1u] : 0u, L.end[tid], table_bytes);
-        finish_header<NT>(g, F, out, words, off_cb, off_cb + cb_tot, n_esc, tid);
+        if constexpr (LZ) {
+            if (on) {  // (by the thread that has written the entry)
+                reinterpret_cast<uint64_t*>(out + kHeaderBytes + (uint64_t)kDirBytes * tid + 24)[1] = off_ref + 4ull * on_ex * pitch;
+                table_bytes[tid] += 4ull * g.B;
+            }
+            if (n_on)
+                for (uint64_t i = off_cb + cb_tot + tid; i < off_ref; i += NT) out[i] = 0;
+        }
+        finish_header<NT>(g, F, out, words, off_cb, end, n_esc, tid);
     } else {
         if (tid == 0 && L.dead == 0u) set_status(ctrl, DLC_ECAPACITY);
         if (tid < T) table_bytes[tid] = 0;
     }
-    if (tid == 0) finish_sizes(g, ctrl, out_bytes, dst, fits ? off_cb + cb_tot : 0ull);
+    if (tid == 0) finish_sizes(g, ctrl, out_bytes, dst, fits ? end : 0ull);
 }
 
 }  // namespace dlc

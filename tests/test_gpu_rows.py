@@ -301,6 +301,37 @@ def test_long_rows_and_few_rows(T, B, D, dtype):
     assert o.rc == 0 and np.array_equal(sizes, o.sizes) and np.array_equal(data, o.data)
 
 
+@pytest.mark.parametrize("T,B,D,on", [
+    (3, 301, 40, [1, 0, 1]),                 # blocks padded to 16 bytes; a table without references in between
+    (2, 4500, 16, [0, 1]),                   # more references than a thread loads back to back
+    (3, 64, 16, [0, 0, 0]),                  # none at all
+    (1, 41000, 8, [1]),                      # several work-groups share them
+    (70, 130, 12, [1] * 70),                 # a container of many tables, small blocks
+])
+def test_references_at_the_end_of_the_container(T, B, D, on):
+    """The coding launch writes the references, too: the container is the oracle's; one byte less capacity is refused and leaves
+    the context as it was."""
+    import torch
+    from paper_2407_04272_amd import binding as b
+    print("references in place", T, B, D, flush=True)
+    x = _lookups(T, B, D, 7 * B + T, rows=max(3, B // 5))
+    ebs = np.full(T, 1e-3, np.float32)
+    ctx, d, out, data, sizes = _compress(x, ebs, 64, flags_per_table=on)
+    o = oracle.compress(x, ebs, R, 64, 12, row_match=np.array(on, bool))
+    assert o.rc == 0 and np.array_equal(sizes, o.sizes) and np.array_equal(data, o.data)
+    sz = torch.zeros(1 + T, dtype=torch.int64, device="cuda")
+    for capacity, ok in ((data.size, True), (data.size - 1, False), (data.size - 4 * B, False), (data.size, True)):
+        out.fill_(0xA5)
+        rc = ctx.compress(d, out, sz, capacity=capacity)
+        status = ctx.sync_status()
+        h = out.cpu().numpy()
+        assert np.all(h[capacity:] == 0xA5), capacity
+        if ok:
+            assert rc == 0 and status == 0 and np.array_equal(h[:data.size], data)
+        else:
+            assert status == b.ECAPACITY and int(sz[0]) == 0, capacity
+
+
 def test_more_escapes_in_a_group_than_the_encoder_remembers():
     """More than 128 escapes in one group, many of them in rows that are stored as references: the records are those
     of the coded rows only (the encoder's second look at such a group goes by the symbol plane, where an element of a
