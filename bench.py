@@ -179,8 +179,7 @@ def main():
     kern = {k: (ms / n if n else 0.0) for k, (ms, n) in prof.items()}          # timed region
     kern_all = {k: (ms / n if n else 0.0) for k, (ms, n) in prof_all.items()}  # pre-pass, every kernel
     # dominant kernel = the one with the largest average duration, by the timed region where a kernel is timed there (the
-    # dominant kernel of a direction is; k_encode is there the launch that also counts and builds the codebooks), else by the
-    # pre-pass
+    # dominant kernel of a direction is), else by the pre-pass
     known = {k: kern[k] if kern.get(k, 0) > 0 else v for k, v in kern_all.items()}
     timed_kernels = [k for k in known if known[k] > 0]
     if timed_kernels:
@@ -217,8 +216,8 @@ def main():
         "kernel_ms": {k: round(v, 4) for k, v in kern.items() if v > 0},
         "kernel_ms_all": {k: round(v, 4) for k, v in kern_all.items() if v > 0},
         # (events around every kernel keep counting, codebooks, coding and the containers' end in launches of their own; the timed
-        # step has them in one, whose time kernel_ms gives under k_encode)
-        "kernel_ms_all_note": "each kernel timed by itself, outside the timed region; k_hist, k_codebook and k_finalize are part of the k_encode launch there",
+        # step has them in one, k_flow)
+        "kernel_ms_all_note": "each kernel timed by itself, outside the timed region; there k_flow does the work of k_hist, k_codebook, k_encode and k_finalize",
         "roofline": {"bound": "hbm", "kernel": dom, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": traffic,
                      # what the target is stated on: a whole call of each direction (all its kernels), same bytes

@@ -319,10 +319,10 @@ int dlc_set_row_hash_multipliers(dlc_ctx* ctx, const uint32_t* h_mult, void* str
 
 /*
  * Kernel timing with HIP events on the caller's stream.
- *   dlc_profile_enable  level 0 off; 1 = the dominant kernel of each direction (encode, decode); 2 = every
+ *   dlc_profile_enable  level 0 off; 1 = the dominant kernel of each direction (coding, decode); 2 = every
  *                       kernel.  Each timed kernel costs two event records per call (a few microseconds).
- *                       Where one launch counts, builds the codebooks and encodes (large payloads), level 1 times it as
- *                       k_encode; level 2 makes it separate launches, each timed by itself
+ *                       Where one launch counts, builds the codebooks and encodes (k_flow: large payloads), level 1 times
+ *                       that launch; level 2 makes it separate launches, each timed by itself
  *   dlc_profile_read    synchronises, returns the number of kernel slots; for slot i < max_slots:
  *                       names[i] (static string), total_ms[i], launches[i]; then resets the counters
  */

@@ -45,7 +45,7 @@ void prof_end(void* p, int slot, hipStream_t s) {
 }
 
 static const char* kSlotNames[P_NSLOTS] = {"k_hist", "k_codebook", "k_encode", "k_finalize",
-                                           "k_decode", "k_encode_carry", "k_post", "k_table"};
+                                           "k_decode", "k_encode_carry", "k_post", "k_table", "k_flow"};
 }  // namespace dlc
 
 using namespace dlc;

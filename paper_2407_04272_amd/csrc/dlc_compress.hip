@@ -387,13 +387,13 @@ hipError_t launch_compress(const Geom& g, const void* payload, uint8_t* out, uin
         }
         if (prof_on(pl, P_TABLE)) prof_end(prof, P_TABLE, s);
     } else if (flow) {
-        if (prof_on(pl, P_ENCODE)) prof_begin(prof, P_ENCODE, s);
+        if (prof_on(pl, P_FLOW)) prof_begin(prof, P_FLOW, s);
         switch (g.S) {
             case 64: finished = launch_flow_64(g, F, payload, w, epoch, out, capacity, fin, s); break;
             case 128: finished = launch_flow_128(g, F, payload, w, epoch, out, capacity, fin, s); break;
             default: finished = launch_flow_256(g, F, payload, w, epoch, out, capacity, fin, s); break;
         }
-        if (prof_on(pl, P_ENCODE)) prof_end(prof, P_ENCODE, s);
+        if (prof_on(pl, P_FLOW)) prof_end(prof, P_FLOW, s);
     } else {
         // histogram
         {

@@ -315,9 +315,9 @@ struct Ws {
 // profiling hooks used by the launchers (implemented in dlc_api.hip)
 void prof_begin(void* prof, int slot, hipStream_t s);
 void prof_end(void* prof, int slot, hipStream_t s);
-enum ProfSlot { P_HIST = 0, P_CODEBOOK, P_ENCODE, P_FINALIZE, P_DECODE, P_CARRY, P_POST, P_TABLE, P_NSLOTS };
+enum ProfSlot { P_HIST = 0, P_CODEBOOK, P_ENCODE, P_FINALIZE, P_DECODE, P_CARRY, P_POST, P_TABLE, P_FLOW, P_NSLOTS };
 inline bool prof_on(int level, int slot) {
-    return level >= 2 || (level == 1 && (slot == P_ENCODE || slot == P_DECODE || slot == P_CARRY || slot == P_TABLE));
+    return level >= 2 || (level == 1 && (slot == P_ENCODE || slot == P_DECODE || slot == P_CARRY || slot == P_TABLE || slot == P_FLOW));
 }
 
 }  // namespace dlc

@@ -25,6 +25,13 @@ def _payload(rng, T, B, D, dtype, wide):
     return x, np.maximum(eb, np.float32(1e-4))
 
 
+def _ran(ctx):
+    """The kernels of the compress calls since profiling was switched on, each launched once."""
+    prof = ctx.profile_read()
+    assert all(n <= 1 for _, n in prof.values())
+    return {name for name, (ms, n) in prof.items() if n and ms > 0}
+
+
 CASES = [  # T, B, D, S, dtype, destinations, radius
     (26, 11300, 64, 256, np.float32, 1, 512),    # 45 groups and a part of one
     (1, 150001, 125, 256, np.float32, 1, 512),   # one table off the 16-byte grid, its end inside a unit
@@ -53,7 +60,9 @@ def test_containers_match_the_oracle(T, B, D, S, dtype, nd, R):
         pieces, ebs = zip(*[_payload(rng, T, B, D, dtype, call == 1) for _ in range(nd)])
         ctx.set_error_bounds(eb=ebs[0])
         d = to_device(np.stack(pieces) if nd > 1 else pieces[0])
+        ctx.profile_enable(call)  # (level 1 changes no launch)
         assert ctx.compress(d, out, sizes, capacity=cap) == 0 and ctx.sync_status() == 0
+        assert not call or _ran(ctx) == {"k_flow"}
         h = out.cpu().numpy()
         assert np.all(h[cap:] == 0xA5)
         sz = sizes.cpu().numpy().astype(np.uint64)
@@ -125,3 +134,32 @@ def test_first_call_of_a_carried_chain():
         n = o.data.size
         assert int(sizes[0]) == n and np.array_equal(out[:n].cpu().numpy(), o.data), call
         prev = o.hist
+
+
+APART = {"k_hist", "k_codebook", "k_encode", "k_finalize"}
+
+
+@pytest.mark.parametrize("T,B,D,S,R,launch,apart", [
+    (2, 144000, 64, 64, 512, "k_flow", APART),        # 72000 units of 256 elements
+    (2, 143996, 64, 64, 512, "k_encode", APART),      # two fewer
+    (600, 500, 64, 64, 512, "k_table", {"k_table", "k_finalize"}),  # 75000 units of small tables
+])
+def test_the_rule_of_the_launches(T, B, D, S, R, launch, apart):
+    """Level 1 names the launch that codes the groups, whichever that is; level 2 keeps counting, codebooks and coding apart."""
+    import torch
+    from paper_2407_04272_amd import binding as b
+    print("rule", T, B, D, S, R, flush=True)
+    cfg = b.make_config(b.F32, T, B, D, R, S, 12, 0)
+    ctx = b.Context(cfg)
+    ctx.set_error_bounds(eb=np.full(T, 2.0 ** -10, np.float32))
+    x = torch.randn((T, B, D), device="cuda") * 0.01
+    out = torch.empty(b.dlc_compress_bound(cfg), dtype=torch.uint8, device="cuda")
+    sizes = torch.zeros(1 + T, dtype=torch.int64, device="cuda")
+    data = []
+    for level, want in ((0, set()), (1, {launch}), (2, apart)):
+        ctx.profile_enable(level)
+        out.fill_(0xA5)
+        assert ctx.compress(x, out, sizes) == 0 and ctx.sync_status() == 0
+        assert _ran(ctx) == want, level
+        data.append((sizes.clone(), out[:int(sizes[0])].clone()))
+    assert all(torch.equal(s, data[0][0]) and torch.equal(o, data[0][1]) for s, o in data)
