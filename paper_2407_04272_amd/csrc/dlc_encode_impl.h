@@ -514,6 +514,7 @@ struct FlowPlan {
     uint32_t cpt, units;  // tickets to count a table, units each (a multiple of kHistBlk)
     uint32_t ept, gpe;    // tickets to code a table, groups each
     uint32_t lag;         // tables counted before the first is coded
+    uint32_t tickets;     // in all
 };
 constexpr uint32_t kFlowWaves = 8;
 
@@ -530,6 +531,10 @@ void k_flow(const void* payload, uint8_t* sym_plane, Geom g, FixedLayout F, cons
     if (tid == 0) { s_ticket = atomicAdd(&ctrl->ticket, 1u); s_lo = 255u; s_hi = 0u; }
     __syncthreads();
     const uint32_t ticket = __builtin_amdgcn_readfirstlane(s_ticket);
+    if (ticket >= P.tickets) {  // uniform; a spare work-group.  The last of all clears the counter
+        if (tid == 0 && ticket + 1u == gridDim.x) __hip_atomic_store(&ctrl->ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    }
     // ticket -> what to do: the first `lag` tables' counting; a table's counting and the coding of the table `lag` before it; the last tables' coding
     uint32_t t, r;
     bool count = true;
@@ -553,7 +558,7 @@ void k_flow(const void* payload, uint8_t* sym_plane, Geom g, FixedLayout F, cons
         }
     }
     if (t >= g.T) {  // uniform; xn for every container
-        finish_container<NT, true>(g, F, tmeta, lens, qp, ctrl, state, ready, epoch, P.ept, out, capacity, out_bytes, ticket - g.T * (P.cpt + P.ept), xn, *reinterpret_cast<FinLds<NT>*>(smem), tid);
+        finish_container<NT, true, false, false>(g, F, tmeta, lens, qp, ctrl, state, ready, epoch, P.ept, out, capacity, out_bytes, ticket - g.T * (P.cpt + P.ept), xn, *reinterpret_cast<FinLds<NT>*>(smem), tid);
         return;
     }
     if (count) {
@@ -831,7 +836,13 @@ bool DLC_CAT(launch_flow_, DLC_S)(const Geom& g, const FixedLayout& F, const voi
     // as many shares ahead as to have a table counted when its coding starts, with all of the work-groups between at work (512 MiB,
     // 600, 1000 and 1600 shares: 176, 171 and 172 us)
     P.lag = std::min(g.T, (1024u + P.cpt - 1u) / P.cpt);
-    const uint32_t n_wg = g.T * (P.cpt + P.ept) + (out_bytes ? g.ND * xn : 0u);
+    P.tickets = g.T * (P.cpt + P.ept) + (out_bytes ? g.ND * xn : 0u);
+    // An eighth more work-groups than tickets: the hardware gives every XCD as many work-groups as the others, whatever theirs have to do,
+    // so the XCDs whose tickets took long have as many left to start when the tickets of the others run out.  Spare ones end at
+    // once (us, without and with: 128 tables of 8192 x 128 at bounds of 0.03, 0.004 and 0.001 of the range 169 and 169, 240 and 239, 848 and 803, 64 of
+    // them at 0.001 562 and 491, 64 of 4099 x 77 at 0.03 55.6 and 53.6; a sixteenth more 524 for the 491, a quarter as much more 477 for a
+    // percent on small payloads).
+    const uint32_t n_wg = P.tickets + P.tickets / 8u + 1u;
     const uint32_t budget = kLdsMax / 2u - kTableStatic;
     uint32_t cap = (uint32_t)S * 12u / 32u;
     while (cap > (uint32_t)S / 8u && enc_lds(NW, P.gpe, cap, 60u).end > budget) --cap;

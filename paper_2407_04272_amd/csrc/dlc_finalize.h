@@ -44,8 +44,9 @@ __device__ __forceinline__ void finish_table(const Geom& g, uint8_t* out, uint32
 
 // Sizes: one destination -> out_bytes[0] is its container's size.  Several -> every destination stores its size
 // behind the per-table entries, and the last one to do so adds them up into out_bytes[0] (0 if any did not fit).
-// The next call starts with ticket 0 and no abort (the histograms were cleared by the codebook step).  By one thread.
-__device__ __forceinline__ void finish_sizes(const Geom& g, Ctrl* ctrl, uint64_t* out_bytes, uint32_t dst, uint64_t container_bytes) {
+// The next call starts with ticket 0 (clear_ticket: by this) and no abort (the histograms were cleared by the codebook step).  By
+// one thread.
+__device__ __forceinline__ void finish_sizes(const Geom& g, Ctrl* ctrl, uint64_t* out_bytes, uint32_t dst, uint64_t container_bytes, bool clear_ticket) {
     bool last = g.ND == 1;
     if (last) {
         out_bytes[0] = container_bytes;
@@ -67,7 +68,7 @@ __device__ __forceinline__ void finish_sizes(const Geom& g, Ctrl* ctrl, uint64_t
         }
     }
     if (last) {
-        __hip_atomic_store(&ctrl->ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (clear_ticket) __hip_atomic_store(&ctrl->ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&ctrl->abort, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
@@ -224,7 +225,7 @@ __device__ __forceinline__ void finalize_dest(const Geom& g, const FixedLayout& 
     } else {
         finish_header<NT>(g, F, out, words, off_cb, end_bytes, nout_carry, tid);
     }
-    if (tid == 0) finish_sizes(g, ctrl, out_bytes, dst, s_abort ? 0ull : end_bytes);  // (0: it did not fit)
+    if (tid == 0) finish_sizes(g, ctrl, out_bytes, dst, s_abort ? 0ull : end_bytes, true);  // (0: it did not fit)
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -233,7 +234,7 @@ __device__ __forceinline__ void finalize_dest(const Geom& g, const FixedLayout& 
 // is running already.  They have the code-length blocks' words in LDS before the groups are coded: from the launch
 // before, or (LATE) when the tables' work-groups say that their codebooks are there; when the last word's place is known, all
 // that is left is to write.  The work-groups with a container's share 0, which write everything but the blocks' other
-// words, are the last: the ticket counter is cleared when nobody can ask for one any more.
+// words, are the last: the ticket counter is cleared when nobody can ask for one any more (TICKET false: the kernel clears it).
 // (A launch of its own costs 4 us whatever it does: one table of 4096 elements 16.6 us a call, so 14.2; 26 tables of 4096 x 64
 // 47.6, so 43.7; 512 MiB 202, so 197.  With row matching, where that launch copies the references as well: 3 tables of 1000 x 64
 // 47.2, so 43.4, one of 65536 x 128, whose references one work-group copied, 143, so 124, 64 of 8192 x 128 170.5, so 166.4.)
@@ -254,7 +255,7 @@ struct FinLds {
 
 constexpr uint32_t kFinishRefs = 16;  // references a thread loads back to back
 
-template <uint32_t NT, bool LATE, bool LZ = false>
+template <uint32_t NT, bool LATE, bool LZ = false, bool TICKET = true>
 __device__ __forceinline__ void finish_container(const Geom& g, const FixedLayout& F, const TMeta* tmeta, const uint8_t* lens, const QParam* qp,
                                                  Ctrl* ctrl, const uint64_t* state, const uint32_t* ready, uint64_t epoch, uint32_t bpt, uint8_t* out, uint64_t capacity,
                                                  uint64_t* out_bytes, uint32_t f, uint32_t xn, FinLds<NT>& L, uint32_t tid,
@@ -382,7 +383,7 @@ __device__ __forceinline__ void finish_container(const Geom& g, const FixedLayou
         if (tid == 0 && L.dead == 0u) set_status(ctrl, DLC_ECAPACITY);
         if (tid < T) table_bytes[tid] = 0;
     }
-    if (tid == 0) finish_sizes(g, ctrl, out_bytes, dst, fits ? end : 0ull);
+    if (tid == 0) finish_sizes(g, ctrl, out_bytes, dst, fits ? end : 0ull, TICKET);
 }
 
 }  // namespace dlc
