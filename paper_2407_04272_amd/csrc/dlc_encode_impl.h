@@ -833,9 +833,12 @@ bool DLC_CAT(launch_flow_, DLC_S)(const Geom& g, const FixedLayout& F, const voi
     P.cpt = (U + P.units - 1u) / P.units;
     P.gpe = NW;
     P.ept = (g.G + P.gpe - 1u) / P.gpe;
-    // as many shares ahead as to have a table counted when its coding starts, with all of the work-groups between at work (512 MiB,
-    // 600, 1000 and 1600 shares: 176, 171 and 172 us)
-    P.lag = std::min(g.T, (1024u + P.cpt - 1u) / P.cpt);
+    // As many shares ahead as to have a table counted when its coding starts, with all of the work-groups between at work, and a fifth
+    // more: a codebook of hundreds of symbols takes 130 us, and the tickets that wait for it keep those behind them, which count,
+    // from starting.  (Us at 1024, 1216 and 1600 shares: 128 tables of 8192 x 128 at bounds of 0.03, 0.002 and 0.001 of the range 162.9, 162.9
+    // and 164.2, 296, 283 and 242, 806, 778 and 747, by three launches 785 at the last; 400 of them at 0.03 484, 490 and 501: more tables
+    // are coded alone at the end.  In half precision, with shares twice as large, 128 of 16384 x 128 391, 396 and 394.)
+    P.lag = std::min(g.T, ((g.dtype == DLC_F16 ? 1024u : 1216u) + P.cpt - 1u) / P.cpt);
     P.tickets = g.T * (P.cpt + P.ept) + (out_bytes ? g.ND * xn : 0u);
     // An eighth more work-groups than tickets: the hardware gives every XCD as many work-groups as the others, whatever theirs have to do,
     // so the XCDs whose tickets took long have as many left to start when the tickets of the others run out.  Spare ones end at

@@ -38,6 +38,7 @@ CASES = [  # T, B, D, S, dtype, destinations, radius
     (35, 5001, 111, 128, np.float32, 1, 512),
     (19, 16385, 64, 64, np.float32, 1, 2048),    # an alphabet of 4096 symbols
     (560, 1100, 64, 64, np.float16, 1, 512),     # more tables than a work-group has threads: the container by a launch of its own
+    (900, 1030, 64, 64, np.float16, 1, 512),     # two shares a table: the first tables are coded before the last are counted
     (23, 10001, 96, 128, np.float16, 1, 128),
     (9, 1700, 333, 256, np.float32, 4, 512),     # four containers
 ]
