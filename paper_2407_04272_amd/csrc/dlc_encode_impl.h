@@ -833,8 +833,9 @@ bool DLC_CAT(launch_flow_, DLC_S)(const Geom& g, const FixedLayout& F, const voi
     P.cpt = (U + P.units - 1u) / P.units;
     // Eight groups a ticket, fewer where there would not be a ticket for every compute unit: groups that take long need the units more
     // than the tables in LDS cost (40 tables of 4096 x 128, 1280 groups, at 0.001 of the range 358 us with eight, 324 with five, 341 by
-    // three launches; at 0.03, where a ticket takes 20 us, 12 of 16384 x 128 55.3 and 56.9, by three launches 61.2).
-    P.gpe = std::min(NW, std::max(1u, g.NG / 256u));
+    // three launches; at 0.03, where a ticket takes 20 us, 12 of 16384 x 128 55.3 and 56.9, by three launches 61.2).  Not in half precision:
+    // 3 tables of 60000 x 128 at 0.03 70 us with eight, 72 with five, 100 of 4000 x 48 at 0.001, eight, 454, by three launches 447.
+    P.gpe = g.dtype == DLC_F16 ? NW : std::min(NW, std::max(1u, g.NG / 256u));
     P.ept = (g.G + P.gpe - 1u) / P.gpe;
     // As many shares ahead as to have a table counted when its coding starts, with all of the work-groups between at work, and a fifth
     // more: a codebook of hundreds of symbols takes 130 us, and the tickets that wait for it keep those behind them, which count,
