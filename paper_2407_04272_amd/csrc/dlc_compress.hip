@@ -352,14 +352,21 @@ hipError_t launch_compress(const Geom& g, const void* payload, uint8_t* out, uin
         }
         return hipGetLastError();
     }
-    // Larger tables go from payload to coded groups in one launch as well, a table being the work of many work-groups (k_flow), where
-    // the payload is so large that the coding of some tables has the counting of others beside it: then memory works all the time.
-    // Where it is not, the waits for counts and codebooks inside the launch are longer than the gaps between three launches (us, three
-    // launches and one: 65536 units 47.5 and 53, 65536 of 16 tables in chunks of 64 symbols 50 and 54; 75000 56 and 54, 106496 66
-    // and 62, 163840 78 and 75, 262144 106 and 100, 307200 of 300 tables 126 and 112, 524288 184 and 171; in half precision 65536 66
-    // and 71, 75000 81 and 78, 524288 205 and 188).  When every kernel is to be timed by itself the launches stay apart.
+    // Larger tables go from payload to coded groups in one launch as well, a table being the work of many work-groups (k_flow): the
+    // work-groups that count take 1024 shares of the payload and more, and those that code begin when the first of the counting ones
+    // are done instead of after the last.  Above 262144 units of 256 elements (524288 in half precision) there are more shares than
+    // that, and the coding of some tables has the counting of others beside it.  Fewer units than 72000 and the waits for counts and
+    // codebooks inside the launch are longer than the gaps between three launches (us, three launches and one: 65536 units of 16, 64 and
+    // of one table 46 and 52, 47 and 50, 52 and 51; 72000 of 64 57 and 52; 75000 of one 58 and 53, of two 54 and 52; 163840 of 64 78 and 71, 262144 of 64
+    // and of one 102 and 97, 120 and 100, 307200 of 300 123 and 108, 524288 178 and 163; in half precision 65536 of 16 and 64 66 and 70, 77 and 77,
+    // 75000 83 and 79, 524288 201 and 189).  From 512 tables on a work-group of the three launches builds four codebooks at a time, which
+    // is the shorter way for many tables of large alphabets: tables times symbols 3 * 2^19 at most (4096 symbols: 400 tables of four
+    // groups 109 and 87, 512 of three 81 and 87, 700 of two 99 and 110, 2000 of one 141 and 230; 2048: 700 of two 90 and 85, 1000 of two 95 and 110,
+    // 2000 of one 131 and 165; 1024: 1000 of 17 in chunks of 64 181 and 173, 1800 296 and 301.  Where such tables use hundreds of symbols,
+    // it builds their codebooks one after the other: 700 of eight groups 1337 and 882).  When every kernel is to be timed by itself the
+    // launches stay apart.
     const uint64_t units = (uint64_t)g.T * ((g.n + kW * kV - 1u) / (kW * kV));
-    const bool flow = !g.lz && units >= 72000u && !prof_on(pl, P_HIST);
+    const bool flow = !g.lz && units >= 72000u && (g.T < 512u || (uint64_t)g.T * g.K <= 3u << 19) && !prof_on(pl, P_HIST);
     // Small tables: a work-group per table.  Up to eight groups that is the
     // shorter way whatever the number of tables (one launch for three; 26 tables of eight groups: 35.6 us a call against
     // 36.3, one of one group 17.6 against 24.8).  From nine to sixteen groups, what a work-group has wavefronts for, a
@@ -368,7 +375,7 @@ hipError_t launch_compress(const Geom& g, const void* payload, uint8_t* out, uin
     // round of work-groups is nearly empty, and less so the longer the codes are (at ratios of 10 and 5.9: 257 tables of
     // twelve groups 110 and 197 us against 98 and 153; 300: 113 and 202 against 109 and 168; 350: 118 and 205 against 121 and
     // 184; 400: 124 and 211 against 132 and 197; 512: 142 and 229 against 159 and 344), and not in several rounds of larger tables
-    // where k_flow does it (400 of sixteen groups 148 and 141, in half precision 196 and 176; of nine 94 and 96, of twelve in chunks of 64 symbols 52 and 62).  Row matching needs every row's
+    // where k_flow does it (400 of sixteen groups 147 and 137, in half precision 191 and 173; of nine 94 and 96, of twelve in chunks of 64 symbols 52 and 62).  Row matching needs every row's
     // symbols before it knows the counts: it keeps the launches apart, and so do many tables
     // of a large alphabet, whose scratch memory would leave a compute unit one work-group at a time.
     const bool whole_rounds = (g.T >= 128u && g.T <= 256u) || (g.T > 352u && !(flow && g.n >= 200000u));

@@ -41,6 +41,8 @@ CASES = [  # T, B, D, S, dtype, destinations, radius
     (900, 1030, 64, 64, np.float16, 1, 512),     # two shares a table: the first tables are coded before the last are counted
     (23, 10001, 96, 128, np.float16, 1, 128),
     (9, 1700, 333, 256, np.float32, 4, 512),     # four containers
+    (300, 1030, 64, 256, np.float32, 1, 2048),   # tables of fewer groups than a ticket takes
+    (513, 601, 60, 64, np.float32, 1, 2048),     # alphabets too large for so many tables: three launches
 ]
 
 
@@ -63,7 +65,7 @@ def test_containers_match_the_oracle(T, B, D, S, dtype, nd, R):
         d = to_device(np.stack(pieces) if nd > 1 else pieces[0])
         ctx.profile_enable(call)  # (level 1 changes no launch)
         assert ctx.compress(d, out, sizes, capacity=cap) == 0 and ctx.sync_status() == 0
-        assert not call or _ran(ctx) == {"k_flow"}
+        assert not call or _ran(ctx) == {"k_flow" if nd * T < 512 or nd * T * 2 * R <= 3 << 19 else "k_encode"}
         h = out.cpu().numpy()
         assert np.all(h[cap:] == 0xA5)
         sz = sizes.cpu().numpy().astype(np.uint64)
@@ -144,6 +146,10 @@ APART = {"k_hist", "k_codebook", "k_encode", "k_finalize"}
     (2, 144000, 64, 64, 512, "k_flow", APART),        # 72000 units of 256 elements
     (2, 143996, 64, 64, 512, "k_encode", APART),      # two fewer
     (600, 500, 64, 64, 512, "k_table", {"k_table", "k_finalize"}),  # 75000 units of small tables
+    (511, 565, 64, 256, 2048, "k_flow", APART),       # the same with an alphabet of 4096 symbols
+    (512, 564, 64, 256, 2048, "k_encode", APART),     # one table more
+    (768, 376, 64, 256, 1024, "k_flow", APART),
+    (769, 376, 64, 256, 1024, "k_encode", APART),
 ])
 def test_the_rule_of_the_launches(T, B, D, S, R, launch, apart):
     """Level 1 names the launch that codes the groups, whichever that is; level 2 keeps counting, codebooks and coding apart."""
