@@ -22,20 +22,24 @@ def _payload(rng, T, B, D, R):
     return x
 
 
-@pytest.mark.parametrize("path", ["own", "rows", "carried", "sampled"])
+@pytest.mark.parametrize("path", ["own", "own, apart", "rows", "carried", "sampled"])
 @pytest.mark.parametrize("radius", [8, 16, 32])
 @pytest.mark.parametrize("tables", [512, 514])
 def test_four_codebooks_per_work_group(tables, radius, path):
     import torch
     from paper_2407_04272_amd import binding as b
-    # (a table of up to 16 groups of the default path has a work-group to itself: 17 here)
-    T, B, D, S = tables, 1025 if path == "own" else 70, 64, 64
+    # (a table of up to 16 groups of the default path has a work-group to itself: 17 here.  So large a payload is one launch, whose codebooks a
+    # work-group builds one at a time; with every kernel timed by itself they are the work of k_codebook, four a work-group)
+    own = path.startswith("own")
+    T, B, D, S = tables, 1025 if own else 70, 64, 64
     rng = np.random.default_rng(1000 * tables + radius)
     ebs = np.full(T, EB, np.float32)
-    flags = {"own": 0, "rows": b.FLAG_ROW_MATCH, "carried": b.FLAG_CARRY_CODEBOOK, "sampled": b.FLAG_SAMPLE_CODEBOOK}[path]
+    flags = {"own": 0, "own, apart": 0, "rows": b.FLAG_ROW_MATCH, "carried": b.FLAG_CARRY_CODEBOOK, "sampled": b.FLAG_SAMPLE_CODEBOOK}[path]
     cfg = b.make_config(b.F32, T, B, D, radius, S, 12, flags)
     ctx = b.Context(cfg)
     ctx.set_error_bounds(eb=ebs)
+    launches = {"own": {"k_flow"}, "own, apart": {"k_hist", "k_codebook", "k_encode", "k_finalize"}}
+    ctx.profile_enable({"own": 1, "own, apart": 2}.get(path, 0))
     cap = b.dlc_compress_bound(cfg)
     out = torch.empty(cap + 64, dtype=torch.uint8, device="cuda")
     sizes = torch.zeros(1 + T, dtype=torch.int64, device="cuda")
@@ -46,14 +50,15 @@ def test_four_codebooks_per_work_group(tables, radius, path):
         rec = torch.full_like(d, 7.0)
         out.fill_(0xA5)
         assert ctx.compress(d, out, sizes, capacity=cap) == 0 and ctx.sync_status() == 0
+        assert {k for k, (ms, n) in ctx.profile_read().items() if n} - {"k_decode"} == launches.get(path, set())
         h, n = out.cpu().numpy(), int(sizes[0])
         assert np.all(h[cap:] == 0xA5)
-        o = oracle.compress(x, ebs, radius, S, 12, carry_hist=prev, want_hist=path in ("own", "carried"),
+        o = oracle.compress(x, ebs, radius, S, 12, carry_hist=prev, want_hist=own or path == "carried",
                             row_match=True if path == "rows" else None, sample_codebook=path == "sampled")
         assert o.rc == 0
         assert n == o.data.size and np.array_equal(h[:n], o.data), call
         assert np.array_equal(sizes.cpu().numpy().astype(np.uint64), o.sizes), call
-        if path in ("own", "carried"):
+        if own or path == "carried":
             assert np.array_equal(ctx.read_histogram().reshape(T, -1), o.hist), call
         assert ctx.decompress(out, n, rec) == 0 and ctx.sync_status() == 0
         rc, orec = oracle.decompress(o.data, x.shape, x.dtype)
