@@ -354,8 +354,8 @@ hipError_t launch_compress(const Geom& g, const void* payload, uint8_t* out, uin
     }
     // Larger tables go from payload to coded groups in one launch as well, a table being the work of many work-groups (k_flow): the
     // work-groups that count take 1024 shares of the payload and more, and those that code begin when the first of the counting ones
-    // are done instead of after the last.  Above 262144 units of 256 elements (524288 in half precision) there are more shares than
-    // that, and the coding of some tables has the counting of others beside it.  Fewer units than 72000 and the waits for counts and
+    // are done instead of after the last.  Above 311296 units of 256 elements (524288 in half precision) more are counted than are
+    // ahead, and the coding of some tables has the counting of others beside it.  Fewer units than 72000 and the waits for counts and
     // codebooks inside the launch are longer than the gaps between three launches (us, three launches and one: 65536 units of 16, 64 and
     // of one table 46 and 52, 47 and 50, 52 and 51; 72000 of 64 57 and 52; 75000 of one 58 and 53, of two 54 and 52; 163840 of 64 78 and 71, 262144 of 64
     // and of one 102 and 97, 120 and 100, 307200 of 300 123 and 108, 524288 178 and 163; in half precision 65536 of 16 and 64 66 and 70, 77 and 77,

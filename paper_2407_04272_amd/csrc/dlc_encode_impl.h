@@ -1,6 +1,7 @@
 // The encode kernels for one chunk size S (DLC_S, defined by the including source file: one file per S keeps the
 // compile times apart): k_encode, which codes the symbol plane of tables of any size with codebooks that are there
-// already, and k_table, which does everything from the payload to the coded groups of a small table in one launch.
+// already; k_table, which does everything from the payload to the coded groups of a small table in one work-group; and
+// k_flow, which does it for large payloads, many work-groups a table, in one launch as well.
 #include <algorithm>
 
 #include "dlc_codec_dev.h"
@@ -505,10 +506,12 @@ void k_encode(const void* payload, const uint8_t* sym_plane, Geom g, FixedLayout
 //   Work-groups take tickets in the order in which they start.  Of every table there are `cpt` tickets to count a share of it (plane out, past
 //   the caches; counts added to the table's), the last of which to finish builds the codebook, and `ept` to code `gpe` groups each, which
 //   wait for that.  The tickets to code a table come `lag` tables after those to count it, so the codebook is there when they start;
-//   whoever is waited for has an earlier ticket and waits for nobody (counting) or for still earlier ones (the scan).
-//   What bounds it: memory (512 MiB: payload read, plane out and in, words out, 850 MB in the 150 us until the last table is
-//   counted), then the last tables' chain of codebook 6, tables 2, walk 9, scan 4 and copy 3 us.  Three launches, each of which ends with
-//   a part of the chip, took 184 us where this takes 171; 300 tables of 262144 elements 126, so 112.
+//   whoever is waited for has an earlier ticket and waits for nobody (counting) or for still earlier ones (the scan).  With no more
+//   tables than that (up to 311296 units of 256 elements, 524288 in half precision, or nearly; of 128 tables of 8192 x 128 76 are ahead) all counting
+//   tickets come first, and what overlaps is the end of the counting with the codebooks and the first tables' coding, instead of two gaps.
+//   What bounds it: memory (512 MiB: payload read, plane out and in, words out, 862 MB in 162 us; the last table is counted at 135), then
+//   the last tables' chain of codebook 7, tables 2, walk 9, scan 4 and copy 3 us.  Three launches, each of which ends with a part of the
+//   chip, take 178 us where this takes 163; 300 tables of 262144 elements 123 and 108.
 // ------------------------------------------------------------------------------------------------
 struct FlowPlan {
     uint32_t cpt, units;  // tickets to count a table, units each (a multiple of kHistBlk)
@@ -824,7 +827,7 @@ bool DLC_CAT(launch_flow_, DLC_S)(const Geom& g, const FixedLayout& F, const voi
     const uint32_t xn = finish_groups(g, 64u * NW);
     FlowPlan P;
     // Shares of a table alike, 1024 in all, two rounds of the work-groups that run at a time, so that what a share costs
-    // besides its loads (3 us: counters cleared, counts added) is little; no larger than 256 KiB of fp32 where memory bounds the
+    // besides its loads (3 us: counters cleared, counts added) is little; but no larger than 256 KiB of fp32 (512 MiB: 2048 of them) where memory bounds the
     // counting (512 MiB by 128, 256 and 512 units 175, 171 and 177 us), 512 units where it does not (half precision 241, 208 and 188).
     const uint32_t U = (g.n + kW * kV - 1u) / (kW * kV), most = g.dtype == DLC_F16 ? 512u : 256u;
     const uint32_t want = (uint32_t)std::min<uint64_t>(most, std::max<uint64_t>(64u, (uint64_t)g.T * U / 1024u));
