@@ -534,10 +534,8 @@ void k_flow(const void* payload, uint8_t* sym_plane, Geom g, FixedLayout F, cons
     if (tid == 0) { s_ticket = atomicAdd(&ctrl->ticket, 1u); s_lo = 255u; s_hi = 0u; }
     __syncthreads();
     const uint32_t ticket = __builtin_amdgcn_readfirstlane(s_ticket);
-    if (ticket >= P.tickets) {  // uniform; a spare work-group.  The last of all clears the counter
-        if (tid == 0 && ticket + 1u == gridDim.x) __hip_atomic_store(&ctrl->ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return;
-    }
+    if (ticket + 1u == gridDim.x && tid == 0) __hip_atomic_store(&ctrl->ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // (the last of all)
+    if (ticket >= P.tickets) return;  // uniform; a spare work-group
     // ticket -> what to do: the first `lag` tables' counting; a table's counting and the coding of the table `lag` before it; the last tables' coding
     uint32_t t, r;
     bool count = true;
@@ -849,10 +847,11 @@ bool DLC_CAT(launch_flow_, DLC_S)(const Geom& g, const FixedLayout& F, const voi
     P.tickets = g.T * (P.cpt + P.ept) + (out_bytes ? g.ND * xn : 0u);
     // An eighth more work-groups than tickets: the hardware gives every XCD as many work-groups as the others, whatever theirs have to do,
     // so the XCDs whose tickets took long have as many left to start when the tickets of the others run out.  Spare ones end at
-    // once (us, without and with: 128 tables of 8192 x 128 at bounds of 0.03, 0.004 and 0.001 of the range 169 and 169, 240 and 239, 848 and 803, 64 of
-    // them at 0.001 562 and 491, 64 of 4099 x 77 at 0.03 55.6 and 53.6; a sixteenth more 524 for the 491, a quarter as much more 477 for a
-    // percent on small payloads).
-    const uint32_t n_wg = P.tickets + P.tickets / 8u + 1u;
+    // once.  Not where every coding ticket can have a compute unit to itself: where they go as they are dealt they nearly do.
+    // (Us, without and with: 64 tables of 8192 x 128, 512 coding tickets, at bounds of 0.001, 0.003 and 0.03 of the range 558 and 480, 163 and 161, 98.4 and
+    // 97.5, 64 of 16384 x 128 in half precision, 1024, at 0.001 864 and 812, at 0.03 190 and 190; one table of 500000 x 64 in half precision, 245, at 0.03
+    // and 0.003 75.9 and 78.4, 168 and 173, one of 262144 x 128, 256, at 0.03 and 0.001 68.7 and 71.2, 301 and 308, 40 of 4096 x 128 327 and 325.)
+    const uint32_t n_wg = P.tickets + (g.T * P.ept > 256u ? P.tickets / 8u : 0u);
     const uint32_t budget = kLdsMax / 2u - kTableStatic;
     uint32_t cap = (uint32_t)S * 12u / 32u;
     while (cap > (uint32_t)S / 8u && enc_lds(NW, P.gpe, cap, 60u).end > budget) --cap;
